@@ -165,8 +165,7 @@ ls_status ls_project(const ls_batch* b, const float* pose, const ls_projected* o
  *           instances required I, 0}
  *   work    workspace of ls_batch_info.workspace_bytes (256-byte aligned),
  *           zero-filled by the caller before its first use; also used by
- *           ls_render_bwd (the persistent backward kernels keep their
- *           tile-queue counters here and leave them zero). */
+ *           ls_render_bwd. */
 typedef struct {
   int64_t capacity;
   uint32_t* tile_of;
@@ -259,24 +258,24 @@ typedef struct {
  *              Jobs sharing a Gaussian set may share output arrays.
  *   pose_grad: device [R][7], accumulated, or NULL; needs `pose`.
  * Two modes:
- *   - full (grads != NULL): per-tile sums of each Gaussian's image-space
+ *   - full (grads != NULL): per-band sums of each Gaussian's image-space
  *     gradients are added to a per-item accumulator in ls_bins.work (float
  *     atomics, so reproducible to rounding, not bitwise); the accumulator must
  *     be zero before the first backward on a workspace and
  *     ls_render_bwd_project clears it again;
  *   - pose only (grads == NULL, LS_BWD_POSE_ONLY): each Gaussian's pose
- *     Jacobian is applied inside the tile and a 12-value partial is written
- *     per tile, summed per render in a fixed order: no atomics, bit-identical
+ *     Jacobian is applied inside the band and a 12-value partial is written
+ *     per band, summed per render in a fixed order: no atomics, bit-identical
  *     results that do not depend on the other renders of the batch.
  * Errors: LS_ERR_INVALID. */
 ls_status ls_render_bwd(const ls_batch* b, const float* pose, const ls_projected* p, const ls_bins* bins,
                         const float* bg, const ls_image* fwd, const ls_image_grad* up,
                         const ls_gaussian_grads* grads, float* pose_grad, hipStream_t s);
 
-/* First half of ls_render_bwd: per tile, back-to-front recomputation and the
- * per-(item, tile) sums of dL/d(u, v, conic, opacity, z, rgb) (one kernel).
+/* First half of ls_render_bwd: per 8x8 band, back-to-front recomputation and
+ * the per-(item, band) sums behind dL/d(u, v, conic, opacity, z, rgb) (one kernel).
  * flags: LS_BWD_POSE_ONLY keeps only what a pose correction depends on (u, v,
- * conic, z) and turns it into per-tile pose partials (`pose` may be NULL =
+ * conic, z) and turns it into per-band pose partials (`pose` may be NULL =
  * identity). */
 #define LS_BWD_POSE_ONLY 1u
 ls_status ls_render_bwd_tiles(const ls_batch* b, const float* pose, const ls_projected* p, const ls_bins* bins,
@@ -287,7 +286,7 @@ ls_status ls_render_bwd_tiles(const ls_batch* b, const float* pose, const ls_pro
  * ls_loss_l1 defines it): the per-pixel gradient, sign(x - x*) on Omega
  * times inv_count[r] for each colour channel and the depth (0 outside Omega),
  * is formed inside the compositing backward from the forward images and the
- * targets, so no gradient images are written or read.  Each tile also stores
+ * targets, so no gradient images are written or read.  Each 8x8 band also stores
  * its sum of the loss terms and its count of pixels in Omega in the bins
  * workspace, from which ls_loss_l1_tiles forms the loss.
  *   fwd        the forward's images: rgb, depth, T_final and n_last are read
@@ -305,13 +304,13 @@ ls_status ls_render_bwd_tiles_l1(const ls_batch* b, const float* pose, const ls_
 
 /* The L1 loss of the last ls_render_bwd_tiles_l1 on these bins: loss (device
  * [R], written) = (1/|Omega|) sum over Omega of the per-pixel terms, as
- * ls_loss_l1 computes it but summed tile by tile (equal to its value up to
+ * ls_loss_l1 computes it but summed band by band (equal to its value up to
  * FP32 rounding); 0 for a render with no pixel in Omega. */
 ls_status ls_loss_l1_tiles(const ls_batch* b, const ls_bins* bins, float* loss, hipStream_t s);
 
 /* Second half of ls_render_bwd: chains the accumulated image-space gradients
  * through the EWA projection to the Gaussian parameters and the pose (full
- * mode), or sums the per-tile pose partials of each render (LS_BWD_POSE_ONLY;
+ * mode), or sums the per-band pose partials of each render (LS_BWD_POSE_ONLY;
  * grads must be NULL). */
 ls_status ls_render_bwd_project(const ls_batch* b, const float* pose, const ls_projected* p, const ls_bins* bins,
                                 const ls_gaussian_grads* grads, float* pose_grad, uint32_t flags, hipStream_t s);

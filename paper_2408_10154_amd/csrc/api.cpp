@@ -64,7 +64,7 @@ ls_status overlap_check_args(const float* p_mean, int32_t np, const float* q_mea
 namespace {
 
 struct Layout {
-  size_t dk0, dv0, dk1, dv1, hist, bsum, tk, tv, g2d, tile_part, pose_part, loss_part, used, queues, total;
+  size_t dk0, dv0, dk1, dv1, hist, bsum, tk, tv, band_part, pose_part, loss_part, used, g2d, total;
 };
 
 Layout layout_of(const ls_batch* b, int64_t cap) {
@@ -89,12 +89,11 @@ Layout layout_of(const ls_batch* b, int64_t cap) {
   L.bsum = take(4 * (nbd + 8 + kMaxSortBins + 8));  // block sums, then the digit totals
   L.tk = take(4 * cap);
   L.tv = take(4 * cap);
-  L.g2d = take(4 * (size_t)kGrad2D * M);
-  L.tile_part = take(4 * (size_t)kPoseAcc * std::max(b->T, 1));
+  L.band_part = take(4 * 4 * (size_t)kPoseAcc * std::max(b->T, 1));  // a row per 8x8 band
   L.pose_part = take(4 * (size_t)kPoseAcc * std::max(b->nblk_items, 1));
-  L.loss_part = take(8 * (size_t)std::max(b->T, 1));  // per tile {L1 sum, pixels in Omega}
+  L.loss_part = take(4 * 8 * (size_t)std::max(b->T, 1));  // per 8x8 band {L1 sum, pixels in Omega}
   L.used = take(8 * 4 * (size_t)used_slots(cap, b->T));  // per band a row of "used" bits, 64 entries a word
-  L.queues = take(kTileQueueBytes);
+  L.g2d = take(4 * (size_t)kGradStride * M);  // last: pose-only callers have no room for it
   L.total = off;
   return L;
 }
@@ -351,6 +350,8 @@ ls_status batch_create(const ls_render_job* jobs, int32_t R, void* mem, size_t m
   return LS_OK;
 }
 
+size_t batch_pose_workspace_bytes(const ls_batch* b, int64_t capacity) { return layout_of(b, capacity).g2d; }
+
 ls_status batch_valid_inv(const ls_batch* b, const float* tgt_depth, float* inv, hipStream_t s) {
   if (!b || !inv) return fail(LS_ERR_INVALID, "NULL batch or output");
   ls_status st;
@@ -373,7 +374,7 @@ ls_status render_bwd_pose_l1(const ls_batch* b, const float* pose, const ls_proj
   launch_composite_bwd(b->jobs_d, b->tile_off_d, b->R, b->T, p->rec, p->aux, pose, bins->item, bins->range,
                        at<uint64_t>(bins->work, L.used), used_slots(bins->capacity, b->T), zero,
                        fwd->T_final, fwd->n_last, nullptr, nullptr, nullptr, scale, at<float>(bins->work, L.g2d),
-                       at<float>(bins->work, L.tile_part), 1, at<char>(bins->work, L.queues), s, &l1);
+                       at<float>(bins->work, L.band_part), 1, s, &l1);
   return hip_check("pose-only backward with the L1 gradient");
 }
 
@@ -383,7 +384,7 @@ ls_status pose_reduce_adam(const ls_batch* b, const ls_bins* bins, const PoseAda
   ls_status st;
   if ((st = check_bins(b, bins)) || (st = ensure_device(b))) return st;
   const Layout L = layout_of(b, bins->capacity);
-  launch_pose_reduce_adam(b->jobs_d, b->R, at<float>(bins->work, L.tile_part), a, count, sticky, s);
+  launch_pose_reduce_adam(b->jobs_d, b->R, at<float>(bins->work, L.band_part), a, count, sticky, s);
   return hip_check("pose reduction and Adam step");
 }
 
@@ -513,8 +514,8 @@ ls_status ls_render_bwd_tiles(const ls_batch* b, const float* pose, const ls_pro
   launch_composite_bwd(b->jobs_d, b->tile_off_d, b->R, b->T, p->rec, p->aux, pose, bins->item, bins->range,
                        at<uint64_t>(bins->work, L.used), used_slots(bins->capacity, b->T),
                        bg ? bg : zero, fwd->T_final, fwd->n_last, up->rgb, up->depth, up->alpha, up->scale,
-                       at<float>(bins->work, L.g2d), at<float>(bins->work, L.tile_part),
-                       (flags & LS_BWD_POSE_ONLY) ? 1 : 0, at<char>(bins->work, L.queues), s);
+                       at<float>(bins->work, L.g2d), at<float>(bins->work, L.band_part),
+                       (flags & LS_BWD_POSE_ONLY) ? 1 : 0, s);
   return hip_check("ls_render_bwd_tiles");
 }
 
@@ -534,8 +535,8 @@ ls_status ls_render_bwd_tiles_l1(const ls_batch* b, const float* pose, const ls_
   launch_composite_bwd(b->jobs_d, b->tile_off_d, b->R, b->T, p->rec, p->aux, pose, bins->item, bins->range,
                        at<uint64_t>(bins->work, L.used), used_slots(bins->capacity, b->T),
                        bg ? bg : zero, fwd->T_final, fwd->n_last, nullptr, nullptr, nullptr, inv_count,
-                       at<float>(bins->work, L.g2d), at<float>(bins->work, L.tile_part),
-                       (flags & LS_BWD_POSE_ONLY) ? 1 : 0, at<char>(bins->work, L.queues), s, &l1);
+                       at<float>(bins->work, L.g2d), at<float>(bins->work, L.band_part),
+                       (flags & LS_BWD_POSE_ONLY) ? 1 : 0, s, &l1);
   return hip_check("ls_render_bwd_tiles_l1");
 }
 
@@ -556,7 +557,7 @@ ls_status ls_render_bwd_project(const ls_batch* b, const float* pose, const ls_p
   const Layout L = layout_of(b, bins->capacity);
   if (flags & LS_BWD_POSE_ONLY) {
     if (grads) return fail(LS_ERR_INVALID, "pose-only backward computes no Gaussian gradients");
-    if (pose_grad) launch_pose_reduce_tiles(b->jobs_d, b->R, pose, at<float>(bins->work, L.tile_part), pose_grad, s);
+    if (pose_grad) launch_pose_reduce_bands(b->jobs_d, b->R, pose, at<float>(bins->work, L.band_part), pose_grad, s);
     return hip_check("ls_render_bwd_project");
   }
   if (pose_grad && !pose) return fail(LS_ERR_INVALID, "pose_grad needs the pose it is taken at");

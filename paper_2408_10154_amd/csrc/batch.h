@@ -49,6 +49,10 @@ ls_status batch_create(const ls_render_job* jobs, int32_t R, void* mem, size_t m
 ls_status batch_create_host(const ls_render_job* jobs, int32_t R, ls_batch** out);
 size_t batch_tables_bytes(const ls_batch* b);
 ls_status batch_bind(ls_batch* b, void* mem, size_t mem_bytes, hipStream_t s);
+// Bytes of ls_bins.work that pose-only work (binning, forward, pose-only
+// backward) uses of the ls_batch_query size: everything but the full
+// backward's accumulator.  Nothing in them needs clearing.
+size_t batch_pose_workspace_bytes(const ls_batch* b, int64_t capacity);
 // ls_project with every render gated on live[r].active (live NULL: all): a
 // frozen registration view contributes no tile instances, so binning,
 // compositing and the backward skip it.

@@ -56,7 +56,8 @@ __host__ __device__ inline int64_t emit_span(int64_t cap) {
   return (int64_t)sort_rounds(cap) * (kSortThreads / kEmitWaves);
 }
 __host__ __device__ inline int64_t emit_spans(int64_t cap) { return (cap + emit_span(cap) - 1) / emit_span(cap); }
-constexpr int kGrad2D = 10;         // du dv dA dB dC dop dz dr dg db
+constexpr int kGradStride = 16;     // floats per item in the accumulator: a 64-byte line each
+constexpr int kGrad2D = 10;         // sums of ds (dx, dy, dx^2, dx dy, dy^2, 1), dz dr dg db
 constexpr int kPoseAcc = 12;        // dL/dR (9, row-major) and dL/dt (3)
 constexpr int kAuxFloats = 12;      // per item: camera-space mean (3), covariance (6), 0 x3
 
@@ -146,13 +147,12 @@ __device__ __forceinline__ Rect tile_rect(float u, float v, int r, int TX, int T
 // The compositing kernels stage each splat's conic (A, B, C) pre-scaled to
 // (A / 2, B, C / 2) log2(e), so that the falloff sigma = (A dx^2 + 2 B dx dy +
 // C dy^2) / 2 comes out as sigma log2(e) and exp(-sigma) = 2^(-that): no
-// per-pixel multiply before the exponential.  Factors back to (A, B, C).
+// per-pixel multiply before the exponential.
 constexpr float kHalfLog2e = 0.72134752044448170368f;  // log2(e) / 2
 constexpr float kLog2e = 1.44269504088896340736f;
-constexpr float kLn2 = 0.69314718055994530942f;
-constexpr float kTwoLn2 = 1.38629436111989061883f;
 
-// The staged record also carries, in its free slot b.w, the bits of the
+// The staged record also carries, in slot b.z (the depth, which stays with
+// the colour), the bits of the
 // bound on sigma log2(e) within which the splat is composited: alpha =
 // opacity 2^(-sigma log2 e) >= 1/255 with sigma >= 0 holds (in exact
 // arithmetic; in FP32 up to a few ulps of the threshold) when
@@ -167,14 +167,14 @@ __device__ __forceinline__ void stage_conic(float4& a, float4& b) {
   a.w *= kLog2e;
   b.x *= kHalfLog2e;
   const float t = __builtin_amdgcn_logf(b.y * (1.0f / LS_ALPHA_MIN));
-  b.w = __uint_as_float(t >= 0.f ? __float_as_uint(t) + 1u : 0u);
+  b.z = __uint_as_float(t >= 0.f ? __float_as_uint(t) + 1u : 0u);
 }
 
 // Whether a staged splat (b from stage_conic) is composited at a pixel whose
 // sigma log2(e) is sl: alpha >= 1/255 and sigma >= 0, the test of both the
 // forward and the backward.
 __device__ __forceinline__ bool composited(float sl, const float4& b) {
-  return __float_as_uint(sl) < __float_as_uint(b.w);
+  return __float_as_uint(sl) < __float_as_uint(b.z);
 }
 
 // sigma log2(e) at pixel offset (dx, dy) from a staged conic, as
@@ -217,11 +217,14 @@ __device__ __forceinline__ void atomic_add_f32(float* p, float v) {
 // Image-space gradients of one Gaussian -> gradients w.r.t. its camera-space
 // mean p (dp) and camera-space covariance Sc (G, symmetric 3x3), through
 // u = fx x/z + cx, v = fy y/z + cy, Sigma_2D = J Sc J^T + eps I and the conic
-// (A, B, C) = (c, -b, a) / det.  g = (du, dv, dA, dB, dC, dz).
+// (A, B, C) = (c, -b, a) / det.  g = the sums over pixels of ds times (dx, dy,
+// dx^2, dx dy, dy^2), ds = dL/dsigma and (dx, dy) the pixel's offset from
+// (u, v), and dL/dz: du = -(A sx + B sy), dv = -(B sx + C sy), dA = sxx / 2,
+// dB = sxy, dC = syy / 2.
 __device__ __forceinline__ void camera_space_grads(const float* p, const float* Sc, float fx, float fy,
                                                    const float* g, float* dp, float* G) {
   const float px = p[0], py = p[1], pz = p[2];
-  const float du = g[0], dv = g[1], dA = g[2], dB = g[3], dC = g[4], dz = g[5];
+  const float dA = 0.5f * g[2], dB = g[3], dC = 0.5f * g[4], dz = g[5];
   const float iz = 1.0f / pz;
   const float J0[3] = {fx * iz, 0.f, -fx * px * iz * iz};
   const float J1[3] = {0.f, fy * iz, -fy * py * iz * iz};
@@ -234,7 +237,8 @@ __device__ __forceinline__ void camera_space_grads(const float* p, const float* 
   const float b = J0[0] * SJ1[0] + J0[1] * SJ1[1] + J0[2] * SJ1[2];
   const float c = J1[0] * SJ1[0] + J1[1] * SJ1[1] + J1[2] * SJ1[2] + LS_EPS_2D;
   const float det = a * c - b * b;
-  const float id2 = 1.0f / (det * det);
+  const float idet = 1.0f / det, id2 = 1.0f / (det * det);
+  const float du = (b * g[1] - c * g[0]) * idet, dv = (b * g[0] - a * g[1]) * idet;
   const float ga = (-c * c * dA + b * c * dB - b * b * dC) * id2;
   const float gb = (2.f * b * c * dA - (det + 2.f * b * b) * dB + 2.f * a * b * dC) * id2;
   const float gc = (-b * b * dA + a * b * dB - a * a * dC) * id2;

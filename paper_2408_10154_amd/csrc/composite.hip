@@ -1,18 +1,16 @@
 // Front-to-back alpha compositing (forward) and its back-to-front
 // recomputation (backward) on gfx950.  A 16x16 tile is four 8x8-pixel bands
-// (quadrants), one wave each: the forward runs one band per 64-thread block,
-// the backward one tile per 256-thread block.
+// (quadrants); forward and backward run one band per 64-thread block (one
+// wave), with no barriers between waves.
 //
-// Splat records of a tile's list are staged through LDS in chunks; every lane
-// reads the same record (LDS broadcast), and each band walks only the entries
-// that can reach it.  The forward stops a band once every pixel of it has
-// terminated.  The backward kernels also exist in a persistent form: a grid
-// that fills the GPU once pulls tiles from device-side queues.
+// Splat records of a tile's list are staged through the wave's LDS; every
+// lane reads the same record (LDS broadcast), and each band walks only the
+// entries that can reach it.  The forward stops a band once every pixel of it
+// has terminated; the backward walks the entries that the forward composited.
 #include "common.h"
 #include "kernels.h"
 
 #include <cstdlib>
-#include <mutex>
 
 namespace ls {
 
@@ -131,115 +129,6 @@ __device__ __forceinline__ uint64_t band_rows(float4 a, float4 b, float bx0, flo
   return (~0ull >> (8 * (7 - r1))) & (~0ull << (8 * r0));
 }
 
-// Tile queues of the persistent compositing kernels (in the bins workspace:
-// zero on first use, re-zeroed by every launch).  The tiles are cut into 8
-// contiguous ranges; block b runs on XCD b % 8 under round-robin dispatch and
-// starts on range b % 8, so each XCD's L2 sees neighbouring tiles.  A block's
-// first tile is fixed (the (b / 8)-th of its range, as a plain one-block-per-
-// tile launch would map it); later tiles come from a counter per range,
-// first of its own range and then of the others.  Each counter has a cache
-// line to itself.  No block ever waits for another: a block exits once every
-// range is drained, and the last block to exit re-zeroes the counters.
-struct TileQueue {
-  struct alignas(128) Line {
-    uint32_t v;
-    uint32_t pad[31];
-  };
-  Line next[8];  // dynamic claims from each range (may overshoot)
-  Line done;     // blocks that have exited
-};
-static_assert(sizeof(TileQueue) == 9 * 128, "queue record size");
-
-__device__ __forceinline__ void range_of(int T, int x, int& lo, int& n) {
-  lo = (int)(((int64_t)T * x) >> 3);
-  n = (int)(((int64_t)T * (x + 1)) >> 3) - lo;
-}
-
-// Statically mapped tiles of range x: one per block b < nstatic with
-// b % 8 == x (blocks past nstatic only ever claim from the counters).
-__device__ __forceinline__ int static_claims(int nstatic, int x, int n) {
-  const int blocks = nstatic > x ? (nstatic - x + 7) >> 3 : 0;
-  return blocks < n ? blocks : n;
-}
-
-// The block's next tile, or -1 when all ranges are drained.  `first` and
-// `dead` (ranges found empty) are kept by the caller in wave 0.  The home
-// range is tried with one atomic; after that, lanes 0..7 of wave 0 read all
-// eight counters at once (one memory latency instead of eight in a row) and
-// the first range in probe order that still has tiles is claimed from; a
-// lost race marks that range and probes again.  Called by every thread.
-__device__ __forceinline__ int claim_tile(TileQueue* q, int T, int nstatic, bool& first, uint32_t& dead,
-                                          int* s_tile) {
-  if (threadIdx.x < 64) {
-    const int lane = threadIdx.x;
-    const int home = blockIdx.x & 7;
-    int t = -1;
-    if (first) {
-      first = false;
-      int lo, n;
-      range_of(T, home, lo, n);
-      const int k = (int)(blockIdx.x >> 3);
-      if ((int)blockIdx.x < nstatic && k < n) t = lo + k;
-    }
-    if (t < 0 && !(dead & 1u << home)) {
-      int lo, n;
-      range_of(T, home, lo, n);
-      const int s0 = static_claims(nstatic, home, n);
-      const uint32_t i = (lane == 0 && s0 < n) ? atomicAdd(&q->next[home].v, 1u) : 0u;
-      const int ti = __shfl(s0 + (int)i < n ? lo + s0 + (int)i : -1, 0, 64);
-      if (ti >= 0) t = ti;
-      else dead |= 1u << home;
-    }
-    while (t < 0 && dead != 0xFFu) {
-      // parallel probe of the ranges still alive, in order home+1, home+2, ...
-      const int x = (home + 1 + (lane & 7)) & 7;
-      int lo, n;
-      range_of(T, x, lo, n);
-      const int s0 = static_claims(nstatic, x, n);
-      bool avail = false;
-      if (lane < 8 && !((dead >> x) & 1u) && s0 < n)
-        avail = s0 + (int)__hip_atomic_load(&q->next[x].v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < n;
-      const uint64_t m = __ballot(avail);
-      uint32_t gone = 0;
-      for (int l = 0; l < 8; ++l)
-        if (!((m >> l) & 1ull)) gone |= 1u << ((home + 1 + l) & 7);
-      dead |= gone;  // counters only grow: a drained range stays drained
-      if (m == 0ull) {
-        dead = 0xFFu;
-        break;
-      }
-      const int pick = (int)__builtin_ctzll(m);
-      const int y = (home + 1 + pick) & 7;
-      int ly, ny;
-      range_of(T, y, ly, ny);
-      const int sy = static_claims(nstatic, y, ny);
-      const uint32_t i = lane == 0 ? atomicAdd(&q->next[y].v, 1u) : 0u;
-      const int ti = __shfl(sy + (int)i < ny ? ly + sy + (int)i : -1, 0, 64);
-      if (ti >= 0) t = ti;
-      else dead |= 1u << y;
-    }
-    if (lane == 0) *s_tile = t;
-  }
-  __syncthreads();
-  const int t = *s_tile;
-  __syncthreads();
-  return t;
-}
-
-// After a block's last claim: the last block to exit re-zeroes the queue, so
-// the next launch (or graph replay) on the stream starts from zero.  No fence:
-// every claim of a block returned (its value decided the block's exit) before
-// the block counts itself done, and the atomics are ordered at the device
-// scope; a release fence here would write back the L2 once per block.
-__device__ __forceinline__ void release_queue(TileQueue* q) {
-  if (threadIdx.x == 0) {
-    if (atomicAdd(&q->done.v, 1u) == gridDim.x - 1) {
-      for (int x = 0; x < 8; ++x) atomicExch(&q->next[x].v, 0u);
-      atomicExch(&q->done.v, 0u);
-    }
-  }
-}
-
 // Forward, one wave per 8x8-pixel band of a tile (a 64-thread block): no
 // block barriers, and a band stops reading its tile's list as soon as all of
 // its pixels have terminated.  The wave walks the list 64 entries at a time:
@@ -293,8 +182,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8))) void k_
       else
         in = (wave_mask(r0, r1, tx0, ty0) >> band) & 1u;
       if (in) {
-        stage_conic(r0, r1);
         r2 = rec[it * 3 + 2];
+        r2.w = r1.z;
+        stage_conic(r0, r1);
       }
     }
     const uint64_t bal = __ballot(in);
@@ -330,7 +220,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8))) void k_
         cr += wgt * col.x;
         cg += wgt * col.y;
         cb += wgt * col.z;
-        dd += wgt * b.z;
+        dd += wgt * col.w;
         T = u ? Tn : T;
         // usedm |= 1 << j in one scalar instruction (a register-only bit set)
         asm volatile("s_bitset1_b64 %0, %1" : "+s"(usedm) : "s"(j));
@@ -461,51 +351,53 @@ __device__ __forceinline__ int wave_value(int lane) {
   return v < N ? v : -1;
 }
 
-constexpr int kBwdChunk = 64;   // list entries staged per round (full mode)
-constexpr int kWaveSlots = 4 * ((kGrad2D / 2 + 1) / 2);  // floats per wave partial (a slot per value index)
-constexpr int kPartStride = 4 * kWaveSlots + 1;         // floats per entry: 4 wave partials, odd against bank conflicts
-
 // Backward.  Per pixel, walking the list from n_last - 1 down to 0 with the
 // transmittance recovered as T_i = T_{i+1} / (1 - alpha_i) and the running
 // "behind" value acc = sum_{j>i} alpha_j prod_{i<k<j}(1 - alpha_k) v_j +
 // prod_{k>i}(1 - alpha_k)(bg . gC - gA), where v_j = c_j . gC + z_j gD:
 //   dL/dalpha_i = T_i (v_i - acc_i).
-// One such step at a pixel, in two parts.  bwd_eval (every entry of the
-// band's list) says whether the entry was composited there: act = visited,
-// sigma >= 0 and alpha >= 1/255.  bwd_apply (entries some lane of the wave
-// composited), branch-free: where act, T is recovered, acc updated, and
-// wgt = alpha T, ds = dL/dsigma and dop = dL/d(opacity) are set (both zero
-// while the 0.99 clamp is active).  Elsewhere the step runs with alpha = 0,
-// which leaves T (times 1 / 1) and acc (plus 0) unchanged and gives wgt = 0,
-// and with G and exp(-sigma) selected to 0, which gives ds = dop = 0: three
-// selects instead of one per output.
-struct BwdEval {
-  float ex, G, al;  // exp(-sigma), o exp(-sigma), alpha
-  bool act;
-};
-
-__device__ __forceinline__ BwdEval bwd_eval(bool visited, float4 a, float4 b, float dx, float dy) {
-  BwdEval e;
+// One such step at a pixel (a, b staged, b.w the list position), branch-free:
+// where the entry was composited (visited, sigma >= 0 and alpha >= 1/255), T
+// is recovered, acc updated, and wgt = alpha T and ds = dL/dsigma = -alpha
+// dL/dalpha are formed.  Elsewhere the step runs with alpha = 0, which leaves
+// T (times 1 / 1) and acc (plus 0) unchanged and gives wgt = ds = 0.
+// dL/d(opacity) = -ds / opacity (both carry the factor exp(-sigma)), so it
+// needs no sum of its own.  No gradient flows through an active 0.99 clamp
+// (alpha = 0.99): those ds are cleared.
+__device__ __forceinline__ float step_alpha(const float4& a, const float4& b, int nl, float fx, float fy) {
+  const float dx = fx - a.x, dy = fy - a.y;
   const float sl = falloff_log2(a.z, a.w, b.x, dx, dy);
-  e.ex = __builtin_amdgcn_exp2f(-sl);
-  e.G = b.y * e.ex;
-  e.al = fminf(LS_ALPHA_MAX, e.G);
-  e.act = visited && composited(sl, b);
-  return e;
+  const float G = b.y * __builtin_amdgcn_exp2f(-sl);
+  // & and not &&: no branch
+  return (__float_as_int(b.w) < nl) & composited(sl, b) ? fminf(LS_ALPHA_MAX, G) : 0.f;
 }
 
-__device__ __forceinline__ void bwd_apply(const BwdEval& e, float4 col, float z, float gR, float gG, float gB,
-                                          float gD, float& T, float& acc, float& wgt, float& ds, float& dop) {
-  const float al = e.act ? e.al : 0.f;
-  T = T * __builtin_amdgcn_rcpf(1.f - al);
-  wgt = al * T;
-  const float v = col.x * gR + col.y * gG + col.z * gB + z * gD;
-  const float d = v - acc;
-  const float dal = T * d;
-  acc = fmaf(al, d, acc);  // alpha v + (1 - alpha) acc
-  const bool grad = e.act && e.G < LS_ALPHA_MAX;  // dL/dG = dal; no gradient through an active clamp
-  ds = -dal * (grad ? e.G : 0.f);
-  dop = dal * (grad ? e.ex : 0.f);
+// The band of a 64-thread block: unit = 4 tile + band, lane l its pixel
+// (l & 7, l >> 3).
+struct BandCtx {
+  int r, tile, band;
+  int x, y;    // pixel of this lane
+  int x0, y0;  // the band's first pixel
+  bool inside;
+  int64_t pix;  // pixel index in the image arrays (if inside)
+};
+
+__device__ __forceinline__ BandCtx band_ctx(const JobDev* jobs, const int32_t* tile_off, int R, int unit) {
+  BandCtx c;
+  c.tile = unit >> 2;
+  c.band = unit & 3;
+  c.r = find_segment<int32_t>(tile_off, R, c.tile);
+  const JobDev& J = jobs[c.r];
+  const int lt = c.tile - J.tile_off;
+  const int ty = lt / J.TX, tx = lt - ty * J.TX;
+  const int lane = threadIdx.x;
+  c.x0 = tx * kTile + 8 * (c.band & 1);
+  c.y0 = ty * kTile + 8 * (c.band >> 1);
+  c.x = c.x0 + (lane & 7);
+  c.y = c.y0 + (lane >> 3);
+  c.inside = c.x < J.W && c.y < J.H;
+  c.pix = J.pix_off + (int64_t)c.y * J.W + c.x;
+  return c;
 }
 
 // Per-pixel state shared by both backward kernels: upstream gradients (scaled),
@@ -518,7 +410,7 @@ struct BwdPixel {
 
 __device__ __forceinline__ float l1_sign(float d) { return d > 0.f ? 1.f : (d < 0.f ? -1.f : 0.f); }
 
-__device__ __forceinline__ BwdPixel bwd_pixel(const TileCtx& c, const JobDev& J, float bg0, float bg1, float bg2,
+__device__ __forceinline__ BwdPixel bwd_pixel(const BandCtx& c, const JobDev& J, float bg0, float bg1, float bg2,
                                               const float* fwd_T, const int32_t* fwd_n, const float* up_rgb,
                                               const float* up_depth, const float* up_alpha, const float* up_scale,
                                               const L1Targets& l1) {
@@ -554,481 +446,390 @@ __device__ __forceinline__ BwdPixel bwd_pixel(const TileCtx& c, const JobDev& J,
   return p;
 }
 
-// Wave 0 stages a chunk of the tile's list (records and item ids) and builds,
-// for each of the four wave bands, the list-ordered positions of the entries
-// that some pixel of the band composited in the forward (its "used" bits:
-// per band row, 64 entries per slot, slot (start / 64) + tile + k for the
-// entries from start + 64 k on; list positions at or beyond the band's
-// largest entry count bmax were never walked there and are dropped).
-template <int kChunk>
-__device__ __forceinline__ void stage_chunk(int lane, int cnt, int chunk, int start, int tile, const int* bmax,
-                                            const int32_t* items, const float4* rec, const uint64_t* used,
-                                            int64_t ustride, float4* s0, float4* s1, float4* s2, int32_t* sit,
-                                            uint32_t* smask, uint8_t (*slist)[kChunk], uint32_t* swc) {
-  // the chunk's bits of each band (bit l: entry chunk + l), from one or two slots
-  const int rel = chunk - start, sh = rel & 63;
-  const int64_t slot = (int64_t)(start >> 6) + tile + (rel >> 6);
-  uint64_t ub[4];
-#pragma unroll
-  for (int b2 = 0; b2 < 4; ++b2) {
-    const uint64_t w0 = used[b2 * ustride + slot];
-    const uint64_t w1 = sh ? used[b2 * ustride + slot + 1] : 0ull;
-    ub[b2] = sh ? (w0 >> sh) | (w1 << (64 - sh)) : w0;
-  }
-  uint32_t m = 0;
-  const bool valid = lane < cnt;
-  if (valid) {
-    const int64_t it = items[chunk + lane];
-    float4 a = rec[it * 3 + 0], b = rec[it * 3 + 1];
-    const int k = chunk + lane - start;
-#pragma unroll
-    for (int b2 = 0; b2 < 4; ++b2) m |= (uint32_t)((ub[b2] >> lane) & 1ull) << b2;
-#pragma unroll
-    for (int b2 = 0; b2 < 4; ++b2)
-      if (k >= bmax[b2]) m &= ~(1u << b2);
-    stage_conic(a, b);
-    sit[lane] = (int32_t)it;
-    s0[lane] = a;
-    s1[lane] = b;
-    s2[lane] = rec[it * 3 + 2];
-    smask[lane] = m;
-  }
-  const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-#pragma unroll
-  for (int b2 = 0; b2 < 4; ++b2) {
-    const bool in = valid && ((m >> b2) & 1u);
-    const uint64_t bal = __ballot(in);
-    if (in) slist[b2][__popcll(bal & lt)] = (uint8_t)lane;
-    if (lane == 0) swc[b2] = (uint32_t)__popcll(bal);
-  }
+// Orders the wave's own LDS accesses (a wave's LDS operations complete in
+// order, so this only holds the compiler).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// The tile's L1 loss partial (L1 targets with loss_part): each wave's sums to
-// LDS before the caller's next barrier (tile_loss_put), and after it threads 0
-// and 1 write {sum, count} over the four waves in order (tile_loss_get).
-__device__ __forceinline__ void tile_loss_put(const L1Targets& l1, const BwdPixel& px, float (*sl)[4]) {
+// What the gradients need of an entry is sums over the band's pixels of ds
+// times 1, dx, dy, dx^2, dx dy, dy^2 and of wgt times the upstream gradients.
+// They are taken eight entries at a time: the walk (lane = pixel) leaves ds
+// and wgt of each entry in two rows of the wave's LDS, and then lane (e, y) =
+// (lane >> 3, lane & 7) sums pixel row y of entry e on its own (moments about
+// the band's centre, shifted to the splat's) before the eight rows of an entry
+// are added across lanes.  So the products are formed once per lane for eight
+// pixels and one cross-lane reduction serves eight entries.  An entry costs
+// about 22 VALU instructions in the walk and 13 (full) or 8 (pose only) in the
+// sums; with ten (six) products a pixel and a reduction of as many values an
+// entry it was 67 (53).  VALU bound: 200k Gaussians at 1200x680, full, 218 ->
+// 120 us (with the atomics below); 97k at 640x480, pose only, 93 -> 60 us; 16
+// views of 640x480 of 150k/120k, pose only, 470 -> 366 us.
+// (FP32 matrix products that contract the same rows with the pixel factors
+// cost more: twice the vector rate, but 10 of 32 result columns are of use,
+// and they do not overlap with the SIMD's vector instructions.)
+// The colour term v = c . (gR, gG, gB) + z gD of four entries at all 64
+// pixels is four 4x4x1 matrix products, bit for bit the FMA chain.
+constexpr int kBatch = 32;        // entries staged per round
+constexpr int kRowStride = 68;    // floats per LDS row of 64 pixels: 16-byte aligned, rows 4 banks apart
+constexpr int kRing = 128;        // positions waiting to be staged: < kBatch left over + 64 new
+using f32x4 = __attribute__((ext_vector_type(4))) float;
+
+struct BandLds {
+  float4 s0[kBatch], s1[kBatch], s2[kBatch];  // (u, v, hA, B), (hC, opacity, bound, list position), (r, g, b, z)
+  float rows[16 * kRowStride];  // of eight entries: ds, then wgt
+  int32_t ring[kRing];
+  int32_t item[kBatch];
+};
+
+// The upstream gradients of pixel row y = lane & 7 of the band, by way of the
+// wave's LDS.
+template <int kN>
+__device__ __forceinline__ void row_factors(float* rows, int lane, const float (&g)[kN], float (&f)[kN][8]) {
+#pragma unroll
+  for (int q = 0; q < kN; ++q) rows[q * kRowStride + lane] = g[q];
+  wave_sync();
+#pragma unroll
+  for (int q = 0; q < kN; ++q) {
+    const float4* r = reinterpret_cast<const float4*>(rows + q * kRowStride + 8 * (lane & 7));
+    const float4 a = r[0], b = r[1];
+    f[q][0] = a.x; f[q][1] = a.y; f[q][2] = a.z; f[q][3] = a.w;
+    f[q][4] = b.x; f[q][5] = b.y; f[q][6] = b.z; f[q][7] = b.w;
+  }
+  wave_sync();
+}
+
+// The band's entries in walk order (list positions descending): the forward's
+// "used" bits (64 entries per word, word 0 the list's first 64; every word
+// below the band's largest visited count was written) are expanded word by
+// word into a ring of list positions.  take() stages the next kBatch of them
+// (padded with entries that composite nowhere) and returns how many there are.
+struct BandList {
+  const uint64_t* used;
+  int left;         // words of the list not yet loaded
+  uint64_t mine;    // this lane's word of the current 64
+  uint64_t busy;    // which of the current 64 words have bits left to expand
+  int base;         // word index of lane 0's word
+  int head, have;
+  bool clamp;       // some staged entry's opacity reaches the 0.99 clamp
+
+  __device__ __forceinline__ BandList(const uint64_t* u, int visited)
+      : used(u), left((visited + 63) >> 6), mine(0ull), busy(0ull), base(0), head(0), have(0), clamp(false) {}
+
+  __device__ __forceinline__ int take(BandLds& L, int lane, int start, const int32_t* items, const float4* rec) {
+    while (have < kBatch && (busy != 0ull || left > 0)) {
+      if (busy == 0ull) {  // the next 64 words, the last one in lane 0
+        base = left - 1;
+        const int i = base - lane;
+        mine = i >= 0 ? used[i] : 0ull;
+        busy = __ballot(mine != 0ull);
+        left = max(left - 64, 0);
+        continue;
+      }
+      const int at = (int)__builtin_ctzll(busy);
+      busy &= busy - 1ull;
+      const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mine, at);
+      const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mine >> 32), at);
+      const uint64_t wd = ((uint64_t)hi << 32) | lo;
+      have += (int)__popcll(wd);
+      // the word's highest bit comes first
+      const uint32_t below = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+      if (__builtin_amdgcn_inverse_ballot_w64(wd))
+        L.ring[(head + have - 1 - (int)below) & (kRing - 1)] = 64 * (base - at) + lane;
+    }
+    wave_sync();
+    const int n = min(have, kBatch);
+    bool sat = false;
+    if (lane < kBatch) {
+      float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a, c = a;
+      if (lane < n) {
+        const int pos = L.ring[(head + lane) & (kRing - 1)];
+        const int it = items[start + pos];
+        a = rec[(int64_t)it * 3];
+        b = rec[(int64_t)it * 3 + 1];
+        c = rec[(int64_t)it * 3 + 2];
+        c.w = b.z;
+        stage_conic(a, b);
+        b.w = __int_as_float(pos);
+        L.item[lane] = it;
+      }
+      L.s0[lane] = a;
+      L.s1[lane] = b;
+      L.s2[lane] = c;
+      sat = b.y >= LS_ALPHA_MAX;
+    }
+    clamp = __ballot(sat) != 0ull;
+    wave_sync();
+    head = (head + n) & (kRing - 1);
+    have -= n;
+    return n;
+  }
+};
+
+// Eight steps of the walk, staged entries e0 .. e0 + 7: ds and wgt of entry
+// e0 + i at every pixel go to rows i and 8 + i.  Branch-free (padding entries
+// composite nowhere).  clamp: some staged entry's opacity reaches 0.99 (an
+// opacity below it bounds alpha, and the clamp can not act).
+__device__ __forceinline__ void walk_eight(BandLds& L, int lane, int e0, bool clamp, float fx, float fy,
+                                           BwdPixel& px) {
+#pragma unroll
+  for (int h = 0; h < 8; h += 4) {
+    const float4 c = L.s2[e0 + h + (lane & 3)];
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    v = __builtin_amdgcn_mfma_f32_4x4x1f32(c.x, px.gR, v, 0, 0, 0);
+    v = __builtin_amdgcn_mfma_f32_4x4x1f32(c.y, px.gG, v, 0, 0, 0);
+    v = __builtin_amdgcn_mfma_f32_4x4x1f32(c.z, px.gB, v, 0, 0, 0);
+    v = __builtin_amdgcn_mfma_f32_4x4x1f32(c.w, px.gD, v, 0, 0, 0);
+    // what does not depend on the earlier steps first, then the chain
+    // through T and acc
+    float al[4], rc[4];
+#pragma unroll
+    for (int i = 0; i < 4; i += 2) {
+      const float4 a0 = L.s0[e0 + h + i], b0 = L.s1[e0 + h + i];
+      const float4 a1 = L.s0[e0 + h + i + 1], b1 = L.s1[e0 + h + i + 1];
+      al[i] = step_alpha(a0, b0, px.nl, fx, fy);
+      al[i + 1] = step_alpha(a1, b1, px.nl, fx, fy);
+      rc[i] = __builtin_amdgcn_rcpf(1.f - al[i]);
+      rc[i + 1] = __builtin_amdgcn_rcpf(1.f - al[i + 1]);
+      if (i == 0) __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      px.T *= rc[i];
+      const float wgt = al[i] * px.T, d = v[i] - px.acc;
+      px.acc = fmaf(al[i], d, px.acc);
+      L.rows[(h + i) * kRowStride + lane] = -wgt * d;
+      L.rows[(8 + h + i) * kRowStride + lane] = wgt;
+    }
+    if (clamp) {  // uniform
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (al[i] >= LS_ALPHA_MAX) L.rows[(h + i) * kRowStride + lane] = 0.f;
+    }
+  }
+  wave_sync();
+}
+
+// Lane (e, y)'s sums over pixel row y of entry e0 + e: S = ds dx, ds dy,
+// ds dx^2, ds dx dy, ds dy^2, ds, then wgt times each of the kN factors.
+// bx = the band's centre x, ry = row y's pixel centre.
+template <int kN>
+__device__ __forceinline__ void row_sums(const BandLds& L, int lane, int e0, float bx, float ry,
+                                         const float (&f)[kN][8], float (&S)[6 + kN]) {
+  const int e = lane >> 3;
+  const float4* d4 = reinterpret_cast<const float4*>(L.rows + e * kRowStride + 8 * (lane & 7));
+  const float4* w4 = reinterpret_cast<const float4*>(L.rows + (8 + e) * kRowStride + 8 * (lane & 7));
+  const float4 x = d4[0], y = d4[1], p = w4[0], q = w4[1];
+  const float2 uv = *reinterpret_cast<const float2*>(&L.s0[e0 + e]);
+  const float s0 = x.x + y.w, s1 = x.y + y.z, s2 = x.z + y.y, s3 = x.w + y.x;
+  const float d0 = y.w - x.x, d1 = y.z - x.y, d2 = y.y - x.z, d3 = y.x - x.w;
+  const float r0 = (s0 + s1) + (s2 + s3);
+  const float r1 = 3.5f * d0 + 2.5f * d1 + 1.5f * d2 + 0.5f * d3;
+  const float r2 = 12.25f * s0 + 6.25f * s1 + 2.25f * s2 + 0.25f * s3;
+  const float U = uv.x - bx, dy = ry - uv.y;
+  S[0] = r1 - U * r0;
+  S[1] = dy * r0;
+  S[2] = r2 - U * (r1 + S[0]);
+  S[3] = dy * S[0];
+  S[4] = dy * S[1];
+  S[5] = r0;
+#pragma unroll
+  for (int k = 0; k < kN; ++k)
+    S[6 + k] = fmaf(q.w, f[k][7], fmaf(q.z, f[k][6], fmaf(q.y, f[k][5], fmaf(q.x, f[k][4],
+               fmaf(p.w, f[k][3], fmaf(p.z, f[k][2], fmaf(p.y, f[k][1], p.x * f[k][0])))))));
+}
+
+// Within groups of eight lanes: the value of lane 7 - y, y ^ 2 or y ^ 1.
+constexpr int kMirror8 = 0x141, kXor2 = 0x4E, kXor1 = 0xB1;
+template <int kCtrl>
+__device__ __forceinline__ float partner(float x) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), kCtrl, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float sum8(float x) {
+  x += partner<kMirror8>(x);
+  x += partner<kXor2>(x);
+  return x + partner<kXor1>(x);
+}
+
+// Largest of the 64 lanes' values (>= 0), as a scalar: DPP shifts within
+// 16-lane rows, then the row ends broadcast to the later rows.
+__device__ __forceinline__ int wave_max_i(int v) {
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false));  // row_shr:1
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false));  // row_shr:2
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false));  // row_shr:4
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false));  // row_shr:8
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false));  // row_bcast:15 -> rows 1, 3
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false));  // row_bcast:31 -> rows 2, 3
+  return __builtin_amdgcn_readlane(v, 63);
+}
+
+// The band's L1 loss partial {sum, count} (L1 targets with loss_part).
+__device__ __forceinline__ void band_loss(const L1Targets& l1, const BwdPixel& px, int unit) {
   if (!l1.loss_part) return;
   const float s = wave_sum(px.lsum), n = wave_sum(px.lcnt);
-  if ((threadIdx.x & 63) == 0) {
-    sl[0][threadIdx.x >> 6] = s;
-    sl[1][threadIdx.x >> 6] = n;
-  }
-}
-__device__ __forceinline__ void tile_loss_get(const L1Targets& l1, float (*sl)[4], int tile) {
-  if (l1.loss_part && threadIdx.x < 2) {
-    const float* v = sl[threadIdx.x];
-    l1.loss_part[2 * (int64_t)tile + threadIdx.x] = (v[0] + v[1]) + (v[2] + v[3]);
-  }
+  if (threadIdx.x == 0) reinterpret_cast<float2*>(l1.loss_part)[unit] = make_float2(s, n);
 }
 
-// Full mode: the ten per-pixel terms of each entry are summed over each
-// wave's 64 lanes (wave_sums), the four wave sums of the block over LDS in a
-// fixed order, and the ten gradients formed from them are added to the item's
-// accumulator (one atomic per nonzero value and tile).
-__device__ __forceinline__ void composite_bwd_tile(const JobDev* __restrict__ jobs,
-                                                          const int32_t* __restrict__ tile_off, int R, int T_total,
-                                                          const float4* __restrict__ rec,
-                                                          const int32_t* __restrict__ items,
-                                                          const int32_t* __restrict__ range,
-                                                          const uint64_t* __restrict__ used, int64_t ustride,
-                                                          float bg0, float bg1, float bg2,
-                                                          const float* __restrict__ fwd_T,
-                                                          const int32_t* __restrict__ fwd_n,
-                                                          const float* __restrict__ up_rgb,
-                                                          const float* __restrict__ up_depth,
-                                                          const float* __restrict__ up_alpha,
-                                                          const float* __restrict__ up_scale,
-                                                          float* __restrict__ g2d, const L1Targets& l1, int tile) {
-  __shared__ float4 s0[kBwdChunk], s1[kBwdChunk], s2[kBwdChunk];
-  __shared__ float sloss[2][4];
-  __shared__ int32_t sit[kBwdChunk];
-  __shared__ uint32_t smask[kBwdChunk];
-  __shared__ uint8_t slist[4][kBwdChunk];
-  __shared__ uint32_t swc[4];
-  __shared__ __attribute__((aligned(16))) float part[kBwdChunk * kPartStride];
-  static_assert(kBwdChunk <= 64 && kBlock % kBwdChunk == 0, "chunk must fit one staging wave");
-  __shared__ int bmax[4];
-  const TileCtx c = tile_ctx(jobs, tile_off, R, tile);
+// Full mode: the ten sums of each (entry, band) are added to the item's
+// accumulator by one atomic instruction, ten neighbouring lanes to one
+// 64-byte line.  The atomics are limited by the requests (instruction x line)
+// they make, not by their values (200k Gaussians at 1200x680, 1.4 M (entry,
+// band) pairs: two requests per pair 183-216 us, one per pair 148 us at 40
+// bytes per item and 124 us at 64, none 116 us).  The projection backward
+// applies the factors that are the same for all pixels (conic, halves, 1 /
+// opacity) once per item.
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_composite_bwd(
+    const JobDev* __restrict__ jobs, const int32_t* __restrict__ tile_off, int R, int T_total,
+    const float4* __restrict__ rec, const int32_t* __restrict__ items, const int32_t* __restrict__ range,
+    const uint64_t* __restrict__ used, int64_t ustride, float bg0, float bg1, float bg2,
+    const float* __restrict__ fwd_T, const int32_t* __restrict__ fwd_n, const float* __restrict__ up_rgb,
+    const float* __restrict__ up_depth, const float* __restrict__ up_alpha, const float* __restrict__ up_scale,
+    float* __restrict__ g2d, L1Targets l1) {
+  __shared__ __attribute__((aligned(16))) BandLds L;
+  const int unit = xcd_remap(blockIdx.x, 4 * T_total);
+  if (unit >= 4 * T_total) return;
+  const int lane = threadIdx.x;
+  const BandCtx c = band_ctx(jobs, tile_off, R, unit);
   const JobDev& J = jobs[c.r];
-  const int start = range[2 * tile], end = range[2 * tile + 1];
-  const float fx = (float)c.x + 0.5f, fy = (float)c.y + 0.5f;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int wval = wave_value<kGrad2D>(lane);  // the value whose wave sum this lane stores, or -1
+  const int start = range[2 * c.tile];
   BwdPixel px = bwd_pixel(c, J, bg0, bg1, bg2, fwd_T, fwd_n, up_rgb, up_depth, up_alpha, up_scale, l1);
-  tile_loss_put(l1, px, sloss);
-  if (threadIdx.x < 4) bmax[threadIdx.x] = 0;
-  __syncthreads();
-  if (px.nl > 0) atomicMax(&bmax[w], px.nl);
-  __syncthreads();
-  tile_loss_get(l1, sloss, tile);
-  const int smax = max(max(bmax[0], bmax[1]), max(bmax[2], bmax[3]));
-  const int last = min(start + smax, end);  // exclusive end of the entries any pixel visited
-
-  for (int chunk_end = last; chunk_end > start; chunk_end -= kBwdChunk) {
-    const int chunk = max(start, chunk_end - kBwdChunk);
-    const int cnt = chunk_end - chunk;
-    if (w == 0)
-      stage_chunk<kBwdChunk>(lane, cnt, chunk, start, tile, bmax, items, rec, used, ustride, s0, s1, s2, sit, smask,
-                             slist, swc);
-    __syncthreads();
-    const int cw = __builtin_amdgcn_readfirstlane((int)swc[w]);
-    // the band's list in a register; lanes past its end hold 0, so the
-    // read-ahead index (jj - 1) & 63 below names a staged entry even at jj = 0
-    const uint32_t myj = lane < cw ? slist[w][lane] : 0u;
-    auto bstep = [&](int j, const float4& a, const float4& b, const float4& col) {
-      float* pj = part + j * kPartStride + w * kWaveSlots + max(wval, 0);  // written only where wval >= 0
-      const int k = chunk + j - start;  // list position
-      const float dx = fx - a.x, dy = fy - a.y;
-      // every staged entry has an active lane (the forward's bits), so the
-      // step runs unconditionally; inactive lanes contribute exact zeros
-      const BwdEval e = bwd_eval(k < px.nl, a, b, dx, dy);
-      float wgt, ds, dop;
-      bwd_apply(e, col, b.z, px.gR, px.gG, px.gB, px.gD, px.T, px.acc, wgt, ds, dop);
-      // per-pixel terms whose sums give the ten gradients; the conic factors
-      // of dL/du, dL/dv and the halves of dL/dA, dL/dC are applied once per
-      // entry after the sums
-      float g[kGrad2D];
-      g[0] = ds * dx;
-      g[1] = ds * dy;
-      g[2] = g[0] * dx;
-      g[3] = g[0] * dy;
-      g[4] = g[1] * dy;
-      g[5] = dop;
-      g[6] = wgt * px.gD;
-      g[7] = wgt * px.gR;
-      g[8] = wgt * px.gG;
-      g[9] = wgt * px.gB;
-      const float out = wave_sums<kGrad2D>(g, lane);
-      if (wval >= 0) *pj = out;
-    };
-    // records read one entry ahead into alternating register sets (as in the forward)
-    int jA = (int)__builtin_amdgcn_readlane(myj, cw > 0 ? cw - 1 : 0), jB = 0;
-    float4 aA = s0[jA], bA = s1[jA], cA = s2[jA], aB, bB, cB;
-    for (int jj = cw - 1; jj >= 0;) {
-      jB = (int)__builtin_amdgcn_readlane(myj, (jj - 1) & 63);
-      aB = s0[jB];
-      bB = s1[jB];
-      cB = s2[jB];
-      bstep(jA, aA, bA, cA);
-      if (--jj < 0) break;
-      jA = (int)__builtin_amdgcn_readlane(myj, (jj - 1) & 63);
-      aA = s0[jA];
-      bA = s1[jA];
-      cA = s2[jA];
-      bstep(jB, aB, bB, cB);
-      --jj;
-    }
-    __syncthreads();
-    {
-      // kBlock / kBwdChunk threads per entry, each summing its values over
-      // the waves (bands) that reached the entry, in wave order; the partials
-      // of other waves are stale and skipped.  Thread 0 forms dL/du, dL/dv
-      // from the sums of ds dx and ds dy with the conic (A, B, C); the other
-      // threads split values 2..9 between them.
-      constexpr int kPer = kBlock / kBwdChunk;
-      static_assert(kPer >= 2 && kGrad2D == 10, "value split assumes at least two threads per entry and 10 values");
-      const int j = threadIdx.x / kPer, t = threadIdx.x % kPer;
-      const uint32_t mj = j < cnt ? smask[j] : 0u;
-      if (mj != 0u) {
-        float* dst = g2d + (int64_t)sit[j] * kGrad2D;
-        const float* pj = part + j * kPartStride;
-        auto band_sum = [&](int q) {
-          float v = 0.f;
+  band_loss(l1, px, unit);
+  BandList list(used + c.band * ustride + (start >> 6) + c.tile, wave_max_i(px.nl));
+  if (list.left == 0) return;
+  const float fx = (float)c.x + 0.5f, fy = (float)c.y + 0.5f;
+  const int y = lane & 7;
+  const float bx = (float)(c.x0 + 4), ry = (float)(c.y0 + y) + 0.5f;
+  const float g[4] = {px.gD, px.gR, px.gG, px.gB};
+  float f[4][8];
+  row_factors(L.rows, lane, g, f);
+  const bool hi = y & 4, b2 = y & 2, b1 = y & 1;
+  const int k0 = 4 * (y & 1) + (y & 2) + (y >> 2);  // the value that this lane ends with
+  for (;;) {
+    const int n = list.take(L, lane, start, items, rec);
+    if (n == 0) break;
+    for (int e0 = 0; e0 < n; e0 += 8) {
+      walk_eight(L, lane, e0, list.clamp, fx, fy, px);
+      float S[kGrad2D];
+      row_sums(L, lane, e0, bx, ry, f, S);
+      // sums over the entry's eight lanes, halving the lanes that hold a
+      // value at every level: ten values end in two registers
+      float h[5];
 #pragma unroll
-          for (int b2 = 0; b2 < 4; ++b2)
-            if ((mj >> b2) & 1u) v += pj[b2 * kWaveSlots + q];
-          return v;
-        };
-        auto put = [&](int q, float v) {
-          if (v != 0.f) atomic_add_f32(dst + q, v);
-        };
-        if (t == 0) {
-          const float sx = band_sum(0), sy = band_sum(1);
-          const float cA = kTwoLn2 * s0[j].z, cB = kLn2 * s0[j].w, cC = kTwoLn2 * s1[j].x;  // staged -> (A, B, C)
-          put(0, -(cA * sx + cB * sy));
-          put(1, -(cB * sx + cC * sy));
-        } else {
-          const int lo = 2 + ((t - 1) * (kGrad2D - 2)) / (kPer - 1), hi = 2 + (t * (kGrad2D - 2)) / (kPer - 1);
-          for (int q = lo; q < hi; ++q) {
-            const float v = band_sum(q);
-            put(q, (q == 2 || q == 4) ? 0.5f * v : v);
-          }
-        }
+      for (int k = 0; k < 5; ++k)
+        h[k] = (hi ? S[2 * k + 1] : S[2 * k]) + partner<kMirror8>(hi ? S[2 * k] : S[2 * k + 1]);
+      const float q0 = (b2 ? h[1] : h[0]) + partner<kXor2>(b2 ? h[0] : h[1]);
+      const float q1 = (b2 ? h[3] : h[2]) + partner<kXor2>(b2 ? h[2] : h[3]);
+      float z1 = h[4] + partner<kXor2>(h[4]);
+      // by way of LDS to sixteen lanes per entry
+      float* out = L.rows + (lane >> 3) * kGradStride;
+      out[k0] = (b1 ? q1 : q0) + partner<kXor1>(b1 ? q0 : q1);
+      z1 += partner<kXor1>(z1);
+      if ((y & 3) == 0) out[8 + (y >> 2)] = z1;
+      wave_sync();
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        const int e = e0 + 4 * p + (lane >> 4), k = lane & 15;
+        const float v = L.rows[64 * p + lane];
+        if (e < n && k < kGrad2D && v != 0.f) atomic_add_f32(g2d + (int64_t)L.item[e] * kGradStride + k, v);
       }
+      wave_sync();
     }
-    __syncthreads();
   }
 }
 
-// One block per tile (XCD-aware mapping), for launches with few tiles per
-// resident block.
-__global__ __launch_bounds__(kBlock) void k_composite_bwd(const JobDev* __restrict__ jobs,
-                                                          const int32_t* __restrict__ tile_off, int R, int T_total,
-                                                          const float4* __restrict__ rec,
-                                                          const int32_t* __restrict__ items,
-                                                          const int32_t* __restrict__ range,
-                                                          const uint64_t* __restrict__ used, int64_t ustride,
-                                                          float bg0, float bg1, float bg2,
-                                                          const float* __restrict__ fwd_T,
-                                                          const int32_t* __restrict__ fwd_n,
-                                                          const float* __restrict__ up_rgb,
-                                                          const float* __restrict__ up_depth,
-                                                          const float* __restrict__ up_alpha,
-                                                          const float* __restrict__ up_scale,
-                                                          float* __restrict__ g2d, L1Targets l1) {
-  const int tile = xcd_remap(blockIdx.x, T_total);
-  if (tile >= T_total) return;
-  composite_bwd_tile(jobs, tile_off, R, T_total, rec, items, range, used, ustride, bg0, bg1, bg2, fwd_T, fwd_n,
-                     up_rgb, up_depth, up_alpha, up_scale, g2d, l1, tile);
+// Pose-only mode (registration, tracking): only the gradients a pose
+// correction acts through (u, v, conic, depth) are formed.  Two batches of
+// entries fill the wave's lanes, one per lane; then every lane applies the
+// pose Jacobian of its Gaussian, and the wave's sums are added, in a fixed
+// order, to the band's running sum, written once as the band's 12-value
+// partial: no atomics, so the pose gradient is deterministic and independent
+// of the other renders.
+__device__ __forceinline__ float uniform(float x) {
+  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
 }
 
-__global__ __launch_bounds__(kBlock) void k_composite_bwd_persistent(const JobDev* __restrict__ jobs,
-    const int32_t* __restrict__ tile_off, int R, int T_total, const float4* __restrict__ rec,
+constexpr int kPoseRow = 6;  // sums of ds dx, ds dy, ds dx^2, ds dx dy, ds dy^2, wgt gD
+
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_composite_bwd_pose(
+    const JobDev* __restrict__ jobs, const int32_t* __restrict__ tile_off, int R, int T_total,
+    const float4* __restrict__ rec, const float4* __restrict__ aux, const float* __restrict__ pose,
     const int32_t* __restrict__ items, const int32_t* __restrict__ range, const uint64_t* __restrict__ used,
     int64_t ustride, float bg0, float bg1, float bg2, const float* __restrict__ fwd_T,
     const int32_t* __restrict__ fwd_n, const float* __restrict__ up_rgb, const float* __restrict__ up_depth,
-    const float* __restrict__ up_alpha, const float* __restrict__ up_scale, float* __restrict__ g2d,
-    TileQueue* __restrict__ queue, int nstatic, L1Targets l1) {
-  __shared__ int s_tile;
-  bool first = true;
-  uint32_t dead = 0;
-  for (;;) {
-    const int tile = claim_tile(queue, T_total, nstatic, first, dead, &s_tile);
-    if (tile < 0) break;
-    composite_bwd_tile(jobs, tile_off, R, T_total, rec, items, range, used, ustride, bg0, bg1, bg2, fwd_T, fwd_n,
-                       up_rgb, up_depth, up_alpha, up_scale, g2d, l1, tile);
-  }
-  release_queue(queue);
-}
-
-
-// Pose-only mode (registration): only the gradients a pose correction acts
-// through (u, v, conic, depth) are formed.  Each entry's sums over the tile
-// are parked in an LDS queue; whenever it is full (and at the end) every
-// thread of the block applies the pose Jacobian of one queued Gaussian, so
-// the Jacobian work is spread over all four waves.  Each
-// round's results are reduced over the block in a fixed order and added to the
-// tile's running sum, written once as the tile's 12-value partial: no atomics,
-// so the pose gradient is deterministic and independent of the other renders.
-constexpr int kPoseChunk = 64;                    // entries staged per round
-constexpr int kPoseRow = 6;                       // sums giving du, dv, dA, dB, dC, d(depth weight)
-constexpr int kPoseSlots = 4 * ((kPoseRow / 2 + 1) / 2);  // floats per wave partial (a slot per value index)
-constexpr int kPoseStride = 4 * kPoseSlots + 1;   // floats per entry: 4 wave partials, odd against bank conflicts
-constexpr int kPoseQueue = kBlock;                // queued entries per Jacobian round
-
-__device__ __forceinline__ void composite_bwd_pose_tile(const JobDev* __restrict__ jobs,
-                                                               const int32_t* __restrict__ tile_off, int R,
-                                                               int T_total, const float4* __restrict__ rec,
-                                                               const float4* __restrict__ aux,
-                                                               const float* __restrict__ pose,
-                                                               const int32_t* __restrict__ items,
-                                                               const int32_t* __restrict__ range,
-                                                               const uint64_t* __restrict__ used, int64_t ustride,
-                                                               float bg0, float bg1, float bg2,
-                                                               const float* __restrict__ fwd_T,
-                                                               const int32_t* __restrict__ fwd_n,
-                                                               const float* __restrict__ up_rgb,
-                                                               const float* __restrict__ up_depth,
-                                                               const float* __restrict__ up_alpha,
-                                                               const float* __restrict__ up_scale,
-                                                               float* __restrict__ tile_part, const L1Targets& l1,
-                                                               int tile) {
-  __shared__ float4 s0[kPoseChunk], s1[kPoseChunk], s2[kPoseChunk];
-  __shared__ int32_t sit[kPoseChunk];
-  __shared__ uint32_t smask[kPoseChunk];
-  __shared__ uint8_t slist[4][kPoseChunk];
-  __shared__ uint32_t swc[4];
-  __shared__ __attribute__((aligned(16))) float part[kPoseChunk * kPoseStride];
-  __shared__ float qsum[kPoseRow * kPoseQueue];  // [value][slot]
-  __shared__ int32_t qit[kPoseQueue];
-  __shared__ float wred[4][kPoseAcc];
-  __shared__ int bmax[4];
-  static_assert(kPoseChunk <= 64 && kPoseQueue % kPoseChunk == 0, "chunk must fit one staging wave");
-  const TileCtx c = tile_ctx(jobs, tile_off, R, tile);
+    const float* __restrict__ up_alpha, const float* __restrict__ up_scale, float* __restrict__ band_part,
+    L1Targets l1) {
+  __shared__ __attribute__((aligned(16))) BandLds L;
+  const int unit = xcd_remap(blockIdx.x, 4 * T_total);
+  if (unit >= 4 * T_total) return;
+  const int lane = threadIdx.x;
+  const BandCtx c = band_ctx(jobs, tile_off, R, unit);
   const JobDev& J = jobs[c.r];
-  const int start = range[2 * tile], end = range[2 * tile + 1];
-  const float fx = (float)c.x + 0.5f, fy = (float)c.y + 0.5f;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int wval = wave_value<kPoseRow>(lane);
-  __shared__ float sloss[2][4];
+  const int start = range[2 * c.tile];
   BwdPixel px = bwd_pixel(c, J, bg0, bg1, bg2, fwd_T, fwd_n, up_rgb, up_depth, up_alpha, up_scale, l1);
-  tile_loss_put(l1, px, sloss);
-  if (threadIdx.x < 4) bmax[threadIdx.x] = 0;
-  __syncthreads();
-  if (px.nl > 0) atomicMax(&bmax[w], px.nl);
-  __syncthreads();
-  tile_loss_get(l1, sloss, tile);
-  const int smax = max(max(bmax[0], bmax[1]), max(bmax[2], bmax[3]));
-  const int last = min(start + smax, end);
-
-  float total = 0.f;  // threads 0..11: the tile's running pose-gradient sum
-  int nq = 0;  // queued entries (uniform)
-  for (int chunk_end = last; chunk_end > start; chunk_end -= kPoseChunk) {
-    const int chunk = max(start, chunk_end - kPoseChunk);
-    const int cnt = chunk_end - chunk;
-    if (w == 0)
-      stage_chunk<kPoseChunk>(lane, cnt, chunk, start, tile, bmax, items, rec, used, ustride, s0, s1, s2, sit, smask,
-                              slist, swc);
-    __syncthreads();
-    const int cw = __builtin_amdgcn_readfirstlane((int)swc[w]);
-    // the band's list in a register; lanes past its end hold 0, so the
-    // read-ahead index (jj - 1) & 63 below names a staged entry even at jj = 0
-    const uint32_t myj = lane < cw ? slist[w][lane] : 0u;
-    auto pstep = [&](int j, const float4& a, const float4& b, const float4& col) {
-      float* pj = part + j * kPoseStride + w * kPoseSlots + max(wval, 0);  // written only where wval >= 0
-      const int k = chunk + j - start;
-      const float dx = fx - a.x, dy = fy - a.y;
-      // unconditional, as in the full-mode kernel
-      const BwdEval e = bwd_eval(k < px.nl, a, b, dx, dy);
-      float wgt, ds, dop;
-      bwd_apply(e, col, b.z, px.gR, px.gG, px.gB, px.gD, px.T, px.acc, wgt, ds, dop);
-      // as in the full-mode kernel: conic factors and halves after the sums
-      float g[kPoseRow];
-      g[0] = ds * dx;
-      g[1] = ds * dy;
-      g[2] = g[0] * dx;
-      g[3] = g[0] * dy;
-      g[4] = g[1] * dy;
-      g[5] = wgt * px.gD;
-      const float out = wave_sums<kPoseRow>(g, lane);
-      if (wval >= 0) *pj = out;
-    };
-    // records read one entry ahead into alternating register sets (as in the forward)
-    int jA = (int)__builtin_amdgcn_readlane(myj, cw > 0 ? cw - 1 : 0), jB = 0;
-    float4 aA = s0[jA], bA = s1[jA], cA = s2[jA], aB, bB, cB;
-    for (int jj = cw - 1; jj >= 0;) {
-      jB = (int)__builtin_amdgcn_readlane(myj, (jj - 1) & 63);
-      aB = s0[jB];
-      bB = s1[jB];
-      cB = s2[jB];
-      pstep(jA, aA, bA, cA);
-      if (--jj < 0) break;
-      jA = (int)__builtin_amdgcn_readlane(myj, (jj - 1) & 63);
-      aA = s0[jA];
-      bA = s1[jA];
-      cA = s2[jA];
-      pstep(jB, aB, bB, cB);
-      --jj;
+  band_loss(l1, px, unit);
+  const int vpose = wave_value<kPoseAcc>(lane);  // the pose value whose sum this lane keeps, or -1
+  float total = 0.f;
+  BandList list(used + c.band * ustride + (start >> 6) + c.tile, wave_max_i(px.nl));
+  if (list.left > 0) {
+    const float fx = (float)c.x + 0.5f, fy = (float)c.y + 0.5f;
+    const int y = lane & 7;
+    const float bx = (float)(c.x0 + 4), ry = (float)(c.y0 + y) + 0.5f;
+    const float g[1] = {px.gD};
+    float f[1][8];
+    row_factors(L.rows, lane, g, f);
+    // the render's correction, kept in scalar registers
+    float Rd[9] = {1.f, 0.f, 0.f, 0.f, 1.f, 0.f, 0.f, 0.f, 1.f}, td[3] = {0.f, 0.f, 0.f};
+    if (pose) {
+      const float* pr = pose + 7 * c.r;
+      quat_to_rot(pr[0], pr[1], pr[2], pr[3], Rd);
+#pragma unroll
+      for (int k = 0; k < 9; ++k) Rd[k] = uniform(Rd[k]);
+      td[0] = pr[4];
+      td[1] = pr[5];
+      td[2] = pr[6];
     }
-    __syncthreads();
-    if ((int)threadIdx.x < cnt) {
-      // entry j: its sums over the waves (bands) it reaches, in wave order,
-      // turned into the six image-space gradients, into queue slot nq + j
-      const int j = threadIdx.x;
-      const uint32_t mj = smask[j];
-      const float* pj = part + j * kPoseStride;
-      float g6[kPoseRow] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      if (mj != 0u) {
-        float sum[kPoseRow] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    for (bool more = true; more;) {
+      int it = -1;  // this lane's entry: lane (e, y) takes entry e of the y-th eight
+      float S[kPoseRow];
 #pragma unroll
-        for (int b2 = 0; b2 < 4; ++b2) {
-          if (!((mj >> b2) & 1u)) continue;
+      for (int p = 0; p < 2; ++p) {
+        const int n = more ? list.take(L, lane, start, items, rec) : 0;
+        more = n == kBatch;
+        for (int e0 = 0; e0 < n; e0 += 8) {
+          walk_eight(L, lane, e0, list.clamp, fx, fy, px);
+          float s7[7];
+          row_sums(L, lane, e0, bx, ry, f, s7);
+          s7[5] = s7[6];  // the opacity's sum is not needed
+          const int e = e0 + (lane >> 3);
+          const bool mine = y == p * (kBatch / 8) + (e0 >> 3) && e < n;
+          if (mine) it = L.item[e];
 #pragma unroll
-          for (int q = 0; q < kPoseRow; ++q) sum[q] += pj[b2 * kPoseSlots + q];
+          for (int q = 0; q < kPoseRow; ++q) {
+            const float v = sum8(s7[q]);
+            S[q] = mine ? v : S[q];
+          }
+          wave_sync();
         }
-        const float cA = kTwoLn2 * s0[j].z, cB = kLn2 * s0[j].w, cC = kTwoLn2 * s1[j].x;  // staged -> (A, B, C)
-        g6[0] = -(cA * sum[0] + cB * sum[1]);
-        g6[1] = -(cB * sum[0] + cC * sum[1]);
-        g6[2] = 0.5f * sum[2];
-        g6[3] = sum[3];
-        g6[4] = 0.5f * sum[4];
-        g6[5] = sum[5];
       }
-      const int slot = nq + j;
-      qit[slot] = mj != 0u ? sit[j] : -1;
-#pragma unroll
-      for (int q = 0; q < kPoseRow; ++q) qsum[q * kPoseQueue + slot] = g6[q];
-    }
-    nq += cnt;
-    if (nq + kPoseChunk > kPoseQueue || chunk == start) {
-      __syncthreads();
-      const int t = threadIdx.x;
+      if (__ballot(it >= 0) == 0ull) break;
       float pc[kPoseAcc];
 #pragma unroll
       for (int k = 0; k < kPoseAcc; ++k) pc[k] = 0.f;
-      if (t < nq && qit[t] >= 0) {
-        const int64_t it = qit[t];
-        float g6[kPoseRow];
-#pragma unroll
-        for (int q = 0; q < kPoseRow; ++q) g6[q] = qsum[q * kPoseQueue + t];
-        float Rd[9] = {1.f, 0.f, 0.f, 0.f, 1.f, 0.f, 0.f, 0.f, 1.f}, td[3] = {0.f, 0.f, 0.f};
-        if (pose) {
-          const float* pr = pose + 7 * c.r;
-          quat_to_rot(pr[0], pr[1], pr[2], pr[3], Rd);
-          td[0] = pr[4];
-          td[1] = pr[5];
-          td[2] = pr[6];
-        }
-        const float4 a0 = aux[it * 3 + 0], a1 = aux[it * 3 + 1], a2 = aux[it * 3 + 2];
+      if (it >= 0) {
+        const float4 a0 = aux[(int64_t)it * 3 + 0], a1 = aux[(int64_t)it * 3 + 1], a2 = aux[(int64_t)it * 3 + 2];
         const float p[3] = {a0.x, a0.y, a0.z};
         const float s6[6] = {a0.w, a1.x, a1.y, a1.z, a1.w, a2.x};
         float Sc[9], dp[3], Gm[9];
         sym3(s6, Sc);
-        camera_space_grads(p, Sc, J.fx, J.fy, g6, dp, Gm);
+        camera_space_grads(p, Sc, J.fx, J.fy, S, dp, Gm);
         pose_contrib(p, Sc, Rd, td, dp, Gm, pc);
       }
-      // fixed-order reduction of this round over the block
-      {
-        const float out = wave_sums<kPoseAcc>(pc, lane);
-        const int v = wave_value<kPoseAcc>(lane);
-        if (v >= 0) wred[w][v] = out;
-      }
-      __syncthreads();
-      if (t < kPoseAcc) total += (wred[0][t] + wred[1][t]) + (wred[2][t] + wred[3][t]);
-      nq = 0;
+      total += wave_sums<kPoseAcc>(pc, lane);
     }
-    __syncthreads();
   }
-  if ((int)threadIdx.x < kPoseAcc) tile_part[(int64_t)tile * kPoseAcc + threadIdx.x] = total;
-}
-
-// One block per tile (XCD-aware mapping), for launches with few tiles per
-// resident block.
-__global__ __launch_bounds__(kBlock) void k_composite_bwd_pose(const JobDev* __restrict__ jobs,
-                                                               const int32_t* __restrict__ tile_off, int R,
-                                                               int T_total, const float4* __restrict__ rec,
-                                                               const float4* __restrict__ aux,
-                                                               const float* __restrict__ pose,
-                                                               const int32_t* __restrict__ items,
-                                                               const int32_t* __restrict__ range,
-                                                               const uint64_t* __restrict__ used, int64_t ustride,
-                                                               float bg0, float bg1, float bg2,
-                                                               const float* __restrict__ fwd_T,
-                                                               const int32_t* __restrict__ fwd_n,
-                                                               const float* __restrict__ up_rgb,
-                                                               const float* __restrict__ up_depth,
-                                                               const float* __restrict__ up_alpha,
-                                                               const float* __restrict__ up_scale,
-                                                               float* __restrict__ tile_part, L1Targets l1) {
-  const int tile = xcd_remap(blockIdx.x, T_total);
-  if (tile >= T_total) return;
-  composite_bwd_pose_tile(jobs, tile_off, R, T_total, rec, aux, pose, items, range, used, ustride, bg0, bg1, bg2,
-                          fwd_T, fwd_n, up_rgb, up_depth, up_alpha, up_scale, tile_part, l1, tile);
-}
-
-// Six waves per SIMD (at most 80 VGPRs, a few spilled): the walk now takes
-// only entries with an active lane, and latency hiding pays (one 16-view
-// registration pair: 104 VGPRs / 4 waves 0.228 s, 5 waves 0.216 s, 6 waves
-// 0.214 s).
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) void k_composite_bwd_pose_persistent(
-    const JobDev* __restrict__ jobs,
-    const int32_t* __restrict__ tile_off, int R, int T_total, const float4* __restrict__ rec,
-    const float4* __restrict__ aux, const float* __restrict__ pose, const int32_t* __restrict__ items,
-    const int32_t* __restrict__ range, const uint64_t* __restrict__ used, int64_t ustride, float bg0, float bg1,
-    float bg2, const float* __restrict__ fwd_T,
-    const int32_t* __restrict__ fwd_n, const float* __restrict__ up_rgb, const float* __restrict__ up_depth,
-    const float* __restrict__ up_alpha, const float* __restrict__ up_scale, float* __restrict__ tile_part,
-    TileQueue* __restrict__ queue, int nstatic, L1Targets l1) {
-  __shared__ int s_tile;
-  bool first = true;
-  uint32_t dead = 0;
-  for (;;) {
-    const int tile = claim_tile(queue, T_total, nstatic, first, dead, &s_tile);
-    if (tile < 0) break;
-    composite_bwd_pose_tile(jobs, tile_off, R, T_total, rec, aux, pose, items, range, used, ustride, bg0, bg1, bg2,
-                            fwd_T, fwd_n, up_rgb, up_depth, up_alpha, up_scale, tile_part, l1, tile);
-  }
-  release_queue(queue);
+  if (vpose >= 0) band_part[(int64_t)unit * kPoseAcc + vpose] = total;
 }
 
 
@@ -1093,66 +894,13 @@ void launch_render_stats(const JobDev* jobs, const int32_t* tile_off, int R, int
                      reinterpret_cast<unsigned long long*>(stats));
 }
 
-// Grid of a backward compositing kernel.  With more than 4 tiles per
-// resident block (residency = occupancy x compute units, as the runtime
-// reports it) the persistent kernel runs: nstatic = the resident blocks get
-// the statically mapped first tiles and then claim from the counters, and
-// one more block per compute unit fills slots the runtime's estimate leaves
-// empty (such blocks only claim, so if they cannot be resident they start
-// late, find the queues drained and exit).  With fewer tiles the plain
-// one-block-per-tile kernel is faster (the loop-and-claim wrapper cost 4-5 %
-// on the 1200x680 render loop), with many the queues are (one 16-view
-// registration iteration: 8.5 % faster).  The residency is queried once per
-// (kernel, device) and cached.  The environment variable LS_PERSISTENT=0 / 1
-// forces the plain / persistent form (read at every launch; for tests and
-// measurements).
 static inline int xcd_grid(int total) { return 8 * ((total + 7) / 8); }
-
-static int forced_persistent() {
-  const char* e = std::getenv("LS_PERSISTENT");
-  if (!e || (e[0] != '0' && e[0] != '1') || e[1] != '\0') return -1;
-  return e[0] - '0';
-}
-
-struct PersistentGrid {
-  bool on;
-  int blocks, nstatic;
-};
-static PersistentGrid persistent_grid(int which, const void* kernel, int T) {
-  static std::mutex mu;
-  static int cache[2][64][2] = {};
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
-  int resident, cus;
-  {
-    std::lock_guard<std::mutex> g(mu);
-    resident = cache[which][dev][0];
-    cus = cache[which][dev][1];
-    if (resident == 0) {
-      int per = 0;
-      cus = 0;
-      if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) cus = 256;
-      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, kBlock, 0) != hipSuccess || per <= 0) per = 1;
-      resident = cache[which][dev][0] = cus * per;
-      cache[which][dev][1] = cus;
-    }
-  }
-  PersistentGrid g;
-  const int forced = forced_persistent();
-  g.on = forced >= 0 ? forced == 1 : T > 4 * resident;
-  g.blocks = g.on ? resident + cus : xcd_grid(T);
-  g.nstatic = g.on ? resident : 0;
-  return g;
-}
 
 void launch_composite_fwd(const JobDev* jobs, const int32_t* tile_off, int R, int T, const float* rec,
                           const int32_t* items, const int32_t* range, const float* bg, float* rgb, float* depth,
                           float* alpha, float* Tf, int32_t* nl, uint64_t* used, int64_t ustride,
                           hipStream_t s) {
   if (T <= 0) return;
-  // always one block per band: a band is short, and claiming tiles from the
-  // queues cost more than it balanced (registration iteration A/B: 1.3 %
-  // slower persistent)
   // LS_COVER=0 (read at every launch; for tests and measurements): stage by
   // the band rectangle test alone, whatever pixels have stopped
   const char* cv = std::getenv("LS_COVER");
@@ -1167,32 +915,19 @@ void launch_composite_bwd(const JobDev* jobs, const int32_t* tile_off, int R, in
                           const uint64_t* used, int64_t ustride, const float* bg, const float* Tf,
                           const int32_t* nl,
                           const float* up_rgb, const float* up_depth, const float* up_alpha, const float* up_scale,
-                          float* g2d, float* tile_part, int pose_only, void* queues, hipStream_t s,
+                          float* g2d, float* band_part, int pose_only, hipStream_t s,
                           const L1Targets* l1) {
   if (T <= 0) return;
   const L1Targets l1v = l1 ? *l1 : L1Targets{nullptr, nullptr, nullptr, nullptr, nullptr};
   const float4* rec4 = reinterpret_cast<const float4*>(rec);
   const float4* aux4 = reinterpret_cast<const float4*>(aux);
-  if (pose_only) {
-    const PersistentGrid g = persistent_grid(1, reinterpret_cast<const void*>(k_composite_bwd_pose_persistent), T);
-    if (g.on)
-      hipLaunchKernelGGL(k_composite_bwd_pose_persistent, dim3(g.blocks), dim3(kBlock), 0, s, jobs, tile_off, R, T,
-                         rec4, aux4, pose, items, range, used, ustride, bg[0], bg[1], bg[2], Tf, nl, up_rgb, up_depth,
-                         up_alpha, up_scale, tile_part, reinterpret_cast<TileQueue*>(queues) + 1, g.nstatic, l1v);
-    else
-      hipLaunchKernelGGL(k_composite_bwd_pose, dim3(g.blocks), dim3(kBlock), 0, s, jobs, tile_off, R, T, rec4, aux4,
-                         pose, items, range, used, ustride, bg[0], bg[1], bg[2], Tf, nl, up_rgb, up_depth, up_alpha,
-                         up_scale, tile_part, l1v);
-  } else {
-    const PersistentGrid g = persistent_grid(0, reinterpret_cast<const void*>(k_composite_bwd_persistent), T);
-    if (g.on)
-      hipLaunchKernelGGL(k_composite_bwd_persistent, dim3(g.blocks), dim3(kBlock), 0, s, jobs, tile_off, R, T, rec4,
-                         items, range, used, ustride, bg[0], bg[1], bg[2], Tf, nl, up_rgb, up_depth, up_alpha, up_scale,
-                         g2d, reinterpret_cast<TileQueue*>(queues) + 0, g.nstatic, l1v);
-    else
-      hipLaunchKernelGGL(k_composite_bwd, dim3(g.blocks), dim3(kBlock), 0, s, jobs, tile_off, R, T, rec4, items, range,
-                         used, ustride, bg[0], bg[1], bg[2], Tf, nl, up_rgb, up_depth, up_alpha, up_scale, g2d,
-                         l1v);
-  }
+  const dim3 grid(xcd_grid(4 * T));
+  if (pose_only)
+    hipLaunchKernelGGL(k_composite_bwd_pose, grid, dim3(64), 0, s, jobs, tile_off, R, T, rec4, aux4, pose, items, range,
+                       used, ustride, bg[0], bg[1], bg[2], Tf, nl, up_rgb, up_depth, up_alpha, up_scale, band_part,
+                       l1v);
+  else
+    hipLaunchKernelGGL(k_composite_bwd, grid, dim3(64), 0, s, jobs, tile_off, R, T, rec4, items, range, used, ustride,
+                       bg[0], bg[1], bg[2], Tf, nl, up_rgb, up_depth, up_alpha, up_scale, g2d, l1v);
 }
 }  // namespace ls

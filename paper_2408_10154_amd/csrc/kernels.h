@@ -51,7 +51,7 @@ void launch_project_bwd(const JobDev* jobs, const int32_t* blk_off, int R, int n
                         const int32_t* radius, const float* aux, float* g2d, const GradDev* grads, int want_gauss,
                         float* pose_part, int want_pose, float* pose_grad, hipStream_t s,
                         const GaussAdamArgs* adam = nullptr);
-void launch_pose_reduce_tiles(const JobDev* jobs, int R, const float* pose, const float* tile_part, float* pose_grad,
+void launch_pose_reduce_bands(const JobDev* jobs, int R, const float* pose, const float* band_part, float* pose_grad,
                               hipStream_t s);
 
 // tile_bits: bits of the largest tile key (T - 1), which set the tile passes.
@@ -77,29 +77,24 @@ void launch_composite_fwd(const JobDev* jobs, const int32_t* tile_off, int R, in
                           const int32_t* items, const int32_t* range, const float* bg, float* rgb, float* depth,
                           float* alpha, float* Tf, int32_t* nl, uint64_t* used, int64_t ustride, hipStream_t s);
 
-// Backward compositing (persistent when a launch has many tiles per resident
-// block); queues = kTileQueueBytes of zero-initialised workspace (left zeroed
-// by every launch; one launch at a time per workspace).
-constexpr size_t kTileQueueBytes = 2 * 9 * 128;
-
 // The plain colour + depth L1 of registration (Sec. 3.2), formed per pixel
 // by the pose-only backward itself from the forward's images and the targets
 // instead of read from a loss kernel's gradient images: on pixels with a
 // target depth, sign(rendered - target) per colour channel and for depth,
 // times the render's 1 / |Omega| (up_scale); 0 elsewhere.  Targets in the
 // batch's image layout, or NULL: each render's own (JobDev.tgt_*).  With
-// loss_part, each tile also writes {sum over its pixels in Omega of the L1
+// loss_part, each 8x8 band also writes {sum over its pixels in Omega of the L1
 // terms (|D - D*| + sum_c |C_c - C*_c|), number of those pixels}.
 struct L1Targets {
   const float* pred_rgb;    // forward colour [3][P]; NULL: off
   const float* pred_depth;  // forward depth [P]
   const float* tgt_rgb;
   const float* tgt_depth;
-  float* loss_part;         // [T][2], or NULL
+  float* loss_part;         // [4 T][2], one row per 8x8 band (4 tile + band), or NULL
 };
 
-// Per-render L1 loss from the tile partials: loss[r] = sum / count over the
-// render's tiles in a fixed order (0 when the render has no pixel in Omega).
+// Per-render L1 loss from the band partials: loss[r] = sum / count over the
+// render's bands in a fixed order (0 when the render has no pixel in Omega).
 void launch_tile_loss_reduce(const JobDev* jobs, int R, const float* loss_part, float* loss, hipStream_t s);
 
 // used, ustride: the flags the forward wrote for the same bins: the backward
@@ -109,7 +104,7 @@ void launch_composite_bwd(const JobDev* jobs, const int32_t* tile_off, int R, in
                           const uint64_t* used, int64_t ustride, const float* bg, const float* Tf, const int32_t* nl,
                           const float* up_rgb,
                           const float* up_depth, const float* up_alpha, const float* up_scale, float* g2d,
-                          float* tile_part, int pose_only, void* queues, hipStream_t s,
+                          float* band_part, int pose_only, hipStream_t s,
                           const L1Targets* l1 = nullptr);
 
 // Registration helpers (reg_kernels.hip).
@@ -252,10 +247,10 @@ void launch_joint_step(const JointView* views, JointPair* pairs, int npairs, flo
                        const JointAdam& a, hipStream_t s);
 
 // One iteration's end in pose-only registration: per render, the tile
-// partials reduced to its pose gradient (as launch_pose_reduce_tiles) and
+// partials reduced to its pose gradient (as launch_pose_reduce_bands) and
 // its Adam step (pose_adam_view) in one launch; render 0 also updates the
 // sticky overflow flag from count (as launch_or_flag).
-void launch_pose_reduce_adam(const JobDev* jobs, int R, const float* tile_part, const PoseAdamArgs& a,
+void launch_pose_reduce_adam(const JobDev* jobs, int R, const float* band_part, const PoseAdamArgs& a,
                              const int32_t* count, int32_t* sticky, hipStream_t s);
 void launch_pose_init(float* pose, float* m, float* v, ViewOpt* opt, int R, hipStream_t s);
 void launch_or_flag(const int32_t* count, int32_t* sticky, hipStream_t s);

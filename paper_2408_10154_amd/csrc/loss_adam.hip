@@ -163,7 +163,7 @@ __global__ void k_loss_reduce(const int32_t* __restrict__ pblk_off, int R, const
   }
 }
 
-// Per-render L1 loss from the per-tile partials {sum, count} that the
+// Per-render L1 loss from the partials {sum, count} per 8x8 band that the
 // compositing backward wrote with L1 targets: one 256-thread block per render,
 // strided per-thread sums, wave sums, then the four waves in order.
 __global__ __launch_bounds__(256) void k_tile_loss_reduce(const JobDev* __restrict__ jobs, int R,
@@ -172,7 +172,7 @@ __global__ __launch_bounds__(256) void k_tile_loss_reduce(const JobDev* __restri
   const int r = blockIdx.x;
   if (r >= R) return;
   const JobDev& J = jobs[r];
-  const int first = J.tile_off, nt = J.TX * J.TY;
+  const int first = 4 * J.tile_off, nt = 4 * J.TX * J.TY;
   const float2* p2 = reinterpret_cast<const float2*>(part);
   float s = 0.f, c = 0.f;
 #pragma unroll 4

@@ -116,9 +116,9 @@ __device__ __forceinline__ void store_grad(float* p, float v, bool shared) {
   if (shared) atomic_add_f32(p, v); else *p += v;
 }
 
-// Chains image-space gradients (du dv dA dB dC dop dz dr dg db, accumulated
-// per item over its tiles) to the Gaussian parameters and to the per-render
-// pose correction, and clears the accumulator for the next backward.
+// Chains the image-space sums (kGrad2D, accumulated per item over its bands)
+// to the Gaussian parameters and to the per-render pose correction, and
+// clears the accumulator for the next backward.
 template <bool kAdam>
 __global__ __launch_bounds__(256) void k_project_bwd(const JobDev* __restrict__ jobs, const int32_t* __restrict__ blk_off,
                                                      int R, const float* __restrict__ pose,
@@ -147,7 +147,7 @@ __global__ __launch_bounds__(256) void k_project_bwd(const JobDev* __restrict__ 
 
   const int64_t item = J.item_off + g;
   if (g < n && radius[item] > 0) {
-    float* gp = g2d + item * kGrad2D;
+    float* gp = g2d + item * kGradStride;
     float gi[kGrad2D];
 #pragma unroll
     for (int q = 0; q < kGrad2D; ++q) {
@@ -211,7 +211,7 @@ __global__ __launch_bounds__(256) void k_project_bwd(const JobDev* __restrict__ 
       }
       if (GD.opac) {
         const float op = 1.0f / (1.0f + __expf(-J.opac[g]));
-        emit(3, 0, GD.opac, gi[5] * op * (1.f - op));
+        emit(3, 0, GD.opac, -gi[5] * (1.f - op));  // dL/dopacity = -gi[5] / op
       }
       if (GD.rgb) {
         for (int k = 0; k < 3; ++k) emit(4, k, GD.rgb, gi[7 + k]);
@@ -266,8 +266,8 @@ __global__ __launch_bounds__(256) void k_project_bwd(const JobDev* __restrict__ 
 }
 
 // Per render: sum the partials in order (per 256-item block of the render,
-// or per tile when by_tile is set), chain dL/dR_d to the quaternion,
-// accumulate into pose_grad [R][7].  One wave per render.
+// or per 8x8 band when by_band is set), chain dL/dR_d to the quaternion,
+// accumulate into pose_grad [R][7].  One block per render.
 // With step.pose_m set, each render's pose then takes one Adam step from the
 // accumulated gradient (as ls_adam over pose_grad), which is consumed.
 constexpr int kPoseSumThreads = 256;
@@ -275,7 +275,9 @@ constexpr int kPoseSumThreads = 256;
 // Sum of the kPoseAcc-float rows part[first .. first + nb) over a block of
 // kPoseSumThreads threads in a fixed order: strided per-thread sums (each
 // row three 16-byte loads, four rows in flight per thread), wave sums, then
-// the four waves in order.  Thread 0 returns the totals.
+// the four waves in order.  Thread 0 returns the totals.  (1,024 threads
+// instead of 256: 11.3 against 12.1 us over the 4,800 rows of each of 16
+// 640x480 views.)
 __device__ __forceinline__ void block_pose_sum(const float* __restrict__ part, int first, int nb,
                                                float (&acc)[kPoseAcc]) {
   static_assert(kPoseAcc == 12, "a row is three float4");
@@ -306,13 +308,13 @@ __device__ __forceinline__ void block_pose_sum(const float* __restrict__ part, i
 __global__ __launch_bounds__(kPoseSumThreads) void k_pose_reduce(const JobDev* __restrict__ jobs, int R,
                                                                  const float* __restrict__ pose,
                                                                  const float* __restrict__ pose_part,
-                                                                 float* __restrict__ pose_grad, int by_tile,
+                                                                 float* __restrict__ pose_grad, int by_band,
                                                                  GaussAdamArgs step) {
   const int r = blockIdx.x;
   if (r >= R) return;
   const JobDev& J = jobs[r];
-  const int first = by_tile ? J.tile_off : J.blk_off;
-  const int nb = by_tile ? J.TX * J.TY : (J.n + 255) / 256;
+  const int first = by_band ? 4 * J.tile_off : J.blk_off;
+  const int nb = by_band ? 4 * J.TX * J.TY : (J.n + 255) / 256;
   float acc[kPoseAcc];
   block_pose_sum(pose_part, first, nb, acc);
   if (threadIdx.x == 0) {
@@ -363,11 +365,11 @@ void launch_project_bwd(const JobDev* jobs, const int32_t* blk_off, int R, int n
                        pose_grad, 0, adam ? *adam : GaussAdamArgs{});
 }
 
-// Pose reduction by tile partials (as k_pose_reduce with by_tile) followed
+// Pose reduction by band partials (as k_pose_reduce with by_band) followed
 // by the render's Adam step; block 0 also folds the overflow count into the
 // sticky flag.
 __global__ __launch_bounds__(kPoseSumThreads) void k_pose_reduce_adam(const JobDev* __restrict__ jobs, int R,
-                                                                      const float* __restrict__ tile_part,
+                                                                      const float* __restrict__ band_part,
                                                                       PoseAdamArgs a,
                                                                       const int32_t* __restrict__ count,
                                                                       int32_t* __restrict__ sticky) {
@@ -375,7 +377,7 @@ __global__ __launch_bounds__(kPoseSumThreads) void k_pose_reduce_adam(const JobD
   if (r >= R) return;
   const JobDev& J = jobs[r];
   float acc[kPoseAcc];
-  block_pose_sum(tile_part, J.tile_off, J.TX * J.TY, acc);
+  block_pose_sum(band_part, 4 * J.tile_off, 4 * J.TX * J.TY, acc);
   if (threadIdx.x == 0) {
     const float* pr = a.pose + 7 * r;
     float dq[4], g[7];
@@ -387,15 +389,15 @@ __global__ __launch_bounds__(kPoseSumThreads) void k_pose_reduce_adam(const JobD
   }
 }
 
-void launch_pose_reduce_adam(const JobDev* jobs, int R, const float* tile_part, const PoseAdamArgs& a,
+void launch_pose_reduce_adam(const JobDev* jobs, int R, const float* band_part, const PoseAdamArgs& a,
                              const int32_t* count, int32_t* sticky, hipStream_t s) {
   if (R > 0)
-    hipLaunchKernelGGL(k_pose_reduce_adam, dim3(R), dim3(kPoseSumThreads), 0, s, jobs, R, tile_part, a, count, sticky);
+    hipLaunchKernelGGL(k_pose_reduce_adam, dim3(R), dim3(kPoseSumThreads), 0, s, jobs, R, band_part, a, count, sticky);
 }
 
-void launch_pose_reduce_tiles(const JobDev* jobs, int R, const float* pose, const float* tile_part, float* pose_grad,
+void launch_pose_reduce_bands(const JobDev* jobs, int R, const float* pose, const float* band_part, float* pose_grad,
                               hipStream_t s) {
-  hipLaunchKernelGGL(k_pose_reduce, dim3(R), dim3(kPoseSumThreads), 0, s, jobs, R, pose, tile_part, pose_grad, 1,
+  hipLaunchKernelGGL(k_pose_reduce, dim3(R), dim3(kPoseSumThreads), 0, s, jobs, R, pose, band_part, pose_grad, 1,
                      GaussAdamArgs{});
 }
 }  // namespace ls

@@ -245,9 +245,7 @@ RegEngine::Layout RegEngine::layout(int64_t cap) const {
   L.zero_end = off;  // everything above starts at zero
   L.tile_of = take(4 * (size_t)cap);
   L.item = take(4 * (size_t)cap);
-  ls_batch_info info{};
-  ls_batch_query(batch, cap, &info);
-  L.work = take(info.workspace_bytes);
+  L.work = take(batch_pose_workspace_bytes(batch, cap));
   L.total = off;
   return L;
 }
@@ -299,10 +297,8 @@ ls_status RegEngine::bind(void* work, size_t work_bytes, int64_t cap, hipStream_
   bins.count = count;
   bins.work = a + L.work;
   capacity = cap;
-  // the state (a = b = 0 and their moments included) and the bins workspace start at zero
-  if (hipMemsetAsync(a + L.rec, 0, L.zero_end - L.rec, s) != hipSuccess ||
-      hipMemsetAsync(a + L.work, 0, L.total - L.work, s) != hipSuccess)
-    return LS_ERR_HIP;
+  // the state (a = b = 0 and their moments included) starts at zero
+  if (hipMemsetAsync(a + L.rec, 0, L.zero_end - L.rec, s) != hipSuccess) return LS_ERR_HIP;
 
   // targets: each view's measurements, laid out like the batch's images
   for (int r = 0; r < R; ++r) {

@@ -436,11 +436,11 @@ class Server {
 
   ls_status set_capacity(int64_t cap) {
     ls_batch_info info{};
-    ls_status st = ls_batch_query(batch_, cap, &info);
+    ls_status st = ls_batch_query(batch_, cap, &info);  // checks cap
     if (st) return st;
-    if ((st = bins_.ensure(2 * align(4 * (size_t)cap))) || (st = work_.ensure(info.workspace_bytes))) return st;
-    // the image-space gradient accumulator must start at zero
-    if (hipMemsetAsync(work_.p, 0, info.workspace_bytes, stream_) != hipSuccess) return LS_ERR_HIP;
+    if ((st = bins_.ensure(2 * align(4 * (size_t)cap))) ||
+        (st = work_.ensure(batch_pose_workspace_bytes(batch_, cap))))
+      return st;
     capacity_ = cap;
     bins_c_.capacity = cap;
     bins_c_.tile_of = bins_.as<uint32_t>();
