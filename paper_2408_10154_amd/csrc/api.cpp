@@ -64,7 +64,8 @@ ls_status overlap_check_args(const float* p_mean, int32_t np, const float* q_mea
 namespace {
 
 struct Layout {
-  size_t dk0, dv0, dk1, dv1, hist, bsum, tk, tv, band_part, pose_part, loss_part, used, g2d, total;
+  size_t k0, v0, k1, v1, hist, blk_cnt, kept, cnt, tile_total, tile_start, blk_total, band_part, pose_part, loss_part, used, g2d,
+      total;
 };
 
 Layout layout_of(const ls_batch* b, int64_t cap) {
@@ -76,19 +77,18 @@ Layout layout_of(const ls_batch* b, int64_t cap) {
     return o;
   };
   const int64_t M = b->M;
-  const int64_t nbd = sort_blocks(M);
-  const int64_t nbt = sort_blocks(cap);
-  L.dk0 = take(4 * M);
-  L.dv0 = take(4 * M);
-  L.dk1 = take(4 * M);
-  L.dv1 = take(4 * M);
-  // digit histograms; after the depth sort, the first tile pass's histogram
-  // followed by the first item of each emission span
-  L.hist = take(4 * std::max<int64_t>({(int64_t)(1 << kDepthDigitBits) * nbd,
-                                        (int64_t)(1 << kTileDigitBits) * nbt + emit_spans(cap), 256}));
-  L.bsum = take(4 * (nbd + 8 + kMaxSortBins + 8));  // block sums, then the digit totals
-  L.tk = take(4 * cap);
-  L.tv = take(4 * cap);
+  const size_t T = (size_t)std::max(b->T, 1);
+  L.k0 = take(4 * M);
+  L.v0 = take(4 * M);
+  L.k1 = take(4 * M);
+  L.v1 = take(4 * M);
+  L.hist = take(4 * (size_t)seg_hist_words(b->sort_blocks));
+  L.blk_cnt = take(4 * (size_t)b->sort_blocks);
+  L.kept = take(4 * (size_t)b->R);
+  L.cnt = take(4 * (size_t)b->bincnt_off[b->R]);
+  L.tile_total = take(4 * T);
+  L.tile_start = take(4 * T);
+  L.blk_total = take(8 * ((T + 63) / 64));
   L.band_part = take(4 * 4 * (size_t)kPoseAcc * std::max(b->T, 1));  // a row per 8x8 band
   L.pose_part = take(4 * (size_t)kPoseAcc * std::max(b->nblk_items, 1));
   L.loss_part = take(4 * 8 * (size_t)std::max(b->T, 1));  // per 8x8 band {L1 sum, pixels in Omega}
@@ -183,7 +183,8 @@ ls_status batch_loss_tracking(const ls_batch* b, const ls_image* pred, const ls_
 
 // Device tables of a batch, in the order they are carved from one region.
 struct BatchTables {
-  size_t jobs, item_off, tile_off, blk_off, pblk_off, sblk_off, loss_part, map_part, grads, sel, median, total;
+  size_t jobs, item_off, tile_off, blk_off, pblk_off, sblk_off, sortblk_off, binwork_off, bincnt_off, loss_part,
+      map_part, grads, sel, median, total;
 };
 
 static BatchTables batch_tables(const ls_batch* b) {
@@ -201,6 +202,9 @@ static BatchTables batch_tables(const ls_batch* b) {
   t.blk_off = take(4 * R1);
   t.pblk_off = take(4 * R1);
   t.sblk_off = take(4 * R1);
+  t.sortblk_off = take(4 * R1);
+  t.binwork_off = take(4 * R1);
+  t.bincnt_off = take(8 * R1);
   t.loss_part = take(8 * (size_t)std::max(b->nblk_pix, 1));
   t.map_part = take(4 * (3 * (size_t)b->nblk_ssim + b->R));
   t.grads = take(sizeof(GradDev) * b->R);
@@ -281,9 +285,36 @@ static ls_status batch_host(const ls_render_job* jobs, int32_t R, ls_batch** out
   b->nblk_items = b->blk_off[R];
   b->nblk_pix = b->pblk_off[R];
   b->nblk_ssim = b->sblk_off[R];
-  int bits = 0;
-  while (bits < 32 && ((int64_t)1 << bits) < (int64_t)b->T) ++bits;
-  b->tile_bits = bits;
+  // binning: radix sort blocks; then chunks of sorted items with their tile
+  // windows and count matrices, at most about 4,096 chunks (half as many for
+  // 16 renders of 150k and 120k items: lists 67 -> 101 us) and 16 M counts
+  // (64 MiB, 20 us to write and 40 us to scan; only large images reach it)
+  b->bin_chunk = 512;
+  const auto counts = [&] {
+    int64_t n = 0;
+    for (const JobDev& d : b->jobs_h) n += (int64_t)ls::bin_chunks(d.n, b->bin_chunk, R) * d.TX * d.TY;
+    return n;
+  };
+  while (b->bin_chunk < 1 << 20 && (b->M / b->bin_chunk > 4096 || counts() > 1 << 24)) b->bin_chunk *= 2;
+  b->sortblk_off.assign(R + 1, 0);
+  b->binwork_off.assign(R + 1, 0);
+  b->bincnt_off.assign(R + 1, 0);
+  int64_t units = 0;
+  for (int r = 0; r < R; ++r) {
+    const JobDev& d = b->jobs_h[r];
+    const int64_t chunks = ls::bin_chunks(d.n, b->bin_chunk, R);
+    b->max_items = std::max(b->max_items, d.n);
+    b->sortblk_off[r + 1] = b->sortblk_off[r] + (d.n + kSortKeys - 1) / kSortKeys;
+    units += chunks * ls::windows_of(d.TX, d.TY);
+    if (units > INT32_MAX / 2) {
+      delete b;
+      return fail(LS_ERR_INVALID, "batch too large (binning work units exceed int32)");
+    }
+    b->binwork_off[r + 1] = (int32_t)units;
+    b->bincnt_off[r + 1] = b->bincnt_off[r] + chunks * ((int64_t)d.TX * d.TY);
+  }
+  b->sort_blocks = b->sortblk_off[R];
+  b->bin_units = (int)units;
   *out = b;
   return LS_OK;
 }
@@ -317,6 +348,9 @@ ls_status batch_bind(ls_batch* b, void* mem, size_t mem_bytes, hipStream_t s) {
   b->blk_off_d = reinterpret_cast<int32_t*>(base + t.blk_off);
   b->pblk_off_d = reinterpret_cast<int32_t*>(base + t.pblk_off);
   b->sblk_off_d = reinterpret_cast<int32_t*>(base + t.sblk_off);
+  b->sortblk_off_d = reinterpret_cast<int32_t*>(base + t.sortblk_off);
+  b->binwork_off_d = reinterpret_cast<int32_t*>(base + t.binwork_off);
+  b->bincnt_off_d = reinterpret_cast<int64_t*>(base + t.bincnt_off);
   b->loss_part_d = reinterpret_cast<float*>(base + t.loss_part);
   b->map_part_d = reinterpret_cast<float*>(base + t.map_part);
   b->grads_d = reinterpret_cast<GradDev*>(base + t.grads);
@@ -330,6 +364,9 @@ ls_status batch_bind(ls_batch* b, void* mem, size_t mem_bytes, hipStream_t s) {
       hipMemcpyAsync(b->blk_off_d, b->blk_off.data(), 4 * (R + 1), hipMemcpyHostToDevice, s) == hipSuccess &&
       hipMemcpyAsync(b->pblk_off_d, b->pblk_off.data(), 4 * (R + 1), hipMemcpyHostToDevice, s) == hipSuccess &&
       hipMemcpyAsync(b->sblk_off_d, b->sblk_off.data(), 4 * (R + 1), hipMemcpyHostToDevice, s) == hipSuccess &&
+      hipMemcpyAsync(b->sortblk_off_d, b->sortblk_off.data(), 4 * (R + 1), hipMemcpyHostToDevice, s) == hipSuccess &&
+      hipMemcpyAsync(b->binwork_off_d, b->binwork_off.data(), 4 * (R + 1), hipMemcpyHostToDevice, s) == hipSuccess &&
+      hipMemcpyAsync(b->bincnt_off_d, b->bincnt_off.data(), 8 * (R + 1), hipMemcpyHostToDevice, s) == hipSuccess &&
       hipMemsetAsync(b->sel_d, 0, 4 * (size_t)ls::sel_words(R), s) == hipSuccess &&
       hipMemsetAsync(b->median_d, 0, 4 * (size_t)R, s) == hipSuccess;
   if (!ok || (!mem && hipStreamSynchronize(s) != hipSuccess))
@@ -479,10 +516,35 @@ ls_status ls_bin_sort(const ls_batch* b, const ls_projected* p, const ls_bins* b
     launch_fill_i32(bins->range, 2 * (int64_t)b->T, 0, s);
     return hip_check("ls_bin_sort");
   }
-  launch_bin_sort(b->jobs_d, b->item_off_d, b->R, b->M, b->T, b->tile_bits, p->rec, p->radius, p->tiles,
-                  bins->capacity, bins->tile_of, bins->item, bins->range, bins->count, at<uint32_t>(w, L.dk0),
-                  at<uint32_t>(w, L.dv0), at<uint32_t>(w, L.dk1), at<uint32_t>(w, L.dv1), at<uint32_t>(w, L.hist),
-                  at<uint32_t>(w, L.bsum), at<uint32_t>(w, L.tk), at<uint32_t>(w, L.tv), s);
+  BinLaunch bl{};
+  bl.jobs = b->jobs_d;
+  bl.item_off = b->item_off_d;
+  bl.tile_off = b->tile_off_d;
+  bl.tab = BinTables{b->sortblk_off_d, b->binwork_off_d, b->bincnt_off_d, b->R, b->bin_chunk};
+  bl.T = b->T;
+  bl.max_items = b->max_items;
+  bl.sort_blocks = b->sort_blocks;
+  bl.units = b->bin_units;
+  bl.rec = p->rec;
+  bl.radius = p->radius;
+  bl.tiles = p->tiles;
+  bl.cap = bins->capacity;
+  bl.k0 = at<uint32_t>(w, L.k0);
+  bl.v0 = at<uint32_t>(w, L.v0);
+  bl.k1 = at<uint32_t>(w, L.k1);
+  bl.v1 = at<uint32_t>(w, L.v1);
+  bl.hist = at<uint32_t>(w, L.hist);
+  bl.blk_cnt = at<int32_t>(w, L.blk_cnt);
+  bl.kept = at<int32_t>(w, L.kept);
+  bl.cnt = at<uint32_t>(w, L.cnt);
+  bl.tile_total = at<uint32_t>(w, L.tile_total);
+  bl.tile_start = at<uint32_t>(w, L.tile_start);
+  bl.blk_total = at<uint64_t>(w, L.blk_total);
+  bl.tile_of = bins->tile_of;
+  bl.item = bins->item;
+  bl.range = bins->range;
+  bl.count = bins->count;
+  launch_bin_sort(bl, s);
   return hip_check("ls_bin_sort");
 }
 

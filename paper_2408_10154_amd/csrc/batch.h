@@ -16,17 +16,24 @@ struct ls_batch {
   int nblk_items = 0;
   int nblk_pix = 0;
   int nblk_ssim = 0;  // mapping-loss SSIM blocks (3 channels x 32x32 tiles per render)
-  int tile_bits = 0;  // bits of the largest tile key
+  int max_items = 0;      // most items of a render
+  int sort_blocks = 0;    // radix sort blocks over all renders
+  int bin_chunk = 0;      // sorted items per binning chunk
+  int bin_units = 0;      // binning work units (chunk x tile window) over all renders
   int device = 0;
   std::vector<JobDev> jobs_h;
   std::vector<int64_t> item_off, pix_off;
-  std::vector<int32_t> tile_off, blk_off, pblk_off, sblk_off;
+  std::vector<int32_t> tile_off, blk_off, pblk_off, sblk_off, sortblk_off, binwork_off;
+  std::vector<int64_t> bincnt_off;
   JobDev* jobs_d = nullptr;
   int64_t* item_off_d = nullptr;
   int32_t* tile_off_d = nullptr;
   int32_t* blk_off_d = nullptr;
   int32_t* pblk_off_d = nullptr;
   int32_t* sblk_off_d = nullptr;
+  int32_t* sortblk_off_d = nullptr;
+  int32_t* binwork_off_d = nullptr;
+  int64_t* bincnt_off_d = nullptr;
   float* loss_part_d = nullptr;
   float* map_part_d = nullptr;   // mapping loss: 3 floats per SSIM block, then 1/|Omega| per render
   uint32_t* sel_d = nullptr;     // median selection workspace (ls::sel_words(R)), kept zeroed

@@ -1,14 +1,30 @@
-// Tile binning on gfx950: depth keys, LSD radix sorts (stable; 8-bit digits),
-// count scan, instance emission in depth order, tile ranges.
+// Tile binning on gfx950: a depth sort of each render's items and a stable
+// distribution of the sorted items over the render's tiles.
 //
-// Order of the final list: (tile, FP32 depth bits, item).  It is produced as
-// a stable depth sort of the items (ties keep ascending item order), then
-// emission of each item's tiles in that order, then a stable sort of the
-// instances by tile key.
+// Order of the final list: (tile, FP32 depth bits, item).
+//
+//  1. The items with tiles are sorted by depth bits, render by render (LSD
+//     radix sort, 8-bit digits, stable: ties keep ascending item order).  A
+//     render of up to 16,384 items is sorted by one block in LDS, in one
+//     launch; larger ones take a histogram and a scatter per digit, and the
+//     scatter forms its digit bases from the block histograms itself.
+//  2. The sorted items are cut into chunks.  One block per chunk counts the
+//     items of every tile of its render, a scan over the chunks turns the
+//     counts into each chunk's first place in each tile's list, and one block
+//     per chunk then writes the instances straight to their final places.
+//
+// Every instance is written once, and no (tile, item) pairs are sorted: the
+// pair sort it replaces moved each instance three times in 8 launches (all of
+// binning: 200k items, 1200 x 680, 143 -> 100 us and 22 launches -> 12; eight
+// renders of 150k items, 640 x 480, 157 -> 118 us; 4,096 items, 160 x 120,
+// 81 -> 38 us and 5 launches).  What is left is bound by latency: launches of
+// 3 to 10 us on tens to hundreds of blocks, each a chain of dependent loads.
 #include "common.h"
 
 #include <algorithm>
 #include <cstdlib>
+
+#include "kernels.h"
 
 namespace ls {
 
@@ -18,349 +34,18 @@ __global__ void k_fill_i32(int32_t* __restrict__ p, int64_t n, int32_t v) {
   for (int64_t k = i; k < n; k += stride) p[k] = v;
 }
 
-__device__ __forceinline__ int sort_count(const int32_t* n_dev, int64_t n_static, int64_t cap) {
-  int64_t n = n_static;
-  if (n_dev) n = min((int64_t)n_dev[0], cap);
-  return (int)n;
-}
+// ---------------------------------------------------------------------------
+// Segmented stable radix sort: segment s holds its (key, value) pairs at
+// base[s] .. base[s] + len[s] (len on the device) and owns the sort blocks
+// blk_off[s] .. blk_off[s + 1), kSortKeys keys each, of which those with keys
+// work.
 
-// Sort blocks that hold keys (n keys, rounds x 256 per block): the histogram
-// columns of later blocks are neither written nor read (a capacity sized for
-// the worst case leaves most blocks of a pass idle).
-__device__ __forceinline__ int active_blocks(int n, int rounds) {
-  return (int)(((int64_t)n + (int64_t)rounds * kSortThreads - 1) / ((int64_t)rounds * kSortThreads));
-}
-
-// Digit histogram of one sort block's keys (kSortItems registers per thread,
-// rounds of them valid, nb keys in all) into LDS h, then to
-// hist[d * nblocks + block] (digit-major).  Equal digits within a wave are
-// merged before the LDS atomic.
-template <int kBits>
-__device__ __forceinline__ void block_digit_hist(const uint32_t (&key)[kSortItems], int rounds, int nb, int shift,
-                                                 uint32_t* h, uint32_t* __restrict__ hist, int nblocks) {
-  constexpr int kBins = 1 << kBits;
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {
-    if (r < rounds && r * kSortThreads < nb) {  // uniform; a guard, not a break, so the loop unrolls
-      const bool valid = r * kSortThreads + (int)threadIdx.x < nb;
-      const uint32_t d = (key[r] >> shift) & (uint32_t)(kBins - 1);
-      // aggregate equal digits within the wave before touching LDS
-      uint64_t peers = __ballot(valid);
-#pragma unroll
-      for (int b = 0; b < kBits; ++b) {
-        const bool bit = (d >> b) & 1u;
-        const uint64_t m = __ballot(bit);
-        peers &= bit ? m : ~m;
-      }
-      if (valid && lane == (int)__builtin_ctzll(peers)) atomicAdd(&h[d], (uint32_t)__popcll(peers));
-    }
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < kBins; i += kSortThreads) hist[(int64_t)i * nblocks + blockIdx.x] = h[i];
-}
-
-// Per-block digit histogram of kBits-bit digits, stored digit-major:
-// hist[d * nblocks + block], for the blocks that hold keys.  Every key of the
-// block is loaded before any is counted, so the block waits for memory once,
-// not once per round.
-template <int kBits>
-__global__ __launch_bounds__(kSortThreads) void k_sort_hist(const uint32_t* __restrict__ keys, const int32_t* n_dev,
-                                                            int64_t n_static, int64_t cap, int shift,
-                                                            uint32_t* __restrict__ hist, int nblocks, int rounds) {
-  constexpr int kBins = 1 << kBits;
-  __shared__ uint32_t h[kBins];
-  const int n = sort_count(n_dev, n_static, cap);
-  const int64_t base = (int64_t)blockIdx.x * rounds * kSortThreads;
-  if (base >= n) return;  // uniform for the block: no keys, no column
-  for (int i = threadIdx.x; i < kBins; i += kSortThreads) h[i] = 0;
-  const int nb = (int)min((int64_t)rounds * kSortThreads, (int64_t)n - base);
-  uint32_t key[kSortItems];
-#pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {
-    const int i = r * kSortThreads + threadIdx.x;
-    key[r] = (r < rounds && i < nb) ? keys[base + i] : 0u;
-  }
-  __syncthreads();
-  block_digit_hist<kBits>(key, rounds, nb, shift, h, hist, nblocks);
-}
-
-// Depth keys of one sort block's items (FP32 depth bits: positive depths
-// order like their bits; culled items get 0xFFFFFFFF and sort last), item ids
-// as values, and the histogram of the first radix pass's digits, so that pass
-// needs no histogram launch of its own.
-template <int kBits>
-__global__ __launch_bounds__(kSortThreads) void k_depth_keys(const float4* __restrict__ rec,
-                                                             const int32_t* __restrict__ tiles, int64_t M,
-                                                             uint32_t* __restrict__ keys, uint32_t* __restrict__ vals,
-                                                             uint32_t* __restrict__ hist, int nblocks, int rounds) {
-  constexpr int kBins = 1 << kBits;
-  __shared__ uint32_t h[kBins];
-  for (int i = threadIdx.x; i < kBins; i += kSortThreads) h[i] = 0;
-  const int64_t base = (int64_t)blockIdx.x * rounds * kSortThreads;
-  const int nb = base < M ? (int)min((int64_t)rounds * kSortThreads, M - base) : 0;
-  uint32_t key[kSortItems];
-#pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {
-    const int i = r * kSortThreads + threadIdx.x;
-    key[r] = 0u;
-    if (r < rounds && i < nb) {
-      const int64_t it = base + i;
-      key[r] = tiles[it] > 0 ? __float_as_uint(rec[it * 3 + 1].z) : 0xFFFFFFFFu;
-      keys[it] = key[r];
-      vals[it] = (uint32_t)it;
-    }
-  }
-  __syncthreads();
-  block_digit_hist<kBits>(key, rounds, nb, 0, h, hist, nblocks);
-}
-
-// Block-wide exclusive scan of one value per thread (256 threads); returns
-// the exclusive prefix and writes the block total to *total.
-__device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* wsum, uint32_t* total) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  uint32_t x = v;
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t y = __shfl_up(x, off, 64);
-    if (lane >= off) x += y;
-  }
-  if (lane == 63) wsum[w] = x;
-  __syncthreads();
-  uint32_t wofs = 0;
-  for (int k = 0; k < w; ++k) wofs += wsum[k];
-  const uint32_t tot = wsum[0] + wsum[1] + wsum[2] + wsum[3];
-  __syncthreads();
-  *total = tot;
-  return wofs + x - v;
-}
-
-// Exclusive scan of each row of a [rows][len] array in place, one 256-thread
-// block per row; row totals go to totals[row].  Only the columns of the sort
-// blocks that hold keys are scanned (n keys, rounds x 256 per block).
-__global__ __launch_bounds__(256) void k_scan_rows(uint32_t* __restrict__ data, int64_t stride,
-                                                   uint32_t* __restrict__ totals, const int32_t* n_dev,
-                                                   int64_t n_static, int64_t cap, int rounds) {
-  __shared__ uint32_t wsum[4];
-  uint32_t* row = data + (int64_t)blockIdx.x * stride;
-  const int64_t len = min(stride, (int64_t)active_blocks(sort_count(n_dev, n_static, cap), rounds));
-  const int64_t per = (len + 255) / 256;
-  const int64_t b = threadIdx.x * per;
-  const int64_t e = min(b + per, len);
-  uint32_t s = 0;
-  for (int64_t i = b; i < e; ++i) s += row[i];
-  uint32_t tot;
-  uint32_t run = block_excl_scan(s, wsum, &tot);
-  for (int64_t i = b; i < e; ++i) { const uint32_t t = row[i]; row[i] = run; run += t; }
-  if (threadIdx.x == 0) totals[blockIdx.x] = tot;
-}
-
-// Stable scatter of one kBits-bit digit pass.  The block's keys (rounds x
-// 256 consecutive positions) are split into four consecutive quarters, one
-// per wave, each taken 64 at a time in order:
-//  - every wave ranks its own keys alone: per 64 keys, a ballot match gives
-//    each key its rank among equal digits, and the wave's running count of
-//    that digit (its own LDS row) the number of earlier ones; the leader of
-//    each digit present adds the group's count.  No barrier until the wave
-//    has ranked all its keys;
-//  - one thread per digit then turns the four wave counts into the digit's
-//    place in LDS order (digits ascending, then waves in order) and its
-//    global run start (the scanned histogram entry plus the digit totals'
-//    block-wide scan);
-//  - each key goes to LDS at its wave's base for its digit plus its rank, so
-//    LDS holds the block's keys ordered by digit and, within a digit, by
-//    position: the pass is stable;
-//  - the block writes its keys out in LDS order: item i of digit d goes to
-//    global base(d) - local base(d) + i, so neighbouring threads write
-//    neighbouring addresses along each digit's run.
-template <int kBits>
-__global__ __launch_bounds__(kSortThreads) void k_sort_scatter(const uint32_t* __restrict__ kin,
-                                                               const uint32_t* __restrict__ vin,
-                                                               uint32_t* __restrict__ kout, uint32_t* __restrict__ vout,
-                                                               const int32_t* n_dev, int64_t n_static, int64_t cap,
-                                                               int shift, const uint32_t* __restrict__ hist, int nblocks,
-                                                               const uint32_t* __restrict__ digit_total, int rounds) {
-  constexpr int kBins = 1 << kBits;
-  constexpr int kPer = kBins >= kSortThreads ? kBins / kSortThreads : 1;  // digits per thread in the set-up
-  static_assert(kBins % kSortThreads == 0 || kSortThreads % kBins == 0, "digits and threads must divide");
-  static_assert(kSortThreads == 256, "four waves per block");
-  __shared__ uint32_t wcnt[4][kBins];  // per wave: running count of each digit, then the wave's LDS base for it
-  __shared__ uint32_t delta[kBins];    // global minus local start of each digit's run (mod 2^32)
-  __shared__ uint32_t wsum[4];
-  __shared__ uint32_t sk[kSortTile], sv[kSortTile];
-  const int n = sort_count(n_dev, n_static, cap);
-  const int64_t bbase = (int64_t)blockIdx.x * rounds * kSortThreads;
-  if (bbase >= n) return;  // uniform for the block
-  const int nb = (int)min((int64_t)rounds * kSortThreads, (int64_t)n - bbase);
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int wpos = w * rounds * 64;  // the wave's first position in the block
-  uint32_t key[kSortItems], val[kSortItems], rk[kSortItems];
-#pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {
-    const int i = wpos + r * 64 + lane;
-    const bool ok = r < rounds && i < nb;
-    key[r] = ok ? kin[bbase + i] : 0u;
-    val[r] = ok ? vin[bbase + i] : 0u;
-    rk[r] = 0u;
-  }
-  for (int d = lane; d < kBins; d += 64) wcnt[w][d] = 0u;
-  __builtin_amdgcn_wave_barrier();
-  const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-#pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {
-    if (r < rounds && wpos + r * 64 < nb) {  // uniform for the wave; a guard, not a break, so the loop unrolls
-      const bool valid = wpos + r * 64 + lane < nb;
-      const uint32_t d = (key[r] >> shift) & (uint32_t)(kBins - 1);
-      uint64_t peers = __ballot(valid);
-#pragma unroll
-      for (int b = 0; b < kBits; ++b) {
-        const bool bit = (d >> b) & 1u;
-        const uint64_t m = __ballot(bit);
-        peers &= bit ? m : ~m;
-      }
-      const uint32_t rank = (uint32_t)__popcll(peers & lt);
-      const uint32_t before = valid ? wcnt[w][d] : 0u;
-      rk[r] = before + rank;
-      if (valid && rank == 0) wcnt[w][d] = before + (uint32_t)__popcll(peers);
-      __builtin_amdgcn_wave_barrier();
-    }
-  }
-  __syncthreads();
-  {
-    // threads 0 .. kBins / kPer - 1 hold kPer digits each (fewer digits than
-    // threads: the other threads add zeros to the scans)
-    const bool has = tid * kPer < kBins;
-    uint32_t tot[kPer], cnt[kPer], here[kPer], c0[kPer], c1[kPer], c2[kPer];
-    uint32_t gsum = 0, lsum = 0;
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-      const int d = tid * kPer + k;
-      tot[k] = cnt[k] = here[k] = c0[k] = c1[k] = c2[k] = 0u;
-      if (has) {
-        c0[k] = wcnt[0][d];
-        c1[k] = wcnt[1][d];
-        c2[k] = wcnt[2][d];
-        cnt[k] = c0[k] + c1[k] + c2[k] + wcnt[3][d];
-        here[k] = hist[(int64_t)d * nblocks + blockIdx.x];
-        tot[k] = digit_total[d];
-      }
-      gsum += tot[k];
-      lsum += cnt[k];
-    }
-    uint32_t all;
-    uint32_t grun = block_excl_scan(gsum, wsum, &all);
-    uint32_t lrun = block_excl_scan(lsum, wsum, &all);
-    if (has) {
-#pragma unroll
-      for (int k = 0; k < kPer; ++k) {
-        const int d = tid * kPer + k;
-        delta[d] = grun + here[k] - lrun;
-        wcnt[0][d] = lrun;
-        wcnt[1][d] = lrun + c0[k];
-        wcnt[2][d] = lrun + c0[k] + c1[k];
-        wcnt[3][d] = lrun + c0[k] + c1[k] + c2[k];
-        grun += tot[k];
-        lrun += cnt[k];
-      }
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {
-    if (r < rounds && wpos + r * 64 + lane < nb) {
-      const uint32_t d = (key[r] >> shift) & (uint32_t)(kBins - 1);
-      const uint32_t pos = wcnt[w][d] + rk[r];
-      sk[pos] = key[r];
-      sv[pos] = val[r];
-    }
-  }
-  __syncthreads();
-  for (int i = tid; i < nb; i += kSortThreads) {
-    const uint32_t k = sk[i];
-    const uint32_t pos = delta[(k >> shift) & (uint32_t)(kBins - 1)] + (uint32_t)i;
-    kout[pos] = k;
-    vout[pos] = sv[i];
-  }
-}
-
-// Compaction of the items that have tiles before the depth sort (most items
-// of a registration view lie outside it): kept items per sort block ...
-__global__ __launch_bounds__(kSortThreads) void k_keep_count(const int32_t* __restrict__ tiles, int64_t M, int rounds,
-                                                             uint32_t* __restrict__ bsum) {
-  __shared__ uint32_t ws[4];
-  const int64_t base = (int64_t)blockIdx.x * rounds * kSortThreads;
-  uint32_t c = 0;
-  for (int i = 0; i < rounds; ++i) {
-    const int64_t k = base + i * kSortThreads + threadIdx.x;
-    if (k < M && tiles[k] > 0) ++c;
-  }
-  for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off, 64);
-  if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = c;
-  __syncthreads();
-  if (threadIdx.x == 0) bsum[blockIdx.x] = ws[0] + ws[1] + ws[2] + ws[3];
-}
-
-// ... then their depth keys and item ids, written in item order from the
-// block's offset (the sum of the preceding blocks' counts, formed here); block
-// 0 writes the kept total to *nkeep.  The stable sort then orders them exactly
-// as the uncompacted keys (where culled items sort last).
-__global__ __launch_bounds__(kSortThreads) void k_depth_keys_compact(const float4* __restrict__ rec,
-                                                                     const int32_t* __restrict__ tiles, int64_t M,
-                                                                     int rounds, const uint32_t* __restrict__ bsum,
-                                                                     int nbd, uint32_t* __restrict__ keys,
-                                                                     uint32_t* __restrict__ vals,
-                                                                     int32_t* __restrict__ nkeep) {
-  __shared__ uint32_t wsum[4], wtot[4];
-  const int64_t base = (int64_t)blockIdx.x * rounds * kSortThreads;
-  const int upto = blockIdx.x == 0 ? nbd : (int)blockIdx.x;
-  uint32_t before = 0, total = 0;
-  for (int b = threadIdx.x; b < upto; b += kSortThreads) {
-    const uint32_t v = bsum[b];
-    total += v;
-    if (b < (int)blockIdx.x) before += v;
-  }
-  for (int off = 32; off > 0; off >>= 1) {
-    before += __shfl_xor(before, off, 64);
-    total += __shfl_xor(total, off, 64);
-  }
-  if ((threadIdx.x & 63) == 0) {
-    wsum[threadIdx.x >> 6] = before;
-    wtot[threadIdx.x >> 6] = total;
-  }
-  __syncthreads();
-  uint32_t run = wsum[0] + wsum[1] + wsum[2] + wsum[3];
-  if (blockIdx.x == 0 && threadIdx.x == 0) *nkeep = (int32_t)(wtot[0] + wtot[1] + wtot[2] + wtot[3]);
-  // every round's keep flags first; per wave a ballot gives each lane its rank
-  // and the wave's count; one barrier, then each lane's place follows from
-  // the counts of the earlier rounds and waves (item order kept)
-  __shared__ uint32_t wcnt[kSortItems][4];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  uint64_t bal[kSortItems];
-#pragma unroll
-  for (int i = 0; i < kSortItems; ++i) {
-    const int64_t k = base + i * kSortThreads + threadIdx.x;
-    const bool keep = i < rounds && k < M && tiles[k] > 0;
-    bal[i] = __ballot(keep);
-    if (i < rounds && lane == 0) wcnt[i][w] = (uint32_t)__popcll(bal[i]);
-  }
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < kSortItems; ++i) {
-    if (i >= rounds) break;
-    uint32_t pre = 0;
-    for (int u = 0; u < w; ++u) pre += wcnt[i][u];
-    if ((bal[i] >> lane) & 1ull) {
-      const uint32_t pos = run + pre + (uint32_t)__popcll(bal[i] & lt);
-      const int64_t k = base + i * kSortThreads + threadIdx.x;
-      keys[pos] = __float_as_uint(rec[k * 3 + 1].z);
-      vals[pos] = (uint32_t)k;
-    }
-    run += (wcnt[i][0] + wcnt[i][1]) + (wcnt[i][2] + wcnt[i][3]);
-  }
-}
+constexpr int kBins = 256;
+constexpr int kSortWaves = kSortThreads / 64;
+constexpr int kSortPer = kSortKeys / kSortThreads;  // keys per thread
 
 // Inclusive prefix sum over the 64 lanes (DPP: shifts within 16-lane rows,
-// then the row ends broadcast to the later rows); 0 is the identity.
+// then the row ends broadcast to the later rows).
 __device__ __forceinline__ uint32_t wave_incl_sum(uint32_t v) {
   int x = (int)v;
   x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);  // row_shr:1
@@ -372,270 +57,678 @@ __device__ __forceinline__ uint32_t wave_incl_sum(uint32_t v) {
   return (uint32_t)x;
 }
 
-// Items in the depth order: M, or the kept count when the items were
-// compacted before the sort.
-__device__ __forceinline__ int64_t order_len(int64_t M, const int32_t* n_dev) {
-  return n_dev ? min((int64_t)n_dev[0], M) : M;
+// Exclusive prefix of one value per thread over the first kBins threads (the
+// others' values are ignored); every thread of the block calls it.
+__device__ __forceinline__ uint32_t digit_excl(uint32_t v, uint32_t* wsum) {
+  const int w = threadIdx.x >> 6;
+  const uint32_t x = wave_incl_sum(v);
+  if ((threadIdx.x & 63) == 63 && w < kBins / 64) wsum[w] = x;
+  __syncthreads();
+  uint32_t before = 0;
+#pragma unroll
+  for (int k = 0; k < kBins / 64; ++k) before += k < w ? wsum[k] : 0u;
+  return before + x - v;
 }
 
-// Per-block (rounds x 256 items) sums of the tile counts of depth-sorted items.
-__global__ __launch_bounds__(kSortThreads) void k_count_sum(const uint32_t* __restrict__ order,
-                                                            const int32_t* __restrict__ tiles, int64_t M,
-                                                            const int32_t* n_dev, int rounds,
-                                                            uint32_t* __restrict__ bsum) {
-  __shared__ uint32_t ws[4];
-  const int64_t base = (int64_t)blockIdx.x * rounds * kSortThreads;
-  const int64_t n = order_len(M, n_dev);
-  if (base >= n) {  // no item here
-    if (threadIdx.x == 0) bsum[blockIdx.x] = 0;
-    return;
-  }
-  uint32_t s = 0;
-  for (int i = 0; i < rounds; ++i) {
-    const int64_t k = base + i * kSortThreads + threadIdx.x;
-    if (k < n) s += (uint32_t)tiles[order[k]];
-  }
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-  if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) bsum[blockIdx.x] = ws[0] + ws[1] + ws[2] + ws[3];
-}
-
-// Exclusive offsets of every depth-sorted item: block offset (the sum of the
-// preceding block sums, formed here rather than by a scan launch) plus the
-// in-block prefix, 16 rounds of 256 items in order.  The item whose instance
-// range holds instance m * span (m < nspan) is recorded in first[m].
-// Block 0 also writes count = {min(I, cap), I > cap, min(I, INT32_MAX), 0}.
-__global__ __launch_bounds__(kSortThreads) void k_offsets(const uint32_t* __restrict__ order,
-                                                          const int32_t* __restrict__ tiles, int64_t M,
-                                                          const int32_t* n_dev, const uint32_t* __restrict__ bsum,
-                                                          int nbd,
-                                                          uint32_t* __restrict__ offs, int32_t* __restrict__ count,
-                                                          int64_t cap, int rounds, uint32_t* __restrict__ first,
-                                                          int64_t span, int64_t nspan) {
-  __shared__ uint32_t wsum[4];
-  __shared__ uint64_t wtot[4];
-  const int64_t base = (int64_t)blockIdx.x * rounds * kSortThreads;
-  const int64_t n = order_len(M, n_dev);
-  if (blockIdx.x != 0 && base >= n) return;  // no item here (block 0 writes the counts)
-  // the offset of this block (and, for block 0, the total over all blocks)
-  const int upto = blockIdx.x == 0 ? nbd : (int)blockIdx.x;
-  uint64_t before = 0, total = 0;
-  for (int b = threadIdx.x; b < upto; b += kSortThreads) {
-    const uint64_t v = bsum[b];
-    total += v;
-    if (b < (int)blockIdx.x) before += v;
-  }
-  for (int off = 32; off > 0; off >>= 1) {
-    before += __shfl_xor(before, off, 64);
-    total += __shfl_xor(total, off, 64);
-  }
-  if ((threadIdx.x & 63) == 0) {
-    wsum[threadIdx.x >> 6] = (uint32_t)before;
-    wtot[threadIdx.x >> 6] = total;
-  }
-  __syncthreads();
-  uint32_t run = wsum[0] + wsum[1] + wsum[2] + wsum[3];
-  const uint64_t I64 = wtot[0] + wtot[1] + wtot[2] + wtot[3];
-  // every round's counts first, an inclusive scan per wave and round (DPP),
-  // the wave totals to LDS, one barrier; then each lane's offset follows from
-  // the totals of the earlier rounds and waves
-  __shared__ uint32_t wt[kSortItems][4];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  uint32_t c[kSortItems], x[kSortItems];
+// Ranks of the wave's keys among its earlier keys of the same digit: 64 at a
+// time in order, a ballot match per 64 keys, and the wave's running digit
+// counts in its own LDS row (cleared here).
+template <int kPer>
+__device__ __forceinline__ void wave_ranks(const uint32_t (&key)[kPer], const bool (&ok)[kPer], int shift,
+                                           uint32_t* row, int lane, uint32_t (&rk)[kPer]) {
+  const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
 #pragma unroll
-  for (int i = 0; i < kSortItems; ++i) {
-    const int64_t k = base + i * kSortThreads + threadIdx.x;
-    c[i] = (i < rounds && k < n) ? (uint32_t)tiles[order[k]] : 0u;
-  }
+  for (int d = 0; d < kBins / 64; ++d) row[64 * d + lane] = 0u;
+  __builtin_amdgcn_wave_barrier();
 #pragma unroll
-  for (int i = 0; i < kSortItems; ++i) {
-    if (i >= rounds) break;
-    const uint32_t incl = wave_incl_sum(c[i]);
-    x[i] = incl - c[i];
-    if (lane == 63) wt[i][w] = incl;
-  }
-  __syncthreads();
+  for (int j = 0; j < kPer; ++j) {
+    const uint32_t d = (key[j] >> shift) & (kBins - 1);
+    const uint64_t valid = __ballot(ok[j]);
+    rk[j] = 0u;
+    if (valid != 0ull) {  // uniform
+      uint32_t plo = (uint32_t)valid, phi = (uint32_t)(valid >> 32);
 #pragma unroll
-  for (int i = 0; i < kSortItems; ++i) {
-    if (i >= rounds) break;
-    uint32_t pre = 0;
-    for (int u = 0; u < w; ++u) pre += wt[i][u];
-    const int64_t k = base + i * kSortThreads + threadIdx.x;
-    if (k < n) {
-      const int64_t o = (int64_t)run + pre + x[i];
-      offs[k] = (uint32_t)o;
-      for (int64_t m = (o + span - 1) / span; m < nspan && m * span < o + c[i]; ++m)
-        first[m] = (uint32_t)k;
+      for (int b = 0; b < 8; ++b) {
+        const uint32_t sign = (uint32_t)((int32_t)(d << (31 - b)) >> 31);  // all ones where the bit is set
+        const uint64_t m = __ballot(sign != 0u);
+        plo &= ~((uint32_t)m ^ sign);
+        phi &= ~((uint32_t)(m >> 32) ^ sign);
+      }
+      const uint64_t peers = ((uint64_t)phi << 32) | plo;
+      const uint32_t rank = (uint32_t)__popcll(peers & lt);
+      const uint32_t before = ok[j] ? row[d] : 0u;
+      rk[j] = before + rank;
+      if (ok[j] && rank == 0) row[d] = before + (uint32_t)__popcll(peers);
+      __builtin_amdgcn_wave_barrier();
     }
-    run += (wt[i][0] + wt[i][1]) + (wt[i][2] + wt[i][3]);
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    const int64_t I = (int64_t)I64;
-    count[0] = (int32_t)min(I, cap);
-    count[1] = I > cap ? 1 : 0;
-    count[2] = (int32_t)min(I, (int64_t)INT32_MAX);
+}
+
+// The block's digit starts, after every wave has ranked (and a barrier): each
+// wave's row turns into its first place for each digit in the block's digit
+// order; returns the digit's count (threads below kBins) and its local start.
+__device__ __forceinline__ uint32_t digit_starts(uint32_t (*wcnt)[kBins], uint32_t* wsum, uint32_t& lstart) {
+  const int d = threadIdx.x;
+  uint32_t c[kSortWaves], cnt = 0;
+  if (d < kBins) {
+#pragma unroll
+    for (int k = 0; k < kSortWaves; ++k) {
+      c[k] = wcnt[k][d];
+      cnt += c[k];
+    }
+  }
+  lstart = digit_excl(cnt, wsum);
+  if (d < kBins) {
+    uint32_t run = lstart;
+#pragma unroll
+    for (int k = 0; k < kSortWaves; ++k) {
+      wcnt[k][d] = run;
+      run += c[k];
+    }
+  }
+  return cnt;
+}
+
+// Digit counts of every block's keys: hist[block][digit].
+__global__ __launch_bounds__(kSortThreads) void k_seg_hist(const uint32_t* __restrict__ keys, SegTable seg, int shift,
+                                                           uint32_t* __restrict__ hist) {
+  __shared__ uint32_t h[kBins];
+  const int s = find_segment<int32_t>(seg.blk_off, seg.S, (int32_t)blockIdx.x);
+  const int c = blockIdx.x - seg.blk_off[s];
+  const int m = min(seg.len[s] - c * kSortKeys, kSortKeys);
+  if (m <= 0) return;  // uniform for the block
+  if (threadIdx.x < kBins) h[threadIdx.x] = 0u;
+  const uint32_t* __restrict__ k0 = keys + seg.base[s] + (int64_t)c * kSortKeys;
+  uint32_t key[kSortPer];
+#pragma unroll
+  for (int j = 0; j < kSortPer; ++j) {
+    const int i = j * kSortThreads + threadIdx.x;
+    key[j] = i < m ? k0[i] : 0u;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kSortPer; ++j)
+    if (j * kSortThreads + (int)threadIdx.x < m) atomicAdd(&h[(key[j] >> shift) & (kBins - 1)], 1u);
+  __syncthreads();
+  if (threadIdx.x < kBins) hist[(int64_t)blockIdx.x * kBins + threadIdx.x] = h[threadIdx.x];
+}
+
+// Sums of the digit's counts over the segment's blocks and over those before
+// this one, four threads per digit; the result in threads below kBins.  A
+// block of 1,024 threads with 4,096 keys keeps the rows few (49 for 200k
+// keys), so every block can add them up and no scan launch is needed.
+__device__ __forceinline__ void digit_bases(const uint32_t* __restrict__ rows, int nrows, int c, uint32_t* ta,
+                                            uint32_t* tb, uint32_t& total, uint32_t& before) {
+  const int d = threadIdx.x & (kBins - 1), p = threadIdx.x >> 8;
+  constexpr int kParts = kSortThreads / kBins;
+  uint32_t t = 0, b = 0;
+  for (int r0 = p; r0 < nrows; r0 += 16 * kParts) {
+    uint32_t v[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v[k] = r0 + k * kParts < nrows ? rows[(int64_t)(r0 + k * kParts) * kBins + d] : 0u;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      t += v[k];
+      b += r0 + k * kParts < c ? v[k] : 0u;
+    }
+  }
+  ta[threadIdx.x] = t;
+  tb[threadIdx.x] = b;
+  __syncthreads();
+  total = before = 0u;
+  if (threadIdx.x < kBins)
+#pragma unroll
+    for (int k = 0; k < kParts; ++k) {
+      total += ta[k * kBins + d];
+      before += tb[k * kBins + d];
+    }
+}
+
+// Stable scatter of one digit: ranks in the waves, the block's keys placed in
+// LDS by digit, then written out in that order, so that stores are contiguous
+// along each digit's run.  kFirst: the block's own keys, blk_cnt of them, as
+// k_depth_prep left them (len[s] is written); else kSortKeys of the segment's
+// len[s].  kLast: only the values are written.
+template <bool kFirst, bool kLast>
+__global__ __launch_bounds__(kSortThreads) void k_seg_scatter(const uint32_t* __restrict__ kin,
+                                                              const uint32_t* __restrict__ vin,
+                                                              uint32_t* __restrict__ kout,
+                                                              uint32_t* __restrict__ vout, SegTable seg, int shift,
+                                                              const uint32_t* __restrict__ hist,
+                                                              const int32_t* __restrict__ blk_cnt) {
+  __shared__ uint32_t wcnt[kSortWaves][kBins];
+  __shared__ uint32_t sk[kSortKeys], sv[kSortKeys];
+  __shared__ uint32_t delta[kBins];  // global minus local start of each digit's run (mod 2^32)
+  __shared__ uint32_t wsum[2][kBins / 64];
+  const int s = find_segment<int32_t>(seg.blk_off, seg.S, (int32_t)blockIdx.x);
+  const int b0 = seg.blk_off[s], c = blockIdx.x - b0;
+  const int n = kFirst ? 0 : seg.len[s];
+  const int m = kFirst ? blk_cnt[blockIdx.x] : min(n - c * kSortKeys, kSortKeys);
+  const int nrows = kFirst ? seg.blk_off[s + 1] - b0 : (n + kSortKeys - 1) / kSortKeys;
+  if (m <= 0 && !(kFirst && c == 0)) return;  // uniform for the block
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t in0 = seg.base[s] + (int64_t)c * kSortKeys;
+  uint32_t key[kSortPer], val[kSortPer], rk[kSortPer];
+  bool ok[kSortPer];
+#pragma unroll
+  for (int j = 0; j < kSortPer; ++j) {
+    const int i = w * 64 * kSortPer + j * 64 + lane;
+    ok[j] = i < m;
+    key[j] = ok[j] ? kin[in0 + i] : 0u;
+    val[j] = ok[j] ? vin[in0 + i] : 0u;
+  }
+  uint32_t total, before;
+  digit_bases(hist + (int64_t)b0 * kBins, nrows, c, sk, sv, total, before);
+  const uint32_t gstart = digit_excl(total, wsum[0]) + before;
+  if (kFirst && c == 0 && threadIdx.x == kBins - 1) seg.len[s] = (int32_t)(gstart - before + total);
+  wave_ranks<kSortPer>(key, ok, shift, wcnt[w], lane, rk);
+  __syncthreads();
+  uint32_t lstart;
+  digit_starts(wcnt, wsum[1], lstart);
+  if (threadIdx.x < kBins) delta[threadIdx.x] = gstart - lstart;
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kSortPer; ++j)
+    if (ok[j]) {
+      const uint32_t pos = wcnt[w][(key[j] >> shift) & (kBins - 1)] + rk[j];
+      sk[pos] = key[j];
+      sv[pos] = val[j];
+    }
+  __syncthreads();
+  const int64_t out0 = seg.base[s];
+#pragma unroll
+  for (int j = 0; j < kSortPer; ++j) {
+    const int i = j * kSortThreads + threadIdx.x;
+    if (i < m) {
+      const uint32_t k = sk[i];
+      const int64_t pos = out0 + (uint32_t)(delta[(k >> shift) & (kBins - 1)] + (uint32_t)i);
+      if (!kLast) kout[pos] = k;
+      vout[pos] = sv[i];
+    }
+  }
+}
+
+int64_t seg_hist_words(int nblk) { return (int64_t)kBins * std::max(nblk, 1); }
+
+// ---------------------------------------------------------------------------
+// Depth order of each render's items.
+
+// Larger renders: each block compacts its items with tiles (in item order) and
+// counts the first digit of their depth bits.
+__global__ __launch_bounds__(kSortThreads) void k_depth_prep(const JobDev* __restrict__ jobs, SegTable seg,
+                                                             const float4* __restrict__ rec,
+                                                             const int32_t* __restrict__ tiles,
+                                                             uint32_t* __restrict__ keys, uint32_t* __restrict__ vals,
+                                                             uint32_t* __restrict__ hist,
+                                                             int32_t* __restrict__ blk_cnt) {
+  __shared__ uint32_t h[kBins];
+  __shared__ uint32_t cnt[kSortPer][kSortWaves];
+  const int s = find_segment<int32_t>(seg.blk_off, seg.S, (int32_t)blockIdx.x);
+  const int c = blockIdx.x - seg.blk_off[s];
+  const int n = jobs[s].n, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t base = seg.base[s] + (int64_t)c * kSortKeys;
+  if (threadIdx.x < kBins) h[threadIdx.x] = 0u;
+  uint64_t keep[kSortPer];
+#pragma unroll
+  for (int j = 0; j < kSortPer; ++j) {
+    const int i = j * kSortThreads + threadIdx.x;
+    keep[j] = __ballot(c * kSortKeys + i < n && tiles[base + i] > 0);
+    if (lane == 0) cnt[j][w] = (uint32_t)__popcll(keep[j]);
+  }
+  uint32_t key[kSortPer];
+#pragma unroll
+  for (int j = 0; j < kSortPer; ++j)
+    key[j] = __builtin_amdgcn_inverse_ballot_w64(keep[j])
+                 ? __float_as_uint(rec[(base + j * kSortThreads + threadIdx.x) * 3 + 1].z)
+                 : 0u;
+  __syncthreads();
+  uint32_t run = 0;
+#pragma unroll
+  for (int j = 0; j < kSortPer; ++j) {
+    uint32_t at = run;
+#pragma unroll
+    for (int k = 0; k < kSortWaves; ++k) {
+      at += k < w ? cnt[j][k] : 0u;
+      run += cnt[j][k];
+    }
+    if (__builtin_amdgcn_inverse_ballot_w64(keep[j])) {
+      const int64_t pos = base + at + __builtin_amdgcn_mbcnt_hi((uint32_t)(keep[j] >> 32),
+                                                                __builtin_amdgcn_mbcnt_lo((uint32_t)keep[j], 0u));
+      keys[pos] = key[j];
+      vals[pos] = (uint32_t)(base + j * kSortThreads + threadIdx.x);
+      atomicAdd(&h[key[j] & (kBins - 1)], 1u);
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < kBins) hist[(int64_t)blockIdx.x * kBins + threadIdx.x] = h[threadIdx.x];
+  if (threadIdx.x == 0) blk_cnt[blockIdx.x] = (int32_t)run;
+}
+
+// Small renders: one block sorts a whole render of up to kPer * 1,024 items in
+// LDS.  4,096 items take 16 us, four passes of ranks, digit starts and LDS
+// moves, each a chain of barriers; the other path's eight launches take 3 us
+// or more each however few the items.  16,384 items take 145 KB of LDS, nearly
+// all of a CU's 160, which is where the rule ends.
+template <int kPer>
+__global__ __launch_bounds__(kSortThreads) void k_depth_sort_small(const JobDev* __restrict__ jobs, SegTable seg,
+                                                                   const float4* __restrict__ rec,
+                                                                   const int32_t* __restrict__ tiles,
+                                                                   uint32_t* __restrict__ order) {
+  __shared__ uint32_t wcnt[kSortWaves][kBins];
+  __shared__ uint32_t sk[kPer * kSortThreads], sv[kPer * kSortThreads];
+  __shared__ uint32_t wsum[kBins / 64];
+  __shared__ uint32_t kept;
+  const int s = blockIdx.x;
+  const int n = jobs[s].n, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t base = jobs[s].item_off;
+  uint32_t key[kPer], val[kPer], rk[kPer];
+  bool ok[kPer];
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const int i = w * 64 * kPer + j * 64 + lane;
+    ok[j] = i < n && tiles[base + i] > 0;
+    val[j] = (uint32_t)(base + i);
+  }
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) key[j] = ok[j] ? __float_as_uint(rec[(int64_t)val[j] * 3 + 1].z) : 0u;
+  int m = 0;
+#pragma unroll 1
+  for (int shift = 0; shift < 32; shift += 8) {
+    wave_ranks<kPer>(key, ok, shift, wcnt[w], lane, rk);
+    __syncthreads();
+    uint32_t lstart;
+    const uint32_t cnt = digit_starts(wcnt, wsum, lstart);
+    if (threadIdx.x == kBins - 1) kept = lstart + cnt;
+    __syncthreads();
+    m = (int)kept;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j)
+      if (ok[j]) {
+        const uint32_t pos = wcnt[w][(key[j] >> shift) & (kBins - 1)] + rk[j];
+        sk[pos] = key[j];
+        sv[pos] = val[j];
+      }
+    __syncthreads();
+    if (shift < 24)
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) {
+        const int i = w * 64 * kPer + j * 64 + lane;
+        ok[j] = i < m;
+        key[j] = ok[j] ? sk[i] : 0u;
+        val[j] = ok[j] ? sv[i] : 0u;
+      }
+  }
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const int i = j * kSortThreads + threadIdx.x;
+    if (i < m) order[base + i] = sv[i];
+  }
+  if (threadIdx.x == 0) seg.len[s] = m;
+}
+
+// ---------------------------------------------------------------------------
+// Distribution over the tiles.  A block works on one chunk of a render's
+// sorted items and one window of its tiles (at most kWindowTiles; the whole
+// image up to 1,024 x 1,024 or 1200 x 680 pixels), kPlaceItems items at a
+// time, and a thread on a few tiles of the window.  For 64 items (a wave) the
+// items that reach a tile are a 64-bit word: those that reach its row and its
+// column, and the words of the window's rows and columns are transposed line
+// masks.  So a tile counts its items with a population count and lists them in
+// depth order by walking its words, with no atomics and no matter how large
+// the items' rectangles are.  Measured for 1.6 M instances of 200k items:
+// counts 13 us and lists 27 us (LDS atomics per (item, tile), balanced over
+// items: 81 and 249 us; words by a ballot per line: 20 and 29 us).  Windows of
+// 1,024 tiles instead repeat the words: 21 and 33 us.
+
+constexpr int kWindowSide = 256;    // most tiles of a window's row
+constexpr int kPlaceThreads = 1024;
+constexpr int kPlaceItems = 512;
+constexpr int kPlaceGroups = kPlaceItems / 64;
+constexpr int kPlaceTiles = kWindowTiles / kPlaceThreads;  // tiles per thread
+static_assert(2 * kPlaceGroups * 64 == kPlaceThreads, "a wave per group for the rows and one for the columns");
+
+struct Window {
+  int w, h, nx, ny;  // a window's tiles, windows per row and column
+};
+__host__ __device__ inline Window window_of(int TX, int TY) {
+  Window o;
+  o.w = TX < kWindowSide ? TX : kWindowSide;
+  o.h = kWindowTiles / o.w < TY ? kWindowTiles / o.w : TY;
+  o.h = o.h < kWindowSide ? o.h : kWindowSide;
+  o.nx = (TX + o.w - 1) / o.w;
+  o.ny = (TY + o.h - 1) / o.h;
+  return o;
+}
+int windows_of(int TX, int TY) {
+  const Window w = window_of(TX, TY);
+  return w.nx * w.ny;
+}
+
+// Chunks hold `chunk` items.  The nearest items cover the most tiles; a single
+// render's first chunks are therefore cut finer, 64 items (16 chunks), then
+// 128 and 256 (16 chunks each), so that no block writes many times the others'
+// instances (200k items: 92 -> 29 us for k_place).  A batch's blocks
+// outnumber the CUs several times as they are, and finer chunks only add
+// counts to scan (16 renders of 150k and 120k items: counts and lists 104 us
+// without, 121 us with finer first chunks).
+constexpr int kRamp = 16 * (64 + 128 + 256);
+__host__ __device__ inline int chunk_first(int c, int chunk, bool ramp) {
+  if (!ramp) return chunk * c;
+  return c < 16 ? 64 * c : c < 32 ? 1024 + 128 * (c - 16) : c < 48 ? 3072 + 256 * (c - 32) : kRamp + chunk * (c - 48);
+}
+__host__ __device__ inline int chunks_of(int n, int chunk, bool ramp) {
+  if (!ramp) return (n + chunk - 1) / chunk;
+  return n <= 1024 ? (n + 63) / 64
+         : n <= 3072 ? 16 + (n - 1024 + 127) / 128
+         : n <= kRamp ? 32 + (n - 3072 + 255) / 256 : 48 + (n - kRamp + chunk - 1) / chunk;
+}
+int bin_chunks(int n, int chunk, int R) { return chunks_of(n, chunk, R == 1); }
+
+struct PlaceCtx {
+  int r, chunk, x0, y0, w, h;  // render, chunk, window in tiles
+  int first, n;                // the chunk's items
+};
+
+// Block -> work unit: neighbouring chunks, whose instances are neighbours in
+// the lists, on one XCD.  A single render's units are mapped over those that
+// have items, so that all XCDs work.
+__device__ __forceinline__ int place_unit(const BinTables& t, const JobDev* jobs, const int32_t* kept, int units) {
+  if (t.R > 1) return xcd_remap(blockIdx.x, units);
+  const int busy = units > 0 ? chunks_of(kept[0], t.chunk, true) * (units / chunks_of(jobs[0].n, t.chunk, true)) : 0;
+  const int u = xcd_remap(blockIdx.x, busy);
+  return u < busy && (int)blockIdx.x < 8 * ((busy + 7) / 8) ? u : units;
+}
+
+__device__ __forceinline__ bool place_ctx(const JobDev* jobs, const BinTables& t, const int32_t* kept, int unit,
+                                          PlaceCtx& c) {
+  c.r = find_segment<int32_t>(t.work_off, t.R, unit);
+  const JobDev& J = jobs[c.r];
+  const Window win = window_of(J.TX, J.TY);
+  const int nw = win.nx * win.ny, local = unit - t.work_off[c.r];
+  c.chunk = local / nw;
+  const int k = local - c.chunk * nw, wy = k / win.nx;
+  c.x0 = (k - wy * win.nx) * win.w;
+  c.y0 = wy * win.h;
+  c.w = min(win.w, J.TX - c.x0);
+  c.h = min(win.h, J.TY - c.y0);
+  c.first = chunk_first(c.chunk, t.chunk, t.R == 1);
+  c.n = min(kept[c.r], chunk_first(c.chunk + 1, t.chunk, t.R == 1)) - c.first;
+  return c.n > 0;
+}
+
+struct PlaceLds {
+  uint64_t row[kPlaceGroups][kWindowSide];  // per 64 items and window row: the items that reach it
+  uint64_t col[kPlaceGroups][kWindowSide];
+  uint32_t id[kPlaceItems];
+};
+
+// The lowest k bits (none for k <= 0, all for k >= 64).
+__device__ __forceinline__ uint64_t bits_below(int k) {
+  return k <= 0 ? 0ull : k >= 64 ? ~0ull : (1ull << k) - 1ull;
+}
+
+// One step of the bit transpose: blocks of kStep x kStep bits change places
+// with the lane kStep away.
+template <int kStep>
+__device__ __forceinline__ uint32_t transpose_step(uint32_t v, uint32_t low) {
+  const bool up = (threadIdx.x & kStep) != 0;
+  const uint32_t o = (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, (kStep << 10) | 0x1F);
+  return up ? (v & ~low) | ((o >> kStep) & low) : (v & low) | ((o & low) << kStep);
+}
+
+// Bit k of lane l's word becomes bit l of lane k's: the items' line masks
+// turned into the lines' item masks, 70 instructions against 8 per line with a
+// ballot each.
+__device__ __forceinline__ uint64_t transpose64(uint64_t v) {
+  const auto r = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)(v >> 32), false, false);
+  uint32_t w[2] = {r[0], r[1]};
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    w[i] = transpose_step<16>(w[i], 0x0000FFFFu);
+    w[i] = transpose_step<8>(w[i], 0x00FF00FFu);
+    w[i] = transpose_step<4>(w[i], 0x0F0F0F0Fu);
+    w[i] = transpose_step<2>(w[i], 0x33333333u);
+    w[i] = transpose_step<1>(w[i], 0x55555555u);
+  }
+  return ((uint64_t)w[1] << 32) | w[0];
+}
+
+// The row and column words (and item ids) of n <= kPlaceItems sorted items.
+// Wave g < kPlaceGroups takes the rows of items 64 g .., wave kPlaceGroups + g
+// their columns.  Ends with a barrier.
+__device__ __forceinline__ void window_words(PlaceLds& L, const JobDev& J, const PlaceCtx& c,
+                                             const uint32_t* __restrict__ ord, int n,
+                                             const float4* __restrict__ rec, const int32_t* __restrict__ radius) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, g = w & (kPlaceGroups - 1), i = 64 * g + lane;
+  if (64 * g < n) {
+    int lo = 0, hi = 0;  // this item's first and past-the-last row (column) in the window
+    if (i < n) {
+      const uint32_t it = ord[i];
+      const float2 uv = *reinterpret_cast<const float2*>(rec + (int64_t)it * 3);
+      const Rect rc = tile_rect(uv.x, uv.y, radius[it], J.TX, J.TY);
+      const bool any = rc.x1 > rc.x0 && rc.y1 > rc.y0;
+      if (w < kPlaceGroups) {
+        L.id[i] = it;
+        lo = rc.y0 - c.y0;
+        hi = any ? rc.y1 - c.y0 : lo;
+      } else {
+        lo = rc.x0 - c.x0;
+        hi = any ? rc.x1 - c.x0 : lo;
+      }
+    }
+    uint64_t* out = w < kPlaceGroups ? L.row[g] : L.col[g];
+    const int len = w < kPlaceGroups ? c.h : c.w;
+    for (int k0 = 0; k0 < len; k0 += 64) {
+      const uint64_t word = transpose64(bits_below(hi - k0) & ~bits_below(lo - k0));
+      if (k0 + lane < len) out[k0 + lane] = word;
+    }
+  }
+  __syncthreads();
+}
+
+// Items of the chunk per tile: cnt[chunk][tile of the render].
+__global__ __launch_bounds__(kPlaceThreads) void k_chunk_count(const JobDev* __restrict__ jobs, BinTables t,
+                                                               int units, const int32_t* __restrict__ kept,
+                                                               const uint32_t* __restrict__ order,
+                                                               const float4* __restrict__ rec,
+                                                               const int32_t* __restrict__ radius,
+                                                               uint32_t* __restrict__ cnt) {
+  __shared__ PlaceLds L;
+  const int unit = place_unit(t, jobs, kept, units);
+  if (unit >= units) return;
+  PlaceCtx c;
+  if (!place_ctx(jobs, t, kept, unit, c)) return;  // uniform
+  const JobDev& J = jobs[c.r];
+  const int nt = c.w * c.h;
+  const uint32_t* __restrict__ ord = order + J.item_off + c.first;
+  uint32_t v[kPlaceTiles];
+#pragma unroll
+  for (int j = 0; j < kPlaceTiles; ++j) v[j] = 0u;
+  for (int i0 = 0; i0 < c.n; i0 += kPlaceItems) {
+    const int n = min(c.n - i0, kPlaceItems);
+    if (i0 > 0) __syncthreads();
+    window_words(L, J, c, ord + i0, n, rec, radius);
+#pragma unroll
+    for (int j = 0; j < kPlaceTiles; ++j) {
+      const int k = j * kPlaceThreads + threadIdx.x;
+      if (k < nt) {
+        const int y = k / c.w, x = k - y * c.w;
+        for (int g = 0; 64 * g < n; ++g) v[j] += (uint32_t)__popcll(L.row[g][y] & L.col[g][x]);
+      }
+    }
+  }
+  uint32_t* __restrict__ row = cnt + t.cnt_off[c.r] + (int64_t)c.chunk * (J.TX * J.TY);
+#pragma unroll
+  for (int j = 0; j < kPlaceTiles; ++j) {
+    const int k = j * kPlaceThreads + threadIdx.x, y = k / c.w;
+    if (k < nt) row[(c.y0 + y) * J.TX + c.x0 + (k - y * c.w)] = v[j];
+  }
+}
+
+// Per tile: the chunks' counts turned into exclusive prefixes, and the total;
+// per block of 64 tiles the sum of the totals.  16 threads per tile, each a
+// run of chunks.
+__global__ __launch_bounds__(1024) void k_chunk_scan(const JobDev* __restrict__ jobs, BinTables t,
+                                                     const int32_t* __restrict__ tile_off, int T,
+                                                     const int32_t* __restrict__ kept, uint32_t* __restrict__ cnt,
+                                                     uint32_t* __restrict__ total, uint64_t* __restrict__ blk_total) {
+  constexpr int kParts = 16, kRun = 32;
+  __shared__ uint32_t sums[kParts][64];
+  const int tile = blockIdx.x * 64 + (threadIdx.x & 63), p = threadIdx.x >> 6;
+  const bool in = tile < T;
+  const int r = find_segment<int32_t>(tile_off, t.R, in ? tile : T - 1);
+  const JobDev& J = jobs[r];
+  const int nt = J.TX * J.TY;
+  const int rows = J.n > 0 ? chunks_of(kept[r], t.chunk, t.R == 1) : 0;
+  const int per = (rows + kParts - 1) / kParts;
+  const int lo = min(p * per, rows), hi = in ? min(lo + per, rows) : lo;
+  uint32_t* __restrict__ col = cnt + t.cnt_off[r] + (in ? tile - J.tile_off : 0);
+  uint32_t v[kRun], s = 0;
+#pragma unroll
+  for (int k = 0; k < kRun; ++k) {
+    v[k] = lo + k < hi ? col[(int64_t)(lo + k) * nt] : 0u;
+    s += v[k];
+  }
+  for (int k = lo + kRun; k < hi; ++k) s += col[(int64_t)k * nt];
+  sums[p][threadIdx.x & 63] = s;
+  __syncthreads();
+  uint32_t run = 0, all = 0;
+#pragma unroll
+  for (int k = 0; k < kParts; ++k) {
+    const uint32_t x = sums[k][threadIdx.x & 63];
+    run += k < p ? x : 0u;
+    all += x;
+  }
+#pragma unroll
+  for (int k = 0; k < kRun; ++k)
+    if (lo + k < hi) {
+      col[(int64_t)(lo + k) * nt] = run;
+      run += v[k];
+    }
+  for (int k = lo + kRun; k < hi; ++k) {
+    const uint32_t x = col[(int64_t)k * nt];
+    col[(int64_t)k * nt] = run;
+    run += x;
+  }
+  if (p == 0) {
+    uint64_t sum = in ? all : 0u;
+    if (in) total[tile] = all;
+    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+    if (threadIdx.x == 0) blk_total[blockIdx.x] = sum;
+  }
+}
+
+// Every tile's [start, end) (clamped to the capacity; empty tiles 0, 0), a
+// block per 1,024 tiles: the sums of the 64-tile blocks before it and its own
+// tiles' scan.  The last block writes count = {min(I, cap), I > cap,
+// min(I, INT32_MAX), 0}.
+__global__ __launch_bounds__(1024) void k_tile_starts(const uint32_t* __restrict__ total,
+                                                      const uint64_t* __restrict__ blk_total, int T, int64_t cap,
+                                                      uint32_t* __restrict__ start, int32_t* __restrict__ range,
+                                                      int32_t* __restrict__ count) {
+  __shared__ uint64_t wpre[16], wsum[16];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, i = blockIdx.x * 1024 + threadIdx.x;
+  const uint32_t mine = i < T ? total[i] : 0u;
+  uint64_t pre = 0;
+  for (int k = threadIdx.x; k < (int)blockIdx.x * 16; k += 1024) pre += blk_total[k];
+  uint64_t x = mine;
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint64_t y = __shfl_up(x, off, 64);
+    if (lane >= off) x += y;
+    pre += __shfl_xor(pre, off, 64);
+  }
+  if (lane == 63) {
+    wsum[w] = x;
+    wpre[w] = pre;
+  }
+  __syncthreads();
+  uint64_t run = x - mine, all = 0;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    run += wpre[k] + (k < w ? wsum[k] : 0ull);
+    all += wpre[k] + wsum[k];
+  }
+  const uint64_t c = (uint64_t)cap;
+  if (i < T) {
+    const uint32_t a = (uint32_t)min(run, c), b = (uint32_t)min(run + mine, c);
+    start[i] = a;
+    range[2 * i] = a < b ? (int32_t)a : 0;
+    range[2 * i + 1] = a < b ? (int32_t)b : 0;
+  }
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+    count[0] = (int32_t)min(all, c);
+    count[1] = all > c ? 1 : 0;
+    count[2] = (int32_t)min(all, (uint64_t)INT32_MAX);
     count[3] = 0;
   }
 }
 
-// Inclusive prefix maximum over the 64 lanes (DPP: shifts within 16-lane
-// rows, then the row ends broadcast to the later rows); -1 is the identity.
-__device__ __forceinline__ int wave_incl_max(int v) {
-  v = max(v, __builtin_amdgcn_update_dpp(-1, v, 0x111, 0xF, 0xF, false));  // row_shr:1
-  v = max(v, __builtin_amdgcn_update_dpp(-1, v, 0x112, 0xF, 0xF, false));  // row_shr:2
-  v = max(v, __builtin_amdgcn_update_dpp(-1, v, 0x114, 0xF, 0xF, false));  // row_shr:4
-  v = max(v, __builtin_amdgcn_update_dpp(-1, v, 0x118, 0xF, 0xF, false));  // row_shr:8
-  v = max(v, __builtin_amdgcn_update_dpp(-1, v, 0x142, 0xA, 0xF, false));  // row_bcast:15 -> rows 1, 3
-  v = max(v, __builtin_amdgcn_update_dpp(-1, v, 0x143, 0xC, 0xF, false));  // row_bcast:31 -> rows 2, 3
-  return v;
-}
-
-// Emission of the tile instances in depth order, one wave per span of
-// consecutive instances (so every wave has the same work, however many tiles
-// its items cover).  The wave takes the items from the span's first
-// one on, 64 at a time, lane l item kb + l: its instance offset, its tile
-// rectangle and the key of the rectangle's first tile.  It fills the span 64
-// instances at a time, lane l writing instance W0 + l, so every store is one
-// contiguous run; windows stop at the end of the loaded items, and the next
-// 64 items start there.  The owner of an instance is the last item that starts
-// at or before it: items starting inside the window mark their start position
-// (LDS), a prefix maximum over the lanes carries each mark forward, and
-// positions before the first start keep the previous owner (at first, lane 0:
-// the item that holds the span's first instance).  Within its owner's
-// rectangle, instance q lies in row q / width (row by row, as the tiles are
-// counted).  Instances at or beyond the capacity are not written.  The
-// kEmitWaves spans of a block are the positions of one block of the first
-// tile radix pass, whose histogram of the keys' low `dbits` bits the block
-// counts as it writes (LDS) and stores digit-major in
-// hist[d * gridDim.x + block], as the histogram kernel would.
-__global__ __launch_bounds__(64 * kEmitWaves) void k_emit(const JobDev* __restrict__ jobs, const int64_t* __restrict__ item_off,
-                                              int R, const uint32_t* __restrict__ order,
-                                              const float4* __restrict__ rec, const int32_t* __restrict__ radius,
-                                              const int32_t* __restrict__ tiles, int64_t M_all, const int32_t* n_dev,
-                                              const uint32_t* __restrict__ offs, const int32_t* __restrict__ count,
-                                              const uint32_t* __restrict__ first, int64_t span_len, int64_t nspan,
-                                              uint32_t* __restrict__ kout, int32_t* __restrict__ vout,
-                                              uint32_t* __restrict__ hist, int dbits) {
-  static_assert(kTileDigitBits <= 8 && 64 * kEmitWaves >= 256, "a histogram bin per thread of the first 256");
-  const uint32_t dmask = (1u << dbits) - 1u;
-  __shared__ int marks[kEmitWaves][64];
-  __shared__ uint32_t h[256];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int64_t I = count[0];  // already clamped to the capacity
-  if ((int64_t)blockIdx.x * kEmitWaves * span_len >= I) return;  // uniform: no instance, no histogram column
-  if (threadIdx.x < 256) h[threadIdx.x] = 0u;
-  __syncthreads();
-  const int64_t span = (int64_t)blockIdx.x * kEmitWaves + w;
-  const int64_t M = order_len(M_all, n_dev);
-  const bool work = span < nspan && span * span_len < I;  // uniform for the wave
-  const int64_t iend = work ? min((span + 1) * span_len, I) : 0;
-  int64_t kb = work ? (int64_t)first[span] : M;
-  int64_t W0 = span * span_len;
-  while (W0 < iend && kb < M) {
-    const int64_t k = kb + lane;
-    const int last = (int)min((int64_t)63, M - 1 - kb);  // last lane with an item
-    uint32_t off = 0xFFFFFFFFu, it = 0;
-    int nt = 0, base_key = 0, stride = 0, wdt = 1;
-    if (k < M) {
-      off = offs[k];
-      it = order[k];
-      nt = tiles[it];
-      if (nt > 0) {
-        const int r = find_segment<int64_t>(item_off, R, (int64_t)it);
-        const JobDev& J = jobs[r];
-        const float4 a = rec[(int64_t)it * 3];
-        const Rect rc = tile_rect(a.x, a.y, radius[it], J.TX, J.TY);
-        wdt = rc.x1 - rc.x0;
-        base_key = J.tile_off + rc.y0 * J.TX + rc.x0;
-        stride = J.TX - wdt;
-      }
+// The instances of a chunk, written to their places: every tile lists the
+// chunk's items that reach it, from the tile's start plus the earlier chunks'
+// count on.  A thread walks all words of its tile as one sequence, so a wave
+// takes as many steps as its fullest tile has items.  tile_of is filled tile by
+// tile, each block a share of the tiles, in whole lines: a scattered store
+// costs a CU about a clock per lane, so one per instance is as few as can be.
+__global__ __launch_bounds__(kPlaceThreads) void k_place(const JobDev* __restrict__ jobs, BinTables t, int units,
+                                                         const int32_t* __restrict__ kept,
+                                                         const uint32_t* __restrict__ order,
+                                                         const float4* __restrict__ rec,
+                                                         const int32_t* __restrict__ radius,
+                                                         const uint32_t* __restrict__ cnt,
+                                                         const uint32_t* __restrict__ start,
+                                                         const int32_t* __restrict__ range, int T, uint32_t cap,
+                                                         uint32_t* __restrict__ tile_of, int32_t* __restrict__ item) {
+  __shared__ PlaceLds L;
+  {
+    const int t0 = (int)((int64_t)T * blockIdx.x / gridDim.x), t1 = (int)((int64_t)T * (blockIdx.x + 1) / gridDim.x);
+    for (int k = t0 + (int)(threadIdx.x >> 6); k < t1; k += kPlaceThreads / 64) {
+      const int e = range[2 * k + 1];
+      for (int i = range[2 * k] + (int)(threadIdx.x & 63); i < e; i += 64) tile_of[i] = (uint32_t)k;
     }
-    const float inv = 1.0f / (float)wdt;
-    const int64_t cend = min((int64_t)(uint32_t)__builtin_amdgcn_readlane((int)(off + (uint32_t)nt), last), iend);
-    int carry = 0;
-    while (W0 < cend) {
-      marks[w][lane] = -1;
-      const int64_t rel = (int64_t)off - W0;
-      if (nt > 0 && rel >= 0 && rel < 64) marks[w][(int)rel] = lane;
-      __builtin_amdgcn_wave_barrier();
-      int o = wave_incl_max(marks[w][lane]);
-      o = o < 0 ? carry : o;
-      carry = __builtin_amdgcn_readlane(o, 63);
-      const int64_t i = W0 + lane;
-      const int o_key = __shfl(base_key, o, 64), o_stride = __shfl(stride, o, 64), o_wdt = __shfl(wdt, o, 64);
-      const float o_inv = __shfl(inv, o, 64);
-      const uint32_t o_off = (uint32_t)__shfl((int)off, o, 64), o_it = (uint32_t)__shfl((int)it, o, 64);
-      if (i < cend) {
-        const int q = (int)(i - (int64_t)o_off);
-        int dy = (int)((float)q * o_inv);
-        if ((dy + 1) * o_wdt <= q) ++dy;
-        else if (dy * o_wdt > q) --dy;
-        const uint32_t key = (uint32_t)(o_key + dy * o_stride + q);
-        kout[i] = key;
-        vout[i] = (int32_t)o_it;
-        atomicAdd(&h[key & dmask], 1u);
-      }
-      __builtin_amdgcn_wave_barrier();
-      W0 = min(W0 + 64, cend);
-    }
-    kb += 64;
   }
-  __syncthreads();
-  if (threadIdx.x <= dmask) hist[(int64_t)threadIdx.x * gridDim.x + blockIdx.x] = h[threadIdx.x];
-}
-
-// [start, end) of each tile's run in the sorted instance keys, for every one
-// of the T tiles, empty tiles [0, 0).  A thread takes 4 consecutive keys
-// (one 16-byte load, and its neighbours' edge keys); at the start of a run it
-// also clears the tiles between the previous run's tile and its own (the
-// first key those before the first run, the last key those after the last
-// run).  With no instances, thread t clears tiles 4t..4t+3.  The grid covers
-// ceil(max(capacity, T) / 4) threads (keys not 16-byte aligned are read one
-// by one).
-__global__ void k_tile_ranges(const uint32_t* __restrict__ keys, const int32_t* __restrict__ count,
-                              int32_t* __restrict__ range, int T) {
-  const int64_t k0 = 4 * ((int64_t)blockIdx.x * blockDim.x + threadIdx.x);
-  const int64_t n = count[0];
-  if (n == 0) {
-    for (int64_t u = k0; u < k0 + 4 && u < T; ++u) {
-      range[2 * u] = 0;
-      range[2 * u + 1] = 0;
-    }
-    return;
-  }
-  if (k0 >= n) return;
-  uint32_t kk[6];  // keys k0 - 1 .. k0 + 4 (valid where 0 <= index < n)
-  kk[0] = k0 > 0 ? keys[k0 - 1] : 0u;
-  if (k0 + 4 <= n && (reinterpret_cast<uintptr_t>(keys) & 15) == 0) {
-    const uint4 q = *reinterpret_cast<const uint4*>(keys + k0);
-    kk[1] = q.x;
-    kk[2] = q.y;
-    kk[3] = q.z;
-    kk[4] = q.w;
-  } else {
-    for (int j = 0; j < 4; ++j) kk[1 + j] = k0 + j < n ? keys[k0 + j] : 0u;
-  }
-  kk[5] = k0 + 4 < n ? keys[k0 + 4] : 0u;
+  const int unit = place_unit(t, jobs, kept, units);
+  if (unit >= units) return;
+  PlaceCtx c;
+  if (!place_ctx(jobs, t, kept, unit, c)) return;  // uniform
+  const JobDev& J = jobs[c.r];
+  const int nt = c.w * c.h;
+  const uint32_t* __restrict__ ord = order + J.item_off + c.first;
+  const uint32_t* __restrict__ row = cnt + t.cnt_off[c.r] + (int64_t)c.chunk * (J.TX * J.TY);
+  uint32_t place[kPlaceTiles];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int64_t k = k0 + j;
-    if (k >= n) break;
-    const int64_t t = kk[1 + j];
-    if (k == 0 || kk[j] != (uint32_t)t) {
-      for (int64_t u = k == 0 ? 0 : (int64_t)kk[j] + 1; u < t; ++u) {
-        range[2 * u] = 0;
-        range[2 * u + 1] = 0;
-      }
-      range[2 * t] = (int32_t)k;
-    }
-    if (k == n - 1 || kk[2 + j] != (uint32_t)t) {
-      range[2 * t + 1] = (int32_t)(k + 1);
-      if (k == n - 1)
-        for (int64_t u = t + 1; u < T; ++u) {
-          range[2 * u] = 0;
-          range[2 * u + 1] = 0;
+  for (int j = 0; j < kPlaceTiles; ++j) {
+    const int k = j * kPlaceThreads + threadIdx.x, y = k / c.w, rt = (c.y0 + y) * J.TX + c.x0 + (k - y * c.w);
+    place[j] = k < nt ? start[J.tile_off + rt] + row[rt] : 0u;
+  }
+  for (int i0 = 0; i0 < c.n; i0 += kPlaceItems) {
+    const int n = min(c.n - i0, kPlaceItems);
+    if (i0 > 0) __syncthreads();
+    window_words(L, J, c, ord + i0, n, rec, radius);
+#pragma unroll
+    for (int j = 0; j < kPlaceTiles; ++j) {
+      const int k = j * kPlaceThreads + threadIdx.x;
+      if (k < nt) {
+        const int y = k / c.w, x = k - y * c.w;
+        uint32_t any = 0u;  // groups with items here
+#pragma unroll
+        for (int g = 0; g < kPlaceGroups; ++g)
+          if (64 * g < n) any |= (L.row[g][y] & L.col[g][x]) != 0ull ? 1u << g : 0u;
+        uint32_t at = place[j];
+        int g = 0;
+        uint64_t bits = 0ull;
+        while (bits != 0ull || any != 0u) {
+          if (bits == 0ull) {
+            g = (int)__builtin_ctz(any);
+            any &= any - 1u;
+            bits = L.row[g][y] & L.col[g][x];
+          }
+          const int e = (int)__builtin_ctzll(bits);
+          bits &= bits - 1ull;
+          if (at < cap) item[at] = (int32_t)L.id[64 * g + e];
+          ++at;
         }
+        place[j] = at;
+      }
     }
   }
 }
@@ -649,108 +742,55 @@ void launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s) {
   hipLaunchKernelGGL(k_fill_i32, dim3((unsigned)blocks), dim3(256), 0, s, p, n, v);
 }
 
-// One LSD pass of kBits-bit digits: histogram, per-digit row scan (row totals
-// to digit_total), scatter (which scans the digit totals itself).
-template <int kBits>
-static void radix_pass(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout, const int32_t* n_dev,
-                       int64_t n_static, int64_t cap, int shift, uint32_t* hist, uint32_t* digit_total, int nblocks,
-                       int rounds, hipStream_t s, bool hist_done = false) {
-  if (!hist_done)
-    hipLaunchKernelGGL(k_sort_hist<kBits>, dim3(nblocks), dim3(kSortThreads), 0, s, kin, n_dev, n_static, cap, shift,
-                       hist, nblocks, rounds);
-  hipLaunchKernelGGL(k_scan_rows, dim3(1 << kBits), dim3(256), 0, s, hist, (int64_t)nblocks, digit_total, n_dev,
-                     n_static, cap, rounds);
-  hipLaunchKernelGGL(k_sort_scatter<kBits>, dim3(nblocks), dim3(kSortThreads), 0, s, kin, vin, kout, vout, n_dev,
-                     n_static, cap, shift, (const uint32_t*)hist, nblocks, (const uint32_t*)digit_total, rounds);
-}
-
-int launch_radix_sort_pairs(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, int64_t n, int bits,
-                            uint32_t* hist, uint32_t* digit_total, hipStream_t s) {
-  if (n <= 0) return 0;
-  const int rd = sort_rounds(n), nb = (int)sort_blocks(n);
-  uint32_t *ka = k0, *va = v0, *kb = k1, *vb = v1;
-  int passes = 0;
-  for (int shift = 0; shift < bits; shift += 8, ++passes) {
-    radix_pass<8>(ka, va, kb, vb, nullptr, n, n, shift, hist, digit_total, nb, rd, s);
-    std::swap(ka, kb);
-    std::swap(va, vb);
-  }
-  return passes & 1;
-}
-
-// Compaction before the depth sort for batches of at least 1 M items (the
-// registration views, where most items are culled); the environment variable
-// LS_COMPACT=0 / 1 forces it off / on (read at every launch; for tests and
-// measurements).
-static bool compact_items(int64_t M) {
-  const char* e = std::getenv("LS_COMPACT");
-  if (e && (e[0] == '0' || e[0] == '1') && e[1] == '\0') return e[0] == '1';
-  return M >= (int64_t)1 << 20;
-}
-
-void launch_bin_sort(const JobDev* jobs, const int64_t* item_off_d, int R, int64_t M, int T, int tile_bits,
-                     const float* rec, const int32_t* radius, const int32_t* tiles, int64_t cap, uint32_t* tile_of,
-                     int32_t* item, int32_t* range, int32_t* count, uint32_t* dk0, uint32_t* dv0, uint32_t* dk1,
-                     uint32_t* dv1, uint32_t* hist, uint32_t* bsum, uint32_t* tk, uint32_t* tv, hipStream_t s) {
-  const float4* rec4 = reinterpret_cast<const float4*>(rec);
-  const int rd = sort_rounds(M), nbd = (int)sort_blocks(M);
-  const int npass = tile_passes(tile_bits), tbits = tile_digit_bits(tile_bits);
-  uint32_t* digit_base = bsum + nbd + 8;  // digit totals (up to kMaxSortBins) after the block sums
-  // large batches sort only the items with tiles; the kept count sits in a
-  // spare word after the block sums
-  const bool compact = compact_items(M);
-  int32_t* nkeep = compact ? reinterpret_cast<int32_t*>(bsum + nbd) : nullptr;
-  if (compact) {
-    hipLaunchKernelGGL(k_keep_count, dim3(nbd), dim3(kSortThreads), 0, s, tiles, M, rd, bsum);
-    hipLaunchKernelGGL(k_depth_keys_compact, dim3(nbd), dim3(kSortThreads), 0, s, rec4, tiles, M, rd,
-                       (const uint32_t*)bsum, nbd, dk0, dv0, nkeep);
-  } else {
-    hipLaunchKernelGGL(k_depth_keys<kDepthDigitBits>, dim3(nbd), dim3(kSortThreads), 0, s, rec4, tiles, M, dk0, dv0,
-                       hist, nbd, rd);
-  }
-  uint32_t *ka = dk0, *va = dv0, *kb = dk1, *vb = dv1;
-  for (int shift = 0; shift < 32; shift += kDepthDigitBits) {
-    radix_pass<kDepthDigitBits>(ka, va, kb, vb, nkeep, M, M, shift, hist, digit_base, nbd, rd, s,
-                                shift == 0 && !compact);
-    std::swap(ka, kb);
-    std::swap(va, vb);
-  }
-  const uint32_t* order = va;
-  uint32_t* offs = ka;  // the free key buffer holds the per-item offsets
-  hipLaunchKernelGGL(k_count_sum, dim3(nbd), dim3(kSortThreads), 0, s, order, tiles, M, (const int32_t*)nkeep, rd,
-                     bsum);
-  const int rt = sort_rounds(cap), nbt = (int)sort_blocks(cap);
-  const int64_t span = emit_span(cap), nspan = emit_spans(cap);
-  // the emission spans of block b are the positions of tile-sort block b
-  // (kEmitWaves spans per block: nbt blocks cover the spans)
-  uint32_t* first = hist + (int64_t)(1 << kTileDigitBits) * nbt;  // after the first tile pass's histogram
-  hipLaunchKernelGGL(k_offsets, dim3(nbd), dim3(kSortThreads), 0, s, order, tiles, M, (const int32_t*)nkeep,
-                     (const uint32_t*)bsum, nbd,
-                     offs, count, cap, rd, first, span, nspan);
-  // emission lands in the buffer that, after npass ping-pongs, is the output
-  uint32_t* ek = (npass & 1) ? tk : tile_of;
-  uint32_t* ev = (npass & 1) ? tv : reinterpret_cast<uint32_t*>(item);
-  uint32_t* ok = (npass & 1) ? tile_of : tk;
-  uint32_t* ov = (npass & 1) ? reinterpret_cast<uint32_t*>(item) : tv;
-  const bool emitted = nbt > 0 && M > 0;
-  if (emitted)
-    hipLaunchKernelGGL(k_emit, dim3((unsigned)nbt), dim3(64 * kEmitWaves), 0, s, jobs, item_off_d, R, order, rec4, radius, tiles,
-                       M, (const int32_t*)nkeep, (const uint32_t*)offs, (const int32_t*)count,
-                       (const uint32_t*)first, span, nspan, ek, reinterpret_cast<int32_t*>(ev), hist, tbits);
-  for (int p = 0; p < npass && nbt > 0; ++p) {
-    const bool hd = p == 0 && emitted;
-    if (tbits == 6)
-      radix_pass<6>(ek, ev, ok, ov, count, 0, cap, 6 * p, hist, digit_base, nbt, rt, s, hd);
-    else if (tbits == 7)
-      radix_pass<7>(ek, ev, ok, ov, count, 0, cap, 7 * p, hist, digit_base, nbt, rt, s, hd);
+void launch_bin_sort(const BinLaunch& b, hipStream_t s) {
+  const float4* rec4 = reinterpret_cast<const float4*>(b.rec);
+  const SegTable seg{b.tab.blk_off, b.item_off, b.tab.R, b.kept};
+  const uint32_t* order = b.v0;
+  if (b.max_items <= kSmallSort) {
+    if (b.max_items <= 4 * kSortThreads)
+      hipLaunchKernelGGL(k_depth_sort_small<4>, dim3(b.tab.R), dim3(kSortThreads), 0, s, b.jobs, seg, rec4, b.tiles,
+                         b.v0);
+    else if (b.max_items <= 8 * kSortThreads)
+      hipLaunchKernelGGL(k_depth_sort_small<8>, dim3(b.tab.R), dim3(kSortThreads), 0, s, b.jobs, seg, rec4, b.tiles,
+                         b.v0);
     else
-      radix_pass<8>(ek, ev, ok, ov, count, 0, cap, 8 * p, hist, digit_base, nbt, rt, s, hd);
-    std::swap(ek, ok);
-    std::swap(ev, ov);
+      hipLaunchKernelGGL(k_depth_sort_small<16>, dim3(b.tab.R), dim3(kSortThreads), 0, s, b.jobs, seg, rec4, b.tiles,
+                         b.v0);
+  } else {
+    const dim3 grid(b.sort_blocks), block(kSortThreads);
+    const uint32_t* hist = b.hist;
+    hipLaunchKernelGGL(k_depth_prep, grid, block, 0, s, b.jobs, seg, rec4, b.tiles, b.k0, b.v0, b.hist, b.blk_cnt);
+    const int32_t* cnt = b.blk_cnt;
+    hipLaunchKernelGGL((k_seg_scatter<true, false>), grid, block, 0, s, (const uint32_t*)b.k0, (const uint32_t*)b.v0,
+                       b.k1, b.v1, seg, 0, hist, cnt);
+    launch_seg_pass(b.k1, b.v1, b.k0, b.v0, seg, b.sort_blocks, 8, b.hist, false, s);
+    launch_seg_pass(b.k0, b.v0, b.k1, b.v1, seg, b.sort_blocks, 16, b.hist, false, s);
+    launch_seg_pass(b.k1, b.v1, b.k0, b.v0, seg, b.sort_blocks, 24, b.hist, true, s);
   }
-  const int64_t nr = (std::max<int64_t>(cap, T) + 3) / 4;  // threads of 4 keys (or tiles)
-  if (nr > 0)
-    hipLaunchKernelGGL(k_tile_ranges, dim3((unsigned)((nr + 255) / 256)), dim3(256), 0, s, (const uint32_t*)tile_of,
-                       (const int32_t*)count, range, T);
+  const dim3 work(8 * ((b.units + 7) / 8));
+  if (b.units > 0)
+    hipLaunchKernelGGL(k_chunk_count, work, dim3(kPlaceThreads), 0, s, b.jobs, b.tab, b.units,
+                       (const int32_t*)b.kept, order, rec4, b.radius, b.cnt);
+  hipLaunchKernelGGL(k_chunk_scan, dim3((b.T + 63) / 64), dim3(1024), 0, s, b.jobs, b.tab, b.tile_off, b.T,
+                     (const int32_t*)b.kept, b.cnt, b.tile_total, b.blk_total);
+  hipLaunchKernelGGL(k_tile_starts, dim3((b.T + 1023) / 1024), dim3(1024), 0, s, (const uint32_t*)b.tile_total,
+                     (const uint64_t*)b.blk_total, b.T, b.cap, b.tile_start, b.range, b.count);
+  if (b.units > 0 && b.cap > 0)
+    hipLaunchKernelGGL(k_place, work, dim3(kPlaceThreads), 0, s, b.jobs, b.tab, b.units,
+                       (const int32_t*)b.kept, order, rec4, b.radius, (const uint32_t*)b.cnt,
+                       (const uint32_t*)b.tile_start, (const int32_t*)b.range, b.T, (uint32_t)b.cap, b.tile_of, b.item);
+}
+
+void launch_seg_pass(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout, const SegTable& seg,
+                     int blocks, int shift, uint32_t* hist, bool last, hipStream_t s) {
+  const dim3 grid(blocks), block(kSortThreads);
+  hipLaunchKernelGGL(k_seg_hist, grid, block, 0, s, kin, seg, shift, hist);
+  const int32_t* none = nullptr;
+  if (last)
+    hipLaunchKernelGGL((k_seg_scatter<false, true>), grid, block, 0, s, kin, vin, kout, vout, seg, shift,
+                       (const uint32_t*)hist, none);
+  else
+    hipLaunchKernelGGL((k_seg_scatter<false, false>), grid, block, 0, s, kin, vin, kout, vout, seg, shift,
+                       (const uint32_t*)hist, none);
 }
 }  // namespace ls

@@ -10,52 +10,10 @@ namespace ls {
 
 constexpr int kTile = LS_TILE;
 constexpr int kBlock = 256;         // one 16x16 tile per block, 4 wave64
-constexpr int kSortThreads = 256;   // radix sort block
-// Radix digit widths (the sort kernels take any width whose bin count is a
-// multiple of the block size).  11-bit depth digits (3 passes instead of 4)
-// measured 3 % slower on the render loop: the 2048-bin histograms, row scans
-// and scatter set-up cost more than the pass they save.
-constexpr int kDepthDigitBits = 8;  // depth keys: 4 passes over 32 bits
-constexpr int kTileDigitBits = 8;   // tile keys: ceil(bits / 8) passes of at most 8 bits
-constexpr int kMaxSortBins = 1 << (kDepthDigitBits > kTileDigitBits ? kDepthDigitBits : kTileDigitBits);
-constexpr int kSortItems = 16;      // most items per thread per sort block
-constexpr int kSortTile = kSortThreads * kSortItems;
-constexpr int64_t kSortBlocksTarget = 1024;  // blocks a sort pass aims for (fills the chip)
-
-// Rounds of kSortThreads items per sort block for n keys: as few as keep
-// about kSortBlocksTarget blocks busy, between 2 and kSortItems (one round
-// per block measured slower: the per-block set-up then dominates).  Host and
-// device use it for the launch grids and for the workspace layout.
-__host__ __device__ inline int sort_rounds(int64_t n) {
-  const int64_t r = (n + kSortBlocksTarget * kSortThreads - 1) / (kSortBlocksTarget * kSortThreads);
-  return (int)(r < 2 ? 2 : (r > kSortItems ? kSortItems : r));
-}
-__host__ __device__ inline int64_t sort_blocks(int64_t n) {
-  const int64_t per = (int64_t)sort_rounds(n) * kSortThreads;
-  return (n + per - 1) / per;
-}
-// Digit width of the tile-key passes for keys of `bits` bits: as many passes
-// as 8-bit digits need, the bits split evenly between them, rounded up to 6,
-// 7 or 8 (12-bit keys: two 6-bit passes).  Fewer bins per pass give each sort
-// block longer runs of equal digits to count and to write.
-__host__ __device__ inline int tile_digit_bits(int bits) {
-  const int passes = bits <= 0 ? 1 : (bits + kTileDigitBits - 1) / kTileDigitBits;
-  const int w = (bits + passes - 1) / passes;
-  return w < 6 ? 6 : (w > kTileDigitBits ? kTileDigitBits : w);
-}
-__host__ __device__ inline int tile_passes(int bits) {
-  return bits <= 0 ? 0 : (bits + tile_digit_bits(bits) - 1) / tile_digit_bits(bits);
-}
-
-// Tile instances emitted per wave: an eighth of a tile-sort block, so the
-// kEmitWaves waves of an emission block fill exactly the positions of one
-// block of the first tile pass and can count its digits.  The first item of
-// every span is recorded while the item offsets are formed.
-constexpr int kEmitWaves = 8;
-__host__ __device__ inline int64_t emit_span(int64_t cap) {
-  return (int64_t)sort_rounds(cap) * (kSortThreads / kEmitWaves);
-}
-__host__ __device__ inline int64_t emit_spans(int64_t cap) { return (cap + emit_span(cap) - 1) / emit_span(cap); }
+constexpr int kSortThreads = 1024;  // radix sort block
+constexpr int kSortKeys = 4096;     // keys per radix sort block
+constexpr int kSmallSort = 16 * kSortThreads;  // items that one block sorts by depth on its own
+constexpr int kWindowTiles = 4096;  // most tiles of a binning window
 constexpr int kGradStride = 16;     // floats per item in the accumulator: a 64-byte line each
 constexpr int kGrad2D = 10;         // sums of ds (dx, dy, dx^2, dx dy, dy^2, 1), dz dr dg db
 constexpr int kPoseAcc = 12;        // dL/dR (9, row-major) and dL/dt (3)

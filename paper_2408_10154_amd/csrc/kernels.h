@@ -54,18 +54,59 @@ void launch_project_bwd(const JobDev* jobs, const int32_t* blk_off, int R, int n
 void launch_pose_reduce_bands(const JobDev* jobs, int R, const float* pose, const float* band_part, float* pose_grad,
                               hipStream_t s);
 
-// tile_bits: bits of the largest tile key (T - 1), which set the tile passes.
-void launch_bin_sort(const JobDev* jobs, const int64_t* item_off_d, int R, int64_t M, int T, int tile_bits,
-                     const float* rec, const int32_t* radius, const int32_t* tiles, int64_t cap, uint32_t* tile_of,
-                     int32_t* item, int32_t* range, int32_t* count, uint32_t* dk0, uint32_t* dv0, uint32_t* dk1,
-                     uint32_t* dv1, uint32_t* hist, uint32_t* bsum, uint32_t* tk, uint32_t* tv, hipStream_t s);
+// Segments of a radix sort: segment s holds its keys at base[s] ..
+// base[s] + len[s] and owns the sort blocks blk_off[s] .. blk_off[s + 1), one
+// per kSortKeys keys of the most it may hold.  All arrays on the device.
+struct SegTable {
+  const int32_t* blk_off;  // [S + 1]
+  const int64_t* base;     // [S]
+  int S;
+  int32_t* len;            // [S]
+};
+// Words of the digit histograms of `blocks` sort blocks.
+int64_t seg_hist_words(int blocks);
+// One stable pass over the 8-bit digit at `shift` (binning.hip), from
+// (kin, vin) to (kout, vout); last: kout is not written.
+void launch_seg_pass(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout, const SegTable& seg,
+                     int blocks, int shift, uint32_t* hist, bool last, hipStream_t s);
 
-// Stable LSD radix sort of n (key, value) pairs on the low `bits` key bits,
-// 8 bits per pass (binning.hip); hist holds 256 * sort_blocks(n) words and
-// digit_total 256.  The result is in (k0, v0) when the return value is 0,
-// else in (k1, v1).
-int launch_radix_sort_pairs(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, int64_t n, int bits,
-                            uint32_t* hist, uint32_t* digit_total, hipStream_t s);
+// Device tables of a batch's binning: per render the sort blocks, the chunk x
+// window work units and the count matrices (chunks x tiles words) before it.
+struct BinTables {
+  const int32_t* blk_off;   // [R + 1]
+  const int32_t* work_off;  // [R + 1]
+  const int64_t* cnt_off;   // [R + 1]
+  int R;
+  int chunk;                // sorted items per chunk (past the first, smaller ones)
+};
+// Tile windows of a render and chunks of n sorted items in a batch of R (host tables).
+int windows_of(int TX, int TY);
+int bin_chunks(int n, int chunk, int R);
+
+struct BinLaunch {
+  const JobDev* jobs;
+  const int64_t* item_off;
+  const int32_t* tile_off;
+  BinTables tab;
+  int T, max_items, sort_blocks, units;
+  const float* rec;
+  const int32_t* radius;
+  const int32_t* tiles;
+  int64_t cap;
+  uint32_t *k0, *v0, *k1, *v1;  // sort buffers [M]
+  uint32_t* hist;               // seg_hist_words(sort_blocks)
+  int32_t* blk_cnt;             // [sort_blocks]
+  int32_t* kept;                // [R]: items with tiles
+  uint32_t* cnt;                // count matrices
+  uint32_t* tile_total;         // [T]
+  uint32_t* tile_start;         // [T]
+  uint64_t* blk_total;          // [ceil(T / 64)]
+  uint32_t* tile_of;
+  int32_t* item;
+  int32_t* range;
+  int32_t* count;
+};
+void launch_bin_sort(const BinLaunch& b, hipStream_t s);
 
 // used: 4 rows (one per band) of ustride = used_slots(capacity, T) 64-bit
 // words; the forward sets bit l of slot (start / 64) + tile + k of row q when

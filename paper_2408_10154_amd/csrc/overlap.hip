@@ -97,8 +97,14 @@ __global__ __launch_bounds__(256) void k_ov_box_part(const float* __restrict__ a
   }
 }
 
-__global__ __launch_bounds__(256) void k_ov_box_final(const float* __restrict__ part, int nblk,
-                                                      float* __restrict__ box) {
+// The common box, and the two sets as segments of one sort.
+struct OvSegs {
+  int32_t* blk_off;  // [3]
+  int64_t* base;     // [2]
+  int32_t* len;      // [2]
+};
+__global__ __launch_bounds__(256) void k_ov_box_final(const float* __restrict__ part, int nblk, int np, int nq,
+                                                      float* __restrict__ box, OvSegs seg) {
   __shared__ float ws[4][6];
   float v[6];
 #pragma unroll
@@ -117,6 +123,15 @@ __global__ __launch_bounds__(256) void k_ov_box_final(const float* __restrict__ 
     for (int w = 1; w < 4; ++w) r = d < 3 ? fminf(r, ws[w][d]) : fmaxf(r, ws[w][d]);
     box[d] = r;
   }
+  if (threadIdx.x == 0) {
+    seg.blk_off[0] = 0;
+    seg.blk_off[1] = (np + kSortKeys - 1) / kSortKeys;
+    seg.blk_off[2] = seg.blk_off[1] + (nq + kSortKeys - 1) / kSortKeys;
+    seg.base[0] = 0;
+    seg.base[1] = np;
+    seg.len[0] = np;
+    seg.len[1] = nq;
+  }
 }
 
 __device__ __forceinline__ uint32_t spread10(uint32_t v) {
@@ -128,44 +143,56 @@ __device__ __forceinline__ uint32_t spread10(uint32_t v) {
   return v;
 }
 
-// 30-bit Morton code of every point on a cubic grid of 1024 cells per axis
-// over the common box; value = the point's index.
-__global__ __launch_bounds__(256) void k_ov_codes(const float* __restrict__ p, int n, const float* __restrict__ box,
-                                                  uint32_t* __restrict__ code, uint32_t* __restrict__ idx) {
-  const int i = blockIdx.x * kBlock + threadIdx.x;
-  if (i >= n) return;
+// 30-bit Morton code of every point of both sets (P's first) on a cubic grid
+// of 1024 cells per axis over the common box; value = the point's index in its
+// set.
+__global__ __launch_bounds__(256) void k_ov_codes(const float* __restrict__ p, int np, const float* __restrict__ q,
+                                                  int nq, const float* __restrict__ box, uint32_t* __restrict__ code,
+                                                  uint32_t* __restrict__ idx) {
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (i >= (int64_t)np + nq) return;
+  const float* __restrict__ s = i < np ? p : q;
+  const int64_t n = i < np ? np : nq, k = i < np ? i : i - np;
   const float ext = fmaxf(fmaxf(box[3] - box[0], box[4] - box[1]), box[5] - box[2]);
   const float inv = ext > 0.f ? 1023.f / ext : 0.f;
   uint32_t c = 0;
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
-    const float q = (p[(int64_t)d * n + i] - box[d]) * inv;
-    const uint32_t u = (uint32_t)fminf(fmaxf(q, 0.f), 1023.f);
+    const float v = (s[d * n + k] - box[d]) * inv;
+    const uint32_t u = (uint32_t)fminf(fmaxf(v, 0.f), 1023.f);
     c |= spread10(u) << d;
   }
   code[i] = c;
-  idx[i] = (uint32_t)i;
+  idx[i] = (uint32_t)k;
 }
 
-// Points in curve order (SoA x, y, z, original index, code) and one box per leaf
-// (one wave per leaf).
-__global__ __launch_bounds__(256) void k_ov_gather(const float* __restrict__ p, int n,
-                                                   const uint32_t* __restrict__ order,
-                                                   const uint32_t* __restrict__ code, float* __restrict__ sp,
-                                                   int32_t* __restrict__ sidx, uint32_t* __restrict__ scode,
-                                                   float* __restrict__ leaf_box) {
+struct OvSet {
+  float* p;              // [3][n] in curve order
+  const int32_t* idx;    // original indices
+  const uint32_t* code;  // sorted Morton codes
+  float* leaf;           // [nleaf][6]
+  float* super;          // [nsuper][6]
+  int n, nleaf, nsuper;
+};
+
+// Points in curve order (SoA x, y, z) and one box per leaf (one wave per
+// leaf); grid y: the set.
+__global__ __launch_bounds__(256) void k_ov_gather(const float* __restrict__ p, const float* __restrict__ q,
+                                                   OvSet a, OvSet b) {
+  const OvSet& S = blockIdx.y ? b : a;
+  const float* __restrict__ src = blockIdx.y ? q : p;
+  const int n = S.n;
   const int i = blockIdx.x * kBlock + threadIdx.x;
+  if (blockIdx.x * kBlock >= n) return;  // uniform
   const bool v = i < n;
   float c[3] = {0.f, 0.f, 0.f};
   if (v) {
-    const uint32_t k = order[i];
+    const int32_t k = S.idx[i];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-      c[d] = p[(int64_t)d * n + k];
-      sp[(int64_t)d * n + i] = c[d];
+      c[d] = src[(int64_t)d * n + k];
+      S.p[(int64_t)d * n + i] = c[d];
     }
-    sidx[i] = (int32_t)k;
-    scode[i] = code[i];
   }
   float lo[3], hi[3];
 #pragma unroll
@@ -176,33 +203,25 @@ __global__ __launch_bounds__(256) void k_ov_gather(const float* __restrict__ p, 
   const int leaf = i / kOvLeaf;
   if ((threadIdx.x & 63) == 0 && leaf * kOvLeaf < n)
     for (int d = 0; d < 3; ++d) {
-      leaf_box[6 * leaf + d] = lo[d];
-      leaf_box[6 * leaf + 3 + d] = hi[d];
+      S.leaf[6 * leaf + d] = lo[d];
+      S.leaf[6 * leaf + 3 + d] = hi[d];
     }
 }
 
-__global__ __launch_bounds__(256) void k_ov_super(const float* __restrict__ leaf_box, int nleaf,
-                                                  float* __restrict__ super_box, int nsuper) {
+__global__ __launch_bounds__(256) void k_ov_super(OvSet a, OvSet b_) {
+  const OvSet& S = blockIdx.y ? b_ : a;
   const int s = blockIdx.x * kBlock + threadIdx.x;
-  if (s >= nsuper) return;
+  if (s >= S.nsuper) return;
   float b[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
-  const int l1 = (s + 1) * kOvSuper < nleaf ? (s + 1) * kOvSuper : nleaf;
+  const int l1 = (s + 1) * kOvSuper < S.nleaf ? (s + 1) * kOvSuper : S.nleaf;
   for (int l = s * kOvSuper; l < l1; ++l)
     for (int d = 0; d < 3; ++d) {
-      b[d] = fminf(b[d], leaf_box[6 * l + d]);
-      b[3 + d] = fmaxf(b[3 + d], leaf_box[6 * l + 3 + d]);
+      b[d] = fminf(b[d], S.leaf[6 * l + d]);
+      b[3 + d] = fmaxf(b[3 + d], S.leaf[6 * l + 3 + d]);
     }
-  for (int d = 0; d < 6; ++d) super_box[6 * s + d] = b[d];
+  for (int d = 0; d < 6; ++d) S.super[6 * s + d] = b[d];
 }
 
-struct OvSet {
-  const float* p;        // [3][n] in curve order
-  const int32_t* idx;    // original indices
-  const uint32_t* code;  // sorted Morton codes
-  const float* leaf;     // [nleaf][6]
-  const float* super;    // [nsuper][6]
-  int n, nleaf, nsuper;
-};
 
 // Squared distance from a point to a box (min xyz, max xyz); 0 inside.
 __device__ __forceinline__ float point_box_dist2(float x, float y, float z, const float* b) {
@@ -308,11 +327,15 @@ __global__ __launch_bounds__(256) void k_ov_count(const float* __restrict__ pt, 
   }
 }
 
-// Workspace layout (all pieces 256-byte aligned).
+// Workspace layout (all pieces 256-byte aligned).  The sorted codes and
+// indices stay in the sort's buffers.
 struct OvLayout {
-  size_t pt, box_part, box, code_a, idx_a, code_b, idx_b, hist, digits, set_p[5], set_q[5], total;
+  size_t pt, box_part, box, segs, code_a, idx_a, code_b, idx_b, hist, set_p[3], set_q[3], total;
 };
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
+static int ov_sort_blocks(int np, int nq) {
+  return (np + kSortKeys - 1) / kSortKeys + (nq + kSortKeys - 1) / kSortKeys;
+}
 static OvLayout ov_layout(int np, int nq) {
   OvLayout L{};
   size_t o = 0;
@@ -321,25 +344,23 @@ static OvLayout ov_layout(int np, int nq) {
     o += align256(bytes);
     return at;
   };
-  const int64_t nmax = std::max(np, nq);
+  const size_t both = (size_t)np + nq;
   L.pt = take(12 * (size_t)np);
   L.box_part = take(4 * 6 * kOvBoxBlocks);
   L.box = take(4 * 6);
-  L.code_a = take(4 * (size_t)nmax);
-  L.idx_a = take(4 * (size_t)nmax);
-  L.code_b = take(4 * (size_t)nmax);
-  L.idx_b = take(4 * (size_t)nmax);
-  L.hist = take(4 * 256 * (size_t)std::max<int64_t>(sort_blocks(nmax), 1));
-  L.digits = take(4 * 256);
+  L.segs = take(64);
+  L.code_a = take(4 * both);
+  L.idx_a = take(4 * both);
+  L.code_b = take(4 * both);
+  L.idx_b = take(4 * both);
+  L.hist = take(4 * (size_t)seg_hist_words(ov_sort_blocks(np, nq)));
   for (int s = 0; s < 2; ++s) {
     const int n = s ? nq : np;
     const int nleaf = (n + kOvLeaf - 1) / kOvLeaf, nsuper = (nleaf + kOvSuper - 1) / kOvSuper;
     size_t* S = s ? L.set_q : L.set_p;
     S[0] = take(12 * (size_t)n);         // points in curve order
-    S[1] = take(4 * (size_t)n);          // original indices
-    S[2] = take(4 * (size_t)n);          // sorted codes
-    S[3] = take(24 * (size_t)nleaf);     // leaf boxes
-    S[4] = take(24 * (size_t)nsuper);    // superblock boxes
+    S[1] = take(24 * (size_t)nleaf);     // leaf boxes
+    S[2] = take(24 * (size_t)nsuper);    // superblock boxes
   }
   L.total = o;
   return L;
@@ -365,34 +386,39 @@ void launch_overlap(const float* p_mean, int np, const float* q_mean, int nq, co
   float* box = reinterpret_cast<float*>(w + L.box);
   hipLaunchKernelGGL(k_ov_box_part, dim3(kOvBoxBlocks), dim3(kBlock), 0, s, (const float*)pt, np, q_mean, nq,
                      box_part);
-  hipLaunchKernelGGL(k_ov_box_final, dim3(1), dim3(kBlock), 0, s, (const float*)box_part, kOvBoxBlocks, box);
+  char* sg = w + L.segs;
+  const OvSegs segs{reinterpret_cast<int32_t*>(sg), reinterpret_cast<int64_t*>(sg + 16),
+                    reinterpret_cast<int32_t*>(sg + 32)};
+  hipLaunchKernelGGL(k_ov_box_final, dim3(1), dim3(kBlock), 0, s, (const float*)box_part, kOvBoxBlocks, np, nq, box,
+                     segs);
+  uint32_t* ca = reinterpret_cast<uint32_t*>(w + L.code_a);
+  uint32_t* ia = reinterpret_cast<uint32_t*>(w + L.idx_a);
+  uint32_t* cb = reinterpret_cast<uint32_t*>(w + L.code_b);
+  uint32_t* ib = reinterpret_cast<uint32_t*>(w + L.idx_b);
+  uint32_t* hist = reinterpret_cast<uint32_t*>(w + L.hist);
+  const int64_t both = (int64_t)np + nq;
+  hipLaunchKernelGGL(k_ov_codes, dim3((unsigned)((both + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, (const float*)pt,
+                     np, q_mean, nq, (const float*)box, ca, ia);
+  // both sets in one sort; four passes over the 30-bit codes end in (ca, ia)
+  const SegTable seg{segs.blk_off, segs.base, 2, segs.len};
+  const int nsb = ov_sort_blocks(np, nq);
+  launch_seg_pass(ca, ia, cb, ib, seg, nsb, 0, hist, false, s);
+  launch_seg_pass(cb, ib, ca, ia, seg, nsb, 8, hist, false, s);
+  launch_seg_pass(ca, ia, cb, ib, seg, nsb, 16, hist, false, s);
+  launch_seg_pass(cb, ib, ca, ia, seg, nsb, 24, hist, false, s);
   OvSet set[2];
   for (int k = 0; k < 2; ++k) {
     const int n = k ? nq : np;
-    const float* src = k ? q_mean : pt;
     const size_t* S = k ? L.set_q : L.set_p;
-    uint32_t* ca = reinterpret_cast<uint32_t*>(w + L.code_a);
-    uint32_t* ia = reinterpret_cast<uint32_t*>(w + L.idx_a);
-    uint32_t* cb = reinterpret_cast<uint32_t*>(w + L.code_b);
-    uint32_t* ib = reinterpret_cast<uint32_t*>(w + L.idx_b);
-    hipLaunchKernelGGL(k_ov_codes, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, s, src, n, (const float*)box, ca,
-                       ia);
-    const int which = launch_radix_sort_pairs(ca, ia, cb, ib, n, 30, reinterpret_cast<uint32_t*>(w + L.hist),
-                                              reinterpret_cast<uint32_t*>(w + L.digits), s);
-    const uint32_t* code = which ? cb : ca;
-    const uint32_t* order = which ? ib : ia;
     const int nleaf = (n + kOvLeaf - 1) / kOvLeaf, nsuper = (nleaf + kOvSuper - 1) / kOvSuper;
-    float* sp = reinterpret_cast<float*>(w + S[0]);
-    int32_t* sidx = reinterpret_cast<int32_t*>(w + S[1]);
-    uint32_t* scode = reinterpret_cast<uint32_t*>(w + S[2]);
-    float* leaf = reinterpret_cast<float*>(w + S[3]);
-    float* sup = reinterpret_cast<float*>(w + S[4]);
-    hipLaunchKernelGGL(k_ov_gather, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, s, src, n, order, code, sp,
-                       sidx, scode, leaf);
-    hipLaunchKernelGGL(k_ov_super, dim3((nsuper + kBlock - 1) / kBlock), dim3(kBlock), 0, s, (const float*)leaf,
-                       nleaf, sup, nsuper);
-    set[k] = OvSet{sp, sidx, scode, leaf, sup, n, nleaf, nsuper};
+    set[k] = OvSet{reinterpret_cast<float*>(w + S[0]), reinterpret_cast<int32_t*>(ia) + (k ? np : 0),
+                   ca + (k ? np : 0), reinterpret_cast<float*>(w + S[1]), reinterpret_cast<float*>(w + S[2]), n,
+                   nleaf, nsuper};
   }
+  const int nmax = std::max(np, nq), smax = std::max(set[0].nsuper, set[1].nsuper);
+  hipLaunchKernelGGL(k_ov_gather, dim3((nmax + kBlock - 1) / kBlock, 2), dim3(kBlock), 0, s, (const float*)pt, q_mean,
+                     set[0], set[1]);
+  hipLaunchKernelGGL(k_ov_super, dim3((smax + kBlock - 1) / kBlock, 2), dim3(kBlock), 0, s, set[0], set[1]);
   const int waves_per_block = kBlock / kOvLeaf;
   hipLaunchKernelGGL(k_ov_nn, dim3((set[0].nleaf + waves_per_block - 1) / waves_per_block), dim3(kBlock), 0, s,
                      set[0], set[1], nn_pq);
