@@ -128,11 +128,11 @@ __device__ __forceinline__ void stage_conic(float4& a, float4& b) {
   b.z = __uint_as_float(t >= 0.f ? __float_as_uint(t) + 1u : 0u);
 }
 
-// Whether a staged splat (b from stage_conic) is composited at a pixel whose
+// Whether a staged splat (bound: b.z from stage_conic) is composited at a pixel whose
 // sigma log2(e) is sl: alpha >= 1/255 and sigma >= 0, the test of both the
 // forward and the backward.
-__device__ __forceinline__ bool composited(float sl, const float4& b) {
-  return __float_as_uint(sl) < __float_as_uint(b.z);
+__device__ __forceinline__ bool composited(float sl, float bound) {
+  return __float_as_uint(sl) < __float_as_uint(bound);
 }
 
 // sigma log2(e) at pixel offset (dx, dy) from a staged conic, as

@@ -14,6 +14,8 @@
 
 namespace ls {
 
+typedef float v4f __attribute__((ext_vector_type(4)));
+
 struct TileCtx {
   int r;         // render
   int tile;      // global tile index
@@ -113,17 +115,29 @@ __device__ __forceinline__ uint32_t wave_mask(float4 a, float4 b, int tile_x0, i
 // over the band's column strip (strip_extent, widened as in wave_mask) holds
 // every pixel centre the support contains, so a row whose centre lies outside
 // it holds no pixel that composites the entry.
+// Reciprocals and roots are the instructions' own (1 ulp): the margins of
+// 0.1 % cover them, and one such test per entry and band was a fifth of the
+// forward's instructions with correctly rounded ones.
 __device__ __forceinline__ uint64_t band_rows(float4 a, float4 b, float bx0, float by0) {
   const float o = b.y;
   if (!(o >= LS_ALPHA_MIN)) return 0ull;
   const float A = a.z, B = a.w, C = b.x;
   const float dq = A * C - B * B;
-  if (!(dq > 0.f)) return ~0ull;
-  const float smax = __logf(o * (1.0f / LS_ALPHA_MIN)) * 1.001f + 1e-4f;
-  const float hx = sqrtf(fmaxf(2.f * smax * C / dq, 0.f)) * 1.001f + 0.02f;
-  const float hy = sqrtf(fmaxf(2.f * smax * A / dq, 0.f)) * 1.001f + 0.02f;
-  float ylo, yhi;
-  if (!strip_extent(a.x, a.y, A, B, C, dq, smax, hx, hy, bx0, bx0 + 7.f, ylo, yhi)) return 0ull;
+  if (!(dq > 1e-30f)) return ~0ull;  // (below it the reciprocal may overflow)
+  const float t2 = 2.002f * __logf(o * (1.0f / LS_ALPHA_MIN)) + 2e-4f;  // 2 s, widened
+  const float idq = t2 * __builtin_amdgcn_rcpf(dq), rc = __builtin_amdgcn_rcpf(C);
+  const float hx = __builtin_amdgcn_sqrtf(fmaxf(C * idq, 0.f)) * 1.001f + 0.02f;
+  const float hy = __builtin_amdgcn_sqrtf(fmaxf(A * idq, 0.f)) * 1.001f + 0.02f;
+  const float x0 = bx0 - a.x, x1 = x0 + 7.f;  // the band's columns, from the centre
+  const float sx = B * __builtin_amdgcn_rcpf(A) * hy;  // the highest point sits at -sx, the lowest at sx
+  const float top = fminf(fmaxf(-sx, x0), x1), bot = fminf(fmaxf(sx, x0), x1);
+  const float tc = t2 * C;
+  const float dt = tc - dq * top * top, db = tc - dq * bot * bot;
+  const float eh = top == -sx ? hy : (__builtin_amdgcn_sqrtf(dt) - B * top) * rc;
+  const float el = bot == sx ? hy : (__builtin_amdgcn_sqrtf(db) + B * bot) * rc;
+  // (a negative D makes the extent a NaN; hx decides with the same margin)
+  if (!(x0 <= hx && x1 >= -hx) || !(eh == eh) || !(el == el)) return 0ull;
+  const float yhi = a.y + eh + (fabsf(eh) * 1e-3f + 0.02f), ylo = a.y - el - (fabsf(el) * 1e-3f + 0.02f);
   const int r0 = (int)fmaxf(ceilf(ylo - by0), 0.f), r1 = (int)fminf(floorf(yhi - by0), 7.f);
   if (r0 > r1) return 0ull;
   return (~0ull >> (8 * (7 - r1))) & (~0ull << (8 * r0));
@@ -137,6 +151,16 @@ __device__ __forceinline__ uint64_t band_rows(float4 a, float4 b, float bx0, flo
 // compacted, in list order, into the wave's LDS.  (Measured against a
 // 256-thread block per tile that staged each record once for all four bands:
 // 1 % faster on the render loop and on a registration pair.)
+//
+// Bound by vector instruction issue (at 200k items, 1200 x 680: 43 M of them
+// filled 84 % of 90 us).  A step therefore masks once, the alpha, so that one
+// select covers weight and transmittance; a pixel that has stopped goes on
+// with T = 0; and the four sums take one 4x4x1 matrix instruction (lane l
+// supplies channel l & 3 of the entry's colour and depth, every lane its
+// weight), which gives the FMA chain's bits in the time of two of its four
+// FMAs and reads 4 instead of 16 bytes of LDS per lane.  With the band test
+// on reciprocal and square root instructions: 34 M, 83 us; 16 renders of 150k
+// and 120k items at 640 x 480 231 -> 217 us, 8 of 150k 141 -> 131 us.
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8))) void k_composite_fwd_band(
     const JobDev* __restrict__ jobs, const int32_t* __restrict__ tile_off, int R, int T_total,
     const float4* __restrict__ rec, const int32_t* __restrict__ items, const int32_t* __restrict__ range, float bg0,
@@ -162,7 +186,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8))) void k_
   const float bx0 = (float)(tx0 + 8 * (band & 1)) + 0.5f, by0 = (float)(ty0 + 8 * (band >> 1)) + 0.5f;
   const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
 
-  float T = 1.f, cr = 0.f, cg = 0.f, cb = 0.f, dd = 0.f;
+  float T = inside ? 1.f : 0.f, Tend = 1.f;  // transmittance while compositing (0 once stopped), and at the stop
+  v4f acc = {0.f, 0.f, 0.f, 0.f};              // rgb and depth
   int nlast = end - start;
   uint64_t alive = __ballot(inside);  // lane l is pixel (l & 7, l >> 3) of the band: bit l of band_rows
   // chunk k of the tile's list keeps its "used" bits in slot (start / 64) +
@@ -199,31 +224,34 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8))) void k_
     const int cw = __popcll(bal);
     // one step at staged entry j; returns whether every pixel has now stopped
     // (decided only where pixels stop, so a step that stops none tests nothing)
-    auto step = [&](int j, const float4& a, const float4& b, const float4& col) -> bool {
+    auto step = [&](int j, const float4& a, const float3& b, float col) -> bool {
       bool ended = false;
       const float dx = fx - a.x, dy = fy - a.y;
       const float sl = falloff_log2(a.z, a.w, b.x, dx, dy);
-      const float al = fminf(LS_ALPHA_MAX, b.y * __builtin_amdgcn_exp2f(-sl));
-      // the weight alpha T, and T (1 - alpha) as T - alpha T in one FMA
-      const float w = al * T, Tn = __builtin_fmaf(-al, T, T);
-      const uint64_t hit = alive & __ballot(composited(sl, b));
-      const uint64_t stop = hit & __ballot(Tn < LS_T_STOP);
-      const uint64_t use = hit & ~stop;
-      if (stop != 0ull) {
-        if (__builtin_amdgcn_inverse_ballot_w64(stop)) nlast = spos[j];
-        alive &= ~stop;
-        ended = alive == 0ull;
-      }
-      if (use != 0ull) {
-        const bool u = __builtin_amdgcn_inverse_ballot_w64(use);
-        const float wgt = u ? w : 0.f;  // 0 adds an exact zero below
-        cr += wgt * col.x;
-        cg += wgt * col.y;
-        cb += wgt * col.z;
-        dd += wgt * col.w;
-        T = u ? Tn : T;
-        // usedm |= 1 << j in one scalar instruction (a register-only bit set)
-        asm volatile("s_bitset1_b64 %0, %1" : "+s"(usedm) : "s"(j));
+      const bool c = composited(sl, b.z);
+      const uint64_t hit = alive & __ballot(c);
+      if (hit != 0ull) {
+        // a pixel that does not composite the entry takes alpha 0: weight 0, T as it was
+        const float al = c ? fminf(LS_ALPHA_MAX, b.y * __builtin_amdgcn_exp2f(-sl)) : 0.f;
+        // the weight alpha T, and T (1 - alpha) as T - alpha T in one FMA
+        float w = al * T, Tn = __builtin_fmaf(-al, T, T);
+        const uint64_t stop = hit & __ballot(Tn < LS_T_STOP);
+        if (stop != 0ull) {
+          if (__builtin_amdgcn_inverse_ballot_w64(stop)) {
+            nlast = spos[j];
+            Tend = T;
+            w = 0.f;
+            Tn = 0.f;
+          }
+          alive &= ~stop;
+          ended = alive == 0ull;
+        }
+        T = Tn;
+        if (hit != stop) {
+          acc = __builtin_amdgcn_mfma_f32_4x4x1f32(col, w, acc, 0, 0, 0);
+          // usedm |= 1 << j in one scalar instruction (a register-only bit set)
+          asm volatile("s_bitset1_b64 %0, %1" : "+s"(usedm) : "s"(j));
+        }
       }
       return ended;
     };
@@ -232,15 +260,21 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8))) void k_
     // next entry overlaps the arithmetic of this one; the read past the last
     // staged entry (at most entry 64, the padding) is never used.  The walk
     // ends after the staged entries or once every pixel has stopped.
-    float4 aA = s0[0], bA = s1[0], cA = s2[0], aB, bB, cB;
+    const float4* pa = s0;
+    const float4* pb = s1;
+    const float* pc = reinterpret_cast<const float*>(s2) + (lane & 3);
+    auto b3 = [](const float4& v) { return make_float3(v.x, v.y, v.z); };
+    float4 aA = pa[0], aB;
+    float3 bA = b3(pb[0]), bB;
+    float cA = pc[0], cB;
     for (int jj = 0; jj < cw;) {
-      aB = s0[jj + 1];
-      bB = s1[jj + 1];
-      cB = s2[jj + 1];
+      aB = pa[jj + 1];
+      bB = b3(pb[jj + 1]);
+      cB = pc[4 * (jj + 1)];
       if (step(jj, aA, bA, cA) || ++jj >= cw) break;
-      aA = s0[jj + 1];
-      bA = s1[jj + 1];
-      cA = s2[jj + 1];
+      aA = pa[jj + 1];
+      bA = b3(pb[jj + 1]);
+      cA = pc[4 * (jj + 1)];
       if (step(jj, aB, bB, cB)) break;
       ++jj;
     }
@@ -255,12 +289,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8))) void k_
   const int64_t hw = (int64_t)J.W * J.H;
   const int64_t pix = J.pix_off + (int64_t)y * J.W + x;
   float* rgb = out_rgb + 3 * J.pix_off + (int64_t)y * J.W + x;
-  rgb[0] = cr + T * bg0;
-  rgb[hw] = cg + T * bg1;
-  rgb[2 * hw] = cb + T * bg2;
-  out_depth[pix] = dd;
-  out_alpha[pix] = 1.f - T;
-  out_T[pix] = T;
+  const float Tf = __builtin_amdgcn_inverse_ballot_w64(alive) ? T : Tend;
+  rgb[0] = acc[0] + Tf * bg0;
+  rgb[hw] = acc[1] + Tf * bg1;
+  rgb[2 * hw] = acc[2] + Tf * bg2;
+  out_depth[pix] = acc[3];
+  out_alpha[pix] = 1.f - Tf;
+  out_T[pix] = Tf;
   out_n[pix] = nlast;
 }
 
@@ -369,7 +404,7 @@ __device__ __forceinline__ float step_alpha(const float4& a, const float4& b, in
   const float sl = falloff_log2(a.z, a.w, b.x, dx, dy);
   const float G = b.y * __builtin_amdgcn_exp2f(-sl);
   // & and not &&: no branch
-  return (__float_as_int(b.w) < nl) & composited(sl, b) ? fminf(LS_ALPHA_MAX, G) : 0.f;
+  return (__float_as_int(b.w) < nl) & composited(sl, b.z) ? fminf(LS_ALPHA_MAX, G) : 0.f;
 }
 
 // The band of a 64-thread block: unit = 4 tile + band, lane l its pixel
@@ -867,7 +902,7 @@ __global__ __launch_bounds__(kBlock) void k_render_stats(const JobDev* __restric
       const float4 b = s1[j];
       const float dx = fx - a.x, dy = fy - a.y;
       const float sl = falloff_log2(a.z, a.w, b.x, dx, dy);
-      if (composited(sl, b)) ++comp;
+      if (composited(sl, b.z)) ++comp;
     }
     __syncthreads();
   }
