@@ -170,7 +170,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8))) void k_
   // one entry of padding: the walk reads entry j + 1 ahead without a clamp
   __shared__ float4 s0[65], s1[65], s2[65];
   __shared__ int32_t spos[64];
-  const int unit = xcd_remap(blockIdx.x, 4 * T_total);
+  const int unit = xcd_turns<64>(blockIdx.x, 4 * T_total);
   if (unit >= 4 * T_total) return;
   const int tile = unit >> 2, band = unit & 3;
   const int lane = threadIdx.x;
@@ -723,7 +723,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
     const float* __restrict__ up_depth, const float* __restrict__ up_alpha, const float* __restrict__ up_scale,
     float* __restrict__ g2d, L1Targets l1) {
   __shared__ __attribute__((aligned(16))) BandLds L;
-  const int unit = xcd_remap(blockIdx.x, 4 * T_total);
+  const int unit = xcd_turns<64>(blockIdx.x, 4 * T_total);
   if (unit >= 4 * T_total) return;
   const int lane = threadIdx.x;
   const BandCtx c = band_ctx(jobs, tile_off, R, unit);
@@ -796,7 +796,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
     const float* __restrict__ up_alpha, const float* __restrict__ up_scale, float* __restrict__ band_part,
     L1Targets l1) {
   __shared__ __attribute__((aligned(16))) BandLds L;
-  const int unit = xcd_remap(blockIdx.x, 4 * T_total);
+  const int unit = xcd_turns<64>(blockIdx.x, 4 * T_total);
   if (unit >= 4 * T_total) return;
   const int lane = threadIdx.x;
   const BandCtx c = band_ctx(jobs, tile_off, R, unit);
