@@ -4,12 +4,11 @@
 // distance is below tau_1.
 //
 // Every nearest neighbour is exact: both point sets are sorted along a
-// 30-bit Morton curve and cut into leaf blocks of 64 points (one wave) and
-// superblocks of 32 leaves, each with its bounding box.  A wave of 64 query
-// points visits the candidate superblocks and leaves outward from the
-// query's place on the curve and skips any box that is farther from every
-// one of its points than that point's current best (with a margin over FP32
-// rounding), so no skipped point can win or tie.  Distances and the
+// 30-bit Hilbert curve and cut into leaves of 16 points and superblocks of 64
+// leaves, each with its bounding box.  A wave of 32 query points visits the
+// candidate superblocks and leaves nearest box first and skips any box that is
+// farther from every one of its points than that point's current best (with a
+// margin over FP32 rounding), so no skipped point can win or tie.  Distances and the
 // transform follow one fixed FP32 rounding sequence (no fused multiply-add)
 // so that matches and ties are reproducible: d^2 = (dx^2 + dy^2) + dz^2,
 // ties to the lower index.
@@ -22,8 +21,10 @@
 
 namespace ls {
 
-constexpr int kOvLeaf = 64;       // points per leaf block (one wave)
-constexpr int kOvSuper = 32;      // leaves per superblock
+constexpr int kOvLeaf = 16;       // points per leaf
+constexpr int kOvSuper = 64;      // leaves per superblock (one per lane of a wave)
+constexpr int kOvQuery = 32;      // query points per wave, two lanes each
+constexpr int kOvMany = 16;       // of 64 leaves: more are first tested against every query point
 constexpr int kOvBoxBlocks = 256; // blocks of the bounding-box reduction
 constexpr float kOvPrune = 1.f - 1e-5f;  // a box is skipped only if lb^2 * kOvPrune > bound
 
@@ -143,9 +144,35 @@ __device__ __forceinline__ uint32_t spread10(uint32_t v) {
   return v;
 }
 
-// 30-bit Morton code of every point of both sets (P's first) on a cubic grid
-// of 1024 cells per axis over the common box; value = the point's index in its
-// set.
+// 30-bit Hilbert index of a cell of the 1024^3 grid (J. Skilling, "Programming
+// the Hilbert curve", 2004: undo the excess work from the top bit down, then
+// Gray decode; the bits of the three axes interleave into the index).
+__device__ __forceinline__ uint32_t hilbert30(uint32_t x, uint32_t y, uint32_t z) {
+  uint32_t X[3] = {x, y, z};
+#pragma unroll
+  for (uint32_t q = 512u; q > 1u; q >>= 1) {
+    const uint32_t low = q - 1u;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const uint32_t t = (X[0] ^ X[i]) & low;
+      const bool set = (X[i] & q) != 0u;
+      X[0] ^= set ? low : t;  // invert, or exchange with axis i
+      if (i > 0) X[i] ^= set ? 0u : t;
+    }
+  }
+  X[1] ^= X[0];
+  X[2] ^= X[1];
+  uint32_t t = 0u;
+#pragma unroll
+  for (uint32_t q = 512u; q > 1u; q >>= 1) t ^= (X[2] & q) != 0u ? q - 1u : 0u;
+  return (spread10(X[0] ^ t) << 2) | (spread10(X[1] ^ t) << 1) | spread10(X[2] ^ t);
+}
+
+// Place on the Hilbert curve of every point of both sets (P's first), on a
+// cubic grid of 1024 cells per axis over the common box; value = the point's
+// index in its set.  (A Morton curve jumps: one wave of queries in ten then
+// spans a large part of the scene, and its box meets up to all leaves: 85
+// leaves on average against 46 on this curve, 7,500 at worst against 2,800.)
 __global__ __launch_bounds__(256) void k_ov_codes(const float* __restrict__ p, int np, const float* __restrict__ q,
                                                   int nq, const float* __restrict__ box, uint32_t* __restrict__ code,
                                                   uint32_t* __restrict__ idx) {
@@ -155,28 +182,23 @@ __global__ __launch_bounds__(256) void k_ov_codes(const float* __restrict__ p, i
   const int64_t n = i < np ? np : nq, k = i < np ? i : i - np;
   const float ext = fmaxf(fmaxf(box[3] - box[0], box[4] - box[1]), box[5] - box[2]);
   const float inv = ext > 0.f ? 1023.f / ext : 0.f;
-  uint32_t c = 0;
+  uint32_t u[3];
 #pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    const float v = (s[d * n + k] - box[d]) * inv;
-    const uint32_t u = (uint32_t)fminf(fmaxf(v, 0.f), 1023.f);
-    c |= spread10(u) << d;
-  }
-  code[i] = c;
+  for (int d = 0; d < 3; ++d) u[d] = (uint32_t)fminf(fmaxf((s[d * n + k] - box[d]) * inv, 0.f), 1023.f);
+  code[i] = hilbert30(u[0], u[1], u[2]);
   idx[i] = (uint32_t)k;
 }
 
 struct OvSet {
   float* p;              // [3][n] in curve order
   const int32_t* idx;    // original indices
-  const uint32_t* code;  // sorted Morton codes
-  float* leaf;           // [nleaf][6]
-  float* super;          // [nsuper][6]
+  const uint32_t* code;  // sorted curve places
+  float* leaf;           // [6][nleaf] min xyz, max xyz
+  float* super;          // [6][nsuper]
   int n, nleaf, nsuper;
 };
 
-// Points in curve order (SoA x, y, z) and one box per leaf (one wave per
-// leaf); grid y: the set.
+// Points in curve order (SoA x, y, z) and one box per leaf; grid y: the set.
 __global__ __launch_bounds__(256) void k_ov_gather(const float* __restrict__ p, const float* __restrict__ q,
                                                    OvSet a, OvSet b) {
   const OvSet& S = blockIdx.y ? b : a;
@@ -197,104 +219,236 @@ __global__ __launch_bounds__(256) void k_ov_gather(const float* __restrict__ p, 
   float lo[3], hi[3];
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
-    lo[d] = wave_min_f(v ? c[d] : INFINITY);
-    hi[d] = wave_max_f(v ? c[d] : -INFINITY);
+    lo[d] = v ? c[d] : INFINITY;
+    hi[d] = v ? c[d] : -INFINITY;
+#pragma unroll
+    for (int o = kOvLeaf / 2; o > 0; o >>= 1) {
+      lo[d] = fminf(lo[d], __shfl_xor(lo[d], o, 64));
+      hi[d] = fmaxf(hi[d], __shfl_xor(hi[d], o, 64));
+    }
   }
   const int leaf = i / kOvLeaf;
-  if ((threadIdx.x & 63) == 0 && leaf * kOvLeaf < n)
+  if ((threadIdx.x & (kOvLeaf - 1)) == 0 && v)
     for (int d = 0; d < 3; ++d) {
-      S.leaf[6 * leaf + d] = lo[d];
-      S.leaf[6 * leaf + 3 + d] = hi[d];
+      S.leaf[d * S.nleaf + leaf] = lo[d];
+      S.leaf[(3 + d) * S.nleaf + leaf] = hi[d];
     }
 }
 
-__global__ __launch_bounds__(256) void k_ov_super(OvSet a, OvSet b_) {
+// One wave per superblock, a leaf per lane.
+__global__ __launch_bounds__(64) void k_ov_super(OvSet a, OvSet b_) {
   const OvSet& S = blockIdx.y ? b_ : a;
-  const int s = blockIdx.x * kBlock + threadIdx.x;
+  const int s = blockIdx.x, lane = threadIdx.x, l = s * kOvSuper + lane;
   if (s >= S.nsuper) return;
-  float b[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
-  const int l1 = (s + 1) * kOvSuper < S.nleaf ? (s + 1) * kOvSuper : S.nleaf;
-  for (int l = s * kOvSuper; l < l1; ++l)
-    for (int d = 0; d < 3; ++d) {
-      b[d] = fminf(b[d], S.leaf[6 * l + d]);
-      b[3 + d] = fmaxf(b[3 + d], S.leaf[6 * l + 3 + d]);
-    }
-  for (int d = 0; d < 6; ++d) S.super[6 * s + d] = b[d];
-}
-
-
-// Squared distance from a point to a box (min xyz, max xyz); 0 inside.
-__device__ __forceinline__ float point_box_dist2(float x, float y, float z, const float* b) {
-  const float g0 = fmaxf(fmaxf(b[0] - x, x - b[3]), 0.f);
-  const float g1 = fmaxf(fmaxf(b[1] - y, y - b[4]), 0.f);
-  const float g2 = fmaxf(fmaxf(b[2] - z, z - b[5]), 0.f);
-  return g0 * g0 + g1 * g1 + g2 * g2;
-}
-
-// One wave per query leaf: the exact nearest candidate of each of its points.
-// The wave first scans the candidate leaf at the query leaf's place on the
-// curve (a close first bound), then every superblock outward from there; a
-// superblock or leaf is skipped when, for every lane, its box is farther than
-// that lane's current best (scaled by kOvPrune against FP32 rounding), so a
-// skipped point can neither win nor tie.
-__device__ __forceinline__ void ov_scan_leaf(const OvSet& c, int l, int lane, float px, float py, float pz,
-                                             float& best, int& bi, float4* stage) {
-  // the leaf's candidates go through the wave's LDS slot and are read back
-  // with one uniform (broadcast) load each
-  const int ci = l * kOvLeaf + lane;
-  const bool cv = ci < c.n;
-  const float ax = cv ? c.p[ci] : 0.f, ay = cv ? c.p[(int64_t)c.n + ci] : 0.f;
-  const float az = cv ? c.p[2 * (int64_t)c.n + ci] : 0.f;
-  const int aid = cv ? c.idx[ci] : 0;
-  stage[lane] = make_float4(ax, ay, az, __int_as_float(aid));
-  __builtin_amdgcn_wave_barrier();
-  const int cnt = c.n - l * kOvLeaf < kOvLeaf ? c.n - l * kOvLeaf : kOvLeaf;
-#pragma unroll 4
-  for (int j = 0; j < cnt; ++j) {
-    const float4 b = stage[j];
-    const float d = sq_dist_rn(px, py, pz, b.x, b.y, b.z);
-    const int bid = __float_as_int(b.w);
-    const bool take = d < best || (d == best && bid < bi);
-    best = take ? d : best;
-    bi = take ? bid : bi;
+#pragma unroll
+  for (int d = 0; d < 6; ++d) {
+    const float x = l < S.nleaf ? S.leaf[d * S.nleaf + l] : d < 3 ? INFINITY : -INFINITY;
+    const float m = d < 3 ? wave_min_f(x) : wave_max_f(x);
+    if (lane == 0) S.super[d * S.nsuper + s] = m;
   }
+}
+
+// Minimum and maximum over the wave without LDS (DPP, as a prefix whose last
+// lane is the result).
+template <int kCtrl, int kRows>
+__device__ __forceinline__ float dpp_f(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), kCtrl, kRows, 0xF, false));
+}
+template <bool kMin>
+__device__ __forceinline__ float wave_extreme(float v) {
+  auto pick = [](float a, float b) { return kMin ? fminf(a, b) : fmaxf(a, b); };
+  v = pick(v, dpp_f<0x111, 0xF>(v));  // row_shr:1, 2, 4, 8
+  v = pick(v, dpp_f<0x112, 0xF>(v));
+  v = pick(v, dpp_f<0x114, 0xF>(v));
+  v = pick(v, dpp_f<0x118, 0xF>(v));
+  v = pick(v, dpp_f<0x142, 0xA>(v));  // row_bcast:15 -> rows 1, 3
+  v = pick(v, dpp_f<0x143, 0xC>(v));  // row_bcast:31 -> rows 2, 3
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+
+__device__ __forceinline__ float lane_f(float v, int l) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+
+// Squared distance between two boxes (min xyz, max xyz); 0 where they meet.  A
+// point is a box.  Every gap is at most that of any point in a, as rounding is
+// monotone.
+__device__ __forceinline__ float box_dist2(const float* a, const float* b) {
+  float s = 0.f;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const float g = fmaxf(fmaxf(b[d] - a[3 + d], a[d] - b[3 + d]), 0.f);
+    s += g * g;
+  }
+  return s;
+}
+
+struct OvBest {
+  float px, py, pz;  // this lane's query
+  float best;        // its nearest squared distance so far (-inf: no query)
+  int bi;            // and that point's index
+};
+
+// Point (d, id) against a lane's best: the nearer, of equals the lower index.
+__device__ __forceinline__ void ov_take(OvBest& o, float d, int id) {
+  const bool take = (d < o.best) | ((d == o.best) & (id < o.bi));
+  o.best = take ? d : o.best;
+  o.bi = take ? id : o.bi;
+}
+
+// The two lanes of a query take the better of their bests.
+__device__ __forceinline__ void ov_merge(OvBest& o) {
+  const auto d = __builtin_amdgcn_permlane32_swap(__float_as_uint(o.best), __float_as_uint(o.best), false, false);
+  const auto i = __builtin_amdgcn_permlane32_swap((uint32_t)o.bi, (uint32_t)o.bi, false, false);
+  o.best = __uint_as_float(d[0]);  // the lower lane's, in both
+  o.bi = (int)i[0];
+  ov_take(o, __uint_as_float(d[1]), (int)i[1]);
+}
+
+// All points of leaf l against the queries, half of them in each of a query's
+// lanes.
+__device__ __forceinline__ void ov_scan_leaf(const OvSet& c, int l, int lane, float4* stage, OvBest& o) {
+  // the leaf's candidates go through the wave's LDS slot and are read back
+  // with one (broadcast) load each; places past the end hold a distance of
+  // infinity and the index that never wins
+  const int ci = l * kOvLeaf + lane;
+  if (lane < kOvLeaf) {
+    const bool cv = ci < c.n;
+    stage[lane] = cv ? make_float4(c.p[ci], c.p[(int64_t)c.n + ci], c.p[2 * (int64_t)c.n + ci],
+                                   __int_as_float(c.idx[ci]))
+                     : make_float4(INFINITY, INFINITY, INFINITY, __int_as_float(0x7fffffff));
+  }
+  __builtin_amdgcn_wave_barrier();
+  const float4* half = stage + (lane >> 5) * (kOvLeaf / 2);
+#pragma unroll
+  for (int j = 0; j < kOvLeaf / 2; ++j) {
+    const float4 b = half[j];
+    ov_take(o, sq_dist_rn(o.px, o.py, o.pz, b.x, b.y, b.z), __float_as_int(b.w));
+  }
+  ov_merge(o);
   __builtin_amdgcn_wave_barrier();  // every lane has read the slot before it is refilled
 }
 
-__global__ __launch_bounds__(256) void k_ov_nn(OvSet q, OvSet c, int32_t* __restrict__ nn_out) {
-  __shared__ float4 stage_all[kBlock];
-  const int leaf = (int)((blockIdx.x * (int64_t)kBlock + threadIdx.x) / kOvLeaf);
-  const int lane = threadIdx.x & 63;
-  float4* stage = stage_all + (threadIdx.x & ~63);  // this wave's slot
-  if (leaf >= q.nleaf) return;  // whole waves; no block-wide barrier follows
-  const int qi = leaf * kOvLeaf + lane;
+// Whether lane l's box is near enough to any of the queries.
+__device__ __forceinline__ bool ov_reach(const float* box, int l, const OvBest& o) {
+  float b[6];
+#pragma unroll
+  for (int d = 0; d < 6; ++d) b[d] = lane_f(box[d], l);
+  const float pt[6] = {o.px, o.py, o.pz, o.px, o.py, o.pz};
+  return __ballot(box_dist2(pt, b) * kOvPrune <= o.best) != 0ull;
+}
+
+// Takes the nearest of the boxes in `todo` (bit l: lane l's, at squared
+// distance d), which is left out of it; -1 when it is farther than `bound`.
+__device__ __forceinline__ int ov_nearest(float d, uint64_t& todo, float bound) {
+  const bool mine = __builtin_amdgcn_inverse_ballot_w64(todo);
+  const float m = wave_extreme<true>(mine ? d : INFINITY);
+  if (!(m * kOvPrune <= bound)) return -1;
+  const int l = (int)__builtin_ctzll(__ballot(mine & (d == m)));
+  todo &= ~(1ull << l);
+  return l;
+}
+
+// One wave per 32 query points: the exact nearest candidate of each.  Every
+// query first takes the two candidates at its place on the curve (a close
+// first bound); then come superblocks and their leaves, nearest first, 64
+// boxes tested at a time against the box of the queries, and a box that is
+// near enough once more against each of them.  A box is skipped when it is
+// farther than the current best (scaled by kOvPrune against FP32 rounding), so
+// a skipped point can neither win nor tie.
+//
+// Bound by instruction issue (55 us of it) and by the slowest waves, whose
+// queries lie far apart or far from every candidate: 150k against 120k points,
+// both directions, 94 us.  Walking the boxes one by one in curve order, with
+// leaves of 64 points, left two launches of 2,000 waves waiting for the next
+// box, 966 us; 64 queries per wave, a lane each, 191 us (fewer waves, longer
+// tail); without the test of many leaves against every query 226 us.
+__global__ __launch_bounds__(64) void k_ov_nn(OvSet a, OvSet b, int32_t* __restrict__ nn_a,
+                                              int32_t* __restrict__ nn_b) {
+  __shared__ float4 stage[kOvLeaf];
+  const int ga = (a.n + kOvQuery - 1) / kOvQuery, lane = threadIdx.x;
+  const bool second = (int)blockIdx.x >= ga;
+  const OvSet q = second ? b : a, c = second ? a : b;
+  const int q0 = ((int)blockIdx.x - (second ? ga : 0)) * kOvQuery, qi = q0 + (lane & (kOvQuery - 1));
   const bool qv = qi < q.n;
-  const float px = qv ? q.p[qi] : 0.f, py = qv ? q.p[(int64_t)q.n + qi] : 0.f;
-  const float pz = qv ? q.p[2 * (int64_t)q.n + qi] : 0.f;
-  // the candidate leaf holding the query leaf's first code on the curve
-  const uint32_t code0 = q.code[leaf * kOvLeaf];
-  int lo = 0, hi = c.n;
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (c.code[mid] < code0) lo = mid + 1; else hi = mid;
+  OvBest o;
+  o.px = qv ? q.p[qi] : 0.f;
+  o.py = qv ? q.p[(int64_t)q.n + qi] : 0.f;
+  o.pz = qv ? q.p[2 * (int64_t)q.n + qi] : 0.f;
+  o.best = qv ? INFINITY : -INFINITY;
+  o.bi = 0x7fffffff;
+  float qb[6];  // the queries' box
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const float x = d == 0 ? o.px : d == 1 ? o.py : o.pz;
+    qb[d] = wave_extreme<true>(qv ? x : INFINITY);
+    qb[3 + d] = wave_extreme<false>(qv ? x : -INFINITY);
   }
-  const int l0 = lo / kOvLeaf < c.nleaf - 1 ? lo / kOvLeaf : c.nleaf - 1;
-  const int s0 = l0 / kOvSuper;
-  float best = INFINITY;
-  int bi = 0x7fffffff;
-  ov_scan_leaf(c, l0, lane, px, py, pz, best, bi, stage);
-  for (int k = 0; k < 2 * c.nsuper; ++k) {
-    const int s = (k & 1) ? s0 + (k + 1) / 2 : s0 - k / 2;
-    if (s < 0 || s >= c.nsuper) continue;
-    if (!__ballot(qv && point_box_dist2(px, py, pz, c.super + 6 * s) * kOvPrune <= best)) continue;
-    const int l1 = (s + 1) * kOvSuper < c.nleaf ? (s + 1) * kOvSuper : c.nleaf;
-    for (int l = s * kOvSuper; l < l1; ++l) {
-      if (l == l0) continue;
-      if (!__ballot(qv && point_box_dist2(px, py, pz, c.leaf + 6 * l) * kOvPrune <= best)) continue;
-      ov_scan_leaf(c, l, lane, px, py, pz, best, bi, stage);
+  // the candidates below the first query's place, 64 probes at a time, and
+  // from there those below each query's, its two lanes with one after another
+  {
+    const uint32_t code = q.code[min(qi, q.n - 1)], code0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)code);
+    int lo = 0, len = c.n;
+    while (len > 0) {
+      const int step = (int)(((uint32_t)len + 63u) >> 6), end = lo + len;
+      const uint32_t p = (uint32_t)lo + (uint32_t)(lane + 1) * (uint32_t)step - 1u;
+      const uint64_t below = __ballot(p < (uint32_t)end && c.code[min(p, (uint32_t)end - 1u)] < code0);
+      lo += (int)__popcll(below) * step;
+      len = min(step - 1, end - lo);
+    }
+    int hi = c.n;
+    int64_t reach = 32;  // a query's place is mostly close to the first one's
+    while (lo + reach < hi && __ballot(c.code[lo + reach - 1] < code) != 0ull) reach *= 4;
+    hi = (int)min(lo + reach, (int64_t)hi);
+    while (__ballot(lo < hi) != 0ull) {
+      const int mid = lo + ((hi - lo) >> 1);
+      const bool below = lo < hi && c.code[min(mid, c.n - 1)] < code;
+      lo = below ? mid + 1 : lo;
+      hi = below ? hi : mid;
+    }
+    const int k = min(max(lo - (lane >> 5), 0), c.n - 1);
+    if (qv) ov_take(o, sq_dist_rn(o.px, o.py, o.pz, c.p[k], c.p[(int64_t)c.n + k], c.p[2 * (int64_t)c.n + k]), c.idx[k]);
+    ov_merge(o);
+  }
+  float bound = wave_extreme<false>(o.best);
+
+  for (int sbase = 0; sbase < c.nsuper; sbase += 64) {
+    const int sl = min(sbase + lane, c.nsuper - 1);
+    float sbox[6];
+#pragma unroll
+    for (int d = 0; d < 6; ++d) sbox[d] = c.super[d * c.nsuper + sl];
+    const float ds = box_dist2(qb, sbox);
+    uint64_t supers = __ballot(sbase + lane < c.nsuper);
+    while (supers != 0ull) {
+      const int s = ov_nearest(ds, supers, bound);
+      if (s < 0) break;
+      if (!ov_reach(sbox, s, o)) continue;
+      const int lbase = (sbase + s) * kOvSuper, ll = min(lbase + lane, c.nleaf - 1);
+      float box[6];
+#pragma unroll
+      for (int d = 0; d < 6; ++d) box[d] = c.leaf[d * c.nleaf + ll];
+      const float dl = box_dist2(qb, box);
+      uint64_t leaves = __ballot(lbase + lane < c.nleaf && dl * kOvPrune <= bound);
+      if (__popcll(leaves) > kOvMany) {  // each of them against every query, 64 leaves at a time
+        bool near = false;
+#pragma unroll 4
+        for (int i = 0; i < kOvQuery; ++i) {
+          const float x = lane_f(o.px, i), y = lane_f(o.py, i), z = lane_f(o.pz, i);
+          const float pt[6] = {x, y, z, x, y, z};
+          near |= box_dist2(pt, box) * kOvPrune <= lane_f(o.best, i);
+        }
+        leaves &= __ballot(near);
+      }
+      while (leaves != 0ull) {
+        const int l = ov_nearest(dl, leaves, bound);
+        if (l < 0) break;
+        if (!ov_reach(box, l, o)) continue;
+        ov_scan_leaf(c, lbase + l, lane, stage, o);
+        bound = wave_extreme<false>(o.best);
+      }
     }
   }
-  if (qv) nn_out[q.idx[qi]] = bi;
+  if (qv && lane < kOvQuery) (second ? nn_b : nn_a)[q.idx[qi]] = o.bi;
 }
 
 // Reciprocity and the threshold test per point of P; one integer atomic per
@@ -418,12 +572,9 @@ void launch_overlap(const float* p_mean, int np, const float* q_mean, int nq, co
   const int nmax = std::max(np, nq), smax = std::max(set[0].nsuper, set[1].nsuper);
   hipLaunchKernelGGL(k_ov_gather, dim3((nmax + kBlock - 1) / kBlock, 2), dim3(kBlock), 0, s, (const float*)pt, q_mean,
                      set[0], set[1]);
-  hipLaunchKernelGGL(k_ov_super, dim3((smax + kBlock - 1) / kBlock, 2), dim3(kBlock), 0, s, set[0], set[1]);
-  const int waves_per_block = kBlock / kOvLeaf;
-  hipLaunchKernelGGL(k_ov_nn, dim3((set[0].nleaf + waves_per_block - 1) / waves_per_block), dim3(kBlock), 0, s,
-                     set[0], set[1], nn_pq);
-  hipLaunchKernelGGL(k_ov_nn, dim3((set[1].nleaf + waves_per_block - 1) / waves_per_block), dim3(kBlock), 0, s,
-                     set[1], set[0], nn_qp);
+  hipLaunchKernelGGL(k_ov_super, dim3(smax, 2), dim3(64), 0, s, set[0], set[1]);
+  const int groups = (np + kOvQuery - 1) / kOvQuery + (nq + kOvQuery - 1) / kOvQuery;
+  hipLaunchKernelGGL(k_ov_nn, dim3(groups), dim3(64), 0, s, set[0], set[1], nn_pq, nn_qp);
   const float tau2 = tau * tau;
   hipLaunchKernelGGL(k_ov_count, dim3((np + kBlock - 1) / kBlock), dim3(kBlock), 0, s, (const float*)pt, np, q_mean,
                      nq, (const int32_t*)nn_pq, (const int32_t*)nn_qp, tau2, counts);
