@@ -320,13 +320,15 @@ void launch_loss_l1(const JobDev* jobs, const int32_t* pblk_off_d, int R, int np
                     float* g_depth, float* part, float* loss, float* scale, hipStream_t s,
                     const float* expo = nullptr, float* epart = nullptr, float* egrad = nullptr);
 // Tracking loss with masks; sel = per-render selection workspace
-// (kSelWords(R) uint32, zero on first use, left zeroed after each call).
+// (sel_words(R) uint32, zero on first use, histograms left zeroed after each
+// call).
 void launch_loss_track(const JobDev* jobs, const int32_t* pblk_off_d, int R, int npblk, const float* pred_rgb,
                        const float* pred_depth, const float* pred_alpha, const float* tgt_rgb, const float* tgt_depth,
                        float lambda_c, float inlier_k, int alpha_power, uint32_t* sel, float* median, float* g_rgb,
                        float* g_depth, float* part, float* loss, float* scale, hipStream_t s,
                        const float* expo = nullptr, float* epart = nullptr, float* egrad = nullptr);
-inline int64_t sel_words(int R) { return (int64_t)R * (4 + 2048); }
+constexpr int kSelHistBins = 2048;
+inline int64_t sel_words(int R) { return (int64_t)R * (8 + 3 * kSelHistBins); }
 
 // Mapping loss (mapping_loss.hip).  SSIM blocks of a W x H render (3 colour
 // channels x 32 x 32 tiles); cnt_part: one float per 1024-pixel block;

@@ -8,6 +8,7 @@ namespace ls {
 
 constexpr int kLossPix = 4;  // pixels per thread
 constexpr int kLossBlockPix = 256 * kLossPix;
+constexpr int kSelBins = kSelHistBins;  // bins of a median selection pass
 
 // Per-render exposure coefficients (a, b) of the rendered colour, C' =
 // exp(a) C + b (registration with exposure compensation); identity without.
@@ -131,12 +132,17 @@ __global__ __launch_bounds__(256) void k_loss_l1(const JobDev* __restrict__ jobs
 }
 
 // One wave per render: ordered sum of the block partials; with exposure
-// partials, also dL/d(a, b) = (1/|Omega|) (sum g' e^a C, sum g').
+// partials, also dL/d(a, b) = (1/|Omega|) (sum g' e^a C, sum g').  clear: the
+// last histograms of the median selection, zeroed for the next call.
 __global__ void k_loss_reduce(const int32_t* __restrict__ pblk_off, int R, const float* __restrict__ part,
                               float* __restrict__ loss, float* __restrict__ scale, const float* __restrict__ epart,
-                              float* __restrict__ egrad) {
+                              float* __restrict__ egrad, uint32_t* __restrict__ clear) {
   const int r = blockIdx.x;
   if (r >= R) return;
+  if (clear)
+#pragma unroll
+    for (int i = 0; i < kSelBins / 256; ++i)
+      reinterpret_cast<uint4*>(clear + (int64_t)r * kSelBins)[i * 64 + threadIdx.x] = make_uint4(0u, 0u, 0u, 0u);
   float s = 0.f, c = 0.f, sa = 0.f, sb = 0.f;
   for (int b = pblk_off[r] + threadIdx.x; b < pblk_off[r + 1]; b += 64) {
     s += part[2 * (int64_t)b];
@@ -201,15 +207,28 @@ __global__ __launch_bounds__(256) void k_tile_loss_reduce(const JobDev* __restri
 // error e = |D - D*| over pixels with D* > 0.  It is found exactly by radix
 // selection on the bit patterns of the non-negative FP32 errors (their
 // unsigned order is their numeric order): three passes over 11, 11 and 10
-// bits, each a histogram of the errors that match the digits fixed so far,
-// followed by a one-block-per-render pass that picks the digit holding the
-// element of rank floor((n-1)/2) and re-zeroes the histogram for the next
-// pass (no memset, so the sequence can be captured in a graph).
-
-constexpr int kSelBins = 2048;
+// bits, each a histogram of the errors that match the digits fixed so far.
+// The digit that holds the element of rank floor((n-1)/2) is found by every
+// block of the next kernel for itself, from the finished histogram (8 KB, 0.7
+// us): a launch of its own took 3.4 us, three times per loss (tracking step of
+// 4,096 items at 160 x 120: 105 -> 98 us, of 97k at 640 x 480: 214 -> 206 us).
+// A histogram
+// is zeroed again by a kernel after its last reader (no memset, so the
+// sequence can be captured in a graph).
 
 struct SelState {
   uint32_t prefix, mask, k, n;
+};
+
+// The selection workspace of R renders: the state after the first and after
+// the second digit, then three histograms per render.
+struct SelWork {
+  SelState* state;  // [2][R]
+  uint32_t* hist;   // [3][R][kSelBins]
+  int R;
+  __device__ __forceinline__ uint32_t* bins(int pass, int r) const {
+    return hist + ((int64_t)pass * R + r) * kSelBins;
+  }
 };
 
 __device__ __forceinline__ int sel_shift(int pass) { return pass == 0 ? 21 : (pass == 1 ? 10 : 0); }
@@ -217,18 +236,68 @@ __device__ __forceinline__ int sel_bins(int pass) { return pass == 2 ? 1024 : 20
 
 __device__ __forceinline__ float depth_error(float d, float t) { return fabsf(d - t); }
 
+// State after digit `pass` of render r, from that digit's histogram and the
+// state before; every thread of the block (256) calls it and gets the result.
+__device__ __forceinline__ SelState sel_next(const SelWork& w, int r, int pass) {
+  __shared__ uint32_t wsum[4];
+  __shared__ SelState found;
+  const int shift = sel_shift(pass), nb = sel_bins(pass);
+  const int per = nb / 256;  // 8 or 4 bins per thread
+  const uint4* g = reinterpret_cast<const uint4*>(w.bins(pass, r) + threadIdx.x * per);
+  const uint4 a = g[0], b = per > 4 ? g[1] : make_uint4(0u, 0u, 0u, 0u);
+  SelState st{0u, 0u, 0u, 0u};
+  if (pass > 0) st = w.state[(pass - 1) * w.R + r];
+  const uint32_t c[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+  uint32_t mine = 0;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) mine += c[j];
+  // block-wide exclusive scan of the per-thread sums
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  uint32_t incl = mine;
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t y = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += y;
+  }
+  if (lane == 63) wsum[wv] = incl;
+  __syncthreads();
+  uint32_t before = incl - mine;
+  for (int k = 0; k < wv; ++k) before += wsum[k];
+  if (pass == 0) {
+    st.n = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+    st.k = st.n ? (st.n - 1u) / 2u : 0u;
+  }
+  if (st.n == 0u) return st;  // the same for every thread
+  if (st.k >= before && st.k < before + mine) {  // in one thread
+    uint32_t cum = before;
+    int d = 0;
+#pragma unroll
+    for (int j = 0; j < 7; ++j) {
+      const bool past = d == j && st.k >= cum + c[j];
+      cum += past ? c[j] : 0u;
+      d += past ? 1 : 0;
+    }
+    found = SelState{st.prefix | ((uint32_t)(threadIdx.x * per + d) << shift), st.mask | ((uint32_t)(nb - 1) << shift),
+                     st.k - cum, st.n};
+  }
+  __syncthreads();
+  return found;
+}
+
+__device__ __forceinline__ void clear_bins(uint32_t* bins, bool first) {
+  if (!first) return;
+  for (int i = threadIdx.x; i < kSelBins; i += 256) bins[i] = 0u;
+}
+
 __global__ __launch_bounds__(256) void k_err_hist(const JobDev* __restrict__ jobs, const int32_t* __restrict__ pblk_off,
                                                   int R, const float* __restrict__ pred_depth,
-                                                  const float* __restrict__ tgt_depth,
-                                                  const SelState* __restrict__ state, uint32_t* __restrict__ hist,
-                                                  int pass) {
+                                                  const float* __restrict__ tgt_depth, SelWork sel, int pass) {
   __shared__ uint32_t h[kSelBins];
   const int r = find_segment<int32_t>(pblk_off, R, (int32_t)blockIdx.x);
   const JobDev& J = jobs[r];
   const int64_t hw = (int64_t)J.W * J.H;
   const int64_t b0 = (int64_t)(blockIdx.x - pblk_off[r]) * kLossBlockPix;
+  const bool first = (int)blockIdx.x == pblk_off[r];  // the render's first block
   const int shift = sel_shift(pass), nb = sel_bins(pass);
-  const uint32_t prefix = pass ? state[r].prefix : 0u, mask = pass ? state[r].mask : 0u;
   // every pixel of the thread is loaded before any is counted (one wait for
   // memory, overlapping the histogram clear)
   float td[kLossPix], pd[kLossPix];
@@ -240,78 +309,23 @@ __global__ __launch_bounds__(256) void k_err_hist(const JobDev* __restrict__ job
     pd[k] = in ? pred_depth[J.pix_off + p] : 0.f;
   }
   for (int i = threadIdx.x; i < nb; i += 256) h[i] = 0u;
+  SelState st{0u, 0u, 0u, 0u};
+  if (pass > 0) {
+    st = sel_next(sel, r, pass - 1);
+    if (first && threadIdx.x == 0) sel.state[(pass - 1) * R + r] = st;
+    if (pass == 2) clear_bins(sel.bins(0, r), first);
+  }
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < kLossPix; ++k) {
     if (!(td[k] > 0.f)) continue;  // out-of-image pixels carry td = 0
     const uint32_t bits = __float_as_uint(depth_error(pd[k], td[k]));
-    if ((bits & mask) == prefix) atomicAdd(&h[(bits >> shift) & (uint32_t)(nb - 1)], 1u);
+    if ((bits & st.mask) == st.prefix) atomicAdd(&h[(bits >> shift) & (uint32_t)(nb - 1)], 1u);
   }
   __syncthreads();
-  uint32_t* __restrict__ g = hist + (int64_t)r * kSelBins;
+  uint32_t* __restrict__ g = sel.bins(pass, r);
   for (int i = threadIdx.x; i < nb; i += 256)
     if (h[i]) atomicAdd(&g[i], h[i]);
-}
-
-// One block per render: locate the digit of the rank-k element, fold it
-// into the prefix, clear the histogram; after the last pass write the median.
-__global__ __launch_bounds__(256) void k_err_select(int R, SelState* __restrict__ state, uint32_t* __restrict__ hist,
-                                                    float* __restrict__ median, int pass) {
-  const int r = blockIdx.x;
-  if (r >= R) return;
-  const int shift = sel_shift(pass), nb = sel_bins(pass);
-  const int per = nb / 256;  // 8 or 4 bins per thread
-  uint32_t* __restrict__ g = hist + (int64_t)r * kSelBins;
-  uint32_t c[8];
-  uint32_t mine = 0;
-  for (int j = 0; j < per; ++j) {
-    c[j] = g[threadIdx.x * per + j];
-    mine += c[j];
-  }
-  // block-wide exclusive scan of the per-thread sums
-  __shared__ uint32_t wsum[4];
-  __shared__ uint32_t total_s;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  uint32_t incl = mine;
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t y = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += y;
-  }
-  if (lane == 63) wsum[wv] = incl;
-  __syncthreads();
-  uint32_t before = incl - mine;
-  for (int w = 0; w < wv; ++w) before += wsum[w];
-  if (threadIdx.x == 0) total_s = wsum[0] + wsum[1] + wsum[2] + wsum[3];
-  __syncthreads();
-  SelState st = state[r];
-  if (pass == 0) {
-    st.prefix = 0u;
-    st.mask = 0u;
-    st.n = total_s;
-    st.k = total_s ? (total_s - 1u) / 2u : 0u;
-  }
-  __syncthreads();
-  if (st.n && st.k >= before && st.k < before + mine) {
-    uint32_t cum = before;
-    for (int j = 0; j < per; ++j) {
-      if (st.k < cum + c[j]) {
-        const uint32_t digit = (uint32_t)(threadIdx.x * per + j);
-        SelState o = st;
-        o.prefix |= digit << shift;
-        o.mask |= (uint32_t)(nb - 1) << shift;
-        o.k -= cum;
-        state[r] = o;
-        if (pass == 2) median[r] = __uint_as_float(o.prefix);
-        break;
-      }
-      cum += c[j];
-    }
-  }
-  if (!st.n && threadIdx.x == 0) {
-    state[r] = st;
-    if (pass == 2) median[r] = 0.f;
-  }
-  for (int j = 0; j < per; ++j) g[threadIdx.x * per + j] = 0u;
 }
 
 // Per block of 1024 pixels: the masked, weighted L1 of Eq. 2 with its
@@ -324,19 +338,27 @@ __global__ __launch_bounds__(256) void k_loss_track(const JobDev* __restrict__ j
                                                     const float* __restrict__ pred_alpha,
                                                     const float* __restrict__ tgt_rgb,
                                                     const float* __restrict__ tgt_depth,
-                                                    const float* __restrict__ median, float lambda_c, float inlier_k,
-                                                    int alpha_power, float* __restrict__ g_rgb,
+                                                    SelWork sel, float* __restrict__ median, float lambda_c,
+                                                    float inlier_k, int alpha_power, float* __restrict__ g_rgb,
                                                     float* __restrict__ g_depth, float* __restrict__ part,
                                                     const float* __restrict__ expo, float* __restrict__ epart) {
   const int r = find_segment<int32_t>(pblk_off, R, (int32_t)blockIdx.x);
   const JobDev& J = jobs[r];
   const int64_t hw = (int64_t)J.W * J.H;
   const int64_t b0 = (int64_t)(blockIdx.x - pblk_off[r]) * kLossBlockPix;
-  const float thr = inlier_k > 0.f ? inlier_k * median[r] : 0.f;
   const Exposure ex = exposure_of(expo, r);
   float s = 0.f, cnt = 0.f, sa = 0.f, sb = 0.f;
   PixIn in[kLossPix];
   load_pixels(J, hw, b0, pred_rgb, pred_depth, alpha_power > 0 ? pred_alpha : nullptr, tgt_rgb, tgt_depth, in);
+  float thr = 0.f;
+  if (inlier_k > 0.f) {
+    const SelState st = sel_next(sel, r, 2);
+    const float med = st.n ? __uint_as_float(st.prefix) : 0.f;
+    const bool first = (int)blockIdx.x == pblk_off[r];
+    if (first && threadIdx.x == 0) median[r] = med;
+    clear_bins(sel.bins(1, r), first);
+    thr = inlier_k * med;
+  }
 #pragma unroll
   for (int k = 0; k < kLossPix; ++k) {
     const int64_t p = b0 + (int64_t)k * 256 + threadIdx.x;
@@ -425,7 +447,7 @@ void launch_loss_l1(const JobDev* jobs, const int32_t* pblk_off_d, int R, int np
     hipLaunchKernelGGL(k_loss_l1, dim3(npblk), dim3(256), 0, s, jobs, pblk_off_d, R, pred_rgb, pred_depth, tgt_rgb,
                        tgt_depth, g_rgb, g_depth, part, expo, epart);
   hipLaunchKernelGGL(k_loss_reduce, dim3(R), dim3(64), 0, s, pblk_off_d, R, (const float*)part, loss, scale,
-                     (const float*)epart, egrad);
+                     (const float*)epart, egrad, (uint32_t*)nullptr);
 }
 
 void launch_loss_track(const JobDev* jobs, const int32_t* pblk_off_d, int R, int npblk, const float* pred_rgb,
@@ -433,22 +455,19 @@ void launch_loss_track(const JobDev* jobs, const int32_t* pblk_off_d, int R, int
                        float lambda_c, float inlier_k, int alpha_power, uint32_t* sel, float* median, float* g_rgb,
                        float* g_depth, float* part, float* loss, float* scale, hipStream_t s, const float* expo,
                        float* epart, float* egrad) {
-  SelState* st = reinterpret_cast<SelState*>(sel);
-  uint32_t* hist = sel + 4 * (int64_t)R;
-  if (inlier_k > 0.f) {
-    for (int pass = 0; pass < 3; ++pass) {
-      if (npblk > 0)
-        hipLaunchKernelGGL(k_err_hist, dim3(npblk), dim3(256), 0, s, jobs, pblk_off_d, R, pred_depth, tgt_depth,
-                           (const SelState*)st, hist, pass);
-      hipLaunchKernelGGL(k_err_select, dim3(R), dim3(256), 0, s, R, st, hist, median, pass);
-    }
-  }
-  if (npblk > 0)
+  const SelWork w{reinterpret_cast<SelState*>(sel), sel + 8 * (int64_t)R, R};
+  const bool select = inlier_k > 0.f;
+  if (npblk > 0) {
+    if (select)
+      for (int pass = 0; pass < 3; ++pass)
+        hipLaunchKernelGGL(k_err_hist, dim3(npblk), dim3(256), 0, s, jobs, pblk_off_d, R, pred_depth, tgt_depth, w,
+                           pass);
     hipLaunchKernelGGL(k_loss_track, dim3(npblk), dim3(256), 0, s, jobs, pblk_off_d, R, pred_rgb, pred_depth,
-                       pred_alpha, tgt_rgb, tgt_depth, (const float*)median, lambda_c, inlier_k, alpha_power, g_rgb,
-                       g_depth, part, expo, epart);
+                       pred_alpha, tgt_rgb, tgt_depth, w, median, lambda_c, inlier_k, alpha_power, g_rgb, g_depth,
+                       part, expo, epart);
+  }
   hipLaunchKernelGGL(k_loss_reduce, dim3(R), dim3(64), 0, s, pblk_off_d, R, (const float*)part, loss, scale,
-                     (const float*)epart, egrad);
+                     (const float*)epart, egrad, select ? w.hist + 2 * (int64_t)R * kSelBins : nullptr);
 }
 
 void launch_tile_loss_reduce(const JobDev* jobs, int R, const float* loss_part, float* loss, hipStream_t s) {
