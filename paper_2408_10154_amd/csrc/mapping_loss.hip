@@ -21,28 +21,34 @@ constexpr int kSsimTaps = 2 * kSsimR + 1;
 constexpr int kSsimT = 32;                   // output tile side
 constexpr int kSsimM = kSsimT + 2 * kSsimR;  // 42: side of the region whose SSIM terms reach the tile
 constexpr int kSsimI = kSsimT + 4 * kSsimR;  // 52: side of the input region those terms read
-constexpr int kSsimIn = kSsimI * kSsimI;     // 2704
-constexpr int kSsimLoadPer = (kSsimIn + kBlock - 1) / kBlock;  // 11 input values per thread
-constexpr int kSsimRowMom = kSsimI * kSsimM; // 2184: row-filtered moments per map
-constexpr int kSsimMom = kSsimM * kSsimM;    // 1764: SSIM terms per map
-constexpr int kSsimRowD = kSsimM * kSsimT;   // 1344: row-filtered derivatives per map
-// Each filter pass gives a work item a strip of consecutive outputs along the
-// filter direction, so an input is read from LDS once per strip rather than
-// once per tap.
-constexpr int kRowStrip = 6;                         // moment row pass: 52 rows x 7 strips
-constexpr int kRowStrips = kSsimM / kRowStrip;
-constexpr int kColStrip = 7;                         // moment column pass: 42 columns x 6 strips
-constexpr int kColStrips = kSsimM / kColStrip;
-constexpr int kDRowStrip = 8;                        // derivative row pass: 42 rows x 4 strips
-constexpr int kDRowStrips = kSsimT / kDRowStrip;
+// Each filter pass gives a thread a strip of consecutive outputs along the
+// filter direction, so an input is read once per strip rather than once per
+// tap.  LDS rows have odd lengths and the lanes of a pass run across its
+// strips, so that no pass has bank conflicts.
+constexpr int kInRow = kSsimI + 1;                   // inputs: 52 rows of 52
+constexpr int kInMap = kSsimI * kInRow;
+constexpr int kInLoads = (kSsimI * kSsimI + kBlock - 1) / kBlock;  // 11 per thread and image
+constexpr int kMomRow = kSsimM + 1;                  // row-filtered moments: 52 rows of 42
+constexpr int kMomMap = kSsimI * kMomRow;
+constexpr int kDerMap = kSsimM * kMomRow;            // derivative maps: 42 rows of 42
+constexpr int kOutRow = kSsimT + 1;                  // row-filtered derivatives: 42 rows of 32
+constexpr int kOutMap = kSsimM * kOutRow;
+constexpr int kInStrip = 11;                         // moment row pass: 52 rows x 4 strips
+constexpr int kInStrips = (kSsimM + kInStrip - 1) / kInStrip;
+constexpr int kMomStrip = 7;                         // moment column pass: 42 columns x 6 strips
+constexpr int kMomStrips = kSsimM / kMomStrip;
+constexpr int kDerStrip = 8;                         // derivative row pass: 42 rows x 4 strips
+constexpr int kDerStrips = kSsimT / kDerStrip;
 constexpr int kOutStrip = kSsimT * kSsimT / kBlock;  // derivative column pass: 32 columns x 8 strips of 4
-static_assert(kSsimM % kRowStrip == 0 && kSsimM % kColStrip == 0 && kSsimT % kDRowStrip == 0, "whole strips");
-static_assert(kSsimM * kColStrips <= kBlock, "one column strip per thread");
+static_assert(kSsimM % kMomStrip == 0 && kSsimT % kDerStrip == 0, "whole strips");
+static_assert(kSsimI * kInStrips <= kBlock && kSsimM * kMomStrips <= kBlock && kSsimM * kDerStrips <= kBlock,
+              "one strip per thread");
 static_assert(kSsimT * (kSsimT / kOutStrip) == kBlock, "one output strip per thread");
+constexpr int kSsimLds = 3 * (kDerMap + kOutMap);  // 38 KB: four blocks per CU
+static_assert(2 * kInMap + kInStrip <= kSsimLds && 3 * kMomMap <= kSsimLds,
+              "inputs, three of the moments and derivatives take turns");
 constexpr float kSsimC1 = 0.01f * 0.01f;
 constexpr float kSsimC2 = 0.03f * 0.03f;
-static_assert(3 * kSsimRowD <= 2 * kSsimIn, "row-filtered derivatives fit the input buffer");
-static_assert(3 * kSsimMom <= 5 * kSsimRowMom, "derivative maps fit the moment buffer");
 
 struct SsimWindow {
   float w[kSsimTaps];
@@ -101,6 +107,15 @@ __global__ __launch_bounds__(256) void k_valid_inv(const int32_t* __restrict__ p
 // and writes the weighted colour gradient; channel-0 blocks also handle the
 // depth term.  Partials per block: (sum of SSIM over the tile, L1 colour
 // sum and L1 depth sum over its pixels with a target depth).
+//
+// Bound by vector instruction issue (1,800 instructions per wave and block).
+// All stages share one piece of LDS, for four blocks on a CU: the row pass
+// keeps a strip's 55 moments in registers until every thread is done with the
+// inputs, and then hands over three of them, and the other two after those.
+// 1200 x 680: 49 us; with inputs and five moments apart in 65 KB (two blocks)
+// and strips whose lanes met in the same banks 62 us; all five moments at once
+// in 44 KB (three blocks) 53 us.  (Filtering x^2 + y^2 as one map takes 43 us,
+// but its rounding moves gradients by 2e-5 where a window is nearly flat.)
 __global__ __launch_bounds__(256) void k_loss_ssim(const JobDev* __restrict__ jobs,
                                                    const int32_t* __restrict__ sblk_off, int R, int nblk,
                                                    const float* __restrict__ pred_rgb,
@@ -111,8 +126,7 @@ __global__ __launch_bounds__(256) void k_loss_ssim(const JobDev* __restrict__ jo
                                                    float lambda_ssim, float lambda_color, float lambda_depth,
                                                    float* __restrict__ g_rgb, float* __restrict__ g_depth,
                                                    float* __restrict__ part) {
-  __shared__ float sA[2 * kSsimIn];      // x, y inputs; later the row-filtered derivative maps
-  __shared__ float sB[5 * kSsimRowMom];  // row-filtered moments; later the derivative maps
+  __shared__ float lds[kSsimLds];
   const int blk = xcd_remap(blockIdx.x, nblk);
   if (blk >= nblk) return;
   const int r = find_segment<int32_t>(sblk_off, R, (int32_t)blk);
@@ -127,68 +141,50 @@ __global__ __launch_bounds__(256) void k_loss_ssim(const JobDev* __restrict__ jo
   const float* __restrict__ X = pred_rgb + 3 * J.pix_off + ch * hw;
   const float* __restrict__ Y = (tgt_rgb ? tgt_rgb + 3 * J.pix_off : J.tgt_rgb) + ch * hw;
 
-  float* sx = sA;
-  float* sy = sA + kSsimIn;
   {
     // every load of the input region is issued before the first is used
-    float xv[kSsimLoadPer], yv[kSsimLoadPer];
+    float xv[kInLoads], yv[kInLoads];
 #pragma unroll
-    for (int j = 0; j < kSsimLoadPer; ++j) {
+    for (int j = 0; j < kInLoads; ++j) {
       const int i = threadIdx.x + kBlock * j;
       const int rr = i / kSsimI, cc = i - rr * kSsimI;
       const int gy = y0 - 2 * kSsimR + rr, gx = x0 - 2 * kSsimR + cc;
       xv[j] = 0.f;
       yv[j] = 0.f;
-      if (i < kSsimIn && gx >= 0 && gx < W && gy >= 0 && gy < H) {
+      if (rr < kSsimI && gx >= 0 && gx < W && gy >= 0 && gy < H) {
         const int64_t p = (int64_t)gy * W + gx;
         xv[j] = X[p];
         yv[j] = Y[p];
       }
     }
 #pragma unroll
-    for (int j = 0; j < kSsimLoadPer; ++j) {
+    for (int j = 0; j < kInLoads; ++j) {
       const int i = threadIdx.x + kBlock * j;
-      if (i < kSsimIn) {
-        sx[i] = xv[j];
-        sy[i] = yv[j];
+      const int rr = i / kSsimI, cc = i - rr * kSsimI;
+      if (rr < kSsimI) {
+        lds[rr * kInRow + cc] = xv[j];
+        lds[kInMap + rr * kInRow + cc] = yv[j];
       }
     }
   }
   __syncthreads();
 
-  // this thread's output strip (column ocol, rows o0 .. o0 + kOutStrip - 1):
-  // centre values from LDS, depths issued now and used at the end
-  const int ocol = threadIdx.x % kSsimT, o0 = (threadIdx.x / kSsimT) * kOutStrip;
-  float xq[kOutStrip], yq[kOutStrip], tq[kOutStrip], dq[kOutStrip];
+  // row pass: the five moments of each input row at the 42 moment columns
+  // (the last strip's columns past them are not stored)
+  const int rs = threadIdx.x / kSsimI, rr = threadIdx.x - rs * kSsimI, rc0 = rs * kInStrip;
+  const bool row_item = rs < kInStrips;
+  float a[kInStrip], b[kInStrip], c[kInStrip], d[kInStrip], e[kInStrip];
 #pragma unroll
-  for (int q = 0; q < kOutStrip; ++q) {
-    const int li = (o0 + q + 2 * kSsimR) * kSsimI + ocol + 2 * kSsimR;
-    xq[q] = sx[li];
-    yq[q] = sy[li];
-    const int gy = y0 + o0 + q, gx = x0 + ocol;
-    tq[q] = dq[q] = 0.f;
-    if (gx < W && gy < H) {
-      const int64_t p = (int64_t)gy * W + gx;
-      tq[q] = tgt_depth ? tgt_depth[J.pix_off + p] : J.tgt_depth[p];
-      if (ch == 0) dq[q] = pred_depth[J.pix_off + p];
-    }
-  }
-
-  // row pass: the five moments of each input row at the 42 moment columns,
-  // kRowStrip consecutive columns per work item (each input read once)
-  for (int it = threadIdx.x; it < kSsimI * kRowStrips; it += kBlock) {
-    const int rr = it / kRowStrips, c0 = (it - rr * kRowStrips) * kRowStrip;
-    const float* xr = sx + rr * kSsimI + c0;
-    const float* yr = sy + rr * kSsimI + c0;
-    float a[kRowStrip], b[kRowStrip], c[kRowStrip], d[kRowStrip], e[kRowStrip];
+  for (int o = 0; o < kInStrip; ++o) a[o] = b[o] = c[o] = d[o] = e[o] = 0.f;
+  if (row_item) {
+    const float* xr = lds + rr * kInRow + rc0;
+    const float* yr = xr + kInMap;
 #pragma unroll
-    for (int o = 0; o < kRowStrip; ++o) a[o] = b[o] = c[o] = d[o] = e[o] = 0.f;
-#pragma unroll
-    for (int k = 0; k < kRowStrip + 2 * kSsimR; ++k) {
+    for (int k = 0; k < kInStrip + 2 * kSsimR; ++k) {
       const float xv = xr[k], yv = yr[k];
       const float xx = xv * xv, yy = yv * yv, xy = xv * yv;
 #pragma unroll
-      for (int o = 0; o < kRowStrip; ++o) {
+      for (int o = 0; o < kInStrip; ++o) {
         const int tap = k - o;
         if (tap >= 0 && tap < kSsimTaps) {
           const float w = win.w[tap];
@@ -200,51 +196,74 @@ __global__ __launch_bounds__(256) void k_loss_ssim(const JobDev* __restrict__ jo
         }
       }
     }
-    float* out = sB + rr * kSsimM + c0;
+  }
+  float* row_out = lds + rr * kMomRow + rc0;
+  __syncthreads();  // every thread is done with the inputs
+  if (row_item) {
 #pragma unroll
-    for (int o = 0; o < kRowStrip; ++o) {
-      out[o] = a[o];
-      out[kSsimRowMom + o] = b[o];
-      out[2 * kSsimRowMom + o] = c[o];
-      out[3 * kSsimRowMom + o] = d[o];
-      out[4 * kSsimRowMom + o] = e[o];
-    }
+    for (int o = 0; o < kInStrip; ++o)
+      if (rc0 + o < kSsimM) {
+        row_out[o] = a[o];
+        row_out[kMomMap + o] = b[o];
+        row_out[2 * kMomMap + o] = c[o];
+      }
   }
   __syncthreads();
 
   // column pass, SSIM index and its derivative maps on the 42 x 42 region:
-  // one strip of kColStrip rows of one moment column per thread
-  float dA[kColStrip], dB[kColStrip], dC[kColStrip];
+  // one strip of kMomStrip rows of one moment column per thread, three of the
+  // moments first and then the other two in their place
+  float dA[kMomStrip], dB[kMomStrip], dC[kMomStrip];
   float ssum = 0.f;
-  const int mc = threadIdx.x % kSsimM, r0 = (threadIdx.x / kSsimM) * kColStrip;
-  const bool col_item = threadIdx.x < kSsimM * kColStrips;
+  const int mc = threadIdx.x % kSsimM, r0 = (threadIdx.x / kSsimM) * kMomStrip;
+  const bool col_item = threadIdx.x < kSsimM * kMomStrips;
+  float mx[kMomStrip], my[kMomStrip], exx[kMomStrip], eyy[kMomStrip], exy[kMomStrip];
 #pragma unroll
-  for (int q = 0; q < kColStrip; ++q) dA[q] = dB[q] = dC[q] = 0.f;
-  if (col_item) {
-    float mx[kColStrip], my[kColStrip], exx[kColStrip], eyy[kColStrip], exy[kColStrip];
+  for (int q = 0; q < kMomStrip; ++q) mx[q] = my[q] = exx[q] = eyy[q] = exy[q] = dA[q] = dB[q] = dC[q] = 0.f;
+  const float* col_in = lds + (col_item ? r0 * kMomRow + mc : 0);
 #pragma unroll
-    for (int q = 0; q < kColStrip; ++q) mx[q] = my[q] = exx[q] = eyy[q] = exy[q] = 0.f;
+  for (int k = 0; k < kMomStrip + 2 * kSsimR; ++k) {
+    const float* in = col_in + k * kMomRow;
+    const float v0 = in[0], v1 = in[kMomMap], v2 = in[2 * kMomMap];
 #pragma unroll
-    for (int k = 0; k < kColStrip + 2 * kSsimR; ++k) {
-      const int o = (r0 + k) * kSsimM + mc;
-      const float v0 = sB[o], v1 = sB[kSsimRowMom + o], v2 = sB[2 * kSsimRowMom + o];
-      const float v3 = sB[3 * kSsimRowMom + o], v4 = sB[4 * kSsimRowMom + o];
-#pragma unroll
-      for (int q = 0; q < kColStrip; ++q) {
-        const int tap = k - q;
-        if (tap >= 0 && tap < kSsimTaps) {
-          const float w = win.w[tap];
-          mx[q] += w * v0;
-          my[q] += w * v1;
-          exx[q] += w * v2;
-          eyy[q] += w * v3;
-          exy[q] += w * v4;
-        }
+    for (int q = 0; q < kMomStrip; ++q) {
+      const int tap = k - q;
+      if (tap >= 0 && tap < kSsimTaps) {
+        const float w = win.w[tap];
+        mx[q] += w * v0;
+        my[q] += w * v1;
+        exx[q] += w * v2;
       }
     }
+  }
+  __syncthreads();
+  if (row_item) {
+#pragma unroll
+    for (int o = 0; o < kInStrip; ++o)
+      if (rc0 + o < kSsimM) {
+        row_out[o] = d[o];
+        row_out[kMomMap + o] = e[o];
+      }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kMomStrip + 2 * kSsimR; ++k) {
+    const float* in = col_in + k * kMomRow;
+    const float v3 = in[0], v4 = in[kMomMap];
+#pragma unroll
+    for (int q = 0; q < kMomStrip; ++q) {
+      const int tap = k - q;
+      if (tap >= 0 && tap < kSsimTaps) {
+        const float w = win.w[tap];
+        eyy[q] += w * v3;
+        exy[q] += w * v4;
+      }
+    }
+  }
+  if (col_item) {
     const int gx = x0 - kSsimR + mc;
 #pragma unroll
-    for (int q = 0; q < kColStrip; ++q) {
+    for (int q = 0; q < kMomStrip; ++q) {
       const int mr = r0 + q;
       const int gy = y0 - kSsimR + mr;
       if (gx >= 0 && gx < W && gy >= 0 && gy < H) {
@@ -262,28 +281,44 @@ __global__ __launch_bounds__(256) void k_loss_ssim(const JobDev* __restrict__ jo
   __syncthreads();  // every thread is done with the moments
   if (col_item) {
 #pragma unroll
-    for (int q = 0; q < kColStrip; ++q) {
-      const int i = (r0 + q) * kSsimM + mc;
-      sB[i] = dA[q];
-      sB[kSsimMom + i] = dB[q];
-      sB[2 * kSsimMom + i] = dC[q];
+    for (int q = 0; q < kMomStrip; ++q) {
+      const int i = (r0 + q) * kMomRow + mc;
+      lds[i] = dA[q];
+      lds[kDerMap + i] = dB[q];
+      lds[2 * kDerMap + i] = dC[q];
+    }
+  }
+  // this thread's output strip (column ocol, rows o0 .. o0 + kOutStrip - 1):
+  // its pixels are issued now and used at the end
+  const int ocol = threadIdx.x % kSsimT, o0 = (threadIdx.x / kSsimT) * kOutStrip;
+  float xq[kOutStrip], yq[kOutStrip], tq[kOutStrip], dq[kOutStrip];
+#pragma unroll
+  for (int q = 0; q < kOutStrip; ++q) {
+    const int gy = y0 + o0 + q, gx = x0 + ocol;
+    xq[q] = yq[q] = tq[q] = dq[q] = 0.f;
+    if (gx < W && gy < H) {
+      const int64_t p = (int64_t)gy * W + gx;
+      xq[q] = X[p];
+      yq[q] = Y[p];
+      tq[q] = tgt_depth ? tgt_depth[J.pix_off + p] : J.tgt_depth[p];
+      if (ch == 0) dq[q] = pred_depth[J.pix_off + p];
     }
   }
   __syncthreads();
 
-  // row pass over the derivative maps: 42 rows x 32 output columns,
-  // kDRowStrip columns per work item
-  for (int it = threadIdx.x; it < kSsimM * kDRowStrips; it += kBlock) {
-    const int mr = it / kDRowStrips, c0 = (it - mr * kDRowStrips) * kDRowStrip;
-    const float* in = sB + mr * kSsimM + c0;
-    float a[kDRowStrip], b[kDRowStrip], c[kDRowStrip];
+  // row pass over the derivative maps: 42 rows x 32 output columns
+  float* rowed = lds + 3 * kDerMap;
+  if (threadIdx.x < kSsimM * kDerStrips) {
+    const int row = threadIdx.x % kSsimM, s0 = (threadIdx.x / kSsimM) * kDerStrip;
+    const float* in = lds + row * kMomRow + s0;
+    float a[kDerStrip], b[kDerStrip], c[kDerStrip];
 #pragma unroll
-    for (int o = 0; o < kDRowStrip; ++o) a[o] = b[o] = c[o] = 0.f;
+    for (int o = 0; o < kDerStrip; ++o) a[o] = b[o] = c[o] = 0.f;
 #pragma unroll
-    for (int k = 0; k < kDRowStrip + 2 * kSsimR; ++k) {
-      const float va = in[k], vb = in[kSsimMom + k], vc = in[2 * kSsimMom + k];
+    for (int k = 0; k < kDerStrip + 2 * kSsimR; ++k) {
+      const float va = in[k], vb = in[kDerMap + k], vc = in[2 * kDerMap + k];
 #pragma unroll
-      for (int o = 0; o < kDRowStrip; ++o) {
+      for (int o = 0; o < kDerStrip; ++o) {
         const int tap = k - o;
         if (tap >= 0 && tap < kSsimTaps) {
           const float w = win.w[tap];
@@ -293,12 +328,12 @@ __global__ __launch_bounds__(256) void k_loss_ssim(const JobDev* __restrict__ jo
         }
       }
     }
-    float* out = sA + mr * kSsimT + c0;
+    float* out = rowed + row * kOutRow + s0;
 #pragma unroll
-    for (int o = 0; o < kDRowStrip; ++o) {
+    for (int o = 0; o < kDerStrip; ++o) {
       out[o] = a[o];
-      out[kSsimRowD + o] = b[o];
-      out[2 * kSsimRowD + o] = c[o];
+      out[kOutMap + o] = b[o];
+      out[2 * kOutMap + o] = c[o];
     }
   }
   __syncthreads();
@@ -316,8 +351,8 @@ __global__ __launch_bounds__(256) void k_loss_ssim(const JobDev* __restrict__ jo
     for (int q = 0; q < kOutStrip; ++q) fa[q] = fb[q] = fc[q] = 0.f;
 #pragma unroll
     for (int k = 0; k < kOutStrip + 2 * kSsimR; ++k) {
-      const int li = (o0 + k) * kSsimT + ocol;
-      const float va = sA[li], vb = sA[kSsimRowD + li], vc = sA[2 * kSsimRowD + li];
+      const int li = (o0 + k) * kOutRow + ocol;
+      const float va = rowed[li], vb = rowed[kOutMap + li], vc = rowed[2 * kOutMap + li];
 #pragma unroll
       for (int q = 0; q < kOutStrip; ++q) {
         const int tap = k - q;
