@@ -64,7 +64,7 @@ ls_status overlap_check_args(const float* p_mean, int32_t np, const float* q_mea
 namespace {
 
 struct Layout {
-  size_t k0, v0, k1, v1, hist, blk_cnt, kept, cnt, tile_total, tile_start, blk_total, band_part, pose_part, loss_part, used, g2d,
+  size_t k0, v0, k1, v1, hist, blk_cnt, kept, cnt, tile_total, tile_before, groups, band_part, pose_part, loss_part, used, g2d,
       total;
 };
 
@@ -82,13 +82,13 @@ Layout layout_of(const ls_batch* b, int64_t cap) {
   L.v0 = take(4 * M);
   L.k1 = take(4 * M);
   L.v1 = take(4 * M);
-  L.hist = take(4 * (size_t)seg_hist_words(b->sort_blocks));
+  L.hist = take(4 * (size_t)seg_hist_words(b->sort_blocks, b->max_items <= kWideItems));
   L.blk_cnt = take(4 * (size_t)b->sort_blocks);
   L.kept = take(4 * (size_t)b->R);
   L.cnt = take(4 * (size_t)b->bincnt_off[b->R]);
   L.tile_total = take(4 * T);
-  L.tile_start = take(4 * T);
-  L.blk_total = take(8 * ((T + 63) / 64));
+  L.tile_before = take(4 * T);
+  L.groups = take(8 * ((T + 63) / 64 + 1));
   L.band_part = take(4 * 4 * (size_t)kPoseAcc * std::max(b->T, 1));  // a row per 8x8 band
   L.pose_part = take(4 * (size_t)kPoseAcc * std::max(b->nblk_items, 1));
   L.loss_part = take(4 * 8 * (size_t)std::max(b->T, 1));  // per 8x8 band {L1 sum, pixels in Omega}
@@ -538,8 +538,8 @@ ls_status ls_bin_sort(const ls_batch* b, const ls_projected* p, const ls_bins* b
   bl.kept = at<int32_t>(w, L.kept);
   bl.cnt = at<uint32_t>(w, L.cnt);
   bl.tile_total = at<uint32_t>(w, L.tile_total);
-  bl.tile_start = at<uint32_t>(w, L.tile_start);
-  bl.blk_total = at<uint64_t>(w, L.blk_total);
+  bl.tile_before = at<uint32_t>(w, L.tile_before);
+  bl.groups = at<uint64_t>(w, L.groups);
   bl.tile_of = bins->tile_of;
   bl.item = bins->item;
   bl.range = bins->range;

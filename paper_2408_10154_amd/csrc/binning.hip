@@ -4,10 +4,10 @@
 // Order of the final list: (tile, FP32 depth bits, item).
 //
 //  1. The items with tiles are sorted by depth bits, render by render (LSD
-//     radix sort, 8-bit digits, stable: ties keep ascending item order).  A
-//     render of up to 16,384 items is sorted by one block in LDS, in one
-//     launch; larger ones take a histogram and a scatter per digit, and the
-//     scatter forms its digit bases from the block histograms itself.
+//     radix sort, stable: ties keep ascending item order).  A render of up to
+//     16,384 items is sorted by one block in LDS, in one launch; larger ones
+//     take a histogram and a scatter per digit, and the scatter forms its
+//     digit bases from the block histograms itself.
 //  2. The sorted items are cut into chunks.  One block per chunk counts the
 //     items of every tile of its render, a scan over the chunks turns the
 //     counts into each chunk's first place in each tile's list, and one block
@@ -15,10 +15,11 @@
 //
 // Every instance is written once, and no (tile, item) pairs are sorted: the
 // pair sort it replaces moved each instance three times in 8 launches (all of
-// binning: 200k items, 1200 x 680, 143 -> 100 us and 22 launches -> 12; eight
-// renders of 150k items, 640 x 480, 157 -> 118 us; 4,096 items, 160 x 120,
-// 81 -> 38 us and 5 launches).  What is left is bound by latency: launches of
-// 3 to 10 us on tens to hundreds of blocks, each a chain of dependent loads.
+// binning: 200k items, 1200 x 680, 143 -> 98 us and 22 launches -> 11; eight
+// renders of 150k items, 640 x 480, 157 -> 118 us; 23k items, 317 x 211, 90 ->
+// 63 us and 9 launches; 4,096 items, 160 x 120, 81 -> 36 us and 4 launches).
+// What is left is bound by latency: launches of 3 to 10 us on tens to hundreds
+// of blocks, each a chain of dependent loads.
 #include "common.h"
 
 #include <algorithm>
@@ -40,9 +41,22 @@ __global__ void k_fill_i32(int32_t* __restrict__ p, int64_t n, int32_t v) {
 // blk_off[s] .. blk_off[s + 1), kSortKeys keys each, of which those with keys
 // work.
 
-constexpr int kBins = 256;
+//
+// A digit has 8 or 11 bits: four passes with 256 bins or three (of 11, 11 and
+// 10) with 2,048.  The wide ones pay up to kWideItems = 65,536 items, where a
+// block adds up the others' bins in one round of loads: 23k items 43 us in 8
+// launches against 40 us in 6; but 97k items 46 against 51 us, 200k items 50
+// against 72 us.
+
 constexpr int kSortWaves = kSortThreads / 64;
 constexpr int kSortPer = kSortKeys / kSortThreads;  // keys per thread
+template <int kBits>
+struct Digit {
+  static constexpr int kBins = 1 << kBits;
+  static constexpr int kPer = kBins > kSortThreads ? kBins / kSortThreads : 1;  // bins per thread (1 or 2)
+  static constexpr int kThreads = kBins / kPer;                                 // threads with bins
+  __device__ __forceinline__ static uint32_t of(uint32_t key, int shift) { return (key >> shift) & (kBins - 1); }
+};
 
 // Inclusive prefix sum over the 64 lanes (DPP: shifts within 16-lane rows,
 // then the row ends broadcast to the later rows).
@@ -57,38 +71,39 @@ __device__ __forceinline__ uint32_t wave_incl_sum(uint32_t v) {
   return (uint32_t)x;
 }
 
-// Exclusive prefix of one value per thread over the first kBins threads (the
+// Exclusive prefix of one value per thread over the first kThreads threads (the
 // others' values are ignored); every thread of the block calls it.
+template <int kThreads>
 __device__ __forceinline__ uint32_t digit_excl(uint32_t v, uint32_t* wsum) {
   const int w = threadIdx.x >> 6;
   const uint32_t x = wave_incl_sum(v);
-  if ((threadIdx.x & 63) == 63 && w < kBins / 64) wsum[w] = x;
+  if ((threadIdx.x & 63) == 63 && w < kThreads / 64) wsum[w] = x;
   __syncthreads();
   uint32_t before = 0;
 #pragma unroll
-  for (int k = 0; k < kBins / 64; ++k) before += k < w ? wsum[k] : 0u;
+  for (int k = 0; k < kThreads / 64; ++k) before += k < w ? wsum[k] : 0u;
   return before + x - v;
 }
 
 // Ranks of the wave's keys among its earlier keys of the same digit: 64 at a
 // time in order, a ballot match per 64 keys, and the wave's running digit
 // counts in its own LDS row (cleared here).
-template <int kPer>
+template <int kBits, int kPer>
 __device__ __forceinline__ void wave_ranks(const uint32_t (&key)[kPer], const bool (&ok)[kPer], int shift,
-                                           uint32_t* row, int lane, uint32_t (&rk)[kPer]) {
+                                           uint16_t* row, int lane, uint32_t (&rk)[kPer]) {
   const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
 #pragma unroll
-  for (int d = 0; d < kBins / 64; ++d) row[64 * d + lane] = 0u;
+  for (int d = 0; d < Digit<kBits>::kBins / 128; ++d) reinterpret_cast<uint32_t*>(row)[64 * d + lane] = 0u;
   __builtin_amdgcn_wave_barrier();
 #pragma unroll
   for (int j = 0; j < kPer; ++j) {
-    const uint32_t d = (key[j] >> shift) & (kBins - 1);
+    const uint32_t d = Digit<kBits>::of(key[j], shift);
     const uint64_t valid = __ballot(ok[j]);
     rk[j] = 0u;
     if (valid != 0ull) {  // uniform
       uint32_t plo = (uint32_t)valid, phi = (uint32_t)(valid >> 32);
 #pragma unroll
-      for (int b = 0; b < 8; ++b) {
+      for (int b = 0; b < kBits; ++b) {
         const uint32_t sign = (uint32_t)((int32_t)(d << (31 - b)) >> 31);  // all ones where the bit is set
         const uint64_t m = __ballot(sign != 0u);
         plo &= ~((uint32_t)m ^ sign);
@@ -98,7 +113,7 @@ __device__ __forceinline__ void wave_ranks(const uint32_t (&key)[kPer], const bo
       const uint32_t rank = (uint32_t)__popcll(peers & lt);
       const uint32_t before = ok[j] ? row[d] : 0u;
       rk[j] = before + rank;
-      if (ok[j] && rank == 0) row[d] = before + (uint32_t)__popcll(peers);
+      if (ok[j] && rank == 0) row[d] = (uint16_t)(before + (uint32_t)__popcll(peers));
       __builtin_amdgcn_wave_barrier();
     }
   }
@@ -106,38 +121,50 @@ __device__ __forceinline__ void wave_ranks(const uint32_t (&key)[kPer], const bo
 
 // The block's digit starts, after every wave has ranked (and a barrier): each
 // wave's row turns into its first place for each digit in the block's digit
-// order; returns the digit's count (threads below kBins) and its local start.
-__device__ __forceinline__ uint32_t digit_starts(uint32_t (*wcnt)[kBins], uint32_t* wsum, uint32_t& lstart) {
-  const int d = threadIdx.x;
-  uint32_t c[kSortWaves], cnt = 0;
-  if (d < kBins) {
+// order (below kPerBlock <= 16,384 keys: 16 bits); lstart: the local starts of
+// the thread's digits (threads below kThreads); returns the number of keys up
+// to and with them.
+template <int kBits>
+__device__ __forceinline__ uint32_t digit_starts(uint16_t (*wcnt)[Digit<kBits>::kBins], uint32_t* wsum,
+                                                 uint32_t (&lstart)[Digit<kBits>::kPer]) {
+  using D = Digit<kBits>;
+  const bool mine = (int)threadIdx.x < D::kThreads;
+  uint32_t c[kSortWaves], cnt = 0;  // two 16-bit counts, or one
+  if (mine) {
 #pragma unroll
     for (int k = 0; k < kSortWaves; ++k) {
-      c[k] = wcnt[k][d];
-      cnt += c[k];
+      c[k] = D::kPer == 2 ? reinterpret_cast<const uint32_t*>(wcnt[k])[threadIdx.x] : wcnt[k][threadIdx.x];
+      cnt += c[k];  // (sums stay below 2^16)
     }
   }
-  lstart = digit_excl(cnt, wsum);
-  if (d < kBins) {
-    uint32_t run = lstart;
+  const uint32_t first = cnt & 0xFFFFu, both = first + (cnt >> 16);
+  lstart[0] = digit_excl<D::kThreads>(both, wsum);
+  if (D::kPer == 2) lstart[D::kPer - 1] = lstart[0] + first;
+  if (mine) {
+    uint32_t run = D::kPer == 2 ? lstart[0] | (lstart[D::kPer - 1] << 16) : lstart[0];
 #pragma unroll
     for (int k = 0; k < kSortWaves; ++k) {
-      wcnt[k][d] = run;
+      if (D::kPer == 2)
+        reinterpret_cast<uint32_t*>(wcnt[k])[threadIdx.x] = run;
+      else
+        wcnt[k][threadIdx.x] = (uint16_t)run;
       run += c[k];
     }
   }
-  return cnt;
+  return lstart[0] + both;
 }
 
 // Digit counts of every block's keys: hist[block][digit].
+template <int kBits>
 __global__ __launch_bounds__(kSortThreads) void k_seg_hist(const uint32_t* __restrict__ keys, SegTable seg, int shift,
                                                            uint32_t* __restrict__ hist) {
-  __shared__ uint32_t h[kBins];
+  using D = Digit<kBits>;
+  __shared__ uint32_t h[D::kBins];
   const int s = find_segment<int32_t>(seg.blk_off, seg.S, (int32_t)blockIdx.x);
   const int c = blockIdx.x - seg.blk_off[s];
   const int m = min(seg.len[s] - c * kSortKeys, kSortKeys);
   if (m <= 0) return;  // uniform for the block
-  if (threadIdx.x < kBins) h[threadIdx.x] = 0u;
+  for (int d = threadIdx.x; d < D::kBins; d += kSortThreads) h[d] = 0u;
   const uint32_t* __restrict__ k0 = keys + seg.base[s] + (int64_t)c * kSortKeys;
   uint32_t key[kSortPer];
 #pragma unroll
@@ -148,40 +175,51 @@ __global__ __launch_bounds__(kSortThreads) void k_seg_hist(const uint32_t* __res
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < kSortPer; ++j)
-    if (j * kSortThreads + (int)threadIdx.x < m) atomicAdd(&h[(key[j] >> shift) & (kBins - 1)], 1u);
+    if (j * kSortThreads + (int)threadIdx.x < m) atomicAdd(&h[D::of(key[j], shift)], 1u);
   __syncthreads();
-  if (threadIdx.x < kBins) hist[(int64_t)blockIdx.x * kBins + threadIdx.x] = h[threadIdx.x];
+  for (int d = threadIdx.x; d < D::kBins; d += kSortThreads) hist[(int64_t)blockIdx.x * D::kBins + d] = h[d];
 }
 
-// Sums of the digit's counts over the segment's blocks and over those before
-// this one, four threads per digit; the result in threads below kBins.  A
-// block of 1,024 threads with 4,096 keys keeps the rows few (49 for 200k
-// keys), so every block can add them up and no scan launch is needed.
+// Sums of the thread's digits' counts over the segment's blocks and over those
+// before this one, kParts threads per digit; the results in threads below
+// kThreads.  A block of 1,024 threads with 4,096 keys keeps the rows few (49
+// for 200k keys), so every block can add them up and no scan launch is needed.
+template <int kBits>
 __device__ __forceinline__ void digit_bases(const uint32_t* __restrict__ rows, int nrows, int c, uint32_t* ta,
-                                            uint32_t* tb, uint32_t& total, uint32_t& before) {
-  const int d = threadIdx.x & (kBins - 1), p = threadIdx.x >> 8;
-  constexpr int kParts = kSortThreads / kBins;
-  uint32_t t = 0, b = 0;
-  for (int r0 = p; r0 < nrows; r0 += 16 * kParts) {
-    uint32_t v[16];
+                                            uint32_t* tb, uint32_t (&total)[Digit<kBits>::kPer],
+                                            uint32_t (&before)[Digit<kBits>::kPer]) {
+  using D = Digit<kBits>;
+  constexpr int kParts = kSortThreads / D::kThreads, kAhead = 16;
+  const int d = threadIdx.x & (D::kThreads - 1), p = threadIdx.x / D::kThreads;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) v[k] = r0 + k * kParts < nrows ? rows[(int64_t)(r0 + k * kParts) * kBins + d] : 0u;
+  for (int q = 0; q < D::kPer; ++q) total[q] = before[q] = 0u;
+  for (int r0 = p; r0 < nrows; r0 += kAhead * kParts) {
+    uint32_t v[kAhead][D::kPer];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      t += v[k];
-      b += r0 + k * kParts < c ? v[k] : 0u;
-    }
+    for (int k = 0; k < kAhead; ++k)
+#pragma unroll
+      for (int q = 0; q < D::kPer; ++q)
+        v[k][q] = r0 + k * kParts < nrows ? rows[(int64_t)(r0 + k * kParts) * D::kBins + D::kPer * d + q] : 0u;
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k)
+#pragma unroll
+      for (int q = 0; q < D::kPer; ++q) {
+        total[q] += v[k][q];
+        before[q] += r0 + k * kParts < c ? v[k][q] : 0u;
+      }
   }
-  ta[threadIdx.x] = t;
-  tb[threadIdx.x] = b;
-  __syncthreads();
-  total = before = 0u;
-  if (threadIdx.x < kBins)
+  if (kParts > 1) {
+    ta[threadIdx.x] = total[0];
+    tb[threadIdx.x] = before[0];
+    __syncthreads();
+    total[0] = before[0] = 0u;
+    if ((int)threadIdx.x < D::kThreads)
 #pragma unroll
-    for (int k = 0; k < kParts; ++k) {
-      total += ta[k * kBins + d];
-      before += tb[k * kBins + d];
-    }
+      for (int k = 0; k < kParts; ++k) {
+        total[0] += ta[k * D::kThreads + d];
+        before[0] += tb[k * D::kThreads + d];
+      }
+  }
 }
 
 // Stable scatter of one digit: ranks in the waves, the block's keys placed in
@@ -189,17 +227,18 @@ __device__ __forceinline__ void digit_bases(const uint32_t* __restrict__ rows, i
 // along each digit's run.  kFirst: the block's own keys, blk_cnt of them, as
 // k_depth_prep left them (len[s] is written); else kSortKeys of the segment's
 // len[s].  kLast: only the values are written.
-template <bool kFirst, bool kLast>
+template <int kBits, bool kFirst, bool kLast>
 __global__ __launch_bounds__(kSortThreads) void k_seg_scatter(const uint32_t* __restrict__ kin,
                                                               const uint32_t* __restrict__ vin,
                                                               uint32_t* __restrict__ kout,
                                                               uint32_t* __restrict__ vout, SegTable seg, int shift,
                                                               const uint32_t* __restrict__ hist,
                                                               const int32_t* __restrict__ blk_cnt) {
-  __shared__ uint32_t wcnt[kSortWaves][kBins];
+  using D = Digit<kBits>;
+  __shared__ __attribute__((aligned(4))) uint16_t wcnt[kSortWaves][D::kBins];
   __shared__ uint32_t sk[kSortKeys], sv[kSortKeys];
-  __shared__ uint32_t delta[kBins];  // global minus local start of each digit's run (mod 2^32)
-  __shared__ uint32_t wsum[2][kBins / 64];
+  __shared__ uint32_t delta[D::kBins];  // global minus local start of each digit's run (mod 2^32)
+  __shared__ uint32_t wsum[2][kSortWaves];
   const int s = find_segment<int32_t>(seg.blk_off, seg.S, (int32_t)blockIdx.x);
   const int b0 = seg.blk_off[s], c = blockIdx.x - b0;
   const int n = kFirst ? 0 : seg.len[s];
@@ -217,20 +256,24 @@ __global__ __launch_bounds__(kSortThreads) void k_seg_scatter(const uint32_t* __
     key[j] = ok[j] ? kin[in0 + i] : 0u;
     val[j] = ok[j] ? vin[in0 + i] : 0u;
   }
-  uint32_t total, before;
-  digit_bases(hist + (int64_t)b0 * kBins, nrows, c, sk, sv, total, before);
-  const uint32_t gstart = digit_excl(total, wsum[0]) + before;
-  if (kFirst && c == 0 && threadIdx.x == kBins - 1) seg.len[s] = (int32_t)(gstart - before + total);
-  wave_ranks<kSortPer>(key, ok, shift, wcnt[w], lane, rk);
+  uint32_t total[D::kPer], before[D::kPer], lstart[D::kPer];
+  digit_bases<kBits>(hist + (int64_t)b0 * D::kBins, nrows, c, sk, sv, total, before);
+  const uint32_t both = D::kPer == 2 ? total[0] + total[D::kPer - 1] : total[0];
+  const uint32_t first = digit_excl<D::kThreads>(both, wsum[0]);  // of the thread's digits, in the segment
+  if (kFirst && c == 0 && threadIdx.x == D::kThreads - 1) seg.len[s] = (int32_t)(first + both);
+  wave_ranks<kBits, kSortPer>(key, ok, shift, wcnt[w], lane, rk);
   __syncthreads();
-  uint32_t lstart;
-  digit_starts(wcnt, wsum[1], lstart);
-  if (threadIdx.x < kBins) delta[threadIdx.x] = gstart - lstart;
+  digit_starts<kBits>(wcnt, wsum[1], lstart);
+  if ((int)threadIdx.x < D::kThreads) {
+    delta[D::kPer * threadIdx.x] = first + before[0] - lstart[0];
+    if (D::kPer == 2)
+      delta[2 * threadIdx.x + 1] = first + total[0] + before[D::kPer - 1] - lstart[D::kPer - 1];
+  }
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < kSortPer; ++j)
     if (ok[j]) {
-      const uint32_t pos = wcnt[w][(key[j] >> shift) & (kBins - 1)] + rk[j];
+      const uint32_t pos = wcnt[w][D::of(key[j], shift)] + rk[j];
       sk[pos] = key[j];
       sv[pos] = val[j];
     }
@@ -241,33 +284,35 @@ __global__ __launch_bounds__(kSortThreads) void k_seg_scatter(const uint32_t* __
     const int i = j * kSortThreads + threadIdx.x;
     if (i < m) {
       const uint32_t k = sk[i];
-      const int64_t pos = out0 + (uint32_t)(delta[(k >> shift) & (kBins - 1)] + (uint32_t)i);
+      const int64_t pos = out0 + (uint32_t)(delta[D::of(k, shift)] + (uint32_t)i);
       if (!kLast) kout[pos] = k;
       vout[pos] = sv[i];
     }
   }
 }
 
-int64_t seg_hist_words(int nblk) { return (int64_t)kBins * std::max(nblk, 1); }
+int64_t seg_hist_words(int nblk, bool wide) { return (int64_t)(wide ? 2048 : 256) * std::max(nblk, 1); }
 
 // ---------------------------------------------------------------------------
 // Depth order of each render's items.
 
 // Larger renders: each block compacts its items with tiles (in item order) and
 // counts the first digit of their depth bits.
+template <int kBits>
 __global__ __launch_bounds__(kSortThreads) void k_depth_prep(const JobDev* __restrict__ jobs, SegTable seg,
                                                              const float4* __restrict__ rec,
                                                              const int32_t* __restrict__ tiles,
                                                              uint32_t* __restrict__ keys, uint32_t* __restrict__ vals,
                                                              uint32_t* __restrict__ hist,
                                                              int32_t* __restrict__ blk_cnt) {
-  __shared__ uint32_t h[kBins];
+  using D = Digit<kBits>;
+  __shared__ uint32_t h[D::kBins];
   __shared__ uint32_t cnt[kSortPer][kSortWaves];
   const int s = find_segment<int32_t>(seg.blk_off, seg.S, (int32_t)blockIdx.x);
   const int c = blockIdx.x - seg.blk_off[s];
   const int n = jobs[s].n, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int64_t base = seg.base[s] + (int64_t)c * kSortKeys;
-  if (threadIdx.x < kBins) h[threadIdx.x] = 0u;
+  for (int d = threadIdx.x; d < D::kBins; d += kSortThreads) h[d] = 0u;
   uint64_t keep[kSortPer];
 #pragma unroll
   for (int j = 0; j < kSortPer; ++j) {
@@ -296,27 +341,29 @@ __global__ __launch_bounds__(kSortThreads) void k_depth_prep(const JobDev* __res
                                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)keep[j], 0u));
       keys[pos] = key[j];
       vals[pos] = (uint32_t)(base + j * kSortThreads + threadIdx.x);
-      atomicAdd(&h[key[j] & (kBins - 1)], 1u);
+      atomicAdd(&h[D::of(key[j], 0)], 1u);
     }
   }
   __syncthreads();
-  if (threadIdx.x < kBins) hist[(int64_t)blockIdx.x * kBins + threadIdx.x] = h[threadIdx.x];
+  for (int d = threadIdx.x; d < D::kBins; d += kSortThreads) hist[(int64_t)blockIdx.x * D::kBins + d] = h[d];
   if (threadIdx.x == 0) blk_cnt[blockIdx.x] = (int32_t)run;
 }
 
 // Small renders: one block sorts a whole render of up to kPer * 1,024 items in
-// LDS.  4,096 items take 16 us, four passes of ranks, digit starts and LDS
-// moves, each a chain of barriers; the other path's eight launches take 3 us
-// or more each however few the items.  16,384 items take 145 KB of LDS, nearly
-// all of a CU's 160, which is where the rule ends.
-template <int kPer>
+// LDS.  4,096 items take 16 us, three passes of ranks, digit starts and LDS
+// moves, each a chain of barriers; the other path's launches take 3 us or more
+// each however few the items.  16,384 items take 137 KB of LDS with 8-bit
+// digits (they leave no room for 11), nearly all of a CU's 160, which is where
+// the rule ends.
+template <int kBits, int kPer>
 __global__ __launch_bounds__(kSortThreads) void k_depth_sort_small(const JobDev* __restrict__ jobs, SegTable seg,
                                                                    const float4* __restrict__ rec,
                                                                    const int32_t* __restrict__ tiles,
                                                                    uint32_t* __restrict__ order) {
-  __shared__ uint32_t wcnt[kSortWaves][kBins];
+  using D = Digit<kBits>;
+  __shared__ __attribute__((aligned(4))) uint16_t wcnt[kSortWaves][D::kBins];
   __shared__ uint32_t sk[kPer * kSortThreads], sv[kPer * kSortThreads];
-  __shared__ uint32_t wsum[kBins / 64];
+  __shared__ uint32_t wsum[kSortWaves];
   __shared__ uint32_t kept;
   const int s = blockIdx.x;
   const int n = jobs[s].n, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -333,23 +380,23 @@ __global__ __launch_bounds__(kSortThreads) void k_depth_sort_small(const JobDev*
   for (int j = 0; j < kPer; ++j) key[j] = ok[j] ? __float_as_uint(rec[(int64_t)val[j] * 3 + 1].z) : 0u;
   int m = 0;
 #pragma unroll 1
-  for (int shift = 0; shift < 32; shift += 8) {
-    wave_ranks<kPer>(key, ok, shift, wcnt[w], lane, rk);
+  for (int shift = 0; shift < 32; shift += kBits) {
+    wave_ranks<kBits, kPer>(key, ok, shift, wcnt[w], lane, rk);
     __syncthreads();
-    uint32_t lstart;
-    const uint32_t cnt = digit_starts(wcnt, wsum, lstart);
-    if (threadIdx.x == kBins - 1) kept = lstart + cnt;
+    uint32_t lstart[D::kPer];
+    const uint32_t upto = digit_starts<kBits>(wcnt, wsum, lstart);
+    if (threadIdx.x == D::kThreads - 1) kept = upto;
     __syncthreads();
     m = (int)kept;
 #pragma unroll
     for (int j = 0; j < kPer; ++j)
       if (ok[j]) {
-        const uint32_t pos = wcnt[w][(key[j] >> shift) & (kBins - 1)] + rk[j];
+        const uint32_t pos = wcnt[w][D::of(key[j], shift)] + rk[j];
         sk[pos] = key[j];
         sv[pos] = val[j];
       }
     __syncthreads();
-    if (shift < 24)
+    if (shift + kBits < 32)
 #pragma unroll
       for (int j = 0; j < kPer; ++j) {
         const int i = w * 64 * kPer + j * 64 + lane;
@@ -433,7 +480,7 @@ struct PlaceCtx {
 // the lists, on one XCD.  A single render's units are mapped over those that
 // have items, so that all XCDs work.
 __device__ __forceinline__ int place_unit(const BinTables& t, const JobDev* jobs, const int32_t* kept, int units) {
-  if (t.R > 1) return xcd_remap(blockIdx.x, units);
+  if (t.R > 1) return (int)blockIdx.x < 8 * ((units + 7) / 8) ? xcd_remap(blockIdx.x, units) : units;
   const int busy = units > 0 ? chunks_of(kept[0], t.chunk, true) * (units / chunks_of(jobs[0].n, t.chunk, true)) : 0;
   const int u = xcd_remap(blockIdx.x, busy);
   return u < busy && (int)blockIdx.x < 8 * ((busy + 7) / 8) ? u : units;
@@ -565,13 +612,14 @@ __global__ __launch_bounds__(kPlaceThreads) void k_chunk_count(const JobDev* __r
   }
 }
 
-// Per tile: the chunks' counts turned into exclusive prefixes, and the total;
-// per block of 64 tiles the sum of the totals.  16 threads per tile, each a
-// run of chunks.
+// Per tile: the chunks' counts turned into exclusive prefixes, the total, and
+// the totals of the tiles before it in its group of 64 (at most 2^32 - 1); per
+// group the sum of the totals.  16 threads per tile, each a run of chunks.
 __global__ __launch_bounds__(1024) void k_chunk_scan(const JobDev* __restrict__ jobs, BinTables t,
                                                      const int32_t* __restrict__ tile_off, int T,
                                                      const int32_t* __restrict__ kept, uint32_t* __restrict__ cnt,
-                                                     uint32_t* __restrict__ total, uint64_t* __restrict__ blk_total) {
+                                                     uint32_t* __restrict__ total, uint32_t* __restrict__ before,
+                                                     uint64_t* __restrict__ blk_total) {
   constexpr int kParts = 16, kRun = 32;
   __shared__ uint32_t sums[kParts][64];
   const int tile = blockIdx.x * 64 + (threadIdx.x & 63), p = threadIdx.x >> 6;
@@ -611,81 +659,136 @@ __global__ __launch_bounds__(1024) void k_chunk_scan(const JobDev* __restrict__ 
     run += x;
   }
   if (p == 0) {
-    uint64_t sum = in ? all : 0u;
-    if (in) total[tile] = all;
-    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
-    if (threadIdx.x == 0) blk_total[blockIdx.x] = sum;
+    const uint64_t mine = in ? all : 0u;
+    uint64_t sum = mine;  // inclusive over the lanes
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint64_t y = __shfl_up(sum, off, 64);
+      if ((int)threadIdx.x >= off) sum += y;
+    }
+    if (in) {
+      total[tile] = all;
+      before[tile] = (uint32_t)min(sum - mine, (uint64_t)UINT32_MAX);
+    }
+    if (threadIdx.x == 63) blk_total[blockIdx.x] = sum;
   }
 }
 
-// Every tile's [start, end) (clamped to the capacity; empty tiles 0, 0), a
-// block per 1,024 tiles: the sums of the 64-tile blocks before it and its own
-// tiles' scan.  The last block writes count = {min(I, cap), I > cap,
-// min(I, INT32_MAX), 0}.
-__global__ __launch_bounds__(1024) void k_tile_starts(const uint32_t* __restrict__ total,
-                                                      const uint64_t* __restrict__ blk_total, int T, int64_t cap,
-                                                      uint32_t* __restrict__ start, int32_t* __restrict__ range,
-                                                      int32_t* __restrict__ count) {
-  __shared__ uint64_t wpre[16], wsum[16];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, i = blockIdx.x * 1024 + threadIdx.x;
-  const uint32_t mine = i < T ? total[i] : 0u;
-  uint64_t pre = 0;
-  for (int k = threadIdx.x; k < (int)blockIdx.x * 16; k += 1024) pre += blk_total[k];
-  uint64_t x = mine;
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint64_t y = __shfl_up(x, off, 64);
-    if (lane >= off) x += y;
-    pre += __shfl_xor(pre, off, 64);
+// Where each group of 64 tiles starts in the lists: the groups' sums turned
+// into exclusive prefixes; the whole sum into all[0].  One block.
+__global__ __launch_bounds__(1024) void k_group_starts(uint64_t* __restrict__ group, int n,
+                                                       uint64_t* __restrict__ all) {
+  __shared__ uint64_t wsum[16];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  uint64_t base = 0;
+  for (int i0 = 0; i0 < n; i0 += 1024) {
+    const int i = i0 + threadIdx.x;
+    const uint64_t mine = i < n ? group[i] : 0ull;
+    uint64_t x = mine;
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint64_t y = __shfl_up(x, off, 64);
+      if (lane >= off) x += y;
+    }
+    if (lane == 63) wsum[w] = x;
+    __syncthreads();
+    uint64_t run = base + x - mine;
+    for (int k = 0; k < 16; ++k) {
+      run += k < w ? wsum[k] : 0ull;
+      base += wsum[k];
+    }
+    if (i < n) group[i] = run;
+    __syncthreads();
   }
-  if (lane == 63) {
-    wsum[w] = x;
-    wpre[w] = pre;
-  }
-  __syncthreads();
-  uint64_t run = x - mine, all = 0;
+  if (threadIdx.x == 0) all[0] = base;
+}
+
+// The lists' table, a share of the tiles per block: every tile's [start, end)
+// (clamped to the capacity; empty tiles 0, 0) and tile_of, eight tiles to a
+// wave, in whole lines; and count = {min(I, cap), I > cap, min(I, INT32_MAX),
+// 0}.  group: where a group of 64 tiles starts.
+template <class Group>
+__device__ __forceinline__ void list_table(const Group& group, uint64_t all, const uint32_t* __restrict__ total,
+                                           const uint32_t* __restrict__ before, int T, uint64_t cap,
+                                           uint32_t* __restrict__ tile_of, int32_t* __restrict__ range,
+                                           int32_t* __restrict__ count) {
+  const int lane = threadIdx.x & 63;
+  for (int k = blockIdx.x + (threadIdx.x >> 6) * gridDim.x; 8 * k < T; k += gridDim.x * (kPlaceThreads / 64)) {
+    const int tile = 8 * k + lane;
+    uint64_t a = 0, e = 0;
+    if (lane < 8 && tile < T) {
+      a = group(tile >> 6) + before[tile];
+      e = min(a + total[tile], cap);
+      a = min(a, cap);
+      range[2 * tile] = a < e ? (int32_t)a : 0;
+      range[2 * tile + 1] = a < e ? (int32_t)e : 0;
+    }
 #pragma unroll
-  for (int k = 0; k < 16; ++k) {
-    run += wpre[k] + (k < w ? wsum[k] : 0ull);
-    all += wpre[k] + wsum[k];
+    for (int j = 0; j < 8; ++j) {
+      const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)a, j);
+      const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)e, j);
+      for (uint32_t i = lo + lane; i < hi; i += 64) tile_of[i] = (uint32_t)(8 * k + j);
+    }
   }
-  const uint64_t c = (uint64_t)cap;
-  if (i < T) {
-    const uint32_t a = (uint32_t)min(run, c), b = (uint32_t)min(run + mine, c);
-    start[i] = a;
-    range[2 * i] = a < b ? (int32_t)a : 0;
-    range[2 * i + 1] = a < b ? (int32_t)b : 0;
-  }
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
-    count[0] = (int32_t)min(all, c);
-    count[1] = all > c ? 1 : 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    count[0] = (int32_t)min(all, cap);
+    count[1] = all > cap ? 1 : 0;
     count[2] = (int32_t)min(all, (uint64_t)INT32_MAX);
     count[3] = 0;
   }
 }
 
+// Exclusive prefixes of the n <= kFewGroups group sums in LDS, by one block of
+// 1,024 threads; returns the whole sum.
+__device__ __forceinline__ uint64_t group_starts(const uint64_t* __restrict__ group, int n, uint64_t* out) {
+  __shared__ uint64_t wsum[16];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const uint64_t mine = (int)threadIdx.x < n ? group[threadIdx.x] : 0ull;
+  uint64_t x = mine;
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint64_t y = __shfl_up(x, off, 64);
+    if (lane >= off) x += y;
+  }
+  if (lane == 63) wsum[w] = x;
+  __syncthreads();
+  uint64_t run = x - mine, all = 0;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    run += k < w ? wsum[k] : 0ull;
+    all += wsum[k];
+  }
+  out[threadIdx.x] = run;
+  __syncthreads();
+  return all;
+}
+
 // The instances of a chunk, written to their places: every tile lists the
 // chunk's items that reach it, from the tile's start plus the earlier chunks'
 // count on.  A thread walks all words of its tile as one sequence, so a wave
-// takes as many steps as its fullest tile has items.  tile_of is filled tile by
-// tile, each block a share of the tiles, in whole lines: a scattered store
-// costs a CU about a clock per lane, so one per instance is as few as can be.
+// takes as many steps as its fullest tile has items.  A scattered store costs a
+// CU about a clock per lane, so tile_of is left to list_table.
+//
+// kFew: up to kFewGroups groups of 64 tiles, whose starts every block works out
+// for itself from the groups' sums; a launch for it and for the table took 3 to
+// 5 us.  More come from k_group_starts.
+constexpr int kFewGroups = kPlaceThreads;
+template <bool kFew>
 __global__ __launch_bounds__(kPlaceThreads) void k_place(const JobDev* __restrict__ jobs, BinTables t, int units,
                                                          const int32_t* __restrict__ kept,
                                                          const uint32_t* __restrict__ order,
                                                          const float4* __restrict__ rec,
                                                          const int32_t* __restrict__ radius,
                                                          const uint32_t* __restrict__ cnt,
-                                                         const uint32_t* __restrict__ start,
-                                                         const int32_t* __restrict__ range, int T, uint32_t cap,
-                                                         uint32_t* __restrict__ tile_of, int32_t* __restrict__ item) {
+                                                         const uint32_t* __restrict__ total,
+                                                         const uint32_t* __restrict__ before,
+                                                         const uint64_t* __restrict__ group, int T, uint32_t cap,
+                                                         uint32_t* __restrict__ tile_of, int32_t* __restrict__ item,
+                                                         int32_t* __restrict__ range, int32_t* __restrict__ count) {
   __shared__ PlaceLds L;
-  {
-    const int t0 = (int)((int64_t)T * blockIdx.x / gridDim.x), t1 = (int)((int64_t)T * (blockIdx.x + 1) / gridDim.x);
-    for (int k = t0 + (int)(threadIdx.x >> 6); k < t1; k += kPlaceThreads / 64) {
-      const int e = range[2 * k + 1];
-      for (int i = range[2 * k] + (int)(threadIdx.x & 63); i < e; i += 64) tile_of[i] = (uint32_t)k;
-    }
-  }
+  __shared__ uint64_t starts[kFew ? kFewGroups : 1];
+  const int ngroup = (T + 63) / 64;
+  const uint64_t all = kFew ? group_starts(group, ngroup, starts) : group[ngroup];
+  auto start_of = [&](int g) { return kFew ? starts[g] : group[g]; };
+  // (first: at the end it is every block's tail, 29 -> 36 us at 200k items)
+  list_table(start_of, all, total, before, T, cap, tile_of, range, count);
   const int unit = place_unit(t, jobs, kept, units);
   if (unit >= units) return;
   PlaceCtx c;
@@ -698,7 +801,8 @@ __global__ __launch_bounds__(kPlaceThreads) void k_place(const JobDev* __restric
 #pragma unroll
   for (int j = 0; j < kPlaceTiles; ++j) {
     const int k = j * kPlaceThreads + threadIdx.x, y = k / c.w, rt = (c.y0 + y) * J.TX + c.x0 + (k - y * c.w);
-    place[j] = k < nt ? start[J.tile_off + rt] + row[rt] : 0u;
+    const int tile = J.tile_off + rt;
+    place[j] = k < nt ? (uint32_t)min(start_of(tile >> 6) + before[tile], (uint64_t)cap) + row[rt] : 0u;
   }
   for (int i0 = 0; i0 < c.n; i0 += kPlaceItems) {
     const int n = min(c.n - i0, kPlaceItems);
@@ -742,55 +846,78 @@ void launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s) {
   hipLaunchKernelGGL(k_fill_i32, dim3((unsigned)blocks), dim3(256), 0, s, p, n, v);
 }
 
+template <int kBits>
+static void seg_pass(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout, const SegTable& seg,
+                     int blocks, int shift, uint32_t* hist, bool last, hipStream_t s) {
+  const dim3 grid(blocks), block(kSortThreads);
+  hipLaunchKernelGGL(k_seg_hist<kBits>, grid, block, 0, s, kin, seg, shift, hist);
+  const int32_t* none = nullptr;
+  auto scatter = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, block, 0, s, kin, vin, kout, vout, seg, shift, (const uint32_t*)hist, none);
+  };
+  if (last)
+    scatter(k_seg_scatter<kBits, false, true>);
+  else
+    scatter(k_seg_scatter<kBits, false, false>);
+}
+
 void launch_bin_sort(const BinLaunch& b, hipStream_t s) {
   const float4* rec4 = reinterpret_cast<const float4*>(b.rec);
   const SegTable seg{b.tab.blk_off, b.item_off, b.tab.R, b.kept};
   const uint32_t* order = b.v0;
+  const dim3 grid(b.sort_blocks), block(kSortThreads);
+  const uint32_t* hist = b.hist;
+  const int32_t* cnt = b.blk_cnt;
   if (b.max_items <= kSmallSort) {
+    auto small = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(b.tab.R), block, 0, s, b.jobs, seg, rec4, b.tiles, b.v0);
+    };
     if (b.max_items <= 4 * kSortThreads)
-      hipLaunchKernelGGL(k_depth_sort_small<4>, dim3(b.tab.R), dim3(kSortThreads), 0, s, b.jobs, seg, rec4, b.tiles,
-                         b.v0);
+      small(k_depth_sort_small<11, 4>);
     else if (b.max_items <= 8 * kSortThreads)
-      hipLaunchKernelGGL(k_depth_sort_small<8>, dim3(b.tab.R), dim3(kSortThreads), 0, s, b.jobs, seg, rec4, b.tiles,
-                         b.v0);
+      small(k_depth_sort_small<11, 8>);
     else
-      hipLaunchKernelGGL(k_depth_sort_small<16>, dim3(b.tab.R), dim3(kSortThreads), 0, s, b.jobs, seg, rec4, b.tiles,
-                         b.v0);
+      small(k_depth_sort_small<8, 16>);
+  } else if (b.max_items <= kWideItems) {
+    hipLaunchKernelGGL(k_depth_prep<11>, grid, block, 0, s, b.jobs, seg, rec4, b.tiles, b.k0, b.v0, b.hist, b.blk_cnt);
+    hipLaunchKernelGGL((k_seg_scatter<11, true, false>), grid, block, 0, s, (const uint32_t*)b.k0,
+                       (const uint32_t*)b.v0, b.k1, b.v1, seg, 0, hist, cnt);
+    seg_pass<11>(b.k1, b.v1, b.k0, b.v0, seg, b.sort_blocks, 11, b.hist, false, s);
+    seg_pass<11>(b.k0, b.v0, b.k1, b.v1, seg, b.sort_blocks, 22, b.hist, true, s);
+    order = b.v1;
   } else {
-    const dim3 grid(b.sort_blocks), block(kSortThreads);
-    const uint32_t* hist = b.hist;
-    hipLaunchKernelGGL(k_depth_prep, grid, block, 0, s, b.jobs, seg, rec4, b.tiles, b.k0, b.v0, b.hist, b.blk_cnt);
-    const int32_t* cnt = b.blk_cnt;
-    hipLaunchKernelGGL((k_seg_scatter<true, false>), grid, block, 0, s, (const uint32_t*)b.k0, (const uint32_t*)b.v0,
-                       b.k1, b.v1, seg, 0, hist, cnt);
-    launch_seg_pass(b.k1, b.v1, b.k0, b.v0, seg, b.sort_blocks, 8, b.hist, false, s);
-    launch_seg_pass(b.k0, b.v0, b.k1, b.v1, seg, b.sort_blocks, 16, b.hist, false, s);
-    launch_seg_pass(b.k1, b.v1, b.k0, b.v0, seg, b.sort_blocks, 24, b.hist, true, s);
+    hipLaunchKernelGGL(k_depth_prep<8>, grid, block, 0, s, b.jobs, seg, rec4, b.tiles, b.k0, b.v0, b.hist, b.blk_cnt);
+    hipLaunchKernelGGL((k_seg_scatter<8, true, false>), grid, block, 0, s, (const uint32_t*)b.k0,
+                       (const uint32_t*)b.v0, b.k1, b.v1, seg, 0, hist, cnt);
+    seg_pass<8>(b.k1, b.v1, b.k0, b.v0, seg, b.sort_blocks, 8, b.hist, false, s);
+    seg_pass<8>(b.k0, b.v0, b.k1, b.v1, seg, b.sort_blocks, 16, b.hist, false, s);
+    seg_pass<8>(b.k1, b.v1, b.k0, b.v0, seg, b.sort_blocks, 24, b.hist, true, s);
   }
   const dim3 work(8 * ((b.units + 7) / 8));
   if (b.units > 0)
     hipLaunchKernelGGL(k_chunk_count, work, dim3(kPlaceThreads), 0, s, b.jobs, b.tab, b.units,
                        (const int32_t*)b.kept, order, rec4, b.radius, b.cnt);
-  hipLaunchKernelGGL(k_chunk_scan, dim3((b.T + 63) / 64), dim3(1024), 0, s, b.jobs, b.tab, b.tile_off, b.T,
-                     (const int32_t*)b.kept, b.cnt, b.tile_total, b.blk_total);
-  hipLaunchKernelGGL(k_tile_starts, dim3((b.T + 1023) / 1024), dim3(1024), 0, s, (const uint32_t*)b.tile_total,
-                     (const uint64_t*)b.blk_total, b.T, b.cap, b.tile_start, b.range, b.count);
-  if (b.units > 0 && b.cap > 0)
-    hipLaunchKernelGGL(k_place, work, dim3(kPlaceThreads), 0, s, b.jobs, b.tab, b.units,
-                       (const int32_t*)b.kept, order, rec4, b.radius, (const uint32_t*)b.cnt,
-                       (const uint32_t*)b.tile_start, (const int32_t*)b.range, b.T, (uint32_t)b.cap, b.tile_of, b.item);
+  const int ngroup = (b.T + 63) / 64;
+  hipLaunchKernelGGL(k_chunk_scan, dim3(ngroup), dim3(1024), 0, s, b.jobs, b.tab, b.tile_off, b.T,
+                     (const int32_t*)b.kept, b.cnt, b.tile_total, b.tile_before, b.groups);
+  // at least a block per 1,024 tiles for the table
+  const dim3 place(std::max(work.x, 8u * ((unsigned)b.T / 8192u + 1u)));
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, place, dim3(kPlaceThreads), 0, s, b.jobs, b.tab, b.units, (const int32_t*)b.kept,
+                       order, rec4, b.radius, (const uint32_t*)b.cnt, (const uint32_t*)b.tile_total,
+                       (const uint32_t*)b.tile_before, (const uint64_t*)b.groups, b.T, (uint32_t)b.cap, b.tile_of,
+                       b.item, b.range, b.count);
+  };
+  if (ngroup <= kFewGroups) {
+    launch(k_place<true>);
+  } else {
+    hipLaunchKernelGGL(k_group_starts, dim3(1), dim3(1024), 0, s, b.groups, ngroup, b.groups + ngroup);
+    launch(k_place<false>);
+  }
 }
 
 void launch_seg_pass(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout, const SegTable& seg,
                      int blocks, int shift, uint32_t* hist, bool last, hipStream_t s) {
-  const dim3 grid(blocks), block(kSortThreads);
-  hipLaunchKernelGGL(k_seg_hist, grid, block, 0, s, kin, seg, shift, hist);
-  const int32_t* none = nullptr;
-  if (last)
-    hipLaunchKernelGGL((k_seg_scatter<false, true>), grid, block, 0, s, kin, vin, kout, vout, seg, shift,
-                       (const uint32_t*)hist, none);
-  else
-    hipLaunchKernelGGL((k_seg_scatter<false, false>), grid, block, 0, s, kin, vin, kout, vout, seg, shift,
-                       (const uint32_t*)hist, none);
+  seg_pass<8>(kin, vin, kout, vout, seg, blocks, shift, hist, last, s);
 }
 }  // namespace ls

@@ -13,6 +13,7 @@ constexpr int kBlock = 256;         // one 16x16 tile per block, 4 wave64
 constexpr int kSortThreads = 1024;  // radix sort block
 constexpr int kSortKeys = 4096;     // keys per radix sort block
 constexpr int kSmallSort = 16 * kSortThreads;  // items that one block sorts by depth on its own
+constexpr int kWideItems = 16 * kSortKeys;     // items up to which a larger render's depth sort takes 11-bit digits
 constexpr int kWindowTiles = 4096;  // most tiles of a binning window
 constexpr int kGradStride = 16;     // floats per item in the accumulator: a 64-byte line each
 constexpr int kGrad2D = 10;         // sums of ds (dx, dy, dx^2, dx dy, dy^2, 1), dz dr dg db

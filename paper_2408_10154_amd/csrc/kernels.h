@@ -63,8 +63,8 @@ struct SegTable {
   int S;
   int32_t* len;            // [S]
 };
-// Words of the digit histograms of `blocks` sort blocks.
-int64_t seg_hist_words(int blocks);
+// Words of the digit histograms of `blocks` sort blocks (wide: 11-bit digits).
+int64_t seg_hist_words(int blocks, bool wide);
 // One stable pass over the 8-bit digit at `shift` (binning.hip), from
 // (kin, vin) to (kout, vout); last: kout is not written.
 void launch_seg_pass(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout, const SegTable& seg,
@@ -99,8 +99,8 @@ struct BinLaunch {
   int32_t* kept;                // [R]: items with tiles
   uint32_t* cnt;                // count matrices
   uint32_t* tile_total;         // [T]
-  uint32_t* tile_start;         // [T]
-  uint64_t* blk_total;          // [ceil(T / 64)]
+  uint32_t* tile_before;        // [T]: totals of the tiles before it in its group of 64
+  uint64_t* groups;             // [ceil(T / 64) + 1]: totals of the groups, and room for their sum
   uint32_t* tile_of;
   int32_t* item;
   int32_t* range;

@@ -507,7 +507,7 @@ static OvLayout ov_layout(int np, int nq) {
   L.idx_a = take(4 * both);
   L.code_b = take(4 * both);
   L.idx_b = take(4 * both);
-  L.hist = take(4 * (size_t)seg_hist_words(ov_sort_blocks(np, nq)));
+  L.hist = take(4 * (size_t)seg_hist_words(ov_sort_blocks(np, nq), false));
   for (int s = 0; s < 2; ++s) {
     const int n = s ? nq : np;
     const int nleaf = (n + kOvLeaf - 1) / kOvLeaf, nsuper = (nleaf + kOvSuper - 1) / kOvSuper;

@@ -1,7 +1,7 @@
 """Tile binning at the edges of its paths: renders that one block sorts
 (4,096, 8,192 and 16,384 items) and the first larger one, chunk ends of the
-distribution, images of one and of several tile windows, and batches with
-empty and fully culled renders.  The lists are whole numbers: equality."""
+distribution, images of one and of several tile windows or with most tiles
+empty, and batches with empty and fully culled renders.  The lists are whole numbers: equality."""
 
 import numpy as np
 import pytest
@@ -14,6 +14,7 @@ from tests import _util as U
 pytestmark = pytest.mark.gpu
 
 SMALL, WIDE, TALL = (100, 70), (4200, 40), (1100, 1080)  # 7 x 5, 263 x 3 and 69 x 68 tiles
+HUGE, LARGE = (4112, 4100), (4096, 4096)  # 257 x 257 tiles and the 65,536 up to which one launch is saved
 
 
 def _records(rng, n, cam, culled):
@@ -37,6 +38,7 @@ def _records(rng, n, cam, culled):
     ([8193], SMALL, 0.3), ([16384], SMALL, 0.0), ([16385], SMALL, 0.0), ([21000], SMALL, 0.4), ([17000], SMALL, 1.0),
     ([900], WIDE, 0.1), ([9000], WIDE, 0.1), ([700], TALL, 0.1), ([17000], TALL, 0.9),
     ([512, 0, 513, 40], SMALL, 0.0), ([16385, 0, 4096, 1], SMALL, 0.2), ([600, 30], TALL, 0.2),
+    ([300], HUGE, 0.0), ([300], LARGE, 0.0),
 ])
 def test_lists_equal_the_oracle(gpu, sizes, image, culled):
     from paper_2408_10154_amd.render import GaussianSet, RenderBatch
