@@ -170,22 +170,34 @@ __global__ void k_loss_reduce(const int32_t* __restrict__ pblk_off, int R, const
 }
 
 // Per-render L1 loss from the partials {sum, count} per 8x8 band that the
-// compositing backward wrote with L1 targets: one 256-thread block per render,
-// strided per-thread sums, wave sums, then the four waves in order.
-__global__ __launch_bounds__(256) void k_tile_loss_reduce(const JobDev* __restrict__ jobs, int R,
-                                                          const float* __restrict__ part, float* __restrict__ loss) {
-  __shared__ float ws[2][4];
+// compositing backward wrote with L1 targets: one block per render, strided
+// per-thread sums, wave sums, then the waves in order.  Bound by its loads'
+// latency: 1,024 threads with eight loads in flight each (1200 x 680, 12,900
+// partials: 4.7 us, against 6.7 us with 256 threads and four).
+constexpr int kTileLossThreads = 1024;
+__global__ __launch_bounds__(kTileLossThreads) void k_tile_loss_reduce(const JobDev* __restrict__ jobs, int R,
+                                                                       const float* __restrict__ part,
+                                                                       float* __restrict__ loss) {
+  constexpr int kWaves = kTileLossThreads / 64;
+  __shared__ float ws[2][kWaves];
   const int r = blockIdx.x;
   if (r >= R) return;
   const JobDev& J = jobs[r];
-  const int first = 4 * J.tile_off, nt = 4 * J.TX * J.TY;
-  const float2* p2 = reinterpret_cast<const float2*>(part);
+  const int nt = 4 * J.TX * J.TY;
+  const float2* p2 = reinterpret_cast<const float2*>(part) + 4 * (int64_t)J.tile_off;
   float s = 0.f, c = 0.f;
-#pragma unroll 4
-  for (int t = threadIdx.x; t < nt; t += 256) {
-    const float2 v = p2[first + t];
-    s += v.x;
-    c += v.y;
+  for (int t0 = threadIdx.x; t0 < nt; t0 += 8 * kTileLossThreads) {
+    float2 v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const int t = t0 + k * kTileLossThreads;
+      v[k] = t < nt ? p2[t] : make_float2(0.f, 0.f);
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      s += v[k].x;
+      c += v[k].y;
+    }
   }
   s = wave_sum(s);
   c = wave_sum(c);
@@ -195,8 +207,12 @@ __global__ __launch_bounds__(256) void k_tile_loss_reduce(const JobDev* __restri
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    const float ts = (ws[0][0] + ws[0][1]) + (ws[0][2] + ws[0][3]);
-    const float tc = (ws[1][0] + ws[1][1]) + (ws[1][2] + ws[1][3]);
+    float ts = 0.f, tc = 0.f;
+#pragma unroll
+    for (int k = 0; k < kWaves; ++k) {
+      ts += ws[0][k];
+      tc += ws[1][k];
+    }
     loss[r] = tc > 0.f ? ts / tc : 0.f;
   }
 }
@@ -471,7 +487,7 @@ void launch_loss_track(const JobDev* jobs, const int32_t* pblk_off_d, int R, int
 }
 
 void launch_tile_loss_reduce(const JobDev* jobs, int R, const float* loss_part, float* loss, hipStream_t s) {
-  if (R > 0) hipLaunchKernelGGL(k_tile_loss_reduce, dim3(R), dim3(256), 0, s, jobs, R, loss_part, loss);
+  if (R > 0) hipLaunchKernelGGL(k_tile_loss_reduce, dim3(R), dim3(kTileLossThreads), 0, s, jobs, R, loss_part, loss);
 }
 
 void launch_adam(const ls_adam_group* g, int ng, float beta1, float beta2, float eps, float bc1, float bc2,
