@@ -290,9 +290,10 @@ static ls_status batch_host(const ls_render_job* jobs, int32_t R, ls_batch** out
   // 16 renders of 150k and 120k items: lists 67 -> 101 us) and 16 M counts
   // (64 MiB, 20 us to write and 40 us to scan; only large images reach it)
   b->bin_chunk = 512;
+  b->bin_ramp = R == 1 || b->M / b->bin_chunk <= 512;
   const auto counts = [&] {
     int64_t n = 0;
-    for (const JobDev& d : b->jobs_h) n += (int64_t)ls::bin_chunks(d.n, b->bin_chunk, R) * d.TX * d.TY;
+    for (const JobDev& d : b->jobs_h) n += (int64_t)ls::bin_chunks(d.n, b->bin_chunk, b->bin_ramp) * d.TX * d.TY;
     return n;
   };
   while (b->bin_chunk < 1 << 20 && (b->M / b->bin_chunk > 4096 || counts() > 1 << 24)) b->bin_chunk *= 2;
@@ -302,7 +303,7 @@ static ls_status batch_host(const ls_render_job* jobs, int32_t R, ls_batch** out
   int64_t units = 0;
   for (int r = 0; r < R; ++r) {
     const JobDev& d = b->jobs_h[r];
-    const int64_t chunks = ls::bin_chunks(d.n, b->bin_chunk, R);
+    const int64_t chunks = ls::bin_chunks(d.n, b->bin_chunk, b->bin_ramp);
     b->max_items = std::max(b->max_items, d.n);
     b->sortblk_off[r + 1] = b->sortblk_off[r] + (d.n + kSortKeys - 1) / kSortKeys;
     units += chunks * ls::windows_of(d.TX, d.TY);
@@ -520,7 +521,7 @@ ls_status ls_bin_sort(const ls_batch* b, const ls_projected* p, const ls_bins* b
   bl.jobs = b->jobs_d;
   bl.item_off = b->item_off_d;
   bl.tile_off = b->tile_off_d;
-  bl.tab = BinTables{b->sortblk_off_d, b->binwork_off_d, b->bincnt_off_d, b->R, b->bin_chunk};
+  bl.tab = BinTables{b->sortblk_off_d, b->binwork_off_d, b->bincnt_off_d, b->R, b->bin_chunk, b->bin_ramp};
   bl.T = b->T;
   bl.max_items = b->max_items;
   bl.sort_blocks = b->sort_blocks;

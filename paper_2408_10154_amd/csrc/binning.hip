@@ -451,13 +451,13 @@ int windows_of(int TX, int TY) {
   return w.nx * w.ny;
 }
 
-// Chunks hold `chunk` items.  The nearest items cover the most tiles; a single
-// render's first chunks are therefore cut finer, 64 items (16 chunks), then
-// 128 and 256 (16 chunks each), so that no block writes many times the others'
-// instances (200k items: 92 -> 29 us for k_place).  A batch's blocks
-// outnumber the CUs several times as they are, and finer chunks only add
-// counts to scan (16 renders of 150k and 120k items: counts and lists 104 us
-// without, 121 us with finer first chunks).
+// Chunks hold `chunk` items.  The nearest items cover the most tiles; with
+// `ramp` a render's first chunks are therefore cut finer, 64 items (16 chunks),
+// then 128 and 256 (16 chunks each), so that no block writes many times the
+// others' instances (k_place: 200k items 92 -> 29 us, 4 renders of 21k and 17k
+// items 17 -> 14 us).  A batch of more than 512 chunks fills the CUs as it is,
+// and finer chunks only add counts to scan (16 renders of 150k and 120k items:
+// counts and lists 104 us without, 121 us with; 8 of 150k 53 and 66 us).
 constexpr int kRamp = 16 * (64 + 128 + 256);
 __host__ __device__ inline int chunk_first(int c, int chunk, bool ramp) {
   if (!ramp) return chunk * c;
@@ -469,7 +469,7 @@ __host__ __device__ inline int chunks_of(int n, int chunk, bool ramp) {
          : n <= 3072 ? 16 + (n - 1024 + 127) / 128
          : n <= kRamp ? 32 + (n - 3072 + 255) / 256 : 48 + (n - kRamp + chunk - 1) / chunk;
 }
-int bin_chunks(int n, int chunk, int R) { return chunks_of(n, chunk, R == 1); }
+int bin_chunks(int n, int chunk, bool ramp) { return chunks_of(n, chunk, ramp); }
 
 struct PlaceCtx {
   int r, chunk, x0, y0, w, h;  // render, chunk, window in tiles
@@ -498,8 +498,8 @@ __device__ __forceinline__ bool place_ctx(const JobDev* jobs, const BinTables& t
   c.y0 = wy * win.h;
   c.w = min(win.w, J.TX - c.x0);
   c.h = min(win.h, J.TY - c.y0);
-  c.first = chunk_first(c.chunk, t.chunk, t.R == 1);
-  c.n = min(kept[c.r], chunk_first(c.chunk + 1, t.chunk, t.R == 1)) - c.first;
+  c.first = chunk_first(c.chunk, t.chunk, t.ramp);
+  c.n = min(kept[c.r], chunk_first(c.chunk + 1, t.chunk, t.ramp)) - c.first;
   return c.n > 0;
 }
 
@@ -627,7 +627,7 @@ __global__ __launch_bounds__(1024) void k_chunk_scan(const JobDev* __restrict__ 
   const int r = find_segment<int32_t>(tile_off, t.R, in ? tile : T - 1);
   const JobDev& J = jobs[r];
   const int nt = J.TX * J.TY;
-  const int rows = J.n > 0 ? chunks_of(kept[r], t.chunk, t.R == 1) : 0;
+  const int rows = J.n > 0 ? chunks_of(kept[r], t.chunk, t.ramp) : 0;
   const int per = (rows + kParts - 1) / kParts;
   const int lo = min(p * per, rows), hi = in ? min(lo + per, rows) : lo;
   uint32_t* __restrict__ col = cnt + t.cnt_off[r] + (in ? tile - J.tile_off : 0);

@@ -77,11 +77,12 @@ struct BinTables {
   const int32_t* work_off;  // [R + 1]
   const int64_t* cnt_off;   // [R + 1]
   int R;
-  int chunk;                // sorted items per chunk (past the first, smaller ones)
+  int chunk;                // sorted items per chunk
+  bool ramp;                // the first chunks are smaller
 };
-// Tile windows of a render and chunks of n sorted items in a batch of R (host tables).
+// Tile windows of a render and chunks of n sorted items (host tables).
 int windows_of(int TX, int TY);
-int bin_chunks(int n, int chunk, int R);
+int bin_chunks(int n, int chunk, bool ramp);
 
 struct BinLaunch {
   const JobDev* jobs;
