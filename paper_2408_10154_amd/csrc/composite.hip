@@ -160,14 +160,18 @@ __device__ __forceinline__ uint64_t band_rows(float4 a, float4 b, float bx0, flo
 // weight), which gives the FMA chain's bits in the time of two of its four
 // FMAs and reads 4 instead of 16 bytes of LDS per lane.  With the band test
 // on reciprocal and square root instructions: 34 M, 83 us; 16 renders of 150k
-// and 120k items at 640 x 480 231 -> 217 us, 8 of 150k 141 -> 131 us.
+// and 120k items at 640 x 480 231 -> 217 us, 8 of 150k 141 -> 131 us.  Taking
+// the XCDs' shares in turns (xcd_turns) made that 77, 165 and 104 us, and a
+// step without branches but for stops and unused entries, which leaves T in two
+// registers by turns and LDS offsets in vector registers, 74, 159 and 100 us.
+// At 200k items the last waves, on half-empty SIMDs, are a fifth of the time.
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8))) void k_composite_fwd_band(
     const JobDev* __restrict__ jobs, const int32_t* __restrict__ tile_off, int R, int T_total,
     const float4* __restrict__ rec, const int32_t* __restrict__ items, const int32_t* __restrict__ range, float bg0,
     float bg1, float bg2, float* __restrict__ out_rgb, float* __restrict__ out_depth, float* __restrict__ out_alpha,
     float* __restrict__ out_T, int32_t* __restrict__ out_n, uint64_t* __restrict__ used, int64_t ustride,
     int cover) {
-  // one entry of padding: the walk reads entry j + 1 ahead without a clamp
+  // one entry of padding: the walk takes two entries at a time and reads one ahead
   __shared__ float4 s0[65], s1[65], s2[65];
   __shared__ int32_t spos[64];
   const int unit = xcd_turns<64>(blockIdx.x, 4 * T_total);
@@ -221,62 +225,66 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8))) void k_
       spos[pos] = e - start;
     }
     __builtin_amdgcn_wave_barrier();
-    const int cw = __popcll(bal);
-    // one step at staged entry j; returns whether every pixel has now stopped
-    // (decided only where pixels stop, so a step that stops none tests nothing)
-    auto step = [&](int j, const float4& a, const float3& b, float col) -> bool {
-      bool ended = false;
+    int cw = __popcll(bal);
+    if (lane == 0) {  // the walk takes two entries at a time: a last one that composites nowhere
+      s0[cw] = make_float4(0.f, 0.f, 0.f, 0.f);
+      s1[cw] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    __builtin_amdgcn_wave_barrier();
+    // one step at staged entry j, transmittance Ti before and To after it:
+    // no branch but for pixels that stop and entries that no pixel takes (whose
+    // colour, should it be infinite, must not meet the weight 0)
+    auto step = [&](int j, const float4& a, const float3& b, float col, float Ti, float& To) {
       const float dx = fx - a.x, dy = fy - a.y;
       const float sl = falloff_log2(a.z, a.w, b.x, dx, dy);
       const bool c = composited(sl, b.z);
-      const uint64_t hit = alive & __ballot(c);
-      if (hit != 0ull) {
-        // a pixel that does not composite the entry takes alpha 0: weight 0, T as it was
-        const float al = c ? fminf(LS_ALPHA_MAX, b.y * __builtin_amdgcn_exp2f(-sl)) : 0.f;
-        // the weight alpha T, and T (1 - alpha) as T - alpha T in one FMA
-        float w = al * T, Tn = __builtin_fmaf(-al, T, T);
-        const uint64_t stop = hit & __ballot(Tn < LS_T_STOP);
-        if (stop != 0ull) {
-          if (__builtin_amdgcn_inverse_ballot_w64(stop)) {
-            nlast = spos[j];
-            Tend = T;
-            w = 0.f;
-            Tn = 0.f;
-          }
-          alive &= ~stop;
-          ended = alive == 0ull;
+      // a pixel that does not composite the entry takes alpha 0: weight 0, T as it was
+      const float al = c ? fminf(LS_ALPHA_MAX, b.y * __builtin_amdgcn_exp2f(-sl)) : 0.f;
+      // the weight alpha T, and T (1 - alpha) as T - alpha T in one FMA
+      float w = al * Ti;
+      To = __builtin_fmaf(-al, Ti, Ti);
+      uint64_t use = alive & __ballot(c);
+      const uint64_t stop = alive & __ballot(To < LS_T_STOP);  // (a pixel above it stays there with alpha 0)
+      if (stop != 0ull) {
+        if (__builtin_amdgcn_inverse_ballot_w64(stop)) {
+          nlast = spos[j];
+          Tend = Ti;
+          w = 0.f;
+          To = 0.f;
         }
-        T = Tn;
-        if (hit != stop) {
-          acc = __builtin_amdgcn_mfma_f32_4x4x1f32(col, w, acc, 0, 0, 0);
-          // usedm |= 1 << j in one scalar instruction (a register-only bit set)
-          asm volatile("s_bitset1_b64 %0, %1" : "+s"(usedm) : "s"(j));
-        }
+        use &= ~stop;
+        alive &= ~stop;
+        cw = alive == 0ull ? 0 : cw;  // every pixel has stopped: the walk ends
       }
-      return ended;
+      if (use != 0ull) {
+        acc = __builtin_amdgcn_mfma_f32_4x4x1f32(col, w, acc, 0, 0, 0);
+        // usedm |= 1 << j in one scalar instruction (a register-only bit set)
+        asm volatile("s_bitset1_b64 %0, %1" : "+s"(usedm) : "s"(j));
+      }
     };
     // Records are read one entry ahead into two alternating register sets
     // (the loop unrolled by hand, so no copies), so the LDS latency of the
     // next entry overlaps the arithmetic of this one; the read past the last
-    // staged entry (at most entry 64, the padding) is never used.  The walk
-    // ends after the staged entries or once every pixel has stopped.
-    const float4* pa = s0;
-    const float4* pb = s1;
-    const float* pc = reinterpret_cast<const float*>(s2) + (lane & 3);
-    auto b3 = [](const float4& v) { return make_float3(v.x, v.y, v.z); };
-    float4 aA = pa[0], aB;
-    float3 bA = b3(pb[0]), bB;
-    float cA = pc[0], cB;
-    for (int jj = 0; jj < cw;) {
-      aB = pa[jj + 1];
-      bB = b3(pb[jj + 1]);
-      cB = pc[4 * (jj + 1)];
-      if (step(jj, aA, bA, cA) || ++jj >= cw) break;
-      aA = pa[jj + 1];
-      bA = b3(pb[jj + 1]);
-      cA = pc[4 * (jj + 1)];
-      if (step(jj, aB, bB, cB)) break;
-      ++jj;
+    // staged entry (at most entry 64) is never used.  The offsets advance in
+    // vector registers (the empty asm), as the reads want them.
+    uint32_t at = 0u, atc = 4u * (lane & 3);
+    asm volatile("" : "+v"(at), "+v"(atc));
+    auto read = [&](int k, float4& a, float3& b, float& c) {
+      a = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(s0 + k) + at);
+      b = *reinterpret_cast<const float3*>(reinterpret_cast<const char*>(s1 + k) + at);
+      c = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(s2 + k) + atc);
+    };
+    float4 aA, aB;
+    float3 bA, bB;
+    float cA, cB, T2;
+    read(0, aA, bA, cA);
+    for (int jj = 0; jj < cw; jj += 2) {
+      read(1, aB, bB, cB);
+      step(jj, aA, bA, cA, T, T2);
+      read(2, aA, bA, cA);
+      at += 32u;
+      atc += 32u;
+      step(jj + 1, aB, bB, cB, T2, T);
     }
     // the entries of this chunk that some pixel of the band composited
     // (bit l: entry chunk + l): exactly the (entry, band) pairs in which the

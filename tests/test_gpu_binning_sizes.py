@@ -38,7 +38,7 @@ def _records(rng, n, cam, culled):
     ([8193], SMALL, 0.3), ([16384], SMALL, 0.0), ([16385], SMALL, 0.0), ([21000], SMALL, 0.4), ([17000], SMALL, 1.0),
     ([900], WIDE, 0.1), ([9000], WIDE, 0.1), ([700], TALL, 0.1), ([17000], TALL, 0.9),
     ([512, 0, 513, 40], SMALL, 0.0), ([16385, 0, 4096, 1], SMALL, 0.2), ([600, 30], TALL, 0.2),
-    ([300], HUGE, 0.0), ([300], LARGE, 0.0),
+    ([300], HUGE, 0.0), ([300], LARGE, 0.0), ([140000, 130000], SMALL, 0.97),
 ])
 def test_lists_equal_the_oracle(gpu, sizes, image, culled):
     from paper_2408_10154_amd.render import GaussianSet, RenderBatch
