@@ -305,6 +305,7 @@ static ls_status batch_host(const ls_render_job* jobs, int32_t R, ls_batch** out
     const JobDev& d = b->jobs_h[r];
     const int64_t chunks = ls::bin_chunks(d.n, b->bin_chunk, b->bin_ramp);
     b->max_items = std::max(b->max_items, d.n);
+    b->rank_pairs += (int64_t)d.n * d.n;
     b->sortblk_off[r + 1] = b->sortblk_off[r] + (d.n + kSortKeys - 1) / kSortKeys;
     units += chunks * ls::windows_of(d.TX, d.TY);
     if (units > INT32_MAX / 2) {
@@ -524,6 +525,9 @@ ls_status ls_bin_sort(const ls_batch* b, const ls_projected* p, const ls_bins* b
   bl.tab = BinTables{b->sortblk_off_d, b->binwork_off_d, b->bincnt_off_d, b->R, b->bin_chunk, b->bin_ramp};
   bl.T = b->T;
   bl.max_items = b->max_items;
+  bl.rank_pairs = b->rank_pairs;
+  bl.off256 = b->blk_off_d;
+  bl.blocks256 = b->nblk_items;
   bl.sort_blocks = b->sort_blocks;
   bl.units = b->bin_units;
   bl.rec = p->rec;

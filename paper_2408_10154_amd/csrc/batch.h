@@ -17,6 +17,7 @@ struct ls_batch {
   int nblk_pix = 0;
   int nblk_ssim = 0;  // mapping-loss SSIM blocks (3 channels x 32x32 tiles per render)
   int max_items = 0;      // most items of a render
+  int64_t rank_pairs = 0; // sum over the renders of the squared item count
   int sort_blocks = 0;    // radix sort blocks over all renders
   int bin_chunk = 0;      // sorted items per binning chunk
   bool bin_ramp = false;  // the first chunks are smaller

@@ -5,9 +5,10 @@
 //
 //  1. The items with tiles are sorted by depth bits, render by render (LSD
 //     radix sort, stable: ties keep ascending item order).  A render of up to
-//     16,384 items is sorted by one block in LDS, in one launch; larger ones
-//     take a histogram and a scatter per digit, and the scatter forms its
-//     digit bases from the block histograms itself.
+//     16,384 items has them ranked by comparison, in a batch of such renders a
+//     block each sorts them in LDS, in one launch; larger ones take a histogram
+//     and a scatter per digit, and the scatter forms its digit bases from the
+//     block histograms itself.
 //  2. The sorted items are cut into chunks.  One block per chunk counts the
 //     items of every tile of its render, a scan over the chunks turns the
 //     counts into each chunk's first place in each tile's list, and one block
@@ -17,7 +18,7 @@
 // pair sort it replaces moved each instance three times in 8 launches (all of
 // binning: 200k items, 1200 x 680, 143 -> 98 us and 22 launches -> 11; eight
 // renders of 150k items, 640 x 480, 157 -> 118 us; 23k items, 317 x 211, 90 ->
-// 63 us and 9 launches; 4,096 items, 160 x 120, 81 -> 36 us and 4 launches).
+// 63 us and 9 launches; 4,096 items, 160 x 120, 81 -> 32 us and 4 launches).
 // What is left is bound by latency: launches of 3 to 10 us on tens to hundreds
 // of blocks, each a chain of dependent loads.
 #include "common.h"
@@ -349,12 +350,126 @@ __global__ __launch_bounds__(kSortThreads) void k_depth_prep(const JobDev* __res
   if (threadIdx.x == 0) blk_cnt[blockIdx.x] = (int32_t)run;
 }
 
-// Small renders: one block sorts a whole render of up to kPer * 1,024 items in
-// LDS.  4,096 items take 16 us, three passes of ranks, digit starts and LDS
-// moves, each a chain of barriers; the other path's launches take 3 us or more
-// each however few the items.  16,384 items take 137 KB of LDS with 8-bit
-// digits (they leave no room for 11), nearly all of a CU's 160, which is where
-// the rule ends.
+// Small renders, of up to kItems items: each item's place is the number of
+// items before it, by comparison with all of them.  A block holds the render's
+// depth bits in LDS (all ones: no tiles) and takes 64 of its items, one per
+// lane; a wave counts over a sixteenth of the keys.  off256: the renders' first
+// blocks of 256 items.
+//
+// A key costs a wave a compare and an add with carry, and the keys of 4,096 items
+// 2,000 cycles; the rest is the launch and two dependent loads.  All of binning
+// in a graph, with this and with one block sorting each render in LDS: 1,500
+// items 28 and 32 us, 4,096 33 and 38 us, 8,192 43 and 53 us, 16,000 56 and 76
+// us.  Batches do better with the LDS sort from kRankPairs pairs on: 4 renders
+// of 3,000 items 30 and 34 us, 4 of 8,000 54 and 53 us, 8 of 5,000 53 and 49 us.
+constexpr int kRankWaves = 16;
+
+// n += the number of k's components that are below key (kEqual: or equal).
+// (The masks of four compares at once: used straight after its compare, a mask
+// takes wait states.)
+template <bool kEqual>
+__device__ __forceinline__ void count4(uint32_t& n, uint32_t key, const uint4& k) {
+  uint64_t a, b, c, d;
+  if (kEqual)
+    asm("v_cmp_ge_u32_e64 %1, %5, %6\n\tv_cmp_ge_u32_e64 %2, %5, %7\n\t"
+        "v_cmp_ge_u32_e64 %3, %5, %8\n\tv_cmp_ge_u32_e64 %4, %5, %9\n\t"
+        "v_addc_co_u32_e64 %0, %1, %0, 0, %1\n\tv_addc_co_u32_e64 %0, %2, %0, 0, %2\n\t"
+        "v_addc_co_u32_e64 %0, %3, %0, 0, %3\n\tv_addc_co_u32_e64 %0, %4, %0, 0, %4"
+        : "+v"(n), "=&s"(a), "=&s"(b), "=&s"(c), "=&s"(d)
+        : "v"(key), "v"(k.x), "v"(k.y), "v"(k.z), "v"(k.w));
+  else
+    asm("v_cmp_gt_u32_e64 %1, %5, %6\n\tv_cmp_gt_u32_e64 %2, %5, %7\n\t"
+        "v_cmp_gt_u32_e64 %3, %5, %8\n\tv_cmp_gt_u32_e64 %4, %5, %9\n\t"
+        "v_addc_co_u32_e64 %0, %1, %0, 0, %1\n\tv_addc_co_u32_e64 %0, %2, %0, 0, %2\n\t"
+        "v_addc_co_u32_e64 %0, %3, %0, 0, %3\n\tv_addc_co_u32_e64 %0, %4, %0, 0, %4"
+        : "+v"(n), "=&s"(a), "=&s"(b), "=&s"(c), "=&s"(d)
+        : "v"(key), "v"(k.x), "v"(k.y), "v"(k.z), "v"(k.w));
+}
+
+// Those of keys[lo] .. keys[hi), a multiple of 64 of them, 64 in flight.
+template <bool kEqual>
+__device__ __forceinline__ void count_keys(uint32_t& n, uint32_t key, const uint32_t* keys, int lo, int hi) {
+  for (int i = lo; i < hi; i += 64) {
+    uint4 k[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) k[j] = reinterpret_cast<const uint4*>(keys + i)[j];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) count4<kEqual>(n, key, k[j]);
+  }
+}
+
+template <int kItems>
+__global__ __launch_bounds__(64 * kRankWaves) void k_depth_rank(const JobDev* __restrict__ jobs, SegTable seg,
+                                                                const int32_t* __restrict__ off256,
+                                                                const float4* __restrict__ rec,
+                                                                const int32_t* __restrict__ tiles,
+                                                                uint32_t* __restrict__ order) {
+  constexpr int kThreads = 64 * kRankWaves;
+  constexpr uint32_t kNone = 0xFFFFFFFFu;
+  __shared__ __attribute__((aligned(16))) uint32_t keys[kItems];
+  __shared__ uint32_t part[kRankWaves][64];
+  __shared__ int kept[kRankWaves];
+  const int blk = blockIdx.x >> 2, s = find_segment<int32_t>(off256, seg.S, blk);
+  const int q0 = (blk - off256[s]) * 256 + (blockIdx.x & 3) * 64, n = jobs[s].n;
+  if (q0 >= n) return;  // uniform for the block
+  const int64_t base = seg.base[s];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int padded = (n + kThreads - 1) / kThreads * kThreads;
+  int valid = 0;
+  for (int i0 = 0; i0 < padded; i0 += 4 * kThreads) {
+    bool ok[4];
+    uint32_t z[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int i = i0 + j * kThreads + threadIdx.x;
+      ok[j] = i < n && tiles[base + i] > 0;
+      valid += (int)__popcll(__ballot(ok[j]));
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      z[j] = ok[j] ? min(__float_as_uint(rec[(base + i0 + j * kThreads + threadIdx.x) * 3 + 1].z), kNone - 1u) : kNone;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (i0 + j * kThreads < padded) keys[i0 + j * kThreads + threadIdx.x] = z[j];
+  }
+  if (lane == 0) kept[w] = valid;
+  __syncthreads();
+  if (q0 == 0 && threadIdx.x == 0) {
+    int all = 0;
+    for (int k = 0; k < kRankWaves; ++k) all += kept[k];
+    seg.len[s] = all;
+  }
+  const uint32_t key = keys[q0 + lane];
+  if (__syncthreads_or(key != kNone) == 0) return;
+  // this wave's share, in fours; equal keys keep their order, so those of an
+  // earlier place count as smaller, and the block's own 64 are compared by place
+  const int per = padded / kRankWaves, lo = w * per, hi = lo + per;
+  const int a = min(max(q0, lo), hi), b = max(min(q0 + 64, hi), a);
+  uint32_t below = 0;
+  count_keys<true>(below, key, keys, lo, a);
+  for (int i = a; i < b; i += 4) {
+    const uint4 k = *reinterpret_cast<const uint4*>(keys + i);
+    const int at = q0 + lane - i;
+    below += k.x < key + (at > 0 ? 1u : 0u) ? 1u : 0u;
+    below += k.y < key + (at > 1 ? 1u : 0u) ? 1u : 0u;
+    below += k.z < key + (at > 2 ? 1u : 0u) ? 1u : 0u;
+    below += k.w < key + (at > 3 ? 1u : 0u) ? 1u : 0u;
+  }
+  count_keys<false>(below, key, keys, b, hi);
+  part[w][lane] = below;
+  __syncthreads();
+  if (w == 0 && key != kNone) {
+    uint32_t rank = 0;
+#pragma unroll
+    for (int k = 0; k < kRankWaves; ++k) rank += part[k][lane];
+    order[base + rank] = (uint32_t)(base + q0 + lane);
+  }
+}
+
+// Batches of small renders, where comparing all pairs would take longer: one
+// block sorts a whole render of up to kPer * 1,024 items in LDS, three passes of
+// ranks, digit starts and LDS moves, each a chain of barriers (4,096 items 16
+// us, eight renders of 5,000 20 us, and 24 us by comparison).
 template <int kBits, int kPer>
 __global__ __launch_bounds__(kSortThreads) void k_depth_sort_small(const JobDev* __restrict__ jobs, SegTable seg,
                                                                    const float4* __restrict__ rec,
@@ -868,16 +983,23 @@ void launch_bin_sort(const BinLaunch& b, hipStream_t s) {
   const dim3 grid(b.sort_blocks), block(kSortThreads);
   const uint32_t* hist = b.hist;
   const int32_t* cnt = b.blk_cnt;
-  if (b.max_items <= kSmallSort) {
+  if (b.max_items <= kRankItems && (b.tab.R == 1 || b.rank_pairs <= kRankPairs)) {
+    auto rank = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(4 * b.blocks256), dim3(64 * kRankWaves), 0, s, b.jobs, seg, b.off256, rec4,
+                         b.tiles, b.v0);
+    };
+    if (b.max_items <= 4096)
+      rank(k_depth_rank<4096>);
+    else
+      rank(k_depth_rank<kRankItems>);
+  } else if (b.max_items <= 8 * kSortThreads) {
     auto small = [&](auto kernel) {
       hipLaunchKernelGGL(kernel, dim3(b.tab.R), block, 0, s, b.jobs, seg, rec4, b.tiles, b.v0);
     };
     if (b.max_items <= 4 * kSortThreads)
       small(k_depth_sort_small<11, 4>);
-    else if (b.max_items <= 8 * kSortThreads)
-      small(k_depth_sort_small<11, 8>);
     else
-      small(k_depth_sort_small<8, 16>);
+      small(k_depth_sort_small<11, 8>);
   } else if (b.max_items <= kWideItems) {
     hipLaunchKernelGGL(k_depth_prep<11>, grid, block, 0, s, b.jobs, seg, rec4, b.tiles, b.k0, b.v0, b.hist, b.blk_cnt);
     hipLaunchKernelGGL((k_seg_scatter<11, true, false>), grid, block, 0, s, (const uint32_t*)b.k0,

@@ -12,7 +12,8 @@ constexpr int kTile = LS_TILE;
 constexpr int kBlock = 256;         // one 16x16 tile per block, 4 wave64
 constexpr int kSortThreads = 1024;  // radix sort block
 constexpr int kSortKeys = 4096;     // keys per radix sort block
-constexpr int kSmallSort = 16 * kSortThreads;  // items that one block sorts by depth on its own
+constexpr int kRankItems = 16384;              // items up to which a render's depths are ranked by comparison,
+constexpr int64_t kRankPairs = 1 << 26;        // if all renders of a batch make up to so many pairs
 constexpr int kWideItems = 16 * kSortKeys;     // items up to which a larger render's depth sort takes 11-bit digits
 constexpr int kWindowTiles = 4096;  // most tiles of a binning window
 constexpr int kGradStride = 16;     // floats per item in the accumulator: a 64-byte line each

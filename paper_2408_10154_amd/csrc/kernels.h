@@ -89,7 +89,9 @@ struct BinLaunch {
   const int64_t* item_off;
   const int32_t* tile_off;
   BinTables tab;
-  int T, max_items, sort_blocks, units;
+  int T, max_items, sort_blocks, units, blocks256;
+  const int32_t* off256;        // [R + 1]: first block of 256 items of each render; blocks256 of them
+  int64_t rank_pairs;           // sum over the renders of the squared item count
   const float* rec;
   const int32_t* radius;
   const int32_t* tiles;

@@ -1,7 +1,9 @@
-"""Tile binning at the edges of its paths: renders that one block sorts
-(4,096, 8,192 and 16,384 items) and the first larger one, chunk ends of the
+"""Tile binning at the edges of its paths: renders whose depths are ranked by
+comparison (4,096 and 16,384 items) and the first larger one, batches that one
+block per render sorts (4,096 and 8,192 items), chunk ends of the
 distribution, images of one and of several tile windows or with most tiles
-empty, and batches with empty and fully culled renders.  The lists are whole numbers: equality."""
+empty, and batches with empty and fully culled renders.  The lists are whole
+numbers: equality."""
 
 import numpy as np
 import pytest
@@ -39,6 +41,8 @@ def _records(rng, n, cam, culled):
     ([900], WIDE, 0.1), ([9000], WIDE, 0.1), ([700], TALL, 0.1), ([17000], TALL, 0.9),
     ([512, 0, 513, 40], SMALL, 0.0), ([16385, 0, 4096, 1], SMALL, 0.2), ([600, 30], TALL, 0.2),
     ([300], HUGE, 0.0), ([300], LARGE, 0.0), ([140000, 130000], SMALL, 0.97),
+    ([4000] * 5, SMALL, 0.3), ([6000, 8192, 100], SMALL, 0.0), ([6000, 8193, 100], SMALL, 0.0),
+    ([4096] * 4, SMALL, 0.5),
 ])
 def test_lists_equal_the_oracle(gpu, sizes, image, culled):
     from paper_2408_10154_amd.render import GaussianSet, RenderBatch
