@@ -526,6 +526,7 @@ ls_status ls_bin_sort(const ls_batch* b, const ls_projected* p, const ls_bins* b
   bl.T = b->T;
   bl.max_items = b->max_items;
   bl.rank_pairs = b->rank_pairs;
+  bl.counts = b->bincnt_off[b->R];
   bl.off256 = b->blk_off_d;
   bl.blocks256 = b->nblk_items;
   bl.sort_blocks = b->sort_blocks;

@@ -18,7 +18,7 @@
 // pair sort it replaces moved each instance three times in 8 launches (all of
 // binning: 200k items, 1200 x 680, 143 -> 98 us and 22 launches -> 11; eight
 // renders of 150k items, 640 x 480, 157 -> 118 us; 23k items, 317 x 211, 90 ->
-// 63 us and 9 launches; 4,096 items, 160 x 120, 81 -> 32 us and 4 launches).
+// 60 us and 8 launches; 4,096 items, 160 x 120, 81 -> 29 us and 3 launches).
 // What is left is bound by latency: launches of 3 to 10 us on tens to hundreds
 // of blocks, each a chain of dependent loads.
 #include "common.h"
@@ -819,10 +819,9 @@ __global__ __launch_bounds__(1024) void k_group_starts(uint64_t* __restrict__ gr
 // The lists' table, a share of the tiles per block: every tile's [start, end)
 // (clamped to the capacity; empty tiles 0, 0) and tile_of, eight tiles to a
 // wave, in whole lines; and count = {min(I, cap), I > cap, min(I, INT32_MAX),
-// 0}.  group: where a group of 64 tiles starts.
-template <class Group>
-__device__ __forceinline__ void list_table(const Group& group, uint64_t all, const uint32_t* __restrict__ total,
-                                           const uint32_t* __restrict__ before, int T, uint64_t cap,
+// 0}.  start, total: where a tile's list starts and its length.
+template <class Start, class Total>
+__device__ __forceinline__ void list_table(const Start& start, const Total& total, uint64_t all, int T, uint64_t cap,
                                            uint32_t* __restrict__ tile_of, int32_t* __restrict__ range,
                                            int32_t* __restrict__ count) {
   const int lane = threadIdx.x & 63;
@@ -830,8 +829,8 @@ __device__ __forceinline__ void list_table(const Group& group, uint64_t all, con
     const int tile = 8 * k + lane;
     uint64_t a = 0, e = 0;
     if (lane < 8 && tile < T) {
-      a = group(tile >> 6) + before[tile];
-      e = min(a + total[tile], cap);
+      a = start(tile);
+      e = min(a + total(tile), cap);
       a = min(a, cap);
       range[2 * tile] = a < e ? (int32_t)a : 0;
       range[2 * tile + 1] = a < e ? (int32_t)e : 0;
@@ -883,9 +882,62 @@ __device__ __forceinline__ uint64_t group_starts(const uint64_t* __restrict__ gr
 //
 // kFew: up to kFewGroups groups of 64 tiles, whose starts every block works out
 // for itself from the groups' sums; a launch for it and for the table took 3 to
-// 5 us.  More come from k_group_starts.
+// 5 us.  More come from k_group_starts (kMany).  kOwn: a single render of up to
+// kPlaceThreads tiles whose counts, up to kOwnCounts, every block scans for
+// itself in two rounds of loads at most (4,096 items at 160 x 120, 2,800 counts:
+// 4.2 us for k_chunk_scan against 1.1 us here; 23k items at 317 x 211, 22k
+// counts: 5.0 against 2.1 us).
 constexpr int kFewGroups = kPlaceThreads;
-template <bool kFew>
+constexpr int kOwnCounts = 32768;
+enum PlaceStarts { kMany, kFew, kOwn };
+
+// kOwn: the tiles' totals over all chunks and over those before `chunk`, and
+// the tiles' starts, by the whole block; returns the sum of the totals.
+struct OwnScan {
+  uint32_t total[kPlaceThreads], before[kPlaceThreads], start[kPlaceThreads];
+};
+__device__ __forceinline__ uint32_t own_scan(OwnScan& o, const uint32_t* __restrict__ cnt, int T, int rows, int chunk) {
+  __shared__ uint32_t wsum[kPlaceThreads / 64];
+  const int parts = kPlaceThreads / T, part = threadIdx.x / T, tile = threadIdx.x - part * T;
+  uint32_t all = 0, pre = 0;
+  if (part < parts)
+    for (int r0 = part; r0 < rows; r0 += 16 * parts) {
+      uint32_t v[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) v[k] = r0 + k * parts < rows ? cnt[(r0 + k * parts) * T + tile] : 0u;
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        all += v[k];
+        pre += r0 + k * parts < chunk ? v[k] : 0u;
+      }
+    }
+  o.total[threadIdx.x] = all;
+  o.before[threadIdx.x] = pre;
+  __syncthreads();
+  all = pre = 0u;
+  if ((int)threadIdx.x < T)
+    for (int k = 0; k < parts; ++k) {
+      all += o.total[k * T + threadIdx.x];
+      pre += o.before[k * T + threadIdx.x];
+    }
+  const int w = threadIdx.x >> 6;
+  const uint32_t x = wave_incl_sum(all);
+  if ((threadIdx.x & 63) == 63) wsum[w] = x;
+  __syncthreads();
+  uint32_t run = x - all, sum = 0;
+#pragma unroll
+  for (int k = 0; k < kPlaceThreads / 64; ++k) {
+    run += k < w ? wsum[k] : 0u;
+    sum += wsum[k];
+  }
+  o.total[threadIdx.x] = all;
+  o.before[threadIdx.x] = pre;
+  o.start[threadIdx.x] = run;
+  __syncthreads();
+  return sum;
+}
+
+template <PlaceStarts kStarts>
 __global__ __launch_bounds__(kPlaceThreads) void k_place(const JobDev* __restrict__ jobs, BinTables t, int units,
                                                          const int32_t* __restrict__ kept,
                                                          const uint32_t* __restrict__ order,
@@ -898,16 +950,31 @@ __global__ __launch_bounds__(kPlaceThreads) void k_place(const JobDev* __restric
                                                          uint32_t* __restrict__ tile_of, int32_t* __restrict__ item,
                                                          int32_t* __restrict__ range, int32_t* __restrict__ count) {
   __shared__ PlaceLds L;
-  __shared__ uint64_t starts[kFew ? kFewGroups : 1];
+  __shared__ uint64_t starts[kStarts == kFew ? kFewGroups : 1];
+  __shared__ OwnScan own[1];
   const int ngroup = (T + 63) / 64;
-  const uint64_t all = kFew ? group_starts(group, ngroup, starts) : group[ngroup];
-  auto start_of = [&](int g) { return kFew ? starts[g] : group[g]; };
-  // (first: at the end it is every block's tail, 29 -> 36 us at 200k items)
-  list_table(start_of, all, total, before, T, cap, tile_of, range, count);
-  const int unit = place_unit(t, jobs, kept, units);
-  if (unit >= units) return;
   PlaceCtx c;
-  if (!place_ctx(jobs, t, kept, unit, c)) return;  // uniform
+  bool work;  // uniform
+  auto find_work = [&] {
+    const int unit = place_unit(t, jobs, kept, units);
+    work = unit < units && place_ctx(jobs, t, kept, unit, c);
+  };
+  uint64_t all;
+  if (kStarts == kOwn) {
+    find_work();
+    all = own_scan(own[0], cnt, T, chunks_of(kept[0], t.chunk, t.ramp), work ? c.chunk : 0);
+  } else {
+    all = kStarts == kFew ? group_starts(group, ngroup, starts) : group[ngroup];
+  }
+  auto start_of = [&](int tile) {
+    return kStarts == kOwn ? (uint64_t)own[0].start[tile]
+                           : (kStarts == kFew ? starts[tile >> 6] : group[tile >> 6]) + before[tile];
+  };
+  auto total_of = [&](int tile) { return kStarts == kOwn ? own[0].total[tile] : total[tile]; };
+  // (first: at the end it is every block's tail, 29 -> 36 us at 200k items)
+  list_table(start_of, total_of, all, T, cap, tile_of, range, count);
+  if (kStarts != kOwn) find_work();
+  if (!work) return;
   const JobDev& J = jobs[c.r];
   const int nt = c.w * c.h;
   const uint32_t* __restrict__ ord = order + J.item_off + c.first;
@@ -917,7 +984,8 @@ __global__ __launch_bounds__(kPlaceThreads) void k_place(const JobDev* __restric
   for (int j = 0; j < kPlaceTiles; ++j) {
     const int k = j * kPlaceThreads + threadIdx.x, y = k / c.w, rt = (c.y0 + y) * J.TX + c.x0 + (k - y * c.w);
     const int tile = J.tile_off + rt;
-    place[j] = k < nt ? (uint32_t)min(start_of(tile >> 6) + before[tile], (uint64_t)cap) + row[rt] : 0u;
+    const uint32_t earlier = k >= nt ? 0u : kStarts == kOwn ? own[0].before[tile] : row[rt];
+    place[j] = k < nt ? (uint32_t)min(start_of(tile), (uint64_t)cap) + earlier : 0u;
   }
   for (int i0 = 0; i0 < c.n; i0 += kPlaceItems) {
     const int n = min(c.n - i0, kPlaceItems);
@@ -1020,8 +1088,10 @@ void launch_bin_sort(const BinLaunch& b, hipStream_t s) {
     hipLaunchKernelGGL(k_chunk_count, work, dim3(kPlaceThreads), 0, s, b.jobs, b.tab, b.units,
                        (const int32_t*)b.kept, order, rec4, b.radius, b.cnt);
   const int ngroup = (b.T + 63) / 64;
-  hipLaunchKernelGGL(k_chunk_scan, dim3(ngroup), dim3(1024), 0, s, b.jobs, b.tab, b.tile_off, b.T,
-                     (const int32_t*)b.kept, b.cnt, b.tile_total, b.tile_before, b.groups);
+  const bool own = b.tab.R == 1 && b.T <= kPlaceThreads && b.counts <= kOwnCounts;
+  if (!own)
+    hipLaunchKernelGGL(k_chunk_scan, dim3(ngroup), dim3(1024), 0, s, b.jobs, b.tab, b.tile_off, b.T,
+                       (const int32_t*)b.kept, b.cnt, b.tile_total, b.tile_before, b.groups);
   // at least a block per 1,024 tiles for the table
   const dim3 place(std::max(work.x, 8u * ((unsigned)b.T / 8192u + 1u)));
   auto launch = [&](auto kernel) {
@@ -1030,11 +1100,13 @@ void launch_bin_sort(const BinLaunch& b, hipStream_t s) {
                        (const uint32_t*)b.tile_before, (const uint64_t*)b.groups, b.T, (uint32_t)b.cap, b.tile_of,
                        b.item, b.range, b.count);
   };
-  if (ngroup <= kFewGroups) {
-    launch(k_place<true>);
+  if (own) {
+    launch(k_place<kOwn>);
+  } else if (ngroup <= kFewGroups) {
+    launch(k_place<kFew>);
   } else {
     hipLaunchKernelGGL(k_group_starts, dim3(1), dim3(1024), 0, s, b.groups, ngroup, b.groups + ngroup);
-    launch(k_place<false>);
+    launch(k_place<kMany>);
   }
 }
 

@@ -92,6 +92,7 @@ struct BinLaunch {
   int T, max_items, sort_blocks, units, blocks256;
   const int32_t* off256;        // [R + 1]: first block of 256 items of each render; blocks256 of them
   int64_t rank_pairs;           // sum over the renders of the squared item count
+  int64_t counts;               // words of the count matrices
   const float* rec;
   const int32_t* radius;
   const int32_t* tiles;

@@ -17,6 +17,7 @@ pytestmark = pytest.mark.gpu
 
 SMALL, WIDE, TALL = (100, 70), (4200, 40), (1100, 1080)  # 7 x 5, 263 x 3 and 69 x 68 tiles
 HUGE, LARGE = (4112, 4100), (4096, 4096)  # 257 x 257 tiles and the 65,536 up to which one launch is saved
+SQUARE, OVER = (512, 512), (520, 512)  # the 1,024 tiles up to which another one is, and 33 x 32
 
 
 def _records(rng, n, cam, culled):
@@ -42,7 +43,7 @@ def _records(rng, n, cam, culled):
     ([512, 0, 513, 40], SMALL, 0.0), ([16385, 0, 4096, 1], SMALL, 0.2), ([600, 30], TALL, 0.2),
     ([300], HUGE, 0.0), ([300], LARGE, 0.0), ([140000, 130000], SMALL, 0.97),
     ([4000] * 5, SMALL, 0.3), ([6000, 8192, 100], SMALL, 0.0), ([6000, 8193, 100], SMALL, 0.0),
-    ([4096] * 4, SMALL, 0.5),
+    ([4096] * 4, SMALL, 0.5), ([2000], SQUARE, 0.0), ([2000], OVER, 0.0),
 ])
 def test_lists_equal_the_oracle(gpu, sizes, image, culled):
     from paper_2408_10154_amd.render import GaussianSet, RenderBatch
