@@ -206,7 +206,7 @@ static BatchTables batch_tables(const ls_batch* b) {
   t.binwork_off = take(4 * R1);
   t.bincnt_off = take(8 * R1);
   t.loss_part = take(8 * (size_t)std::max(b->nblk_pix, 1));
-  t.map_part = take(4 * (3 * (size_t)b->nblk_ssim + b->R));
+  t.map_part = take(4 * (3 * (size_t)b->nblk_ssim + (size_t)kValidParts * b->R));
   t.grads = take(sizeof(GradDev) * b->R);
   t.sel = take(4 * (size_t)ls::sel_words(b->R));
   t.median = take(4 * (size_t)b->R);
@@ -777,9 +777,9 @@ ls_status ls_loss_mapping(const ls_batch* b, const ls_image* pred, const float* 
     return fail(LS_ERR_INVALID, "mapping-loss weights must be finite, lambda_ssim in [0, 1]");
   ls_status st;
   if ((st = ensure_device(b))) return st;
-  launch_loss_mapping(b->jobs_d, b->pblk_off_d, b->nblk_pix, b->sblk_off_d, b->nblk_ssim, b->R, pred->rgb,
-                      pred->depth, tgt_rgb, tgt_depth, prm->lambda_ssim, prm->lambda_color, prm->lambda_depth,
-                      grad_rgb, grad_depth, b->loss_part_d, b->map_part_d, loss, grad_scale, s);
+  launch_loss_mapping(b->jobs_d, b->sblk_off_d, b->nblk_ssim, b->R, pred->rgb, pred->depth, tgt_rgb, tgt_depth,
+                      prm->lambda_ssim, prm->lambda_color, prm->lambda_depth, grad_rgb, grad_depth, b->map_part_d,
+                      loss, grad_scale, s);
   return hip_check("ls_loss_mapping");
 }
 

@@ -37,7 +37,7 @@ struct ls_batch {
   int32_t* binwork_off_d = nullptr;
   int64_t* bincnt_off_d = nullptr;
   float* loss_part_d = nullptr;
-  float* map_part_d = nullptr;   // mapping loss: 3 floats per SSIM block, then 1/|Omega| per render
+  float* map_part_d = nullptr;   // mapping loss: 3 floats per SSIM block, then parts of |Omega| per render
   uint32_t* sel_d = nullptr;     // median selection workspace (ls::sel_words(R)), kept zeroed
   float* median_d = nullptr;     // [R] median depth error of the last tracking loss
   GradDev* grads_d = nullptr;

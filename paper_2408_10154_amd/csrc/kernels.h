@@ -335,14 +335,13 @@ constexpr int kSelHistBins = 2048;
 inline int64_t sel_words(int R) { return (int64_t)R * (8 + 3 * kSelHistBins); }
 
 // Mapping loss (mapping_loss.hip).  SSIM blocks of a W x H render (3 colour
-// channels x 32 x 32 tiles); cnt_part: one float per 1024-pixel block;
-// map_part: 3 floats per SSIM block + R.
+// channels x 32 x 32 tiles); map_part: 3 floats per SSIM block + kValidParts per render.
 int ssim_blocks(int W, int H);
-void launch_loss_mapping(const JobDev* jobs, const int32_t* pblk_off_d, int npblk, const int32_t* sblk_off_d,
-                         int nsblk, int R, const float* pred_rgb, const float* pred_depth, const float* tgt_rgb,
-                         const float* tgt_depth, float lambda_ssim, float lambda_color, float lambda_depth,
-                         float* g_rgb, float* g_depth, float* cnt_part, float* map_part, float* loss, float* scale,
-                         hipStream_t s);
+constexpr int kValidParts = 64;
+void launch_loss_mapping(const JobDev* jobs, const int32_t* sblk_off_d, int nsblk, int R, const float* pred_rgb,
+                         const float* pred_depth, const float* tgt_rgb, const float* tgt_depth, float lambda_ssim,
+                         float lambda_color, float lambda_depth, float* g_rgb, float* g_depth, float* map_part,
+                         float* loss, float* scale, hipStream_t s);
 // Per render 1 / |Omega| (pixels with a target depth; 0 when none) into inv
 // [R]; cnt_part = npblk floats.  Targets as for L1Targets.
 void launch_valid_inv(const JobDev* jobs, const int32_t* pblk_off_d, int npblk, int R, const float* tgt_depth,

@@ -99,6 +99,45 @@ __global__ __launch_bounds__(256) void k_valid_inv(const int32_t* __restrict__ p
   if (threadIdx.x == 0) inv[r] = c > 0.f ? 1.f / c : 0.f;
 }
 
+// The same in kValidParts parts per render, for a kernel
+// whose waves add them up for themselves (valid_inv); a launch for that took 2
+// to 5 us.
+constexpr int kValidThreads = 1024;
+__global__ __launch_bounds__(kValidThreads) void k_valid_parts(const JobDev* __restrict__ jobs,
+                                                               const float* __restrict__ tgt_depth,
+                                                               float* __restrict__ part) {
+  constexpr int kAhead = 8;
+  const int b = blockIdx.x & (kValidParts - 1);
+  const JobDev& J = jobs[blockIdx.x / kValidParts];
+  const int64_t hw = (int64_t)J.W * J.H, step = (int64_t)kValidParts * kValidThreads;
+  const float* __restrict__ td = tgt_depth ? tgt_depth + J.pix_off : J.tgt_depth;
+  int cnt = 0;
+  for (int64_t p0 = (int64_t)b * kValidThreads + threadIdx.x; p0 < hw; p0 += kAhead * step) {
+    float v[kAhead];
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) v[k] = p0 + k * step < hw ? td[p0 + k * step] : 0.f;
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) cnt += v[k] > 0.f ? 1 : 0;
+  }
+  const float sum = wave_sum((float)cnt);
+  __shared__ float ws[kValidThreads / 64];
+  if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = sum;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    float all = 0.f;
+#pragma unroll
+    for (int k = 0; k < kValidThreads / 64; ++k) all += ws[k];
+    part[blockIdx.x] = all;
+  }
+}
+
+// 1 / |Omega| of render r (0 when no pixel has a target depth), in every lane.
+__device__ __forceinline__ float valid_inv(const float* __restrict__ part, int r) {
+  static_assert(kValidParts == 64, "a part per lane");
+  const float c = wave_sum(part[r * kValidParts + (threadIdx.x & 63)]);
+  return c > 0.f ? 1.f / c : 0.f;
+}
+
 // One block per (render, colour channel, 32 x 32 output tile).  The block
 // stages the 52 x 52 input region of both images in LDS, filters the five
 // windowed moments separably (rows, then columns) over the 42 x 42 region
@@ -122,7 +161,7 @@ __global__ __launch_bounds__(256) void k_loss_ssim(const JobDev* __restrict__ jo
                                                    const float* __restrict__ pred_depth,
                                                    const float* __restrict__ tgt_rgb,
                                                    const float* __restrict__ tgt_depth,
-                                                   const float* __restrict__ inv_valid, SsimWindow win,
+                                                   const float* __restrict__ valid, SsimWindow win,
                                                    float lambda_ssim, float lambda_color, float lambda_depth,
                                                    float* __restrict__ g_rgb, float* __restrict__ g_depth,
                                                    float* __restrict__ part) {
@@ -137,6 +176,7 @@ __global__ __launch_bounds__(256) void k_loss_ssim(const JobDev* __restrict__ jo
   const int ch = local / (tx * ty);
   const int t = local - ch * tx * ty;
   const int x0 = (t % tx) * kSsimT, y0 = (t / tx) * kSsimT;
+  const float inv = valid_inv(valid, r);
   const int64_t hw = (int64_t)W * H;
   const float* __restrict__ X = pred_rgb + 3 * J.pix_off + ch * hw;
   const float* __restrict__ Y = (tgt_rgb ? tgt_rgb + 3 * J.pix_off : J.tgt_rgb) + ch * hw;
@@ -340,7 +380,6 @@ __global__ __launch_bounds__(256) void k_loss_ssim(const JobDev* __restrict__ jo
 
   // column pass onto the tile (a strip of kOutStrip rows of one column per
   // thread) and the weighted gradients
-  const float inv = inv_valid[r];
   const float k_l1 = lambda_color * (1.f - lambda_ssim) * inv;
   const float k_ss = -lambda_color * lambda_ssim / (3.f * (float)hw);
   const float k_d = lambda_depth * inv;
@@ -406,25 +445,50 @@ __global__ __launch_bounds__(256) void k_loss_ssim(const JobDev* __restrict__ jo
 
 // One block per render: ordered sums of the block partials and the loss
 //   lc ((1 - ls) L1_rgb + ls (1 - mean SSIM)) + ld L1_depth.
-__global__ __launch_bounds__(256) void k_map_reduce(const JobDev* __restrict__ jobs,
-                                                    const int32_t* __restrict__ sblk_off, int R,
-                                                    const float* __restrict__ part,
-                                                    const float* __restrict__ inv_valid, float lambda_ssim,
-                                                    float lambda_color, float lambda_depth, float* __restrict__ loss,
-                                                    float* __restrict__ scale) {
-  __shared__ float ws[3][4];
-  const int r = blockIdx.x;
+constexpr int kMapReduceThreads = 1024;
+__global__ __launch_bounds__(kMapReduceThreads) void k_map_reduce(const JobDev* __restrict__ jobs,
+                                                                  const int32_t* __restrict__ sblk_off, int R,
+                                                                  const float* __restrict__ part,
+                                                                  const float* __restrict__ valid, float lambda_ssim,
+                                                                  float lambda_color, float lambda_depth,
+                                                                  float* __restrict__ loss,
+                                                                  float* __restrict__ scale) {
+  constexpr int kWaves = kMapReduceThreads / 64, kAhead = 4;
+  __shared__ float ws[3][kWaves];
+  const int r = blockIdx.x, end = sblk_off[r + 1];
+  const float inv = valid_inv(valid, r);
   float s = 0.f, c = 0.f, d = 0.f;
-  for (int b = sblk_off[r] + threadIdx.x; b < sblk_off[r + 1]; b += kBlock) {
-    s += part[3 * (int64_t)b];
-    c += part[3 * (int64_t)b + 1];
-    d += part[3 * (int64_t)b + 2];
+  for (int b = sblk_off[r] + threadIdx.x; b < end; b += kAhead * kMapReduceThreads) {
+    float v[kAhead][3];
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k)
+#pragma unroll
+      for (int q = 0; q < 3; ++q)
+        v[k][q] = b + k * kMapReduceThreads < end ? part[3 * (int64_t)(b + k * kMapReduceThreads) + q] : 0.f;
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) {
+      s += v[k][0];
+      c += v[k][1];
+      d += v[k][2];
+    }
   }
-  s = block_sum(s, ws[0]);
-  c = block_sum(c, ws[1]);
-  d = block_sum(d, ws[2]);
+  s = wave_sum(s);
+  c = wave_sum(c);
+  d = wave_sum(d);
+  if ((threadIdx.x & 63) == 0) {
+    ws[0][threadIdx.x >> 6] = s;
+    ws[1][threadIdx.x >> 6] = c;
+    ws[2][threadIdx.x >> 6] = d;
+  }
+  __syncthreads();
   if (threadIdx.x == 0) {
-    const float inv = inv_valid[r];
+    s = c = d = 0.f;
+#pragma unroll
+    for (int k = 0; k < kWaves; ++k) {
+      s += ws[0][k];
+      c += ws[1][k];
+      d += ws[2][k];
+    }
     const float n = 3.f * (float)jobs[r].W * (float)jobs[r].H;
     if (loss)
       loss[r] = lambda_color * ((1.f - lambda_ssim) * c * inv + lambda_ssim * (1.f - s / n)) + lambda_depth * d * inv;
@@ -435,10 +499,11 @@ __global__ __launch_bounds__(256) void k_map_reduce(const JobDev* __restrict__ j
 // Isotropic regulariser (Eq. 5): per Gaussian sum_j |s_j - mean(s)| with
 // s = exp(log_scale); its gradient coef * s_j (sign(d_j) - mean_i sign(d_i))
 // is added to grad; one partial sum per block.
-__global__ __launch_bounds__(256) void k_isotropic(const float* __restrict__ log_scale, int64_t n, float coef,
+template <int kThreads>
+__global__ __launch_bounds__(kThreads) void k_isotropic(const float* __restrict__ log_scale, int64_t n, float coef,
                                                    float* __restrict__ grad, float* __restrict__ part) {
   float acc = 0.f;
-  for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) {
+  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads) {
     const float s0 = expf(log_scale[i]), s1 = expf(log_scale[n + i]), s2 = expf(log_scale[2 * n + i]);
     const float m = (s0 + s1 + s2) * (1.f / 3.f);
     const float d0 = s0 - m, d1 = s1 - m, d2 = s2 - m;
@@ -454,10 +519,15 @@ __global__ __launch_bounds__(256) void k_isotropic(const float* __restrict__ log
     }
   }
   acc = wave_sum(acc);
-  __shared__ float ws[4];
+  __shared__ float ws[kThreads / 64];
   if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = acc;
   __syncthreads();
-  if (threadIdx.x == 0) part[blockIdx.x] = (ws[0] + ws[1]) + (ws[2] + ws[3]);
+  if (threadIdx.x == 0) {
+    float sum = 0.f;
+#pragma unroll
+    for (int k = 0; k < kThreads / 64; ++k) sum += ws[k];
+    part[blockIdx.x] = sum;
+  }
 }
 
 __global__ __launch_bounds__(256) void k_isotropic_reduce(const float* __restrict__ part, int nblk, float coef,
@@ -492,30 +562,33 @@ void launch_valid_inv(const JobDev* jobs, const int32_t* pblk_off_d, int npblk, 
 
 int ssim_blocks(int W, int H) { return 3 * ((W + kSsimT - 1) / kSsimT) * ((H + kSsimT - 1) / kSsimT); }
 
-void launch_loss_mapping(const JobDev* jobs, const int32_t* pblk_off_d, int npblk, const int32_t* sblk_off_d,
-                         int nsblk, int R, const float* pred_rgb, const float* pred_depth, const float* tgt_rgb,
-                         const float* tgt_depth, float lambda_ssim, float lambda_color, float lambda_depth,
-                         float* g_rgb, float* g_depth, float* cnt_part, float* map_part, float* loss, float* scale,
-                         hipStream_t s) {
-  float* inv = map_part + 3 * (int64_t)nsblk;
-  if (npblk > 0)
-    hipLaunchKernelGGL(k_valid_count, dim3(npblk), dim3(256), 0, s, jobs, pblk_off_d, R, tgt_depth, cnt_part);
-  hipLaunchKernelGGL(k_valid_inv, dim3(R), dim3(kBlock), 0, s, pblk_off_d, R, (const float*)cnt_part, inv);
+void launch_loss_mapping(const JobDev* jobs, const int32_t* sblk_off_d, int nsblk, int R, const float* pred_rgb,
+                         const float* pred_depth, const float* tgt_rgb, const float* tgt_depth, float lambda_ssim,
+                         float lambda_color, float lambda_depth, float* g_rgb, float* g_depth, float* map_part,
+                         float* loss, float* scale, hipStream_t s) {
+  float* valid = map_part + 3 * (int64_t)nsblk;
+  hipLaunchKernelGGL(k_valid_parts, dim3(kValidParts * R), dim3(kValidThreads), 0, s, jobs, tgt_depth, valid);
   if (nsblk > 0) {
     const int grid = 8 * ((nsblk + 7) / 8);
     hipLaunchKernelGGL(k_loss_ssim, dim3(grid), dim3(kBlock), 0, s, jobs, sblk_off_d, R, nsblk, pred_rgb, pred_depth,
-                       tgt_rgb, tgt_depth, (const float*)inv, ssim_window(), lambda_ssim, lambda_color, lambda_depth,
+                       tgt_rgb, tgt_depth, (const float*)valid, ssim_window(), lambda_ssim, lambda_color, lambda_depth,
                        g_rgb, g_depth, map_part);
   }
-  hipLaunchKernelGGL(k_map_reduce, dim3(R), dim3(kBlock), 0, s, jobs, sblk_off_d, R, (const float*)map_part,
-                     (const float*)inv, lambda_ssim, lambda_color, lambda_depth, loss, scale);
+  hipLaunchKernelGGL(k_map_reduce, dim3(R), dim3(kMapReduceThreads), 0, s, jobs, sblk_off_d, R, (const float*)map_part,
+                     (const float*)valid, lambda_ssim, lambda_color, lambda_depth, loss, scale);
 }
 
 void launch_loss_isotropic(const float* log_scale, int64_t n, float lambda_reg, float* loss, float* grad, float* part,
                            hipStream_t s) {
   const float coef = n > 0 ? lambda_reg / (float)n : 0.f;
-  const int nblk = (int)std::min<int64_t>(std::max<int64_t>((n + kBlock - 1) / kBlock, 1), kIsotropicBlocks);
-  hipLaunchKernelGGL(k_isotropic, dim3(nblk), dim3(kBlock), 0, s, log_scale, n, coef, grad, part);
+  // the work array holds 256 partials: past a block of 256 items each, larger
+  // blocks (200k items: 7.1 us with four rounds of 256, 4.9 us with one of 1,024)
+  const int per = n <= (int64_t)kIsotropicBlocks * kBlock ? kBlock : 1024;
+  const int nblk = (int)std::min<int64_t>(std::max<int64_t>((n + per - 1) / per, 1), kIsotropicBlocks);
+  if (per == kBlock)
+    hipLaunchKernelGGL(k_isotropic<kBlock>, dim3(nblk), dim3(kBlock), 0, s, log_scale, n, coef, grad, part);
+  else
+    hipLaunchKernelGGL(k_isotropic<1024>, dim3(nblk), dim3(1024), 0, s, log_scale, n, coef, grad, part);
   hipLaunchKernelGGL(k_isotropic_reduce, dim3(1), dim3(kBlock), 0, s, (const float*)part, nblk, coef, loss);
 }
 
