@@ -288,7 +288,8 @@ static ls_status batch_host(const ls_render_job* jobs, int32_t R, ls_batch** out
   // binning: radix sort blocks; then chunks of sorted items with their tile
   // windows and count matrices, at most about 4,096 chunks (half as many for
   // 16 renders of 150k and 120k items: lists 67 -> 101 us) and 16 M counts
-  // (64 MiB, 20 us to write and 40 us to scan; only large images reach it)
+  // (64 MiB: 14 us to write and 28 us to scan at the rate of a large copy; only
+  // large images reach it)
   b->bin_chunk = 512;
   b->bin_ramp = R == 1 || b->M / b->bin_chunk <= 512;
   const auto counts = [&] {

@@ -24,7 +24,6 @@
 #include "common.h"
 
 #include <algorithm>
-#include <cstdlib>
 
 #include "kernels.h"
 

@@ -509,7 +509,8 @@ __device__ __forceinline__ void wave_sync() {
 // sums; with ten (six) products a pixel and a reduction of as many values an
 // entry it was 67 (53).  VALU bound: 200k Gaussians at 1200x680, full, 218 ->
 // 120 us (with the atomics below); 97k at 640x480, pose only, 93 -> 60 us; 16
-// views of 640x480 of 150k/120k, pose only, 470 -> 366 us.
+// views of 640x480 of 150k/120k, pose only, 470 -> 366 us (115, 55 and 290 us
+// since the XCDs take turns, see xcd_turns).
 // (FP32 matrix products that contract the same rows with the pixel factors
 // cost more: twice the vector rate, but 10 of 32 result columns are of use,
 // and they do not overlap with the SIMD's vector instructions.)
@@ -720,9 +721,9 @@ __device__ __forceinline__ void band_loss(const L1Targets& l1, const BwdPixel& p
 // 64-byte line.  The atomics are limited by the requests (instruction x line)
 // they make, not by their values (200k Gaussians at 1200x680, 1.4 M (entry,
 // band) pairs: two requests per pair 183-216 us, one per pair 148 us at 40
-// bytes per item and 124 us at 64, none 116 us).  The projection backward
-// applies the factors that are the same for all pixels (conic, halves, 1 /
-// opacity) once per item.
+// bytes per item and 124 us at 64, none 116 us, before the XCDs took turns).  The
+// projection backward applies the factors that are the same for all pixels
+// (conic, halves, 1 / opacity) once per item.
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_composite_bwd(
     const JobDev* __restrict__ jobs, const int32_t* __restrict__ tile_off, int R, int T_total,
     const float4* __restrict__ rec, const int32_t* __restrict__ items, const int32_t* __restrict__ range,

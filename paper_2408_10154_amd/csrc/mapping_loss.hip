@@ -99,9 +99,8 @@ __global__ __launch_bounds__(256) void k_valid_inv(const int32_t* __restrict__ p
   if (threadIdx.x == 0) inv[r] = c > 0.f ? 1.f / c : 0.f;
 }
 
-// The same in kValidParts parts per render, for a kernel
-// whose waves add them up for themselves (valid_inv); a launch for that took 2
-// to 5 us.
+// The same in kValidParts parts per render, for a kernel whose waves add them up
+// for themselves (valid_inv); a launch for that took 2 to 5 us.
 constexpr int kValidThreads = 1024;
 __global__ __launch_bounds__(kValidThreads) void k_valid_parts(const JobDev* __restrict__ jobs,
                                                                const float* __restrict__ tgt_depth,

@@ -275,9 +275,10 @@ constexpr int kPoseSumThreads = 256;
 // Sum of the kPoseAcc-float rows part[first .. first + nb) over a block of
 // kPoseSumThreads threads in a fixed order: strided per-thread sums (each
 // row three 16-byte loads, four rows in flight per thread), wave sums, then
-// the four waves in order.  Thread 0 returns the totals.  (1,024 threads
-// instead of 256: 11.3 against 12.1 us over the 4,800 rows of each of 16
-// 640x480 views.)
+// the four waves in order.  Thread 0 returns the totals.  Bound by what one CU
+// fetches of rows that lie in all XCDs' L2s: over the 4,800 rows of each of 16
+// 640x480 views 11.6 us, with eight rows in flight 11.4 us, with 1,024 threads
+// 11.3 us.
 __device__ __forceinline__ void block_pose_sum(const float* __restrict__ part, int first, int nb,
                                                float (&acc)[kPoseAcc]) {
   static_assert(kPoseAcc == 12, "a row is three float4");
