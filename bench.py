@@ -56,7 +56,7 @@ if ROOT not in sys.path:
 # mix (per evaluated entry + per composited entry) is reported beside it.
 FWD_OPS_PER_FRAG, BWD_OPS_PER_FRAG = 20, 45
 FWD_EVAL, FWD_COMP = 14, 11
-BWD_EVAL, BWD_COMP = 14, 53
+BWD_EVAL, BWD_COMP = 14, 30
 # mapping-loss kernel, algorithmic work per pixel: HBM bytes (rendered and
 # target colour 24, rendered and target depth 8, colour and depth gradients
 # 16) and FP32 operations (separable 11-tap filtering of five moments and of
