@@ -6,11 +6,14 @@
 // of logit(o_thre) (sigmoid is increasing), so it needs no transcendental and
 // its decisions are reproducible: keep <=> logit >= tau (NaN is pruned).
 //
-// Three launches: per-tile keep counts, one block scanning the counts into
-// tile offsets (and the total), then the scatter, which re-derives each
-// item's rank within its tile from ballots and copies every component of the
-// kept items.  Rows of the outputs are `count` floats apart, so they come out
-// in the ls_gaussians layout for the new Gaussian count.
+// Per-tile keep counts, one block scanning the counts into tile offsets (and
+// the total), then the scatter, which re-derives each item's rank within its
+// tile from ballots and copies every component of the kept items; sets of up
+// to 262,144 items leave the scan to the scatter.  Rows of the outputs are
+// `count` floats apart, so they come out in the ls_gaussians layout for the new
+// Gaussian count.  Bound by launches below 100k items and by the rows' bytes
+// above (15 arrays, 42 rows, half kept: 200k 51 MB, 10.6 us at the rate of a
+// large copy, 16.8 in all; 1M 254 MB, 53 and 75 us).
 #include <algorithm>
 
 #include "kernels.h"
@@ -22,6 +25,18 @@ constexpr int kPruneThreads = 256;
 // submap-sized set still spreads over more blocks than the GPU has CUs.
 constexpr int kPruneSmall = 1 << 20;
 __host__ __device__ constexpr int prune_tile(int rounds) { return kPruneThreads * rounds; }
+// Up to kPruneOwn tiles every scatter block adds up the tile counts for itself
+// and the scan is left out (15 arrays, 42 rows: 20k items 13.1 -> 11.2 us,
+// 200k 23.2 -> 22.0; at 2,700 tiles the blocks read 30 MB of counts: 44 -> 47,
+// so larger sets keep it).  The arrays are then dealt to as many blocks per
+// tile as the chip holds at once (8 blocks on each of 256 CUs), two to five:
+// a wave's rows are a chain of loads and stores.  2k items 11.1 -> 6.5 us, 20k
+// 11.2 -> 6.7, 100k 15.0 -> 10.4 (five parts), 200k 22.0 -> 16.8 (two; three
+// 20.3, five 18.6), 262k 22.5 -> 18.2 (two; five 22.5).
+constexpr int kPruneOwn = 1024;
+static int prune_parts(int tiles, int narrays) {
+  return std::max(1, std::min(narrays, std::min(5, std::max(2, 2048 / tiles))));
+}
 
 __device__ __forceinline__ bool prune_keep(float w, float tau) { return w >= tau; }
 
@@ -42,7 +57,8 @@ __global__ __launch_bounds__(kPruneThreads) void k_prune_count(const float* __re
   if (threadIdx.x == 0) tile_count[blockIdx.x] = (ws[0] + ws[1]) + (ws[2] + ws[3]);
 }
 
-// One block: exclusive scan of the tile counts into offsets, total to *count.
+// One block: exclusive scan of the tile counts into offsets, total to *count
+// (sets of more than kPruneOwn tiles).
 __global__ __launch_bounds__(1024) void k_prune_scan(const int32_t* __restrict__ tile_count, int ntiles,
                                                      int32_t* __restrict__ tile_off, int32_t* __restrict__ count) {
   __shared__ int32_t wsum[16];
@@ -67,12 +83,15 @@ __global__ __launch_bounds__(1024) void k_prune_scan(const int32_t* __restrict__
   if (threadIdx.x == 1023) *count = run;
 }
 
-template <int kPruneRounds>
+// kOwn: tile_off holds the tiles' counts, *count is written here, and the
+// arrays are dealt to gridDim.y blocks.
+template <int kPruneRounds, bool kOwn>
 __global__ __launch_bounds__(kPruneThreads) void k_prune_scatter(const float* __restrict__ logit, int n, float tau,
                                                                  const int32_t* __restrict__ tile_off,
-                                                                 const int32_t* __restrict__ count, PruneArrays arr,
+                                                                 int32_t* __restrict__ count, PruneArrays arr,
                                                                  int32_t* __restrict__ kept) {
   __shared__ int32_t wcnt[kPruneRounds][kPruneThreads / 64];
+  __shared__ int2 wown[kPruneThreads / 64];
   const int64_t base = (int64_t)blockIdx.x * prune_tile(kPruneRounds);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
@@ -86,20 +105,35 @@ __global__ __launch_bounds__(kPruneThreads) void k_prune_scatter(const float* __
     rank[r] = __popcll(m & below);
     if (lane == 0) wcnt[r][w] = __popcll(m);
   }
+  if (kOwn) {
+    int2 s = make_int2(0, 0);  // kept in the tiles before this one, and in all
+    for (int i = threadIdx.x; i < (int)gridDim.x; i += kPruneThreads) {
+      const int c = tile_off[i];
+      s.x += i < (int)blockIdx.x ? c : 0;
+      s.y += c;
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+      s.x += __shfl_xor(s.x, off, 64);
+      s.y += __shfl_xor(s.y, off, 64);
+    }
+    if (lane == 0) wown[w] = s;
+  }
   __syncthreads();
-  const int64_t stride = count[0];
+  const int total = kOwn ? (wown[0].y + wown[1].y) + (wown[2].y + wown[3].y) : count[0];
+  if (kOwn && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *count = total;
+  const int64_t stride = total;
   int64_t pos[kPruneRounds];
-  int run = tile_off[blockIdx.x];
+  int run = kOwn ? (wown[0].x + wown[1].x) + (wown[2].x + wown[3].x) : tile_off[blockIdx.x];
 #pragma unroll
   for (int r = 0; r < kPruneRounds; ++r) {
     int before = run;
     for (int k = 0; k < w; ++k) before += wcnt[r][k];
     pos[r] = before + rank[r];
-    if (keep[r]) kept[pos[r]] = (int32_t)(base + r * kPruneThreads + threadIdx.x);
+    if (keep[r] && blockIdx.y == 0) kept[pos[r]] = (int32_t)(base + r * kPruneThreads + threadIdx.x);
     run += (wcnt[r][0] + wcnt[r][1]) + (wcnt[r][2] + wcnt[r][3]);
   }
   // one row at a time: the four rounds' loads are issued before their stores
-  for (int a = 0; a < kPruneArrays; ++a) {
+  for (int a = blockIdx.y; a < kPruneArrays; a += gridDim.y) {
     if (a >= arr.count) break;  // uniform
     const float* __restrict__ src = arr.src[a];
     float* __restrict__ dst = arr.dst[a];
@@ -129,10 +163,15 @@ static void launch_prune_rounds(const float* logit, int n, float tau, const Prun
   int32_t* tile_count = static_cast<int32_t*>(work);
   int32_t* tile_off = tile_count + (((4 * (size_t)tiles + 255) & ~(size_t)255) / 4);
   hipLaunchKernelGGL(k_prune_count<kRounds>, dim3(tiles), dim3(kPruneThreads), 0, s, logit, n, tau, tile_count);
+  if (kRounds == 1 && tiles <= kPruneOwn) {
+    hipLaunchKernelGGL((k_prune_scatter<kRounds, true>), dim3(tiles, prune_parts(tiles, arr.count)), dim3(kPruneThreads), 0, s, logit, n, tau,
+                       (const int32_t*)tile_count, count, arr, kept);
+    return;
+  }
   hipLaunchKernelGGL(k_prune_scan, dim3(1), dim3(1024), 0, s, (const int32_t*)tile_count, tiles, tile_off, count);
   if (n > 0)
-    hipLaunchKernelGGL(k_prune_scatter<kRounds>, dim3(tiles), dim3(kPruneThreads), 0, s, logit, n, tau,
-                       (const int32_t*)tile_off, (const int32_t*)count, arr, kept);
+    hipLaunchKernelGGL((k_prune_scatter<kRounds, false>), dim3(tiles), dim3(kPruneThreads), 0, s, logit, n, tau,
+                       (const int32_t*)tile_off, count, arr, kept);
 }
 
 void launch_prune(const float* logit, int n, float tau, const PruneArrays& arr, int32_t* kept, int32_t* count,
