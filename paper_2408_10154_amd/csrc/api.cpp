@@ -301,13 +301,18 @@ static ls_status batch_host(const ls_render_job* jobs, int32_t R, ls_batch** out
   b->sortblk_off.assign(R + 1, 0);
   b->binwork_off.assign(R + 1, 0);
   b->bincnt_off.assign(R + 1, 0);
+  for (const JobDev& d : b->jobs_h) b->max_items = std::max(b->max_items, d.n);
+  b->sort_per = ls::sort_per(b->max_items <= kWideItems, [&](int per) {
+    int64_t n = 0;
+    for (const JobDev& d : b->jobs_h) n += ls::sort_blocks_of(d.n, per);
+    return n;
+  });
   int64_t units = 0;
   for (int r = 0; r < R; ++r) {
     const JobDev& d = b->jobs_h[r];
     const int64_t chunks = ls::bin_chunks(d.n, b->bin_chunk, b->bin_ramp);
-    b->max_items = std::max(b->max_items, d.n);
     b->rank_pairs += (int64_t)d.n * d.n;
-    b->sortblk_off[r + 1] = b->sortblk_off[r] + (d.n + kSortKeys - 1) / kSortKeys;
+    b->sortblk_off[r + 1] = b->sortblk_off[r] + ls::sort_blocks_of(d.n, b->sort_per);
     units += chunks * ls::windows_of(d.TX, d.TY);
     if (units > INT32_MAX / 2) {
       delete b;
@@ -531,6 +536,7 @@ ls_status ls_bin_sort(const ls_batch* b, const ls_projected* p, const ls_bins* b
   bl.off256 = b->blk_off_d;
   bl.blocks256 = b->nblk_items;
   bl.sort_blocks = b->sort_blocks;
+  bl.sort_per = b->sort_per;
   bl.units = b->bin_units;
   bl.rec = p->rec;
   bl.radius = p->radius;

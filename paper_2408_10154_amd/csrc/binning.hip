@@ -38,9 +38,8 @@ __global__ void k_fill_i32(int32_t* __restrict__ p, int64_t n, int32_t v) {
 // ---------------------------------------------------------------------------
 // Segmented stable radix sort: segment s holds its (key, value) pairs at
 // base[s] .. base[s] + len[s] (len on the device) and owns the sort blocks
-// blk_off[s] .. blk_off[s + 1), kSortKeys keys each, of which those with keys
-// work.
-
+// blk_off[s] .. blk_off[s + 1), kPer x kSortThreads keys each (sort_per), of
+// which those with keys work.
 //
 // A digit has 8 or 11 bits: four passes with 256 bins or three (of 11, 11 and
 // 10) with 2,048.  The wide ones pay up to kWideItems = 65,536 items, where a
@@ -49,7 +48,6 @@ __global__ void k_fill_i32(int32_t* __restrict__ p, int64_t n, int32_t v) {
 // against 72 us.
 
 constexpr int kSortWaves = kSortThreads / 64;
-constexpr int kSortPer = kSortKeys / kSortThreads;  // keys per thread
 template <int kBits>
 struct Digit {
   static constexpr int kBins = 1 << kBits;
@@ -155,26 +153,27 @@ __device__ __forceinline__ uint32_t digit_starts(uint16_t (*wcnt)[Digit<kBits>::
 }
 
 // Digit counts of every block's keys: hist[block][digit].
-template <int kBits>
+template <int kBits, int kPer>
 __global__ __launch_bounds__(kSortThreads) void k_seg_hist(const uint32_t* __restrict__ keys, SegTable seg, int shift,
                                                            uint32_t* __restrict__ hist) {
   using D = Digit<kBits>;
+  constexpr int kKeys = kPer * kSortThreads;
   __shared__ uint32_t h[D::kBins];
   const int s = find_segment<int32_t>(seg.blk_off, seg.S, (int32_t)blockIdx.x);
   const int c = blockIdx.x - seg.blk_off[s];
-  const int m = min(seg.len[s] - c * kSortKeys, kSortKeys);
+  const int m = min(seg.len[s] - c * kKeys, kKeys);
   if (m <= 0) return;  // uniform for the block
   for (int d = threadIdx.x; d < D::kBins; d += kSortThreads) h[d] = 0u;
-  const uint32_t* __restrict__ k0 = keys + seg.base[s] + (int64_t)c * kSortKeys;
-  uint32_t key[kSortPer];
+  const uint32_t* __restrict__ k0 = keys + seg.base[s] + (int64_t)c * kKeys;
+  uint32_t key[kPer];
 #pragma unroll
-  for (int j = 0; j < kSortPer; ++j) {
+  for (int j = 0; j < kPer; ++j) {
     const int i = j * kSortThreads + threadIdx.x;
     key[j] = i < m ? k0[i] : 0u;
   }
   __syncthreads();
 #pragma unroll
-  for (int j = 0; j < kSortPer; ++j)
+  for (int j = 0; j < kPer; ++j)
     if (j * kSortThreads + (int)threadIdx.x < m) atomicAdd(&h[D::of(key[j], shift)], 1u);
   __syncthreads();
   for (int d = threadIdx.x; d < D::kBins; d += kSortThreads) hist[(int64_t)blockIdx.x * D::kBins + d] = h[d];
@@ -182,7 +181,7 @@ __global__ __launch_bounds__(kSortThreads) void k_seg_hist(const uint32_t* __res
 
 // Sums of the thread's digits' counts over the segment's blocks and over those
 // before this one, kParts threads per digit; the results in threads below
-// kThreads.  A block of 1,024 threads with 4,096 keys keeps the rows few (49
+// kThreads.  Blocks of 1,024 threads keep the rows few (98
 // for 200k keys), so every block can add them up and no scan launch is needed.
 template <int kBits>
 __device__ __forceinline__ void digit_bases(const uint32_t* __restrict__ rows, int nrows, int c, uint32_t* ta,
@@ -225,9 +224,9 @@ __device__ __forceinline__ void digit_bases(const uint32_t* __restrict__ rows, i
 // Stable scatter of one digit: ranks in the waves, the block's keys placed in
 // LDS by digit, then written out in that order, so that stores are contiguous
 // along each digit's run.  kFirst: the block's own keys, blk_cnt of them, as
-// k_depth_prep left them (len[s] is written); else kSortKeys of the segment's
+// k_depth_prep left them (len[s] is written); else kKeys of the segment's
 // len[s].  kLast: only the values are written.
-template <int kBits, bool kFirst, bool kLast>
+template <int kBits, int kPer, bool kFirst, bool kLast>
 __global__ __launch_bounds__(kSortThreads) void k_seg_scatter(const uint32_t* __restrict__ kin,
                                                               const uint32_t* __restrict__ vin,
                                                               uint32_t* __restrict__ kout,
@@ -235,23 +234,24 @@ __global__ __launch_bounds__(kSortThreads) void k_seg_scatter(const uint32_t* __
                                                               const uint32_t* __restrict__ hist,
                                                               const int32_t* __restrict__ blk_cnt) {
   using D = Digit<kBits>;
+  constexpr int kKeys = kPer * kSortThreads;
   __shared__ __attribute__((aligned(4))) uint16_t wcnt[kSortWaves][D::kBins];
-  __shared__ uint32_t sk[kSortKeys], sv[kSortKeys];
+  __shared__ uint32_t sk[kKeys], sv[kKeys];
   __shared__ uint32_t delta[D::kBins];  // global minus local start of each digit's run (mod 2^32)
   __shared__ uint32_t wsum[2][kSortWaves];
   const int s = find_segment<int32_t>(seg.blk_off, seg.S, (int32_t)blockIdx.x);
   const int b0 = seg.blk_off[s], c = blockIdx.x - b0;
   const int n = kFirst ? 0 : seg.len[s];
-  const int m = kFirst ? blk_cnt[blockIdx.x] : min(n - c * kSortKeys, kSortKeys);
-  const int nrows = kFirst ? seg.blk_off[s + 1] - b0 : (n + kSortKeys - 1) / kSortKeys;
+  const int m = kFirst ? blk_cnt[blockIdx.x] : min(n - c * kKeys, kKeys);
+  const int nrows = kFirst ? seg.blk_off[s + 1] - b0 : (n + kKeys - 1) / kKeys;
   if (m <= 0 && !(kFirst && c == 0)) return;  // uniform for the block
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int64_t in0 = seg.base[s] + (int64_t)c * kSortKeys;
-  uint32_t key[kSortPer], val[kSortPer], rk[kSortPer];
-  bool ok[kSortPer];
+  const int64_t in0 = seg.base[s] + (int64_t)c * kKeys;
+  uint32_t key[kPer], val[kPer], rk[kPer];
+  bool ok[kPer];
 #pragma unroll
-  for (int j = 0; j < kSortPer; ++j) {
-    const int i = w * 64 * kSortPer + j * 64 + lane;
+  for (int j = 0; j < kPer; ++j) {
+    const int i = w * 64 * kPer + j * 64 + lane;
     ok[j] = i < m;
     key[j] = ok[j] ? kin[in0 + i] : 0u;
     val[j] = ok[j] ? vin[in0 + i] : 0u;
@@ -261,7 +261,7 @@ __global__ __launch_bounds__(kSortThreads) void k_seg_scatter(const uint32_t* __
   const uint32_t both = D::kPer == 2 ? total[0] + total[D::kPer - 1] : total[0];
   const uint32_t first = digit_excl<D::kThreads>(both, wsum[0]);  // of the thread's digits, in the segment
   if (kFirst && c == 0 && threadIdx.x == D::kThreads - 1) seg.len[s] = (int32_t)(first + both);
-  wave_ranks<kBits, kSortPer>(key, ok, shift, wcnt[w], lane, rk);
+  wave_ranks<kBits, kPer>(key, ok, shift, wcnt[w], lane, rk);
   __syncthreads();
   digit_starts<kBits>(wcnt, wsum[1], lstart);
   if ((int)threadIdx.x < D::kThreads) {
@@ -271,7 +271,7 @@ __global__ __launch_bounds__(kSortThreads) void k_seg_scatter(const uint32_t* __
   }
   __syncthreads();
 #pragma unroll
-  for (int j = 0; j < kSortPer; ++j)
+  for (int j = 0; j < kPer; ++j)
     if (ok[j]) {
       const uint32_t pos = wcnt[w][D::of(key[j], shift)] + rk[j];
       sk[pos] = key[j];
@@ -280,7 +280,7 @@ __global__ __launch_bounds__(kSortThreads) void k_seg_scatter(const uint32_t* __
   __syncthreads();
   const int64_t out0 = seg.base[s];
 #pragma unroll
-  for (int j = 0; j < kSortPer; ++j) {
+  for (int j = 0; j < kPer; ++j) {
     const int i = j * kSortThreads + threadIdx.x;
     if (i < m) {
       const uint32_t k = sk[i];
@@ -298,7 +298,7 @@ int64_t seg_hist_words(int nblk, bool wide) { return (int64_t)(wide ? 2048 : 256
 
 // Larger renders: each block compacts its items with tiles (in item order) and
 // counts the first digit of their depth bits.
-template <int kBits>
+template <int kBits, int kPer>
 __global__ __launch_bounds__(kSortThreads) void k_depth_prep(const JobDev* __restrict__ jobs, SegTable seg,
                                                              const float4* __restrict__ rec,
                                                              const int32_t* __restrict__ tiles,
@@ -306,30 +306,31 @@ __global__ __launch_bounds__(kSortThreads) void k_depth_prep(const JobDev* __res
                                                              uint32_t* __restrict__ hist,
                                                              int32_t* __restrict__ blk_cnt) {
   using D = Digit<kBits>;
+  constexpr int kKeys = kPer * kSortThreads;
   __shared__ uint32_t h[D::kBins];
-  __shared__ uint32_t cnt[kSortPer][kSortWaves];
+  __shared__ uint32_t cnt[kPer][kSortWaves];
   const int s = find_segment<int32_t>(seg.blk_off, seg.S, (int32_t)blockIdx.x);
   const int c = blockIdx.x - seg.blk_off[s];
   const int n = jobs[s].n, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int64_t base = seg.base[s] + (int64_t)c * kSortKeys;
+  const int64_t base = seg.base[s] + (int64_t)c * kKeys;
   for (int d = threadIdx.x; d < D::kBins; d += kSortThreads) h[d] = 0u;
-  uint64_t keep[kSortPer];
+  uint64_t keep[kPer];
 #pragma unroll
-  for (int j = 0; j < kSortPer; ++j) {
+  for (int j = 0; j < kPer; ++j) {
     const int i = j * kSortThreads + threadIdx.x;
-    keep[j] = __ballot(c * kSortKeys + i < n && tiles[base + i] > 0);
+    keep[j] = __ballot(c * kKeys + i < n && tiles[base + i] > 0);
     if (lane == 0) cnt[j][w] = (uint32_t)__popcll(keep[j]);
   }
-  uint32_t key[kSortPer];
+  uint32_t key[kPer];
 #pragma unroll
-  for (int j = 0; j < kSortPer; ++j)
+  for (int j = 0; j < kPer; ++j)
     key[j] = __builtin_amdgcn_inverse_ballot_w64(keep[j])
                  ? __float_as_uint(rec[(base + j * kSortThreads + threadIdx.x) * 3 + 1].z)
                  : 0u;
   __syncthreads();
   uint32_t run = 0;
 #pragma unroll
-  for (int j = 0; j < kSortPer; ++j) {
+  for (int j = 0; j < kPer; ++j) {
     uint32_t at = run;
 #pragma unroll
     for (int k = 0; k < kSortWaves; ++k) {
@@ -1028,28 +1029,42 @@ void launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s) {
   hipLaunchKernelGGL(k_fill_i32, dim3((unsigned)blocks), dim3(256), 0, s, p, n, v);
 }
 
-template <int kBits>
+template <int kBits, int kPer>
 static void seg_pass(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout, const SegTable& seg,
                      int blocks, int shift, uint32_t* hist, bool last, hipStream_t s) {
   const dim3 grid(blocks), block(kSortThreads);
-  hipLaunchKernelGGL(k_seg_hist<kBits>, grid, block, 0, s, kin, seg, shift, hist);
+  hipLaunchKernelGGL((k_seg_hist<kBits, kPer>), grid, block, 0, s, kin, seg, shift, hist);
   const int32_t* none = nullptr;
   auto scatter = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, block, 0, s, kin, vin, kout, vout, seg, shift, (const uint32_t*)hist, none);
   };
   if (last)
-    scatter(k_seg_scatter<kBits, false, true>);
+    scatter(k_seg_scatter<kBits, kPer, false, true>);
   else
-    scatter(k_seg_scatter<kBits, false, false>);
+    scatter(k_seg_scatter<kBits, kPer, false, false>);
+}
+
+// The depth sort of larger renders: three passes end in (k1, v1), four in (k0, v0).
+template <int kBits, int kPer>
+static void depth_passes(const BinLaunch& b, const SegTable& seg, hipStream_t s) {
+  const dim3 grid(b.sort_blocks), block(kSortThreads);
+  hipLaunchKernelGGL((k_depth_prep<kBits, kPer>), grid, block, 0, s, b.jobs, seg,
+                     reinterpret_cast<const float4*>(b.rec), b.tiles, b.k0, b.v0, b.hist, b.blk_cnt);
+  hipLaunchKernelGGL((k_seg_scatter<kBits, kPer, true, false>), grid, block, 0, s, (const uint32_t*)b.k0,
+                     (const uint32_t*)b.v0, b.k1, b.v1, seg, 0, (const uint32_t*)b.hist, (const int32_t*)b.blk_cnt);
+  constexpr int kPasses = kBits == 11 ? 3 : 4;
+  for (int p = 1; p < kPasses; ++p) {
+    const bool odd = p & 1;
+    seg_pass<kBits, kPer>(odd ? b.k1 : b.k0, odd ? b.v1 : b.v0, odd ? b.k0 : b.k1, odd ? b.v0 : b.v1, seg,
+                          b.sort_blocks, p * kBits, b.hist, p == kPasses - 1, s);
+  }
 }
 
 void launch_bin_sort(const BinLaunch& b, hipStream_t s) {
   const float4* rec4 = reinterpret_cast<const float4*>(b.rec);
   const SegTable seg{b.tab.blk_off, b.item_off, b.tab.R, b.kept};
   const uint32_t* order = b.v0;
-  const dim3 grid(b.sort_blocks), block(kSortThreads);
-  const uint32_t* hist = b.hist;
-  const int32_t* cnt = b.blk_cnt;
+  const dim3 block(kSortThreads);
   if (b.max_items <= kRankItems && (b.tab.R == 1 || b.rank_pairs <= kRankPairs)) {
     auto rank = [&](auto kernel) {
       hipLaunchKernelGGL(kernel, dim3(4 * b.blocks256), dim3(64 * kRankWaves), 0, s, b.jobs, seg, b.off256, rec4,
@@ -1068,19 +1083,17 @@ void launch_bin_sort(const BinLaunch& b, hipStream_t s) {
     else
       small(k_depth_sort_small<11, 8>);
   } else if (b.max_items <= kWideItems) {
-    hipLaunchKernelGGL(k_depth_prep<11>, grid, block, 0, s, b.jobs, seg, rec4, b.tiles, b.k0, b.v0, b.hist, b.blk_cnt);
-    hipLaunchKernelGGL((k_seg_scatter<11, true, false>), grid, block, 0, s, (const uint32_t*)b.k0,
-                       (const uint32_t*)b.v0, b.k1, b.v1, seg, 0, hist, cnt);
-    seg_pass<11>(b.k1, b.v1, b.k0, b.v0, seg, b.sort_blocks, 11, b.hist, false, s);
-    seg_pass<11>(b.k0, b.v0, b.k1, b.v1, seg, b.sort_blocks, 22, b.hist, true, s);
+    if (b.sort_per == 3)
+      depth_passes<11, 3>(b, seg, s);
+    else
+      depth_passes<11, 4>(b, seg, s);
     order = b.v1;
+  } else if (b.sort_per == 2) {
+    depth_passes<8, 2>(b, seg, s);
+  } else if (b.sort_per == 3) {
+    depth_passes<8, 3>(b, seg, s);
   } else {
-    hipLaunchKernelGGL(k_depth_prep<8>, grid, block, 0, s, b.jobs, seg, rec4, b.tiles, b.k0, b.v0, b.hist, b.blk_cnt);
-    hipLaunchKernelGGL((k_seg_scatter<8, true, false>), grid, block, 0, s, (const uint32_t*)b.k0,
-                       (const uint32_t*)b.v0, b.k1, b.v1, seg, 0, hist, cnt);
-    seg_pass<8>(b.k1, b.v1, b.k0, b.v0, seg, b.sort_blocks, 8, b.hist, false, s);
-    seg_pass<8>(b.k0, b.v0, b.k1, b.v1, seg, b.sort_blocks, 16, b.hist, false, s);
-    seg_pass<8>(b.k1, b.v1, b.k0, b.v0, seg, b.sort_blocks, 24, b.hist, true, s);
+    depth_passes<8, 4>(b, seg, s);
   }
   const dim3 work(8 * ((b.units + 7) / 8));
   if (b.units > 0)
@@ -1110,7 +1123,8 @@ void launch_bin_sort(const BinLaunch& b, hipStream_t s) {
 }
 
 void launch_seg_pass(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout, const SegTable& seg,
-                     int blocks, int shift, uint32_t* hist, bool last, hipStream_t s) {
-  seg_pass<8>(kin, vin, kout, vout, seg, blocks, shift, hist, last, s);
+                     int blocks, int per, int shift, uint32_t* hist, bool last, hipStream_t s) {
+  const auto pass = per == 2 ? seg_pass<8, 2> : per == 3 ? seg_pass<8, 3> : seg_pass<8, 4>;
+  pass(kin, vin, kout, vout, seg, blocks, shift, hist, last, s);
 }
 }  // namespace ls

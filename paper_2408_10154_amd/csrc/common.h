@@ -11,10 +11,10 @@ namespace ls {
 constexpr int kTile = LS_TILE;
 constexpr int kBlock = 256;         // one 16x16 tile per block, 4 wave64
 constexpr int kSortThreads = 1024;  // radix sort block
-constexpr int kSortKeys = 4096;     // keys per radix sort block
+constexpr int kSortPerMax = 4;      // most keys per thread of it
 constexpr int kRankItems = 16384;              // items up to which a render's depths are ranked by comparison,
 constexpr int64_t kRankPairs = 1 << 26;        // if all renders of a batch make up to so many pairs
-constexpr int kWideItems = 16 * kSortKeys;     // items up to which a larger render's depth sort takes 11-bit digits
+constexpr int kWideItems = 65536;              // items up to which a larger render's depth sort takes 11-bit digits
 constexpr int kWindowTiles = 4096;  // most tiles of a binning window
 constexpr int kGradStride = 16;     // floats per item in the accumulator: a 64-byte line each
 constexpr int kGrad2D = 10;         // sums of ds (dx, dy, dx^2, dx dy, dy^2, 1), dz dr dg db

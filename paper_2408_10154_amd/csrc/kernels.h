@@ -56,19 +56,36 @@ void launch_pose_reduce_bands(const JobDev* jobs, int R, const float* pose, cons
 
 // Segments of a radix sort: segment s holds its keys at base[s] ..
 // base[s] + len[s] and owns the sort blocks blk_off[s] .. blk_off[s + 1), one
-// per kSortKeys keys of the most it may hold.  All arrays on the device.
+// per `per` x kSortThreads keys of the most it may hold.  All arrays on the
+// device.
 struct SegTable {
   const int32_t* blk_off;  // [S + 1]
   const int64_t* base;     // [S]
   int S;
   int32_t* len;            // [S]
 };
+inline int sort_blocks_of(int64_t n, int per) { return (int)((n + per * kSortThreads - 1) / (per * kSortThreads)); }
+// Keys per thread of a sort block, 2 to 4, for `blocks(per)` blocks in all: the
+// fewest with which all blocks are on the chip at once (two on each of 256
+// CUs), since short blocks use more CUs and a second round costs a block's
+// whole time; three at least with 11-bit digits, whose bins are most of a
+// block's work.  Binning with 2, 3 and 4: 97k items 77.5, 80.5 and 84.2 us (48,
+// 32 and 24 blocks), 200k 102, 105 and 107, 3 x 80k 90, 92 and 96; 8 x 150k 210
+// (586 blocks), 192 (391) and 200; 16 x 135k 172, 154 (704) and 148; with 11-bit
+// digits 21k + 17k twice 73, 71 and 74, 40k 76.6, 74.8 and 75.0.
+template <class Blocks>
+inline int sort_per(bool wide, const Blocks& blocks) {
+  constexpr int kResident = 512;
+  int per = wide ? 3 : 2;
+  while (per < kSortPerMax && blocks(per) > kResident) ++per;
+  return per;
+}
 // Words of the digit histograms of `blocks` sort blocks (wide: 11-bit digits).
 int64_t seg_hist_words(int blocks, bool wide);
 // One stable pass over the 8-bit digit at `shift` (binning.hip), from
 // (kin, vin) to (kout, vout); last: kout is not written.
 void launch_seg_pass(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout, const SegTable& seg,
-                     int blocks, int shift, uint32_t* hist, bool last, hipStream_t s);
+                     int blocks, int per, int shift, uint32_t* hist, bool last, hipStream_t s);
 
 // Device tables of a batch's binning: per render the sort blocks, the chunk x
 // window work units and the count matrices (chunks x tiles words) before it.
@@ -89,7 +106,7 @@ struct BinLaunch {
   const int64_t* item_off;
   const int32_t* tile_off;
   BinTables tab;
-  int T, max_items, sort_blocks, units, blocks256;
+  int T, max_items, sort_blocks, sort_per, units, blocks256;
   const int32_t* off256;        // [R + 1]: first block of 256 items of each render; blocks256 of them
   int64_t rank_pairs;           // sum over the renders of the squared item count
   int64_t counts;               // words of the count matrices

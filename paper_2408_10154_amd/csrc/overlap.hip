@@ -98,14 +98,15 @@ __global__ __launch_bounds__(256) void k_ov_box_part(const float* __restrict__ a
   }
 }
 
-// The common box, and the two sets as segments of one sort.
+// The common box, and the two sets as segments of one sort with `keys` keys to a
+// block.
 struct OvSegs {
   int32_t* blk_off;  // [3]
   int64_t* base;     // [2]
   int32_t* len;      // [2]
 };
 __global__ __launch_bounds__(256) void k_ov_box_final(const float* __restrict__ part, int nblk, int np, int nq,
-                                                      float* __restrict__ box, OvSegs seg) {
+                                                      float* __restrict__ box, OvSegs seg, int keys) {
   __shared__ float ws[4][6];
   float v[6];
 #pragma unroll
@@ -126,8 +127,8 @@ __global__ __launch_bounds__(256) void k_ov_box_final(const float* __restrict__ 
   }
   if (threadIdx.x == 0) {
     seg.blk_off[0] = 0;
-    seg.blk_off[1] = (np + kSortKeys - 1) / kSortKeys;
-    seg.blk_off[2] = seg.blk_off[1] + (nq + kSortKeys - 1) / kSortKeys;
+    seg.blk_off[1] = (np + keys - 1) / keys;
+    seg.blk_off[2] = seg.blk_off[1] + (nq + keys - 1) / keys;
     seg.base[0] = 0;
     seg.base[1] = np;
     seg.len[0] = np;
@@ -487,8 +488,9 @@ struct OvLayout {
   size_t pt, box_part, box, segs, code_a, idx_a, code_b, idx_b, hist, set_p[3], set_q[3], total;
 };
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
-static int ov_sort_blocks(int np, int nq) {
-  return (np + kSortKeys - 1) / kSortKeys + (nq + kSortKeys - 1) / kSortKeys;
+static int ov_sort_blocks(int np, int nq, int per) { return sort_blocks_of(np, per) + sort_blocks_of(nq, per); }
+static int ov_sort_per(int np, int nq) {
+  return sort_per(false, [&](int per) { return ov_sort_blocks(np, nq, per); });
 }
 static OvLayout ov_layout(int np, int nq) {
   OvLayout L{};
@@ -507,7 +509,7 @@ static OvLayout ov_layout(int np, int nq) {
   L.idx_a = take(4 * both);
   L.code_b = take(4 * both);
   L.idx_b = take(4 * both);
-  L.hist = take(4 * (size_t)seg_hist_words(ov_sort_blocks(np, nq), false));
+  L.hist = take(4 * (size_t)seg_hist_words(ov_sort_blocks(np, nq, ov_sort_per(np, nq)), false));
   for (int s = 0; s < 2; ++s) {
     const int n = s ? nq : np;
     const int nleaf = (n + kOvLeaf - 1) / kOvLeaf, nsuper = (nleaf + kOvSuper - 1) / kOvSuper;
@@ -541,10 +543,11 @@ void launch_overlap(const float* p_mean, int np, const float* q_mean, int nq, co
   hipLaunchKernelGGL(k_ov_box_part, dim3(kOvBoxBlocks), dim3(kBlock), 0, s, (const float*)pt, np, q_mean, nq,
                      box_part);
   char* sg = w + L.segs;
+  const int per = ov_sort_per(np, nq), nsb = ov_sort_blocks(np, nq, per);
   const OvSegs segs{reinterpret_cast<int32_t*>(sg), reinterpret_cast<int64_t*>(sg + 16),
                     reinterpret_cast<int32_t*>(sg + 32)};
   hipLaunchKernelGGL(k_ov_box_final, dim3(1), dim3(kBlock), 0, s, (const float*)box_part, kOvBoxBlocks, np, nq, box,
-                     segs);
+                     segs, per * kSortThreads);
   uint32_t* ca = reinterpret_cast<uint32_t*>(w + L.code_a);
   uint32_t* ia = reinterpret_cast<uint32_t*>(w + L.idx_a);
   uint32_t* cb = reinterpret_cast<uint32_t*>(w + L.code_b);
@@ -555,11 +558,10 @@ void launch_overlap(const float* p_mean, int np, const float* q_mean, int nq, co
                      np, q_mean, nq, (const float*)box, ca, ia);
   // both sets in one sort; four passes over the 30-bit codes end in (ca, ia)
   const SegTable seg{segs.blk_off, segs.base, 2, segs.len};
-  const int nsb = ov_sort_blocks(np, nq);
-  launch_seg_pass(ca, ia, cb, ib, seg, nsb, 0, hist, false, s);
-  launch_seg_pass(cb, ib, ca, ia, seg, nsb, 8, hist, false, s);
-  launch_seg_pass(ca, ia, cb, ib, seg, nsb, 16, hist, false, s);
-  launch_seg_pass(cb, ib, ca, ia, seg, nsb, 24, hist, false, s);
+  launch_seg_pass(ca, ia, cb, ib, seg, nsb, per, 0, hist, false, s);
+  launch_seg_pass(cb, ib, ca, ia, seg, nsb, per, 8, hist, false, s);
+  launch_seg_pass(ca, ia, cb, ib, seg, nsb, per, 16, hist, false, s);
+  launch_seg_pass(cb, ib, ca, ia, seg, nsb, per, 24, hist, false, s);
   OvSet set[2];
   for (int k = 0; k < 2; ++k) {
     const int n = k ? nq : np;

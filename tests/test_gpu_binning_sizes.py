@@ -75,3 +75,12 @@ def test_lists_equal_the_oracle(gpu, sizes, image, culled):
     first = np.searchsorted(exp_t, np.arange(len(ranges)))
     last = np.searchsorted(exp_t, np.arange(len(ranges)), side="right")
     np.testing.assert_array_equal(ranges, np.where((last > first)[:, None], np.stack([first, last], 1), 0))
+
+
+@pytest.mark.parametrize("sizes,culled", [
+    ([65537], 0.9), ([131072, 131073], 0.9), ([300000], 0.6),  # two keys a thread; more than 64 blocks' counts added up
+    ([70000] * 16, 0.97), ([70000] * 24, 0.97),                # three, four
+    ([17000] * 85, 0.97), ([17000] * 86, 0.97),                # three, four with 11-bit digits
+])
+def test_sort_blocks_of_each_size(gpu, sizes, culled):
+    test_lists_equal_the_oracle(gpu, sizes, SMALL, culled)
