@@ -180,8 +180,9 @@ typedef struct {
  * is ordered by (tile, FP32 depth bit pattern, item) - depth order with ties
  * broken by Gaussian index.  Runs entirely on the device (the items' depth
  * order, then counts per chunk of items and tile, and every instance written
- * to its place).  When I > capacity, count[1] is set to 1, only the first `capacity` instances are kept and the lists are
- * not valid; the caller re-runs with capacity >= count[2].  Errors:
+ * to its place).  When I > capacity, count[1] is set to 1, only the first
+ * `capacity` instances are kept and the lists are not valid; the caller re-runs
+ * with capacity >= count[2].  Errors:
  * LS_ERR_INVALID (NULL buffers, capacity < 0). */
 ls_status ls_bin_sort(const ls_batch* b, const ls_projected* p, const ls_bins* bins, hipStream_t s);
 
