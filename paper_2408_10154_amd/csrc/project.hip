@@ -136,8 +136,10 @@ __global__ __launch_bounds__(256) void k_project_bwd(const JobDev* __restrict__ 
 
   // fused Adam: the 14 gradient values of this Gaussian (mean 0-2,
   // log_scale 3-5, quat 6-9, opacity 10, rgb 11-13; zero for a culled one,
-  // whose moments still decay and which still moves) are gathered first and
-  // stepped together after the chain, every load before any store
+  // whose moments still decay and which still moves) are gathered and stepped
+  // together after the chain.  The state is loaded before the chain, whose own
+  // loads wait for the radius (200k items, 88 MB: 21.4 -> 19.8 us; 18.4 us at the
+  // rate of a large copy)
   float* const params[5] = {const_cast<float*>(J.mean), const_cast<float*>(J.log_scale), const_cast<float*>(J.quat),
                             const_cast<float*>(J.opac), const_cast<float*>(J.rgb)};
   constexpr int kSlot0[5] = {0, 3, 6, 10, 11};
@@ -145,15 +147,30 @@ __global__ __launch_bounds__(256) void k_project_bwd(const JobDev* __restrict__ 
 #pragma unroll
   for (int j = 0; j < 14; ++j) gv[j] = 0.f;
 
+  float pv[14], mv[14], vv[14];
+  if (kAdam && g < n) {
+#pragma unroll
+    for (int q = 0; q < 5; ++q)
+#pragma unroll
+      for (int k = 0; k < (q == 2 ? 4 : q == 3 ? 1 : 3); ++k) {
+        const int j2 = kSlot0[q] + k;
+        const int64_t idx = (int64_t)k * n + g;
+        pv[j2] = params[q][idx];
+        mv[j2] = adam.m[r][q][idx];
+        vv[j2] = adam.v[r][q][idx];
+      }
+  }
+
   const int64_t item = J.item_off + g;
   if (g < n && radius[item] > 0) {
     float* gp = g2d + item * kGradStride;
-    float gi[kGrad2D];
-#pragma unroll
-    for (int q = 0; q < kGrad2D; ++q) {
-      gi[q] = gp[q];
-      gp[q] = 0.f;  // leave the accumulator cleared for the next backward
-    }
+    float4* gp4 = reinterpret_cast<float4*>(gp);
+    const float4 g0 = gp4[0], g1 = gp4[1];
+    const float2 g2 = reinterpret_cast<const float2*>(gp)[4];
+    const float gi[kGrad2D] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w, g2.x, g2.y};
+    // leave the accumulator cleared for the next backward
+    gp4[0] = gp4[1] = make_float4(0.f, 0.f, 0.f, 0.f);
+    reinterpret_cast<float2*>(gp)[4] = make_float2(0.f, 0.f);
     const float4 a0 = aux[item * 3 + 0], a1 = aux[item * 3 + 1], a2 = aux[item * 3 + 2];
     const float p[3] = {a0.x, a0.y, a0.z};
     const float s6[6] = {a0.w, a1.x, a1.y, a1.z, a1.w, a2.x};
@@ -179,10 +196,12 @@ __global__ __launch_bounds__(256) void k_project_bwd(const JobDev* __restrict__ 
           emit(0, k, GD.mean, W[0 * 3 + k] * dp[0] + W[1 * 3 + k] * dp[1] + W[2 * 3 + k] * dp[2]);
       }
       if (GD.log_scale || GD.quat) {
-        const float qw0 = J.quat[g], qx0 = J.quat[n + g], qy0 = J.quat[2 * n + g], qz0 = J.quat[3 * n + g];
+        const float qw0 = kAdam ? pv[6] : J.quat[g], qx0 = kAdam ? pv[7] : J.quat[n + g],
+                    qy0 = kAdam ? pv[8] : J.quat[2 * n + g], qz0 = kAdam ? pv[9] : J.quat[3 * n + g];
         float Rq[9];
         quat_to_rot(qw0, qx0, qy0, qz0, Rq);
-        const float s[3] = {__expf(J.log_scale[g]), __expf(J.log_scale[n + g]), __expf(J.log_scale[2 * n + g])};
+        const float s[3] = {__expf(kAdam ? pv[3] : J.log_scale[g]), __expf(kAdam ? pv[4] : J.log_scale[n + g]),
+                            __expf(kAdam ? pv[5] : J.log_scale[2 * n + g])};
         float M[9];
         for (int i = 0; i < 3; ++i)
           for (int k = 0; k < 3; ++k) M[i * 3 + k] = Rq[i * 3 + k] * s[k];
@@ -210,7 +229,7 @@ __global__ __launch_bounds__(256) void k_project_bwd(const JobDev* __restrict__ 
         }
       }
       if (GD.opac) {
-        const float op = 1.0f / (1.0f + __expf(-J.opac[g]));
+        const float op = 1.0f / (1.0f + __expf(-(kAdam ? pv[10] : J.opac[g])));
         emit(3, 0, GD.opac, -gi[5] * (1.f - op));  // dL/dopacity = -gi[5] / op
       }
       if (GD.rgb) {
@@ -224,17 +243,6 @@ __global__ __launch_bounds__(256) void k_project_bwd(const JobDev* __restrict__ 
     }
   }
   if (kAdam && g < n) {
-    float pv[14], mv[14], vv[14];
-#pragma unroll
-    for (int q = 0; q < 5; ++q)
-#pragma unroll
-      for (int k = 0; k < (q == 2 ? 4 : q == 3 ? 1 : 3); ++k) {
-        const int j2 = kSlot0[q] + k;
-        const int64_t idx = (int64_t)k * n + g;
-        pv[j2] = params[q][idx];
-        mv[j2] = adam.m[r][q][idx];
-        vv[j2] = adam.v[r][q][idx];
-      }
 #pragma unroll
     for (int q = 0; q < 5; ++q)
 #pragma unroll
@@ -276,9 +284,8 @@ constexpr int kPoseSumThreads = 256;
 // kPoseSumThreads threads in a fixed order: strided per-thread sums (each
 // row three 16-byte loads, four rows in flight per thread), wave sums, then
 // the four waves in order.  Thread 0 returns the totals.  Bound by what one CU
-// fetches of rows that lie in all XCDs' L2s: over the 4,800 rows of each of 16
-// 640x480 views 11.6 us, with eight rows in flight 11.4 us, with 1,024 threads
-// 11.3 us.
+// fetches of rows that lie in all XCDs' L2s: with eight rows in flight 0.2 us less
+// of 11.6 for the 4,800 rows of each of 16 640x480 views, with 1,024 threads 0.3.
 __device__ __forceinline__ void block_pose_sum(const float* __restrict__ part, int first, int nb,
                                                float (&acc)[kPoseAcc]) {
   static_assert(kPoseAcc == 12, "a row is three float4");
@@ -316,26 +323,26 @@ __global__ __launch_bounds__(kPoseSumThreads) void k_pose_reduce(const JobDev* _
   const JobDev& J = jobs[r];
   const int first = by_band ? 4 * J.tile_off : J.blk_off;
   const int nb = by_band ? 4 * J.TX * J.TY : (J.n + 255) / 256;
+  PoseState st{};
+  if (threadIdx.x == 0) st = load_pose_state(pose, pose_grad, step.pose_m, step.pose_v, r);
   float acc[kPoseAcc];
   block_pose_sum(pose_part, first, nb, acc);
   if (threadIdx.x == 0) {
-    const float* pr = pose + 7 * r;
-    float dq[4];
-    rot_backward(pr[0], pr[1], pr[2], pr[3], acc, dq);
-    float* out = pose_grad + 7 * r;
-    for (int k = 0; k < 4; ++k) out[k] += dq[k];
-    for (int k = 0; k < 3; ++k) out[4 + k] += acc[9 + k];
-    if (step.pose_m) {
-      for (int k = 0; k < 7; ++k) {
-        const int i = 7 * r + k;
-        float p = step.pose[i], m = step.pose_m[i], v = step.pose_v[i];
-        adam_update(p, m, v, out[k], k < 4 ? step.lr_rot : step.lr_trans, step.beta1, step.beta2, step.eps, step.bc1,
-                    step.bc2);
-        step.pose[i] = p;
-        step.pose_m[i] = m;
-        step.pose_v[i] = v;
-        out[k] = 0.f;
+    float dq[4], g[7];
+    rot_backward(st.p[0], st.p[1], st.p[2], st.p[3], acc, dq);
+#pragma unroll
+    for (int k = 0; k < 7; ++k) g[k] = st.g[k] + (k < 4 ? dq[k & 3] : acc[5 + k]);
+#pragma unroll
+    for (int k = 0; k < 7; ++k) {
+      const int i = 7 * r + k;
+      if (step.pose_m) {
+        adam_update(st.p[k], st.m[k], st.v[k], g[k], k < 4 ? step.lr_rot : step.lr_trans, step.beta1, step.beta2,
+                    step.eps, step.bc1, step.bc2);
+        step.pose[i] = st.p[k];
+        step.pose_m[i] = st.m[k];
+        step.pose_v[i] = st.v[k];
       }
+      pose_grad[i] = step.pose_m ? 0.f : g[k];
     }
   }
 }
@@ -377,15 +384,20 @@ __global__ __launch_bounds__(kPoseSumThreads) void k_pose_reduce_adam(const JobD
   const int r = blockIdx.x;
   if (r >= R) return;
   const JobDev& J = jobs[r];
+  PoseState st{};
+  ViewOpt o{};
+  if (threadIdx.x == 0) {
+    st = load_pose_state(a.pose, a.grad, a.m, a.v, r);
+    o = a.opt[r];
+  }
   float acc[kPoseAcc];
   block_pose_sum(band_part, 4 * J.tile_off, 4 * J.TX * J.TY, acc);
   if (threadIdx.x == 0) {
-    const float* pr = a.pose + 7 * r;
     float dq[4], g[7];
-    rot_backward(pr[0], pr[1], pr[2], pr[3], acc, dq);
-    for (int k = 0; k < 4; ++k) g[k] = a.grad[7 * r + k] + dq[k];
-    for (int k = 0; k < 3; ++k) g[4 + k] = a.grad[7 * r + 4 + k] + acc[9 + k];
-    pose_adam_view(a, r, g);
+    rot_backward(st.p[0], st.p[1], st.p[2], st.p[3], acc, dq);
+#pragma unroll
+    for (int k = 0; k < 7; ++k) g[k] = st.g[k] + (k < 4 ? dq[k & 3] : acc[5 + k]);
+    pose_adam_view(a, r, st, o, g);
     if (r == 0 && count) or_flag(count, sticky);
   }
 }
