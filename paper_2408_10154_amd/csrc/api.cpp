@@ -82,7 +82,7 @@ Layout layout_of(const ls_batch* b, int64_t cap) {
   L.v0 = take(4 * M);
   L.k1 = take(4 * M);
   L.v1 = take(4 * M);
-  L.hist = take(4 * (size_t)seg_hist_words(b->sort_blocks, b->max_items <= kWideItems));
+  L.hist = take(4 * (size_t)seg_hist_words(b->sort_blocks));
   L.blk_cnt = take(4 * (size_t)b->sort_blocks);
   L.kept = take(4 * (size_t)b->R);
   L.cnt = take(4 * (size_t)b->bincnt_off[b->R]);
@@ -302,7 +302,7 @@ static ls_status batch_host(const ls_render_job* jobs, int32_t R, ls_batch** out
   b->binwork_off.assign(R + 1, 0);
   b->bincnt_off.assign(R + 1, 0);
   for (const JobDev& d : b->jobs_h) b->max_items = std::max(b->max_items, d.n);
-  b->sort_per = ls::sort_per(b->max_items <= kWideItems, [&](int per) {
+  b->sort_per = ls::sort_per(b->max_items, [&](int per) {
     int64_t n = 0;
     for (const JobDev& d : b->jobs_h) n += ls::sort_blocks_of(d.n, per);
     return n;

@@ -41,13 +41,12 @@ __global__ void k_fill_i32(int32_t* __restrict__ p, int64_t n, int32_t v) {
 // blk_off[s] .. blk_off[s + 1), kPer x kSortThreads keys each (sort_per), of
 // which those with keys work.
 //
-// A digit has 8 or 11 bits: four passes with 256 bins or three (of 11, 11 and
-// 10) with 2,048.  The wide ones pay up to kWideItems = 65,536 items, where a
-// block adds up the others' bins in one round of loads: 23k items 43 us in 8
-// launches against 40 us in 6; but 97k items 46 against 51 us, 200k items 50
-// against 72 us (in blocks of 4,096 keys).
+// Four passes of 8-bit digits.  (Three of 11, 11 and 10 bits, in two launches
+// less: 17k items' binning 62.3 us against 61.1, 40k 75 against 67, 65k 85
+// against 70; 30 renders of 20k 127 against 129.)
 
 constexpr int kSortWaves = kSortThreads / 64;
+constexpr int kSortBits = 8;
 template <int kBits>
 struct Digit {
   static constexpr int kBins = 1 << kBits;
@@ -153,10 +152,10 @@ __device__ __forceinline__ uint32_t digit_starts(uint16_t (*wcnt)[Digit<kBits>::
 }
 
 // Digit counts of every block's keys: hist[block][digit].
-template <int kBits, int kPer>
+template <int kPer>
 __global__ __launch_bounds__(kSortThreads) void k_seg_hist(const uint32_t* __restrict__ keys, SegTable seg, int shift,
                                                            uint32_t* __restrict__ hist) {
-  using D = Digit<kBits>;
+  using D = Digit<kSortBits>;
   constexpr int kKeys = kPer * kSortThreads;
   __shared__ uint32_t h[D::kBins];
   const int s = find_segment<int32_t>(seg.blk_off, seg.S, (int32_t)blockIdx.x);
@@ -179,46 +178,37 @@ __global__ __launch_bounds__(kSortThreads) void k_seg_hist(const uint32_t* __res
   for (int d = threadIdx.x; d < D::kBins; d += kSortThreads) hist[(int64_t)blockIdx.x * D::kBins + d] = h[d];
 }
 
-// Sums of the thread's digits' counts over the segment's blocks and over those
-// before this one, kParts threads per digit; the results in threads below
-// kThreads.  Blocks of 1,024 threads keep the rows few (98 for 200k keys),
-// so every block can add them up and no scan launch is needed.
-template <int kBits>
+// Sums of digit d's counts over the segment's blocks and over those before this
+// one, kParts threads per digit; the results in threads d below kThreads.
+// Blocks of 1,024 threads keep the rows few (98 for 200k keys), so every block
+// can add them up and no scan launch is needed.
 __device__ __forceinline__ void digit_bases(const uint32_t* __restrict__ rows, int nrows, int c, uint32_t* ta,
-                                            uint32_t* tb, uint32_t (&total)[Digit<kBits>::kPer],
-                                            uint32_t (&before)[Digit<kBits>::kPer]) {
-  using D = Digit<kBits>;
+                                            uint32_t* tb, uint32_t& total, uint32_t& before) {
+  using D = Digit<kSortBits>;
   constexpr int kParts = kSortThreads / D::kThreads, kAhead = 16;
   const int d = threadIdx.x & (D::kThreads - 1), p = threadIdx.x / D::kThreads;
-#pragma unroll
-  for (int q = 0; q < D::kPer; ++q) total[q] = before[q] = 0u;
+  total = before = 0u;
   for (int r0 = p; r0 < nrows; r0 += kAhead * kParts) {
-    uint32_t v[kAhead][D::kPer];
+    uint32_t v[kAhead];
 #pragma unroll
     for (int k = 0; k < kAhead; ++k)
+      v[k] = r0 + k * kParts < nrows ? rows[(int64_t)(r0 + k * kParts) * D::kBins + d] : 0u;
 #pragma unroll
-      for (int q = 0; q < D::kPer; ++q)
-        v[k][q] = r0 + k * kParts < nrows ? rows[(int64_t)(r0 + k * kParts) * D::kBins + D::kPer * d + q] : 0u;
-#pragma unroll
-    for (int k = 0; k < kAhead; ++k)
-#pragma unroll
-      for (int q = 0; q < D::kPer; ++q) {
-        total[q] += v[k][q];
-        before[q] += r0 + k * kParts < c ? v[k][q] : 0u;
-      }
+    for (int k = 0; k < kAhead; ++k) {
+      total += v[k];
+      before += r0 + k * kParts < c ? v[k] : 0u;
+    }
   }
-  if (kParts > 1) {
-    ta[threadIdx.x] = total[0];
-    tb[threadIdx.x] = before[0];
-    __syncthreads();
-    total[0] = before[0] = 0u;
-    if ((int)threadIdx.x < D::kThreads)
+  ta[threadIdx.x] = total;
+  tb[threadIdx.x] = before;
+  __syncthreads();
+  total = before = 0u;
+  if ((int)threadIdx.x < D::kThreads)
 #pragma unroll
-      for (int k = 0; k < kParts; ++k) {
-        total[0] += ta[k * D::kThreads + d];
-        before[0] += tb[k * D::kThreads + d];
-      }
-  }
+    for (int k = 0; k < kParts; ++k) {
+      total += ta[k * D::kThreads + d];
+      before += tb[k * D::kThreads + d];
+    }
 }
 
 // Stable scatter of one digit: ranks in the waves, the block's keys placed in
@@ -226,14 +216,14 @@ __device__ __forceinline__ void digit_bases(const uint32_t* __restrict__ rows, i
 // along each digit's run.  kFirst: the block's own keys, blk_cnt of them, as
 // k_depth_prep left them (len[s] is written); else kKeys of the segment's
 // len[s].  kLast: only the values are written.
-template <int kBits, int kPer, bool kFirst, bool kLast>
+template <int kPer, bool kFirst, bool kLast>
 __global__ __launch_bounds__(kSortThreads) void k_seg_scatter(const uint32_t* __restrict__ kin,
                                                               const uint32_t* __restrict__ vin,
                                                               uint32_t* __restrict__ kout,
                                                               uint32_t* __restrict__ vout, SegTable seg, int shift,
                                                               const uint32_t* __restrict__ hist,
                                                               const int32_t* __restrict__ blk_cnt) {
-  using D = Digit<kBits>;
+  using D = Digit<kSortBits>;
   constexpr int kKeys = kPer * kSortThreads;
   __shared__ __attribute__((aligned(4))) uint16_t wcnt[kSortWaves][D::kBins];
   __shared__ uint32_t sk[kKeys], sv[kKeys];
@@ -256,19 +246,14 @@ __global__ __launch_bounds__(kSortThreads) void k_seg_scatter(const uint32_t* __
     key[j] = ok[j] ? kin[in0 + i] : 0u;
     val[j] = ok[j] ? vin[in0 + i] : 0u;
   }
-  uint32_t total[D::kPer], before[D::kPer], lstart[D::kPer];
-  digit_bases<kBits>(hist + (int64_t)b0 * D::kBins, nrows, c, sk, sv, total, before);
-  const uint32_t both = D::kPer == 2 ? total[0] + total[D::kPer - 1] : total[0];
-  const uint32_t first = digit_excl<D::kThreads>(both, wsum[0]);  // of the thread's digits, in the segment
-  if (kFirst && c == 0 && threadIdx.x == D::kThreads - 1) seg.len[s] = (int32_t)(first + both);
-  wave_ranks<kBits, kPer>(key, ok, shift, wcnt[w], lane, rk);
+  uint32_t total, before, lstart[1];
+  digit_bases(hist + (int64_t)b0 * D::kBins, nrows, c, sk, sv, total, before);
+  const uint32_t first = digit_excl<D::kThreads>(total, wsum[0]);  // of the thread's digit, in the segment
+  if (kFirst && c == 0 && threadIdx.x == D::kThreads - 1) seg.len[s] = (int32_t)(first + total);
+  wave_ranks<kSortBits, kPer>(key, ok, shift, wcnt[w], lane, rk);
   __syncthreads();
-  digit_starts<kBits>(wcnt, wsum[1], lstart);
-  if ((int)threadIdx.x < D::kThreads) {
-    delta[D::kPer * threadIdx.x] = first + before[0] - lstart[0];
-    if (D::kPer == 2)
-      delta[2 * threadIdx.x + 1] = first + total[0] + before[D::kPer - 1] - lstart[D::kPer - 1];
-  }
+  digit_starts<kSortBits>(wcnt, wsum[1], lstart);
+  if ((int)threadIdx.x < D::kThreads) delta[threadIdx.x] = first + before - lstart[0];
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < kPer; ++j)
@@ -291,21 +276,21 @@ __global__ __launch_bounds__(kSortThreads) void k_seg_scatter(const uint32_t* __
   }
 }
 
-int64_t seg_hist_words(int nblk, bool wide) { return (int64_t)(wide ? 2048 : 256) * std::max(nblk, 1); }
+int64_t seg_hist_words(int nblk) { return (int64_t)Digit<kSortBits>::kBins * std::max(nblk, 1); }
 
 // ---------------------------------------------------------------------------
 // Depth order of each render's items.
 
 // Larger renders: each block compacts its items with tiles (in item order) and
 // counts the first digit of their depth bits.
-template <int kBits, int kPer>
+template <int kPer>
 __global__ __launch_bounds__(kSortThreads) void k_depth_prep(const JobDev* __restrict__ jobs, SegTable seg,
                                                              const float4* __restrict__ rec,
                                                              const int32_t* __restrict__ tiles,
                                                              uint32_t* __restrict__ keys, uint32_t* __restrict__ vals,
                                                              uint32_t* __restrict__ hist,
                                                              int32_t* __restrict__ blk_cnt) {
-  using D = Digit<kBits>;
+  using D = Digit<kSortBits>;
   constexpr int kKeys = kPer * kSortThreads;
   __shared__ uint32_t h[D::kBins];
   __shared__ uint32_t cnt[kPer][kSortWaves];
@@ -1029,35 +1014,32 @@ void launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s) {
   hipLaunchKernelGGL(k_fill_i32, dim3((unsigned)blocks), dim3(256), 0, s, p, n, v);
 }
 
-template <int kBits, int kPer>
+template <int kPer>
 static void seg_pass(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout, const SegTable& seg,
                      int blocks, int shift, uint32_t* hist, bool last, hipStream_t s) {
   const dim3 grid(blocks), block(kSortThreads);
-  hipLaunchKernelGGL((k_seg_hist<kBits, kPer>), grid, block, 0, s, kin, seg, shift, hist);
+  hipLaunchKernelGGL(k_seg_hist<kPer>, grid, block, 0, s, kin, seg, shift, hist);
   const int32_t* none = nullptr;
   auto scatter = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, block, 0, s, kin, vin, kout, vout, seg, shift, (const uint32_t*)hist, none);
   };
   if (last)
-    scatter(k_seg_scatter<kBits, kPer, false, true>);
+    scatter(k_seg_scatter<kPer, false, true>);
   else
-    scatter(k_seg_scatter<kBits, kPer, false, false>);
+    scatter(k_seg_scatter<kPer, false, false>);
 }
 
-// The depth sort of larger renders: three passes end in (k1, v1), four in (k0, v0).
-template <int kBits, int kPer>
+// The depth sort of larger renders; the order ends in v0.
+template <int kPer>
 static void depth_passes(const BinLaunch& b, const SegTable& seg, hipStream_t s) {
   const dim3 grid(b.sort_blocks), block(kSortThreads);
-  hipLaunchKernelGGL((k_depth_prep<kBits, kPer>), grid, block, 0, s, b.jobs, seg,
-                     reinterpret_cast<const float4*>(b.rec), b.tiles, b.k0, b.v0, b.hist, b.blk_cnt);
-  hipLaunchKernelGGL((k_seg_scatter<kBits, kPer, true, false>), grid, block, 0, s, (const uint32_t*)b.k0,
+  hipLaunchKernelGGL(k_depth_prep<kPer>, grid, block, 0, s, b.jobs, seg, reinterpret_cast<const float4*>(b.rec),
+                     b.tiles, b.k0, b.v0, b.hist, b.blk_cnt);
+  hipLaunchKernelGGL((k_seg_scatter<kPer, true, false>), grid, block, 0, s, (const uint32_t*)b.k0,
                      (const uint32_t*)b.v0, b.k1, b.v1, seg, 0, (const uint32_t*)b.hist, (const int32_t*)b.blk_cnt);
-  constexpr int kPasses = kBits == 11 ? 3 : 4;
-  for (int p = 1; p < kPasses; ++p) {
-    const bool odd = p & 1;
-    seg_pass<kBits, kPer>(odd ? b.k1 : b.k0, odd ? b.v1 : b.v0, odd ? b.k0 : b.k1, odd ? b.v0 : b.v1, seg,
-                          b.sort_blocks, p * kBits, b.hist, p == kPasses - 1, s);
-  }
+  seg_pass<kPer>(b.k1, b.v1, b.k0, b.v0, seg, b.sort_blocks, 8, b.hist, false, s);
+  seg_pass<kPer>(b.k0, b.v0, b.k1, b.v1, seg, b.sort_blocks, 16, b.hist, false, s);
+  seg_pass<kPer>(b.k1, b.v1, b.k0, b.v0, seg, b.sort_blocks, 24, b.hist, true, s);
 }
 
 void launch_bin_sort(const BinLaunch& b, hipStream_t s) {
@@ -1082,18 +1064,12 @@ void launch_bin_sort(const BinLaunch& b, hipStream_t s) {
       small(k_depth_sort_small<11, 4>);
     else
       small(k_depth_sort_small<11, 8>);
-  } else if (b.max_items <= kWideItems) {
-    if (b.sort_per == 3)
-      depth_passes<11, 3>(b, seg, s);
-    else
-      depth_passes<11, 4>(b, seg, s);
-    order = b.v1;
-  } else if (b.sort_per == 2) {
-    depth_passes<8, 2>(b, seg, s);
-  } else if (b.sort_per == 3) {
-    depth_passes<8, 3>(b, seg, s);
   } else {
-    depth_passes<8, 4>(b, seg, s);
+    const auto passes = b.sort_per == 1   ? depth_passes<1>
+                        : b.sort_per == 2 ? depth_passes<2>
+                        : b.sort_per == 3 ? depth_passes<3>
+                                          : depth_passes<4>;
+    passes(b, seg, s);
   }
   const dim3 work(8 * ((b.units + 7) / 8));
   if (b.units > 0)
@@ -1124,7 +1100,7 @@ void launch_bin_sort(const BinLaunch& b, hipStream_t s) {
 
 void launch_seg_pass(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout, const SegTable& seg,
                      int blocks, int per, int shift, uint32_t* hist, bool last, hipStream_t s) {
-  const auto pass = per == 2 ? seg_pass<8, 2> : per == 3 ? seg_pass<8, 3> : seg_pass<8, 4>;
+  const auto pass = per == 1 ? seg_pass<1> : per == 2 ? seg_pass<2> : per == 3 ? seg_pass<3> : seg_pass<4>;
   pass(kin, vin, kout, vout, seg, blocks, shift, hist, last, s);
 }
 }  // namespace ls

@@ -14,7 +14,6 @@ constexpr int kSortThreads = 1024;  // radix sort block
 constexpr int kSortPerMax = 4;      // most keys per thread of it
 constexpr int kRankItems = 16384;              // items up to which a render's depths are ranked by comparison,
 constexpr int64_t kRankPairs = 1 << 26;        // if all renders of a batch make up to so many pairs
-constexpr int kWideItems = 65536;              // items up to which a larger render's depth sort takes 11-bit digits
 constexpr int kWindowTiles = 4096;  // most tiles of a binning window
 constexpr int kGradStride = 16;     // floats per item in the accumulator: a 64-byte line each
 constexpr int kGrad2D = 10;         // sums of ds (dx, dy, dx^2, dx dy, dy^2, 1), dz dr dg db

@@ -65,23 +65,27 @@ struct SegTable {
   int32_t* len;            // [S]
 };
 inline int sort_blocks_of(int64_t n, int per) { return (int)((n + per * kSortThreads - 1) / (per * kSortThreads)); }
-// Keys per thread of a sort block, 2 to 4, for `blocks(per)` blocks in all: the
-// fewest with which all blocks are on the chip at once (two on each of 256
-// CUs), since short blocks use more CUs and a second round costs a block's
-// whole time; three at least with 11-bit digits, whose bins are most of a
-// block's work.  Binning with 2, 3 and 4: 97k items 77.5, 80.5 and 84.2 us (48,
-// 32 and 24 blocks), 200k 102, 105 and 107, 3 x 80k 90, 92 and 96; 8 x 150k 210
-// (586 blocks), 192 (391) and 200; 16 x 135k 172, 154 (704) and 148; with 11-bit
-// digits 21k + 17k twice 73, 71 and 74, 40k 76.6, 74.8 and 75.0.
+// Keys per thread of a sort block, 1 to 4, for segments of up to max_n keys in
+// `blocks(per)` blocks in all.  Short blocks use more CUs, but every block adds
+// up its segment's counts, 64 blocks' in one round of loads, and a second round
+// of blocks costs a whole block's time.  So: one key if the largest segment has
+// up to 64 such blocks and each has a CU to itself, else the fewest from two with
+// which all blocks are on the chip at once (two on each of 256 CUs).  Binning of
+// renders with 1 and 2 keys: 17k items 56.7 and 61.2 us, 65k 68.1 and 70.6, 97k
+// 77.3 and 76.7, 200k 109 and 103, 10 x 17k (170 blocks) 81.4 and 83.6, 16 x 20k
+// (320) 98.8 and 92.4, 3 x 80k 90.1 and 88.1; with 2, 3 and 4: 97k 77.5, 80.5
+// and 84.2, 200k 102, 105 and 107, 3 x 80k 90, 92 and 96, 8 x 150k 210 (586
+// blocks), 192 (391) and 200, 16 x 135k 172, 154 (704) and 148.
 template <class Blocks>
-inline int sort_per(bool wide, const Blocks& blocks) {
-  constexpr int kResident = 512;
-  int per = wide ? 3 : 2;
+inline int sort_per(int64_t max_n, const Blocks& blocks) {
+  constexpr int kRound = 64, kCus = 256, kResident = 2 * kCus;
+  if (sort_blocks_of(max_n, 1) <= kRound && blocks(1) <= kCus) return 1;
+  int per = 2;
   while (per < kSortPerMax && blocks(per) > kResident) ++per;
   return per;
 }
-// Words of the digit histograms of `blocks` sort blocks (wide: 11-bit digits).
-int64_t seg_hist_words(int blocks, bool wide);
+// Words of the digit histograms of `blocks` sort blocks.
+int64_t seg_hist_words(int blocks);
 // One stable pass over the 8-bit digit at `shift` (binning.hip), from
 // (kin, vin) to (kout, vout); last: kout is not written.
 void launch_seg_pass(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout, const SegTable& seg,

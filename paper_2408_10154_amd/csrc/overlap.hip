@@ -490,7 +490,7 @@ struct OvLayout {
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 static int ov_sort_blocks(int np, int nq, int per) { return sort_blocks_of(np, per) + sort_blocks_of(nq, per); }
 static int ov_sort_per(int np, int nq) {
-  return sort_per(false, [&](int per) { return ov_sort_blocks(np, nq, per); });
+  return sort_per(std::max(np, nq), [&](int per) { return ov_sort_blocks(np, nq, per); });
 }
 static OvLayout ov_layout(int np, int nq) {
   OvLayout L{};
@@ -509,7 +509,7 @@ static OvLayout ov_layout(int np, int nq) {
   L.idx_a = take(4 * both);
   L.code_b = take(4 * both);
   L.idx_b = take(4 * both);
-  L.hist = take(4 * (size_t)seg_hist_words(ov_sort_blocks(np, nq, ov_sort_per(np, nq)), false));
+  L.hist = take(4 * (size_t)seg_hist_words(ov_sort_blocks(np, nq, ov_sort_per(np, nq))));
   for (int s = 0; s < 2; ++s) {
     const int n = s ? nq : np;
     const int nleaf = (n + kOvLeaf - 1) / kOvLeaf, nsuper = (nleaf + kOvSuper - 1) / kOvSuper;

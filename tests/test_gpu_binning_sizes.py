@@ -80,7 +80,8 @@ def test_lists_equal_the_oracle(gpu, sizes, image, culled):
 @pytest.mark.parametrize("sizes,culled", [
     ([65537], 0.9), ([131072, 131073], 0.9), ([300000], 0.6),  # two keys a thread; more than 64 blocks' counts added up
     ([70000] * 16, 0.97), ([70000] * 24, 0.97),                # three, four
-    ([17000] * 85, 0.97), ([17000] * 86, 0.97),                # three, four with 11-bit digits
+    ([17000] * 85, 0.97), ([17000] * 86, 0.97),                # three, four in many small renders
+    ([65536], 0.2), ([17408, 0, 1, 16385], 0.2), ([17408] * 15, 0.9), ([17409] * 15, 0.9),  # one; the last not
 ])
 def test_sort_blocks_of_each_size(gpu, sizes, culled):
     test_lists_equal_the_oracle(gpu, sizes, SMALL, culled)
