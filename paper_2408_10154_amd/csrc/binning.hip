@@ -16,9 +16,9 @@
 //
 // Every instance is written once, and no (tile, item) pairs are sorted: the
 // pair sort it replaces moved each instance three times in 8 launches (all of
-// binning: 200k items, 1200 x 680, 143 -> 98 us and 22 launches -> 11; eight
-// renders of 150k items, 640 x 480, 157 -> 118 us; 23k items, 317 x 211, 90 ->
-// 60 us and 8 launches; 4,096 items, 160 x 120, 81 -> 29 us and 3 launches).
+// binning: 200k items, 1200 x 680, 143 -> 91 us and 22 launches -> 11; eight
+// renders of 150k items, 640 x 480, 157 -> 109 us; 23k items, 317 x 211, 90 ->
+// 52 us and 10 launches; 4,096 items, 160 x 120, 81 -> 29 us and 3 launches).
 // What is left is bound by latency: launches of 3 to 10 us on tens to hundreds
 // of blocks, each a chain of dependent loads.
 #include "common.h"
