@@ -344,9 +344,11 @@ __global__ __launch_bounds__(kSortThreads) void k_depth_prep(const JobDev* __res
 // A key costs a wave a compare and an add with carry, and the keys of 4,096 items
 // 2,000 cycles; the rest is the launch and two dependent loads.  All of binning
 // in a graph, with this and with one block sorting each render in LDS: 1,500
-// items 28 and 32 us, 4,096 33 and 38 us, 8,192 43 and 53 us, 16,000 56 and 76
-// us.  Batches do better with the LDS sort from kRankPairs pairs on: 4 renders
-// of 3,000 items 30 and 34 us, 4 of 8,000 54 and 53 us, 8 of 5,000 53 and 49 us.
+// items 28 and 32 us, 4,096 33 and 38 us, 8,192 43 and 53 us; with this and with
+// the radix passes: 7,000 35 and 51 us, 12,000 47 and 56 us, 16,384 55.5 and 56.5
+// us, where the line lies.  Batches do better with the LDS sort from kRankPairs pairs on: 4 renders
+// of 3,000 items 30 and 34 us, 4 of 8,000 54 and 53 us, 8 of 5,000 53 and 49 us
+// (and the radix passes 4 of 8,000 59 us, 16 of 8,192 82 against 72 us).
 constexpr int kRankWaves = 16;
 
 // n += the number of k's components that are below key (kEqual: or equal).
