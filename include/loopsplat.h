@@ -265,8 +265,8 @@ typedef struct {
  *     be zero before the first backward on a workspace and
  *     ls_render_bwd_project clears it again;
  *   - pose only (grads == NULL, LS_BWD_POSE_ONLY): each Gaussian's pose
- *     Jacobian is applied inside the band and a 12-value partial is written
- *     per band, summed per render in a fixed order: no atomics, bit-identical
+ *     Jacobian is applied inside the tile and a 12-value partial is written
+ *     per tile, summed per render in a fixed order: no atomics, bit-identical
  *     results that do not depend on the other renders of the batch.
  * Errors: LS_ERR_INVALID. */
 ls_status ls_render_bwd(const ls_batch* b, const float* pose, const ls_projected* p, const ls_bins* bins,
@@ -276,7 +276,7 @@ ls_status ls_render_bwd(const ls_batch* b, const float* pose, const ls_projected
 /* First half of ls_render_bwd: per 8x8 band, back-to-front recomputation and
  * the per-(item, band) sums behind dL/d(u, v, conic, opacity, z, rgb) (one kernel).
  * flags: LS_BWD_POSE_ONLY keeps only what a pose correction depends on (u, v,
- * conic, z) and turns it into per-band pose partials (`pose` may be NULL =
+ * conic, z) and turns it into per-tile pose partials (`pose` may be NULL =
  * identity). */
 #define LS_BWD_POSE_ONLY 1u
 ls_status ls_render_bwd_tiles(const ls_batch* b, const float* pose, const ls_projected* p, const ls_bins* bins,
@@ -311,7 +311,7 @@ ls_status ls_loss_l1_tiles(const ls_batch* b, const ls_bins* bins, float* loss, 
 
 /* Second half of ls_render_bwd: chains the accumulated image-space gradients
  * through the EWA projection to the Gaussian parameters and the pose (full
- * mode), or sums the per-band pose partials of each render (LS_BWD_POSE_ONLY;
+ * mode), or sums the per-tile pose partials of each render (LS_BWD_POSE_ONLY;
  * grads must be NULL). */
 ls_status ls_render_bwd_project(const ls_batch* b, const float* pose, const ls_projected* p, const ls_bins* bins,
                                 const ls_gaussian_grads* grads, float* pose_grad, uint32_t flags, hipStream_t s);

@@ -64,7 +64,7 @@ ls_status overlap_check_args(const float* p_mean, int32_t np, const float* q_mea
 namespace {
 
 struct Layout {
-  size_t k0, v0, k1, v1, hist, blk_cnt, kept, cnt, tile_total, tile_before, groups, band_part, pose_part, loss_part, used, g2d,
+  size_t k0, v0, k1, v1, hist, blk_cnt, kept, cnt, tile_total, tile_before, groups, tile_part, pose_part, loss_part, used, g2d,
       total;
 };
 
@@ -89,7 +89,7 @@ Layout layout_of(const ls_batch* b, int64_t cap) {
   L.tile_total = take(4 * T);
   L.tile_before = take(4 * T);
   L.groups = take(8 * ((T + 63) / 64 + 1));
-  L.band_part = take(4 * 4 * (size_t)kPoseAcc * std::max(b->T, 1));  // a row per 8x8 band
+  L.tile_part = take(4 * (size_t)kPoseAcc * std::max(b->T, 1));
   L.pose_part = take(4 * (size_t)kPoseAcc * std::max(b->nblk_items, 1));
   L.loss_part = take(4 * 8 * (size_t)std::max(b->T, 1));  // per 8x8 band {L1 sum, pixels in Omega}
   L.used = take(8 * 4 * (size_t)used_slots(cap, b->T));  // per band a row of "used" bits, 64 entries a word
@@ -419,7 +419,7 @@ ls_status render_bwd_pose_l1(const ls_batch* b, const float* pose, const ls_proj
   launch_composite_bwd(b->jobs_d, b->tile_off_d, b->R, b->T, p->rec, p->aux, pose, bins->item, bins->range,
                        at<uint64_t>(bins->work, L.used), used_slots(bins->capacity, b->T), zero,
                        fwd->T_final, fwd->n_last, nullptr, nullptr, nullptr, scale, at<float>(bins->work, L.g2d),
-                       at<float>(bins->work, L.band_part), 1, s, &l1);
+                       at<float>(bins->work, L.tile_part), 1, s, &l1);
   return hip_check("pose-only backward with the L1 gradient");
 }
 
@@ -429,7 +429,7 @@ ls_status pose_reduce_adam(const ls_batch* b, const ls_bins* bins, const PoseAda
   ls_status st;
   if ((st = check_bins(b, bins)) || (st = ensure_device(b))) return st;
   const Layout L = layout_of(b, bins->capacity);
-  launch_pose_reduce_adam(b->jobs_d, b->R, at<float>(bins->work, L.band_part), a, count, sticky, s);
+  launch_pose_reduce_adam(b->jobs_d, b->R, at<float>(bins->work, L.tile_part), a, count, sticky, s);
   return hip_check("pose reduction and Adam step");
 }
 
@@ -589,7 +589,7 @@ ls_status ls_render_bwd_tiles(const ls_batch* b, const float* pose, const ls_pro
   launch_composite_bwd(b->jobs_d, b->tile_off_d, b->R, b->T, p->rec, p->aux, pose, bins->item, bins->range,
                        at<uint64_t>(bins->work, L.used), used_slots(bins->capacity, b->T),
                        bg ? bg : zero, fwd->T_final, fwd->n_last, up->rgb, up->depth, up->alpha, up->scale,
-                       at<float>(bins->work, L.g2d), at<float>(bins->work, L.band_part),
+                       at<float>(bins->work, L.g2d), at<float>(bins->work, L.tile_part),
                        (flags & LS_BWD_POSE_ONLY) ? 1 : 0, s);
   return hip_check("ls_render_bwd_tiles");
 }
@@ -610,7 +610,7 @@ ls_status ls_render_bwd_tiles_l1(const ls_batch* b, const float* pose, const ls_
   launch_composite_bwd(b->jobs_d, b->tile_off_d, b->R, b->T, p->rec, p->aux, pose, bins->item, bins->range,
                        at<uint64_t>(bins->work, L.used), used_slots(bins->capacity, b->T),
                        bg ? bg : zero, fwd->T_final, fwd->n_last, nullptr, nullptr, nullptr, inv_count,
-                       at<float>(bins->work, L.g2d), at<float>(bins->work, L.band_part),
+                       at<float>(bins->work, L.g2d), at<float>(bins->work, L.tile_part),
                        (flags & LS_BWD_POSE_ONLY) ? 1 : 0, s, &l1);
   return hip_check("ls_render_bwd_tiles_l1");
 }
@@ -632,7 +632,7 @@ ls_status ls_render_bwd_project(const ls_batch* b, const float* pose, const ls_p
   const Layout L = layout_of(b, bins->capacity);
   if (flags & LS_BWD_POSE_ONLY) {
     if (grads) return fail(LS_ERR_INVALID, "pose-only backward computes no Gaussian gradients");
-    if (pose_grad) launch_pose_reduce_bands(b->jobs_d, b->R, pose, at<float>(bins->work, L.band_part), pose_grad, s);
+    if (pose_grad) launch_pose_reduce_tiles(b->jobs_d, b->R, pose, at<float>(bins->work, L.tile_part), pose_grad, s);
     return hip_check("ls_render_bwd_project");
   }
   if (pose_grad && !pose) return fail(LS_ERR_INVALID, "pose_grad needs the pose it is taken at");

@@ -109,6 +109,8 @@ __device__ __forceinline__ Rect tile_rect(float u, float v, int r, int TX, int T
 // per-pixel multiply before the exponential.
 constexpr float kHalfLog2e = 0.72134752044448170368f;  // log2(e) / 2
 constexpr float kLog2e = 1.44269504088896340736f;
+constexpr float kLn2 = 0.69314718055994530942f;  // factors back to (A, B, C)
+constexpr float kTwoLn2 = 1.38629436111989061883f;
 
 // The staged record also carries, in slot b.z (the depth, which stays with
 // the colour), the bits of the

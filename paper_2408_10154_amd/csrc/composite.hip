@@ -415,8 +415,8 @@ __device__ __forceinline__ float step_alpha(const float4& a, const float4& b, in
   return (__float_as_int(b.w) < nl) & composited(sl, b.z) ? fminf(LS_ALPHA_MAX, G) : 0.f;
 }
 
-// The band of a 64-thread block: unit = 4 tile + band, lane l its pixel
-// (l & 7, l >> 3).
+// The band of a wave: unit = 4 tile + band, lane l its pixel (l & 7, l >> 3), or
+// (l >> 3, l & 7) with kColumns.
 struct BandCtx {
   int r, tile, band;
   int x, y;    // pixel of this lane
@@ -425,7 +425,8 @@ struct BandCtx {
   int64_t pix;  // pixel index in the image arrays (if inside)
 };
 
-__device__ __forceinline__ BandCtx band_ctx(const JobDev* jobs, const int32_t* tile_off, int R, int unit) {
+template <bool kColumns>
+__device__ __forceinline__ BandCtx band_ctx(const JobDev* jobs, const int32_t* tile_off, int R, int unit, int lane) {
   BandCtx c;
   c.tile = unit >> 2;
   c.band = unit & 3;
@@ -433,11 +434,10 @@ __device__ __forceinline__ BandCtx band_ctx(const JobDev* jobs, const int32_t* t
   const JobDev& J = jobs[c.r];
   const int lt = c.tile - J.tile_off;
   const int ty = lt / J.TX, tx = lt - ty * J.TX;
-  const int lane = threadIdx.x;
   c.x0 = tx * kTile + 8 * (c.band & 1);
   c.y0 = ty * kTile + 8 * (c.band >> 1);
-  c.x = c.x0 + (lane & 7);
-  c.y = c.y0 + (lane >> 3);
+  c.x = c.x0 + (kColumns ? lane >> 3 : lane & 7);
+  c.y = c.y0 + (kColumns ? lane & 7 : lane >> 3);
   c.inside = c.x < J.W && c.y < J.H;
   c.pix = J.pix_off + (int64_t)c.y * J.W + c.x;
   return c;
@@ -505,12 +505,11 @@ __device__ __forceinline__ void wave_sync() {
 // the band's centre, shifted to the splat's) before the eight rows of an entry
 // are added across lanes.  So the products are formed once per lane for eight
 // pixels and one cross-lane reduction serves eight entries.  An entry costs
-// about 22 VALU instructions in the walk and 13 (full) or 8 (pose only) in the
-// sums; with ten (six) products a pixel and a reduction of as many values an
-// entry it was 67 (53).  VALU bound: 200k Gaussians at 1200x680, full, 218 ->
-// 120 us (with the atomics below); 97k at 640x480, pose only, 93 -> 60 us; 16
-// views of 640x480 of 150k/120k, pose only, 470 -> 366 us (115, 55 and 290 us
-// since the XCDs take turns, see xcd_turns).
+// about 22 VALU instructions in the walk and 13 in the sums; with ten products a
+// pixel and a reduction of as many values an entry it was 67.  VALU bound: 200k
+// Gaussians at 1200x680, full, 218 -> 120 us (with the atomics below; 115 us
+// since the XCDs take turns, see xcd_turns).  (The pose-only sums go by pixel
+// columns, with every product rounded: see column_sums.)
 // (FP32 matrix products that contract the same rows with the pixel factors
 // cost more: twice the vector rate, but 10 of 32 result columns are of use,
 // and they do not overlap with the SIMD's vector instructions.)
@@ -519,14 +518,23 @@ __device__ __forceinline__ void wave_sync() {
 constexpr int kBatch = 32;        // entries staged per round
 constexpr int kRowStride = 68;    // floats per LDS row of 64 pixels: 16-byte aligned, rows 4 banks apart
 constexpr int kRing = 128;        // positions waiting to be staged: < kBatch left over + 64 new
+constexpr int kPoseRow = 6;       // pose only: sums of ds dx, ds dy, ds dx^2, ds dx dy, ds dy^2, wgt gD
 using f32x4 = __attribute__((ext_vector_type(4))) float;
 
 struct BandLds {
   float4 s0[kBatch], s1[kBatch], s2[kBatch];  // (u, v, hA, B), (hC, opacity, bound, list position), (r, g, b, z)
   float rows[16 * kRowStride];  // of eight entries: ds, then wgt
   int32_t ring[kRing];
+};
+struct FullBandLds : BandLds {
   int32_t item[kBatch];
 };
+constexpr int kPoseRound = 256;  // most list positions per round
+struct PoseBandLds : BandLds {
+  float late[kBatch];         // red of the entries that take green first (s2 holds 0 there)
+  uint8_t place[kPoseRound];  // of the round's positions among the round's sums, or kNoPlace
+};
+constexpr uint8_t kNoPlace = 255;
 
 // The upstream gradients of pixel row y = lane & 7 of the band, by way of the
 // wave's LDS.
@@ -552,44 +560,66 @@ __device__ __forceinline__ void row_factors(float* rows, int lane, const float (
 // (padded with entries that composite nowhere) and returns how many there are.
 struct BandList {
   const uint64_t* used;
+  int visited;      // entries the band's pixels visited: none from there on is listed
   int left;         // words of the list not yet loaded
   uint64_t mine;    // this lane's word of the current 64
   uint64_t busy;    // which of the current 64 words have bits left to expand
   int base;         // word index of lane 0's word
   int head, have;
   bool clamp;       // some staged entry's opacity reaches the 0.99 clamp
+  uint32_t odd;     // kPose: whether the last entry taken was its chunk's 2nd, 4th, ...
 
-  __device__ __forceinline__ BandList(const uint64_t* u, int visited)
-      : used(u), left((visited + 63) >> 6), mine(0ull), busy(0ull), base(0), head(0), have(0), clamp(false) {}
+  __device__ __forceinline__ BandList(BandLds& L, const uint64_t* u, int n)
+      : used(u), visited(n), left((n + 63) >> 6), mine(0ull), busy(0ull), base(0), head(0), have(0), clamp(false),
+        odd(0u) {
+    if ((threadIdx.x & 63) == 0) L.ring[kRing - 1] = 1 << 30;  // before the first: of no chunk
+  }
 
-  __device__ __forceinline__ int take(BandLds& L, int lane, int start, const int32_t* items, const float4* rec) {
+  // kPose: of the entries from position `lo` on, which get the places from
+  // `place` on.  Chunks of 64 positions end at `top` (the lowest one at 0), and a
+  // chunk's 2nd, 4th, ... entry keeps its red apart.
+  template <bool kPose, class Lds>
+  __device__ __forceinline__ int take(Lds& L, int lane, int start, const int32_t* items, const float4* rec,
+                                      int lo = 0, int top = 0, int place = 0) {
     while (have < kBatch && (busy != 0ull || left > 0)) {
       if (busy == 0ull) {  // the next 64 words, the last one in lane 0
         base = left - 1;
         const int i = base - lane;
         mine = i >= 0 ? used[i] : 0ull;
+        if (64 * i + 64 > visited) mine &= ~0ull >> (64 * i + 64 - visited);  // (i < ceil(visited / 64): by 63 at most)
         busy = __ballot(mine != 0ull);
         left = max(left - 64, 0);
         continue;
       }
       const int at = (int)__builtin_ctzll(busy);
       busy &= busy - 1ull;
-      const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mine, at);
-      const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mine >> 32), at);
-      const uint64_t wd = ((uint64_t)hi << 32) | lo;
+      const uint32_t w0 = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mine, at);
+      const uint32_t w1 = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mine >> 32), at);
+      const uint64_t wd = ((uint64_t)w1 << 32) | w0;
       have += (int)__popcll(wd);
       // the word's highest bit comes first
-      const uint32_t below = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+      const uint32_t below = __builtin_amdgcn_mbcnt_hi(w1, __builtin_amdgcn_mbcnt_lo(w0, 0u));
       if (__builtin_amdgcn_inverse_ballot_w64(wd))
         L.ring[(head + have - 1 - (int)below) & (kRing - 1)] = 64 * (base - at) + lane;
     }
     wave_sync();
-    const int n = min(have, kBatch);
+    const int pos = lane < min(have, kBatch) ? L.ring[(head + lane) & (kRing - 1)] : -1;
+    const int n = (int)__popcll(__ballot(pos >= lo));  // (descending: the first n)
+    const int chunk = (top - 1 - pos) >> 6;
+    uint32_t late = 0u;
+    if constexpr (kPose) {
+      // (the ring still holds the entry before the first)
+      const int before = L.ring[(head + lane - 1) & (kRing - 1)];
+      const uint32_t first = (uint32_t)__ballot(lane < kBatch && chunk != ((top - 1 - before) >> 6));
+      const uint32_t upto = first & (uint32_t)((2ull << lane) - 1ull);
+      const int since = upto != 0u ? lane - (31 - __builtin_clz(upto)) : lane + 1 + (int)odd;
+      late = (uint32_t)since & 1u;
+      odd = n > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)late, n - 1) : odd;
+    }
     bool sat = false;
     if (lane < kBatch) {
       float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a, c = a;
       if (lane < n) {
-        const int pos = L.ring[(head + lane) & (kRing - 1)];
         const int it = items[start + pos];
         a = rec[(int64_t)it * 3];
         b = rec[(int64_t)it * 3 + 1];
@@ -597,7 +627,14 @@ struct BandList {
         c.w = b.z;
         stage_conic(a, b);
         b.w = __int_as_float(pos);
-        L.item[lane] = it;
+        if constexpr (kPose)
+          L.place[64 * chunk + pos - max(top - 64 * (chunk + 1), 0)] = (uint8_t)(place + lane);
+        else
+          L.item[lane] = it;
+      }
+      if constexpr (kPose) {
+        L.late[lane] = late ? c.x : 0.f;
+        c.x = late ? 0.f : c.x;
       }
       L.s0[lane] = a;
       L.s1[lane] = b;
@@ -612,18 +649,21 @@ struct BandList {
   }
 };
 
-// Eight steps of the walk, staged entries e0 .. e0 + 7: ds and wgt of entry
-// e0 + i at every pixel go to rows i and 8 + i.  Branch-free (padding entries
-// composite nowhere).  clamp: some staged entry's opacity reaches 0.99 (an
-// opacity below it bounds alpha, and the clamp can not act).
+// Eight steps of the walk, staged entries e0 .. e0 + 7: ds and wgt (kPose: wgt
+// gD) of entry e0 + i at every pixel go to rows i and 8 + i.  Branch-free (padding
+// entries composite nowhere).  clamp: some staged entry's opacity reaches 0.99 (an
+// opacity below it bounds alpha, and the clamp can not act).  kPose rounds ds as
+// (T (v - acc)) alpha, and late[e] is the red that entry e adds after its green.
+template <bool kPose>
 __device__ __forceinline__ void walk_eight(BandLds& L, int lane, int e0, bool clamp, float fx, float fy,
-                                           BwdPixel& px) {
+                                           BwdPixel& px, const float* late) {
 #pragma unroll
   for (int h = 0; h < 8; h += 4) {
     const float4 c = L.s2[e0 + h + (lane & 3)];
     f32x4 v = {0.f, 0.f, 0.f, 0.f};
     v = __builtin_amdgcn_mfma_f32_4x4x1f32(c.x, px.gR, v, 0, 0, 0);
     v = __builtin_amdgcn_mfma_f32_4x4x1f32(c.y, px.gG, v, 0, 0, 0);
+    if (kPose) v = __builtin_amdgcn_mfma_f32_4x4x1f32(late[e0 + h + (lane & 3)], px.gR, v, 0, 0, 0);
     v = __builtin_amdgcn_mfma_f32_4x4x1f32(c.z, px.gB, v, 0, 0, 0);
     v = __builtin_amdgcn_mfma_f32_4x4x1f32(c.w, px.gD, v, 0, 0, 0);
     // what does not depend on the earlier steps first, then the chain
@@ -644,8 +684,8 @@ __device__ __forceinline__ void walk_eight(BandLds& L, int lane, int e0, bool cl
       px.T *= rc[i];
       const float wgt = al[i] * px.T, d = v[i] - px.acc;
       px.acc = fmaf(al[i], d, px.acc);
-      L.rows[(h + i) * kRowStride + lane] = -wgt * d;
-      L.rows[(8 + h + i) * kRowStride + lane] = wgt;
+      L.rows[(h + i) * kRowStride + lane] = kPose ? (px.T * -d) * al[i] : -wgt * d;
+      L.rows[(8 + h + i) * kRowStride + lane] = kPose ? wgt * px.gD : wgt;
     }
     if (clamp) {  // uniform
 #pragma unroll
@@ -710,10 +750,10 @@ __device__ __forceinline__ int wave_max_i(int v) {
 }
 
 // The band's L1 loss partial {sum, count} (L1 targets with loss_part).
-__device__ __forceinline__ void band_loss(const L1Targets& l1, const BwdPixel& px, int unit) {
+__device__ __forceinline__ void band_loss(const L1Targets& l1, const BwdPixel& px, int unit, int lane) {
   if (!l1.loss_part) return;
   const float s = wave_sum(px.lsum), n = wave_sum(px.lcnt);
-  if (threadIdx.x == 0) reinterpret_cast<float2*>(l1.loss_part)[unit] = make_float2(s, n);
+  if (lane == 0) reinterpret_cast<float2*>(l1.loss_part)[unit] = make_float2(s, n);
 }
 
 // Full mode: the ten sums of each (entry, band) are added to the item's
@@ -731,16 +771,16 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
     const float* __restrict__ fwd_T, const int32_t* __restrict__ fwd_n, const float* __restrict__ up_rgb,
     const float* __restrict__ up_depth, const float* __restrict__ up_alpha, const float* __restrict__ up_scale,
     float* __restrict__ g2d, L1Targets l1) {
-  __shared__ __attribute__((aligned(16))) BandLds L;
+  __shared__ __attribute__((aligned(16))) FullBandLds L;
   const int unit = xcd_turns<64>(blockIdx.x, 4 * T_total);
   if (unit >= 4 * T_total) return;
   const int lane = threadIdx.x;
-  const BandCtx c = band_ctx(jobs, tile_off, R, unit);
+  const BandCtx c = band_ctx<false>(jobs, tile_off, R, unit, lane);
   const JobDev& J = jobs[c.r];
-  const int start = range[2 * c.tile];
+  const int start = range[2 * c.tile], end = range[2 * c.tile + 1];
   BwdPixel px = bwd_pixel(c, J, bg0, bg1, bg2, fwd_T, fwd_n, up_rgb, up_depth, up_alpha, up_scale, l1);
-  band_loss(l1, px, unit);
-  BandList list(used + c.band * ustride + (start >> 6) + c.tile, wave_max_i(px.nl));
+  band_loss(l1, px, unit, lane);
+  BandList list(L, used + c.band * ustride + (start >> 6) + c.tile, min(wave_max_i(px.nl), end - start));
   if (list.left == 0) return;
   const float fx = (float)c.x + 0.5f, fy = (float)c.y + 0.5f;
   const int y = lane & 7;
@@ -751,10 +791,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
   const bool hi = y & 4, b2 = y & 2, b1 = y & 1;
   const int k0 = 4 * (y & 1) + (y & 2) + (y >> 2);  // the value that this lane ends with
   for (;;) {
-    const int n = list.take(L, lane, start, items, rec);
+    const int n = list.take<false>(L, lane, start, items, rec);
     if (n == 0) break;
     for (int e0 = 0; e0 < n; e0 += 8) {
-      walk_eight(L, lane, e0, list.clamp, fx, fy, px);
+      walk_eight<false>(L, lane, e0, list.clamp, fx, fy, px, nullptr);
       float S[kGrad2D];
       row_sums(L, lane, e0, bx, ry, f, S);
       // sums over the entry's eight lanes, halving the lanes that hold a
@@ -784,98 +824,312 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
 }
 
 // Pose-only mode (registration, tracking): only the gradients a pose
-// correction acts through (u, v, conic, depth) are formed.  Two batches of
-// entries fill the wave's lanes, one per lane; then every lane applies the
-// pose Jacobian of its Gaussian, and the wave's sums are added, in a fixed
-// order, to the band's running sum, written once as the band's 12-value
-// partial: no atomics, so the pose gradient is deterministic and independent
-// of the other renders.
+// correction acts through (u, v, conic, depth) are formed, one block per tile, a
+// wave per band.  The waves walk their bands over a round of list positions
+// (from the tile's last visited one down) and leave each entry's six sums in LDS;
+// then lane j of wave c adds up the bands of the round's position j of chunk c (64
+// positions), turns the sums into the image-space gradients and applies the pose
+// Jacobian of its Gaussian, and the chunks' sums are added, in a fixed order, to
+// the tile's running sum, written once as the tile's 12-value partial: no atomics,
+// so the pose gradient is deterministic and independent of the other renders.
+//
+// Every rounding is fixed: a registration follows its pose gradients for a
+// hundred Adam steps, whose quotient turns a changed last bit of a component that
+// cancels into another pose, and a view's residual moves by up to 1e-4 of itself.
+// Products are therefore rounded per pixel, and an entry's pixels summed as a
+// tree: rows y and y + 4, y + 2, y + 1, then columns x and 7 - x, x ^ 1, x ^ 2;
+// then its bands in order, the chunk's entries by wave_sums, and four chunks as
+// (0 + 1) + (2 + 3).  The colour term v is the FMA chain red, green, blue, depth
+// for a band's 1st, 3rd, ... composited entry of a chunk, and green, red, blue,
+// depth for its 2nd, 4th, ...
+//
+// An entry costs about 23 VALU instructions in the walk and 14 in the sums (53
+// with the products in the walk and a reduction of six values an entry).  Bound
+// by their issue and by the waves that wait for the tile's slowest at a round's
+// end: 16 views of 640x480 of 150k/120k 472 -> 374 us, 97k at 640x480 92 -> 69 us.
+// What a round costs besides its entries is the larger part of the wait, so rounds
+// are long: 256 positions where each band's entries fit kPosePlaces places (39 KB
+// of LDS, four blocks on a CU), else 128, which always fit.  (One place per
+// position: rounds of 128 392 us, of 64 473, of 256 in 51 KB and three blocks 445;
+// one wave per tile, its bands in turn, 476 us, and 97k 146 us.  Sums by pixel
+// rows, a wave per band and no common round, with the Jacobian per (entry, band):
+// 290 and 56 us, but other roundings.)
 __device__ __forceinline__ float uniform(float x) {
   return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
 }
 
-constexpr int kPoseRow = 6;  // sums of ds dx, ds dy, ds dx^2, ds dx dy, ds dy^2, wgt gD
+constexpr int kPosePlaces = 128;  // a band's entries with sums per round
+static_assert(kPosePlaces < kNoPlace && kPosePlaces >= kPoseRound / 2, "a half round always fits");
 
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_composite_bwd_pose(
+// Lane (e, x)'s sums over pixel column x of entry e0 + e.  fx = the column's
+// pixel centre, fy = the eight rows'.  (Products and sums are rounded apart.)
+__device__ __forceinline__ void column_sums(const BandLds& L, int lane, int e0, float fx, const float (&fy)[8],
+                                            float (&S)[kPoseRow]) {
+#pragma clang fp contract(off)
+  const int e = lane >> 3;
+  const float4* d4 = reinterpret_cast<const float4*>(L.rows + e * kRowStride + 8 * (lane & 7));
+  const float4* w4 = reinterpret_cast<const float4*>(L.rows + (8 + e) * kRowStride + 8 * (lane & 7));
+  const float4 d0 = d4[0], d1 = d4[1], w0 = w4[0], w1 = w4[1];
+  const float2 uv = *reinterpret_cast<const float2*>(&L.s0[e0 + e]);
+  const float ds[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
+  const float dx = fx - uv.x;
+  float g[5][8];
+#pragma unroll
+  for (int y = 0; y < 8; ++y) {
+    const float dy = fy[y] - uv.y;
+    g[0][y] = ds[y] * dx;
+    g[1][y] = ds[y] * dy;
+    g[2][y] = g[0][y] * dx;
+    g[3][y] = g[0][y] * dy;
+    g[4][y] = g[1][y] * dy;
+  }
+#pragma unroll
+  for (int q = 0; q < 5; ++q)
+    S[q] = ((g[q][0] + g[q][4]) + (g[q][2] + g[q][6])) + ((g[q][1] + g[q][5]) + (g[q][3] + g[q][7]));
+  S[5] = ((w0.x + w1.x) + (w0.z + w1.z)) + ((w0.y + w1.y) + (w0.w + w1.w));
+}
+
+// One band's walk over the list positions [lo, top): the sums of its i-th entry go
+// to part[i][kPoseRow].  x0, y0: the band's first pixel.
+__device__ __forceinline__ void pose_walk(PoseBandLds& L, int lane, BandList& list, int start, int top, int lo,
+                                          const int32_t* __restrict__ items, const float4* __restrict__ rec, int x0,
+                                          int y0, BwdPixel& px, float* part) {
+  const int x = lane & 7;
+  const float fx = (float)(x0 + (lane >> 3)) + 0.5f, fy = (float)(y0 + x) + 0.5f;
+  const float colx = (float)(x0 + x) + 0.5f;
+  float rowy[8];
+#pragma unroll
+  for (int y = 0; y < 8; ++y) rowy[y] = (float)(y0 + y) + 0.5f;
+  const bool hi = x & 4, b1 = x & 2, b0 = x & 1;
+  const int k0 = b1 ? 4 + (x >> 2) : 2 * (x & 1) + (x >> 2);  // the value that this lane ends with
+  const bool puts = !(b1 && b0);
+  part += (lane >> 3) * kPoseRow + k0;
+  int place = 0;
+  for (int n; (n = list.take<true>(L, lane, start, items, rec, lo, top, place)) > 0; place += n)
+    for (int e0 = 0; e0 < n; e0 += 8) {
+      walk_eight<true>(L, lane, e0, list.clamp, fx, fy, px, L.late);
+      float S[kPoseRow];
+      column_sums(L, lane, e0, colx, rowy, S);
+      // sums over the entry's eight lanes, halving the lanes that hold a value at
+      // every level: six values end in one register
+      float h[3];
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        h[k] = (hi ? S[2 * k + 1] : S[2 * k]) + partner<kMirror8>(hi ? S[2 * k] : S[2 * k + 1]);
+      const float q0 = (b0 ? h[1] : h[0]) + partner<kXor1>(b0 ? h[0] : h[1]);
+      const float q1 = h[2] + partner<kXor1>(h[2]);
+      const float v = (b1 ? q1 : q0) + partner<kXor2>(b1 ? q0 : q1);
+      if (puts && e0 + (lane >> 3) < n) part[(place + e0) * kPoseRow] = v;
+      wave_sync();
+    }
+}
+
+// Whether the used entries of every band among the kPoseRound positions below
+// `top` have places.  words: band 0's row; lanes 8 b .. 8 b + 4 take band b's words.
+__device__ __forceinline__ bool round_fits(const uint64_t* __restrict__ words, int64_t ustride, const int* visited,
+                                           int top, int lane) {
+  const int b = (lane >> 3) & 3, lo = max(top - kPoseRound, 0), i = (lo >> 6) + (lane & 7), end = min(top, visited[b]);
+  uint64_t m = 64 * i < end ? words[b * ustride + i] : 0ull;
+  if (64 * i < lo) m &= ~0ull << (lo & 63);
+  if (64 * i < end && 64 * i + 64 > end) m &= ~0ull >> (64 * i + 64 - end);
+  int n = (int)__popcll(m);
+  n += __builtin_amdgcn_mov_dpp(n, kMirror8, 0xF, 0xF, true);
+  n += __builtin_amdgcn_mov_dpp(n, kXor2, 0xF, 0xF, true);
+  n += __builtin_amdgcn_mov_dpp(n, kXor1, 0xF, 0xF, true);
+  return __ballot(n > kPosePlaces) == 0ull;
+}
+
+// A Gaussian's record and camera-space state, as the pose gradient reads them.
+struct PoseItem {
+  float4 r0, r1, a0, a1, a2;
+};
+__device__ __forceinline__ PoseItem pose_item(const float4* __restrict__ rec, const float4* __restrict__ aux,
+                                              int64_t it) {
+  return PoseItem{rec[it * 3], rec[it * 3 + 1], aux[it * 3], aux[it * 3 + 1], aux[it * 3 + 2]};
+}
+
+// a . b of three, as fma(a2, b2, fma(a0, b0, a1 b1)).
+__device__ __forceinline__ float dot3(float a0, float b0, float a1, float b1, float a2, float b2) {
+#pragma clang fp contract(off)
+  return __builtin_fmaf(a2, b2, __builtin_fmaf(a0, b0, a1 * b1));
+}
+
+// The rotation of q / |q| (row-major).
+__device__ __forceinline__ void pose_rot(float w, float x, float y, float z, float (&R)[9]) {
+#pragma clang fp contract(off)
+  const float inv = rsqrtf(__builtin_fmaf(z, z, __builtin_fmaf(y, y, __builtin_fmaf(w, w, x * x))));
+  w *= inv;
+  x *= inv;
+  y *= inv;
+  z *= inv;
+  const float wx = w * x, wy = w * y, wz = w * z;
+  R[0] = __builtin_fmaf(__builtin_fmaf(y, y, z * z), -2.f, 1.f);
+  R[1] = 2.f * __builtin_fmaf(x, y, -wz);
+  R[2] = 2.f * __builtin_fmaf(x, z, wy);
+  R[3] = 2.f * __builtin_fmaf(x, y, wz);
+  R[4] = __builtin_fmaf(__builtin_fmaf(x, x, z * z), -2.f, 1.f);
+  R[5] = 2.f * __builtin_fmaf(y, z, -wx);
+  R[6] = 2.f * __builtin_fmaf(x, z, -wy);
+  R[7] = 2.f * __builtin_fmaf(y, z, wx);
+  R[8] = __builtin_fmaf(__builtin_fmaf(x, x, y * y), -2.f, 1.f);
+}
+
+// The pose-gradient terms pc of a Gaussian from its list entry's sums: the chain
+// of camera_space_grads and, with p = R_d p0 + t_d and Sc = R_d Sc0 R_d^T, dL/dR_d
+// = dp p0^T + 2 G Sc R_d (pc[0..8]) and dL/dt_d = dp (pc[9..11]).  Contracted by
+// hand: what a compiler would contract changes with the code around it.
+__device__ __forceinline__ void pose_terms(float fx, float fy, const PoseItem& g, const float (&sum)[kPoseRow],
+                                           const float (&Rd)[9], const float (&td)[3], float (&pc)[kPoseAcc]) {
+#pragma clang fp contract(off)
+#define FMA __builtin_fmaf
+  // the conic as the staged one gives it
+  const float cA = kTwoLn2 * (g.r0.z * kHalfLog2e), cB = kLn2 * (g.r0.w * kLog2e);
+  const float cC = kTwoLn2 * (g.r1.x * kHalfLog2e);
+  const float du = -FMA(sum[0], cA, sum[1] * cB), dv = -FMA(sum[0], cB, sum[1] * cC);
+  const float dA = 0.5f * sum[2], dB = sum[3], dC = 0.5f * sum[4], dz = sum[5];
+  const float px = g.a0.x, py = g.a0.y, pz = g.a0.z;
+  const float S[9] = {g.a0.w, g.a1.x, g.a1.y, g.a1.x, g.a1.z, g.a1.w, g.a1.y, g.a1.w, g.a2.x};
+  const float iz = 1.0f / pz, iz2 = iz * iz, iz3 = iz * iz2;
+  // J0 = (j00, 0, j02), J1 = (0, j11, j12); their products with S
+  const float j00 = fx * iz, j02 = px * -fx * iz * iz, j11 = fy * iz, j12 = py * -fy * iz * iz;
+  float s0[3], s1[3];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    s0[i] = FMA(S[3 * i + 2], j02, S[3 * i] * j00);
+    s1[i] = FMA(S[3 * i + 2], j12, S[3 * i + 1] * j11);
+  }
+  const float a = FMA(j02, s0[2], j00 * s0[0]) + LS_EPS_2D;
+  const float b = FMA(j02, s1[2], j00 * s1[0]);
+  const float c = FMA(j12, s1[2], j11 * s1[1]) + LS_EPS_2D;
+  const float bb = b * b, det = FMA(a, c, -bb);
+  const float id2 = 1.0f / (det * det);
+  const float ga = FMA(-dC, bb, FMA(dB, b * c, -(dA * (c * c)))) * id2;
+  const float gb = FMA(dC, b * (a + a), FMA(dA, (b + b) * c, -(dB * FMA(b, b + b, det)))) * id2;
+  const float gc = FMA(-dC, a * a, FMA(dB, b * a, -(dA * bb))) * id2;
+  const float hb = 0.5f * gb, ga2 = ga + ga, gc2 = gc + gc, j22 = j02 * j12;
+  const float G01 = j00 * j11 * hb, m02 = j00 * j12 * hb, m12 = j11 * j02 * hb;
+  const float G[9] = {j00 * (j00 * ga), G01, FMA(j02, j00 * ga, m02),
+                      G01, j11 * (j11 * gc), FMA(j12, j11 * gc, m12),
+                      FMA(j00, j02 * ga, m02), FMA(j11, j12 * gc, m12),
+                      FMA(j12, j12 * gc, FMA(j02, j02 * ga, (j22 + j22) * hb))};
+  const float gJ00 = FMA(s0[0], ga2, s1[0] * gb), gJ02 = FMA(s0[2], ga2, s1[2] * gb);
+  const float gJ11 = FMA(s1[1], gc2, s0[1] * gb), gJ12 = FMA(s1[2], gc2, s0[2] * gb);
+  float dp[3];
+  dp[0] = FMA(iz, fx * du, -(iz2 * (fx * gJ02)));
+  dp[1] = FMA(iz, fy * dv, -(iz2 * (fy * gJ12)));
+  dp[2] = dz + FMA(iz2, px * (fx * -du), -(iz2 * (py * (fy * dv))));
+  dp[2] = FMA(-iz2, fx * gJ00, dp[2]);
+  dp[2] = FMA(iz3, px * (fx * (gJ02 + gJ02)), dp[2]);
+  dp[2] = FMA(-iz2, fy * gJ11, dp[2]);
+  dp[2] = FMA(iz3, py * (fy * (gJ12 + gJ12)), dp[2]);
+  const float d[3] = {px - td[0], py - td[1], pz - td[2]};
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    float gs[3];  // row i of G Sc
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      gs[k] = dot3(S[k], G[3 * i], S[3 + k], G[3 * i + 1], S[6 + k], G[3 * i + 2]);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const float q0 = dot3(Rd[k], d[0], Rd[3 + k], d[1], Rd[6 + k], d[2]);
+      pc[3 * i + k] = FMA(q0, dp[i], 2.f * dot3(Rd[k], gs[0], Rd[3 + k], gs[1], Rd[6 + k], gs[2]));
+    }
+    pc[9 + i] = dp[i];
+  }
+#undef FMA
+}
+
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_composite_bwd_pose(
     const JobDev* __restrict__ jobs, const int32_t* __restrict__ tile_off, int R, int T_total,
     const float4* __restrict__ rec, const float4* __restrict__ aux, const float* __restrict__ pose,
     const int32_t* __restrict__ items, const int32_t* __restrict__ range, const uint64_t* __restrict__ used,
     int64_t ustride, float bg0, float bg1, float bg2, const float* __restrict__ fwd_T,
     const int32_t* __restrict__ fwd_n, const float* __restrict__ up_rgb, const float* __restrict__ up_depth,
-    const float* __restrict__ up_alpha, const float* __restrict__ up_scale, float* __restrict__ band_part,
+    const float* __restrict__ up_alpha, const float* __restrict__ up_scale, float* __restrict__ tile_part,
     L1Targets l1) {
-  __shared__ __attribute__((aligned(16))) BandLds L;
-  const int unit = xcd_turns<64>(blockIdx.x, 4 * T_total);
-  if (unit >= 4 * T_total) return;
-  const int lane = threadIdx.x;
-  const BandCtx c = band_ctx(jobs, tile_off, R, unit);
+  __shared__ __attribute__((aligned(16))) PoseBandLds band[4];
+  __shared__ __attribute__((aligned(16))) float part[4][kPosePlaces * kPoseRow];
+  __shared__ float wred[4][kPoseAcc];
+  __shared__ int visited[4];
+  const int tile = xcd_turns<16>(blockIdx.x, T_total);
+  if (tile >= T_total) return;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  PoseBandLds& L = band[w];
+  const BandCtx c = band_ctx<true>(jobs, tile_off, R, 4 * tile + w, lane);
   const JobDev& J = jobs[c.r];
-  const int start = range[2 * c.tile];
+  const int start = range[2 * tile], end = range[2 * tile + 1];
+  const uint64_t* const words = used + (start >> 6) + tile;
   BwdPixel px = bwd_pixel(c, J, bg0, bg1, bg2, fwd_T, fwd_n, up_rgb, up_depth, up_alpha, up_scale, l1);
-  band_loss(l1, px, unit);
-  const int vpose = wave_value<kPoseAcc>(lane);  // the pose value whose sum this lane keeps, or -1
-  float total = 0.f;
-  BandList list(used + c.band * ustride + (start >> 6) + c.tile, wave_max_i(px.nl));
-  if (list.left > 0) {
-    const float fx = (float)c.x + 0.5f, fy = (float)c.y + 0.5f;
-    const int y = lane & 7;
-    const float bx = (float)(c.x0 + 4), ry = (float)(c.y0 + y) + 0.5f;
-    const float g[1] = {px.gD};
-    float f[1][8];
-    row_factors(L.rows, lane, g, f);
+  band_loss(l1, px, 4 * tile + w, lane);
+  const int mine = min(wave_max_i(px.nl), end - start);
+  if (lane == 0) visited[w] = mine;
+  reinterpret_cast<uint32_t*>(L.place)[lane] = 0x01010101u * kNoPlace;
+  static_assert(kPoseRound == 4 * 64, "a word of places per lane");
+  __syncthreads();
+  const int last = max(max(visited[0], visited[1]), max(visited[2], visited[3]));
+  float total = 0.f;  // of pose value threadIdx.x
+  if (last > 0) {     // uniform for the block
     // the render's correction, kept in scalar registers
     float Rd[9] = {1.f, 0.f, 0.f, 0.f, 1.f, 0.f, 0.f, 0.f, 1.f}, td[3] = {0.f, 0.f, 0.f};
     if (pose) {
       const float* pr = pose + 7 * c.r;
-      quat_to_rot(pr[0], pr[1], pr[2], pr[3], Rd);
+      pose_rot(pr[0], pr[1], pr[2], pr[3], Rd);
 #pragma unroll
       for (int k = 0; k < 9; ++k) Rd[k] = uniform(Rd[k]);
       td[0] = pr[4];
       td[1] = pr[5];
       td[2] = pr[6];
     }
-    for (bool more = true; more;) {
-      int it = -1;  // this lane's entry: lane (e, y) takes entry e of the y-th eight
-      float S[kPoseRow];
+    BandList list(L, words + w * ustride, mine);
+    int chunk0 = 0;  // of the four that are added up, the round's first
+    for (int top = last, lo; top > 0; top = lo) {
+      const bool whole = chunk0 == 0 && (top <= kPosePlaces || round_fits(words, ustride, visited, top, lane));
+      const int chunks = whole ? kPoseRound / 64 : kPosePlaces / 64;
+      lo = max(top - 64 * chunks, 0);
+      pose_walk(L, lane, list, start, top, lo, items, rec, c.x0, c.y0, px, part[w]);
+      const int chunk = w - chunk0;  // this wave's, if the round has it
+      const bool turn = chunk >= 0 && chunk < chunks;
+      const int end = top - 64 * chunk, base = max(end - 64, 0);
+      const bool has = turn && lane < end;
+      PoseItem g;  // (loaded while the other waves walk)
+      if (has) g = pose_item(rec, aux, items[start + base + lane]);
+      __syncthreads();
+      if (turn) {
+        float pc[kPoseAcc];
 #pragma unroll
-      for (int p = 0; p < 2; ++p) {
-        const int n = more ? list.take(L, lane, start, items, rec) : 0;
-        more = n == kBatch;
-        for (int e0 = 0; e0 < n; e0 += 8) {
-          walk_eight(L, lane, e0, list.clamp, fx, fy, px);
-          float s7[7];
-          row_sums(L, lane, e0, bx, ry, f, s7);
-          s7[5] = s7[6];  // the opacity's sum is not needed
-          const int e = e0 + (lane >> 3);
-          const bool mine = y == p * (kBatch / 8) + (e0 >> 3) && e < n;
-          if (mine) it = L.item[e];
+        for (int q = 0; q < kPoseAcc; ++q) pc[q] = 0.f;
+        float sum[kPoseRow] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        bool any = false;
 #pragma unroll
-          for (int q = 0; q < kPoseRow; ++q) {
-            const float v = sum8(s7[q]);
-            S[q] = mine ? v : S[q];
+        for (int b = 0; b < 4; ++b) {
+          const int place = band[b].place[64 * chunk + lane];
+          if (place != kNoPlace) {
+            any = true;
+            band[b].place[64 * chunk + lane] = kNoPlace;
+#pragma unroll
+            for (int q = 0; q < kPoseRow; ++q) sum[q] += part[b][place * kPoseRow + q];
           }
-          wave_sync();
         }
+        if (any) pose_terms(J.fx, J.fy, g, sum, Rd, td, pc);
+        const float out = wave_sums<kPoseAcc>(pc, lane);
+        const int v = wave_value<kPoseAcc>(lane);
+        if (v >= 0) wred[w][v] = out;
       }
-      if (__ballot(it >= 0) == 0ull) break;
-      float pc[kPoseAcc];
+      __syncthreads();
+      chunk0 += chunks;
+      if (chunk0 == 4 || lo == 0) {
+        if ((int)threadIdx.x < kPoseAcc) {
+          float s[4];
 #pragma unroll
-      for (int k = 0; k < kPoseAcc; ++k) pc[k] = 0.f;
-      if (it >= 0) {
-        const float4 a0 = aux[(int64_t)it * 3 + 0], a1 = aux[(int64_t)it * 3 + 1], a2 = aux[(int64_t)it * 3 + 2];
-        const float p[3] = {a0.x, a0.y, a0.z};
-        const float s6[6] = {a0.w, a1.x, a1.y, a1.z, a1.w, a2.x};
-        float Sc[9], dp[3], Gm[9];
-        sym3(s6, Sc);
-        camera_space_grads(p, Sc, J.fx, J.fy, S, dp, Gm);
-        pose_contrib(p, Sc, Rd, td, dp, Gm, pc);
+          for (int q = 0; q < 4; ++q) s[q] = q < chunk0 ? wred[q][threadIdx.x] : 0.f;
+          total += (s[0] + s[1]) + (s[2] + s[3]);
+        }
+        chunk0 = 0;
       }
-      total += wave_sums<kPoseAcc>(pc, lane);
     }
   }
-  if (vpose >= 0) band_part[(int64_t)unit * kPoseAcc + vpose] = total;
+  if ((int)threadIdx.x < kPoseAcc) tile_part[(int64_t)tile * kPoseAcc + threadIdx.x] = total;
 }
-
 
 // Work statistics of a forward pass: entries evaluated and composited.
 __global__ __launch_bounds__(kBlock) void k_render_stats(const JobDev* __restrict__ jobs,
@@ -959,19 +1213,19 @@ void launch_composite_bwd(const JobDev* jobs, const int32_t* tile_off, int R, in
                           const uint64_t* used, int64_t ustride, const float* bg, const float* Tf,
                           const int32_t* nl,
                           const float* up_rgb, const float* up_depth, const float* up_alpha, const float* up_scale,
-                          float* g2d, float* band_part, int pose_only, hipStream_t s,
+                          float* g2d, float* tile_part, int pose_only, hipStream_t s,
                           const L1Targets* l1) {
   if (T <= 0) return;
   const L1Targets l1v = l1 ? *l1 : L1Targets{nullptr, nullptr, nullptr, nullptr, nullptr};
   const float4* rec4 = reinterpret_cast<const float4*>(rec);
   const float4* aux4 = reinterpret_cast<const float4*>(aux);
-  const dim3 grid(xcd_grid(4 * T));
-  if (pose_only)
-    hipLaunchKernelGGL(k_composite_bwd_pose, grid, dim3(64), 0, s, jobs, tile_off, R, T, rec4, aux4, pose, items, range,
-                       used, ustride, bg[0], bg[1], bg[2], Tf, nl, up_rgb, up_depth, up_alpha, up_scale, band_part,
-                       l1v);
-  else
-    hipLaunchKernelGGL(k_composite_bwd, grid, dim3(64), 0, s, jobs, tile_off, R, T, rec4, items, range, used, ustride,
-                       bg[0], bg[1], bg[2], Tf, nl, up_rgb, up_depth, up_alpha, up_scale, g2d, l1v);
+  if (pose_only) {
+    hipLaunchKernelGGL(k_composite_bwd_pose, dim3(xcd_grid(T)), dim3(kBlock), 0, s, jobs, tile_off, R, T, rec4, aux4,
+                       pose, items, range, used, ustride, bg[0], bg[1], bg[2], Tf, nl, up_rgb, up_depth, up_alpha,
+                       up_scale, tile_part, l1v);
+    return;
+  }
+  hipLaunchKernelGGL(k_composite_bwd, dim3(xcd_grid(4 * T)), dim3(64), 0, s, jobs, tile_off, R, T, rec4, items, range,
+                     used, ustride, bg[0], bg[1], bg[2], Tf, nl, up_rgb, up_depth, up_alpha, up_scale, g2d, l1v);
 }
 }  // namespace ls

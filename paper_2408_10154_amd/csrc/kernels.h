@@ -51,7 +51,7 @@ void launch_project_bwd(const JobDev* jobs, const int32_t* blk_off, int R, int n
                         const int32_t* radius, const float* aux, float* g2d, const GradDev* grads, int want_gauss,
                         float* pose_part, int want_pose, float* pose_grad, hipStream_t s,
                         const GaussAdamArgs* adam = nullptr);
-void launch_pose_reduce_bands(const JobDev* jobs, int R, const float* pose, const float* band_part, float* pose_grad,
+void launch_pose_reduce_tiles(const JobDev* jobs, int R, const float* pose, const float* tile_part, float* pose_grad,
                               hipStream_t s);
 
 // Segments of a radix sort: segment s holds its keys at base[s] ..
@@ -170,7 +170,7 @@ void launch_composite_bwd(const JobDev* jobs, const int32_t* tile_off, int R, in
                           const uint64_t* used, int64_t ustride, const float* bg, const float* Tf, const int32_t* nl,
                           const float* up_rgb,
                           const float* up_depth, const float* up_alpha, const float* up_scale, float* g2d,
-                          float* band_part, int pose_only, hipStream_t s,
+                          float* tile_part, int pose_only, hipStream_t s,
                           const L1Targets* l1 = nullptr);
 
 // Registration helpers (reg_kernels.hip).
@@ -213,7 +213,7 @@ struct PoseAdamArgs {
 
 // One render's pose, gradient so far and moments.  A reduction loads them before
 // its sums: read where they are used, seven loads wait for each other's stores
-// (pose reduction with its step, 16 views of 4,800 rows: 12.7 -> 10.4 us, one of
+// (pose reduction with its step, 16 views of 1,200 rows: 7.8 -> 6.8 us, one of
 // 782 rows: 6.0 -> 5.2 us).
 struct PoseState {
   float p[7], g[7], m[7], v[7];
@@ -332,10 +332,10 @@ void launch_joint_step(const JointView* views, JointPair* pairs, int npairs, flo
                        const JointAdam& a, hipStream_t s);
 
 // One iteration's end in pose-only registration: per render, the tile
-// partials reduced to its pose gradient (as launch_pose_reduce_bands) and
+// partials reduced to its pose gradient (as launch_pose_reduce_tiles) and
 // its Adam step (pose_adam_view) in one launch; render 0 also updates the
 // sticky overflow flag from count (as launch_or_flag).
-void launch_pose_reduce_adam(const JobDev* jobs, int R, const float* band_part, const PoseAdamArgs& a,
+void launch_pose_reduce_adam(const JobDev* jobs, int R, const float* tile_part, const PoseAdamArgs& a,
                              const int32_t* count, int32_t* sticky, hipStream_t s);
 void launch_pose_init(float* pose, float* m, float* v, ViewOpt* opt, int R, hipStream_t s);
 void launch_or_flag(const int32_t* count, int32_t* sticky, hipStream_t s);

@@ -274,7 +274,7 @@ __global__ __launch_bounds__(256) void k_project_bwd(const JobDev* __restrict__ 
 }
 
 // Per render: sum the partials in order (per 256-item block of the render,
-// or per 8x8 band when by_band is set), chain dL/dR_d to the quaternion,
+// or per tile when by_tile is set), chain dL/dR_d to the quaternion,
 // accumulate into pose_grad [R][7].  One block per render.
 // With step.pose_m set, each render's pose then takes one Adam step from the
 // accumulated gradient (as ls_adam over pose_grad), which is consumed.
@@ -284,8 +284,7 @@ constexpr int kPoseSumThreads = 256;
 // kPoseSumThreads threads in a fixed order: strided per-thread sums (each
 // row three 16-byte loads, four rows in flight per thread), wave sums, then
 // the four waves in order.  Thread 0 returns the totals.  Bound by what one CU
-// fetches of rows that lie in all XCDs' L2s: with eight rows in flight 0.2 us less
-// of 11.6 for the 4,800 rows of each of 16 640x480 views, with 1,024 threads 0.3.
+// fetches of rows that lie in all XCDs' L2s.
 __device__ __forceinline__ void block_pose_sum(const float* __restrict__ part, int first, int nb,
                                                float (&acc)[kPoseAcc]) {
   static_assert(kPoseAcc == 12, "a row is three float4");
@@ -316,13 +315,13 @@ __device__ __forceinline__ void block_pose_sum(const float* __restrict__ part, i
 __global__ __launch_bounds__(kPoseSumThreads) void k_pose_reduce(const JobDev* __restrict__ jobs, int R,
                                                                  const float* __restrict__ pose,
                                                                  const float* __restrict__ pose_part,
-                                                                 float* __restrict__ pose_grad, int by_band,
+                                                                 float* __restrict__ pose_grad, int by_tile,
                                                                  GaussAdamArgs step) {
   const int r = blockIdx.x;
   if (r >= R) return;
   const JobDev& J = jobs[r];
-  const int first = by_band ? 4 * J.tile_off : J.blk_off;
-  const int nb = by_band ? 4 * J.TX * J.TY : (J.n + 255) / 256;
+  const int first = by_tile ? J.tile_off : J.blk_off;
+  const int nb = by_tile ? J.TX * J.TY : (J.n + 255) / 256;
   PoseState st{};
   if (threadIdx.x == 0) st = load_pose_state(pose, pose_grad, step.pose_m, step.pose_v, r);
   float acc[kPoseAcc];
@@ -373,11 +372,11 @@ void launch_project_bwd(const JobDev* jobs, const int32_t* blk_off, int R, int n
                        pose_grad, 0, adam ? *adam : GaussAdamArgs{});
 }
 
-// Pose reduction by band partials (as k_pose_reduce with by_band) followed
+// Pose reduction by tile partials (as k_pose_reduce with by_tile) followed
 // by the render's Adam step; block 0 also folds the overflow count into the
 // sticky flag.
 __global__ __launch_bounds__(kPoseSumThreads) void k_pose_reduce_adam(const JobDev* __restrict__ jobs, int R,
-                                                                      const float* __restrict__ band_part,
+                                                                      const float* __restrict__ tile_part,
                                                                       PoseAdamArgs a,
                                                                       const int32_t* __restrict__ count,
                                                                       int32_t* __restrict__ sticky) {
@@ -391,7 +390,7 @@ __global__ __launch_bounds__(kPoseSumThreads) void k_pose_reduce_adam(const JobD
     o = a.opt[r];
   }
   float acc[kPoseAcc];
-  block_pose_sum(band_part, 4 * J.tile_off, 4 * J.TX * J.TY, acc);
+  block_pose_sum(tile_part, J.tile_off, J.TX * J.TY, acc);
   if (threadIdx.x == 0) {
     float dq[4], g[7];
     rot_backward(st.p[0], st.p[1], st.p[2], st.p[3], acc, dq);
@@ -402,15 +401,15 @@ __global__ __launch_bounds__(kPoseSumThreads) void k_pose_reduce_adam(const JobD
   }
 }
 
-void launch_pose_reduce_adam(const JobDev* jobs, int R, const float* band_part, const PoseAdamArgs& a,
+void launch_pose_reduce_adam(const JobDev* jobs, int R, const float* tile_part, const PoseAdamArgs& a,
                              const int32_t* count, int32_t* sticky, hipStream_t s) {
   if (R > 0)
-    hipLaunchKernelGGL(k_pose_reduce_adam, dim3(R), dim3(kPoseSumThreads), 0, s, jobs, R, band_part, a, count, sticky);
+    hipLaunchKernelGGL(k_pose_reduce_adam, dim3(R), dim3(kPoseSumThreads), 0, s, jobs, R, tile_part, a, count, sticky);
 }
 
-void launch_pose_reduce_bands(const JobDev* jobs, int R, const float* pose, const float* band_part, float* pose_grad,
+void launch_pose_reduce_tiles(const JobDev* jobs, int R, const float* pose, const float* tile_part, float* pose_grad,
                               hipStream_t s) {
-  hipLaunchKernelGGL(k_pose_reduce, dim3(R), dim3(kPoseSumThreads), 0, s, jobs, R, pose, band_part, pose_grad, 1,
+  hipLaunchKernelGGL(k_pose_reduce, dim3(R), dim3(kPoseSumThreads), 0, s, jobs, R, pose, tile_part, pose_grad, 1,
                      GaussAdamArgs{});
 }
 }  // namespace ls
