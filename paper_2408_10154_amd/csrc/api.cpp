@@ -82,7 +82,7 @@ Layout layout_of(const ls_batch* b, int64_t cap) {
   L.v0 = take(4 * M);
   L.k1 = take(4 * M);
   L.v1 = take(4 * M);
-  L.hist = take(4 * (size_t)seg_hist_words(b->sort_blocks));
+  L.hist = take(4 * (size_t)seg_hist_words(b->sort_blocks, b->R));
   L.blk_cnt = take(4 * (size_t)b->sort_blocks);
   L.kept = take(4 * (size_t)b->R);
   L.cnt = take(4 * (size_t)b->bincnt_off[b->R]);

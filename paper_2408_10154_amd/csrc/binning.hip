@@ -55,19 +55,6 @@ struct Digit {
   __device__ __forceinline__ static uint32_t of(uint32_t key, int shift) { return (key >> shift) & (kBins - 1); }
 };
 
-// Inclusive prefix sum over the 64 lanes (DPP: shifts within 16-lane rows,
-// then the row ends broadcast to the later rows).
-__device__ __forceinline__ uint32_t wave_incl_sum(uint32_t v) {
-  int x = (int)v;
-  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);  // row_shr:1
-  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);  // row_shr:2
-  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);  // row_shr:4
-  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);  // row_shr:8
-  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);  // row_bcast:15 -> rows 1, 3
-  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);  // row_bcast:31 -> rows 2, 3
-  return (uint32_t)x;
-}
-
 // Exclusive prefix of one value per thread over the first kThreads threads (the
 // others' values are ignored); every thread of the block calls it.
 template <int kThreads>
@@ -180,8 +167,8 @@ __global__ __launch_bounds__(kSortThreads) void k_seg_hist(const uint32_t* __res
 
 // Sums of digit d's counts over the segment's blocks and over those before this
 // one, kParts threads per digit; the results in threads d below kThreads.
-// Blocks of 1,024 threads keep the rows few (98 for 200k keys), so every block
-// can add them up and no scan launch is needed.
+// The rows are few (98 for 200k keys; at most kScanRows), so every block can add
+// them up and no scan launch is needed.
 __device__ __forceinline__ void digit_bases(const uint32_t* __restrict__ rows, int nrows, int c, uint32_t* ta,
                                             uint32_t* tb, uint32_t& total, uint32_t& before) {
   using D = Digit<kSortBits>;
@@ -215,14 +202,17 @@ __device__ __forceinline__ void digit_bases(const uint32_t* __restrict__ rows, i
 // LDS by digit, then written out in that order, so that stores are contiguous
 // along each digit's run.  kFirst: the block's own keys, blk_cnt of them, as
 // k_depth_prep left them (len[s] is written); else kKeys of the segment's
-// len[s].  kLast: only the values are written.
+// len[s].  kLast: only the values are written.  sums: k_seg_scan has turned the
+// counts into each block's bases, and these are the segments' digit totals; or
+// NULL, and every block adds the counts up for itself.
 template <int kPer, bool kFirst, bool kLast>
 __global__ __launch_bounds__(kSortThreads) void k_seg_scatter(const uint32_t* __restrict__ kin,
                                                               const uint32_t* __restrict__ vin,
                                                               uint32_t* __restrict__ kout,
                                                               uint32_t* __restrict__ vout, SegTable seg, int shift,
                                                               const uint32_t* __restrict__ hist,
-                                                              const int32_t* __restrict__ blk_cnt) {
+                                                              const int32_t* __restrict__ blk_cnt,
+                                                              const uint32_t* __restrict__ sums) {
   using D = Digit<kSortBits>;
   constexpr int kKeys = kPer * kSortThreads;
   __shared__ __attribute__((aligned(4))) uint16_t wcnt[kSortWaves][D::kBins];
@@ -246,8 +236,13 @@ __global__ __launch_bounds__(kSortThreads) void k_seg_scatter(const uint32_t* __
     key[j] = ok[j] ? kin[in0 + i] : 0u;
     val[j] = ok[j] ? vin[in0 + i] : 0u;
   }
-  uint32_t total, before, lstart[1];
-  digit_bases(hist + (int64_t)b0 * D::kBins, nrows, c, sk, sv, total, before);
+  uint32_t total = 0u, before = 0u, lstart[1];
+  if (sums == nullptr) {
+    digit_bases(hist + (int64_t)b0 * D::kBins, nrows, c, sk, sv, total, before);
+  } else if ((int)threadIdx.x < D::kThreads) {
+    total = sums[s * D::kBins + threadIdx.x];
+    before = hist[(int64_t)blockIdx.x * D::kBins + threadIdx.x];
+  }
   const uint32_t first = digit_excl<D::kThreads>(total, wsum[0]);  // of the thread's digit, in the segment
   if (kFirst && c == 0 && threadIdx.x == D::kThreads - 1) seg.len[s] = (int32_t)(first + total);
   wave_ranks<kSortBits, kPer>(key, ok, shift, wcnt[w], lane, rk);
@@ -276,7 +271,61 @@ __global__ __launch_bounds__(kSortThreads) void k_seg_scatter(const uint32_t* __
   }
 }
 
-int64_t seg_hist_words(int nblk) { return (int64_t)Digit<kSortBits>::kBins * std::max(nblk, 1); }
+// Segments of many blocks: the digits' counts turned into each block's bases, in
+// place, and the segments' digit totals into sums.  32 digits of a segment to a
+// block, 32 threads to a digit, each a run of blocks.  kFirst as above.
+//
+// A block that adds up its segment's counts for itself reads 1 KB per block, so a
+// pass reads the square of the blocks: past kScanRows of them the launch costs
+// less (binning without and with it at 1200 x 680: 500k items, 245 blocks, 96.6
+// and 100.6 us; 1M, 489, 157 and 150 us; 5M, 1,221, 496 and 404 us; 10M, 2,442,
+// 1,161 and 767 us).
+constexpr int kScanRows = 256;
+template <int kPer, bool kFirst>
+__global__ __launch_bounds__(1024) void k_seg_scan(SegTable seg, uint32_t* __restrict__ hist,
+                                                   uint32_t* __restrict__ sums) {
+  using D = Digit<kSortBits>;
+  constexpr int kKeys = kPer * kSortThreads, kDigits = 32, kParts = 1024 / kDigits, kAhead = 8;
+  __shared__ uint32_t part[kParts][kDigits];
+  const int s = blockIdx.x / (D::kBins / kDigits), d0 = blockIdx.x % (D::kBins / kDigits) * kDigits;
+  const int d = threadIdx.x % kDigits, p = threadIdx.x / kDigits;
+  const int b0 = seg.blk_off[s], all = seg.blk_off[s + 1] - b0;
+  const int rows = kFirst ? all : (seg.len[s] + kKeys - 1) / kKeys;
+  const int per = (rows + kParts - 1) / kParts, lo = min(p * per, rows), hi = min(lo + per, rows);
+  uint32_t* __restrict__ col = hist + (int64_t)b0 * D::kBins + d0 + d;
+  uint32_t sum = 0;
+  for (int r = lo; r < hi; r += kAhead) {
+    uint32_t v[kAhead];
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) v[k] = r + k < hi ? col[(int64_t)(r + k) * D::kBins] : 0u;
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) sum += v[k];
+  }
+  part[p][d] = sum;
+  __syncthreads();
+  uint32_t run = 0, total = 0;
+#pragma unroll
+  for (int k = 0; k < kParts; ++k) {
+    run += k < p ? part[k][d] : 0u;
+    total += part[k][d];
+  }
+  for (int r = lo; r < hi; r += kAhead) {
+    uint32_t v[kAhead];
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) v[k] = r + k < hi ? col[(int64_t)(r + k) * D::kBins] : 0u;
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k)
+      if (r + k < hi) {
+        col[(int64_t)(r + k) * D::kBins] = run;
+        run += v[k];
+      }
+  }
+  if (p == 0) sums[s * D::kBins + d0 + d] = total;
+}
+
+int64_t seg_hist_words(int nblk, int nseg) {
+  return (int64_t)Digit<kSortBits>::kBins * ((int64_t)std::max(nblk, 1) + nseg);
+}
 
 // ---------------------------------------------------------------------------
 // Depth order of each render's items.
@@ -1016,14 +1065,25 @@ void launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s) {
   hipLaunchKernelGGL(k_fill_i32, dim3((unsigned)blocks), dim3(256), 0, s, p, n, v);
 }
 
+// The scan of a pass whose largest segment has `rows` blocks, if that is worth it;
+// returns the digit totals for the scatter, or NULL.
+template <int kPer, bool kFirst>
+static const uint32_t* seg_scan(const SegTable& seg, int blocks, int rows, uint32_t* hist, hipStream_t s) {
+  if (rows <= kScanRows) return nullptr;
+  uint32_t* sums = hist + (int64_t)Digit<kSortBits>::kBins * blocks;
+  hipLaunchKernelGGL((k_seg_scan<kPer, kFirst>), dim3(8 * seg.S), dim3(1024), 0, s, seg, hist, sums);
+  return sums;
+}
+
 template <int kPer>
 static void seg_pass(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout, const SegTable& seg,
-                     int blocks, int shift, uint32_t* hist, bool last, hipStream_t s) {
+                     int blocks, int rows, int shift, uint32_t* hist, bool last, hipStream_t s) {
   const dim3 grid(blocks), block(kSortThreads);
   hipLaunchKernelGGL(k_seg_hist<kPer>, grid, block, 0, s, kin, seg, shift, hist);
+  const uint32_t* sums = seg_scan<kPer, false>(seg, blocks, rows, hist, s);
   const int32_t* none = nullptr;
   auto scatter = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, grid, block, 0, s, kin, vin, kout, vout, seg, shift, (const uint32_t*)hist, none);
+    hipLaunchKernelGGL(kernel, grid, block, 0, s, kin, vin, kout, vout, seg, shift, (const uint32_t*)hist, none, sums);
   };
   if (last)
     scatter(k_seg_scatter<kPer, false, true>);
@@ -1035,13 +1095,16 @@ static void seg_pass(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, u
 template <int kPer>
 static void depth_passes(const BinLaunch& b, const SegTable& seg, hipStream_t s) {
   const dim3 grid(b.sort_blocks), block(kSortThreads);
+  const int rows = sort_blocks_of(b.max_items, kPer);
   hipLaunchKernelGGL(k_depth_prep<kPer>, grid, block, 0, s, b.jobs, seg, reinterpret_cast<const float4*>(b.rec),
                      b.tiles, b.k0, b.v0, b.hist, b.blk_cnt);
+  const uint32_t* sums = seg_scan<kPer, true>(seg, b.sort_blocks, rows, b.hist, s);
   hipLaunchKernelGGL((k_seg_scatter<kPer, true, false>), grid, block, 0, s, (const uint32_t*)b.k0,
-                     (const uint32_t*)b.v0, b.k1, b.v1, seg, 0, (const uint32_t*)b.hist, (const int32_t*)b.blk_cnt);
-  seg_pass<kPer>(b.k1, b.v1, b.k0, b.v0, seg, b.sort_blocks, 8, b.hist, false, s);
-  seg_pass<kPer>(b.k0, b.v0, b.k1, b.v1, seg, b.sort_blocks, 16, b.hist, false, s);
-  seg_pass<kPer>(b.k1, b.v1, b.k0, b.v0, seg, b.sort_blocks, 24, b.hist, true, s);
+                     (const uint32_t*)b.v0, b.k1, b.v1, seg, 0, (const uint32_t*)b.hist, (const int32_t*)b.blk_cnt,
+                     sums);
+  seg_pass<kPer>(b.k1, b.v1, b.k0, b.v0, seg, b.sort_blocks, rows, 8, b.hist, false, s);
+  seg_pass<kPer>(b.k0, b.v0, b.k1, b.v1, seg, b.sort_blocks, rows, 16, b.hist, false, s);
+  seg_pass<kPer>(b.k1, b.v1, b.k0, b.v0, seg, b.sort_blocks, rows, 24, b.hist, true, s);
 }
 
 void launch_bin_sort(const BinLaunch& b, hipStream_t s) {
@@ -1101,8 +1164,8 @@ void launch_bin_sort(const BinLaunch& b, hipStream_t s) {
 }
 
 void launch_seg_pass(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout, const SegTable& seg,
-                     int blocks, int per, int shift, uint32_t* hist, bool last, hipStream_t s) {
+                     int blocks, int rows, int per, int shift, uint32_t* hist, bool last, hipStream_t s) {
   const auto pass = per == 1 ? seg_pass<1> : per == 2 ? seg_pass<2> : per == 3 ? seg_pass<3> : seg_pass<4>;
-  pass(kin, vin, kout, vout, seg, blocks, shift, hist, last, s);
+  pass(kin, vin, kout, vout, seg, blocks, rows, shift, hist, last, s);
 }
 }  // namespace ls

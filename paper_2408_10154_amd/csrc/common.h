@@ -163,6 +163,19 @@ __device__ __forceinline__ float wave_sum(float v) {
   return (r0 + r1) + (r2 + r3);
 }
 
+// Inclusive prefix sum over the 64 lanes (DPP: shifts within 16-lane rows,
+// then the row ends broadcast to the later rows).
+__device__ __forceinline__ uint32_t wave_incl_sum(uint32_t v) {
+  int x = (int)v;
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);  // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);  // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);  // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);  // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);  // row_bcast:15 -> rows 1, 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);  // row_bcast:31 -> rows 2, 3
+  return (uint32_t)x;
+}
+
 // XCD-aware block -> work-unit map: consecutive work units (neighbouring
 // tiles) go to the same XCD so its L2 holds the splats they share.  The grid
 // must have 8 * ceil(total / 8) blocks; units >= total are idle.

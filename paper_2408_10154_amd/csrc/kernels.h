@@ -84,12 +84,14 @@ inline int sort_per(int64_t max_n, const Blocks& blocks) {
   while (per < kSortPerMax && blocks(per) > kResident) ++per;
   return per;
 }
-// Words of the digit histograms of `blocks` sort blocks.
-int64_t seg_hist_words(int blocks);
+// Words of the digit histograms of `blocks` sort blocks and of the `segments`'
+// digit totals.
+int64_t seg_hist_words(int blocks, int segments);
 // One stable pass over the 8-bit digit at `shift` (binning.hip), from
-// (kin, vin) to (kout, vout); last: kout is not written.
+// (kin, vin) to (kout, vout); last: kout is not written.  rows: the largest
+// segment's sort blocks.
 void launch_seg_pass(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout, const SegTable& seg,
-                     int blocks, int per, int shift, uint32_t* hist, bool last, hipStream_t s);
+                     int blocks, int rows, int per, int shift, uint32_t* hist, bool last, hipStream_t s);
 
 // Device tables of a batch's binning: per render the sort blocks, the chunk x
 // window work units and the count matrices (chunks x tiles words) before it.
@@ -119,7 +121,7 @@ struct BinLaunch {
   const int32_t* tiles;
   int64_t cap;
   uint32_t *k0, *v0, *k1, *v1;  // sort buffers [M]
-  uint32_t* hist;               // seg_hist_words(sort_blocks)
+  uint32_t* hist;               // seg_hist_words(sort_blocks, R)
   int32_t* blk_cnt;             // [sort_blocks]
   int32_t* kept;                // [R]: items with tiles
   uint32_t* cnt;                // count matrices

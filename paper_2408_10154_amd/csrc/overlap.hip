@@ -509,7 +509,7 @@ static OvLayout ov_layout(int np, int nq) {
   L.idx_a = take(4 * both);
   L.code_b = take(4 * both);
   L.idx_b = take(4 * both);
-  L.hist = take(4 * (size_t)seg_hist_words(ov_sort_blocks(np, nq, ov_sort_per(np, nq))));
+  L.hist = take(4 * (size_t)seg_hist_words(ov_sort_blocks(np, nq, ov_sort_per(np, nq)), 2));
   for (int s = 0; s < 2; ++s) {
     const int n = s ? nq : np;
     const int nleaf = (n + kOvLeaf - 1) / kOvLeaf, nsuper = (nleaf + kOvSuper - 1) / kOvSuper;
@@ -543,7 +543,7 @@ void launch_overlap(const float* p_mean, int np, const float* q_mean, int nq, co
   hipLaunchKernelGGL(k_ov_box_part, dim3(kOvBoxBlocks), dim3(kBlock), 0, s, (const float*)pt, np, q_mean, nq,
                      box_part);
   char* sg = w + L.segs;
-  const int per = ov_sort_per(np, nq), nsb = ov_sort_blocks(np, nq, per);
+  const int per = ov_sort_per(np, nq), nsb = ov_sort_blocks(np, nq, per), rows = sort_blocks_of(std::max(np, nq), per);
   const OvSegs segs{reinterpret_cast<int32_t*>(sg), reinterpret_cast<int64_t*>(sg + 16),
                     reinterpret_cast<int32_t*>(sg + 32)};
   hipLaunchKernelGGL(k_ov_box_final, dim3(1), dim3(kBlock), 0, s, (const float*)box_part, kOvBoxBlocks, np, nq, box,
@@ -558,10 +558,10 @@ void launch_overlap(const float* p_mean, int np, const float* q_mean, int nq, co
                      np, q_mean, nq, (const float*)box, ca, ia);
   // both sets in one sort; four passes over the 30-bit codes end in (ca, ia)
   const SegTable seg{segs.blk_off, segs.base, 2, segs.len};
-  launch_seg_pass(ca, ia, cb, ib, seg, nsb, per, 0, hist, false, s);
-  launch_seg_pass(cb, ib, ca, ia, seg, nsb, per, 8, hist, false, s);
-  launch_seg_pass(ca, ia, cb, ib, seg, nsb, per, 16, hist, false, s);
-  launch_seg_pass(cb, ib, ca, ia, seg, nsb, per, 24, hist, false, s);
+  launch_seg_pass(ca, ia, cb, ib, seg, nsb, rows, per, 0, hist, false, s);
+  launch_seg_pass(cb, ib, ca, ia, seg, nsb, rows, per, 8, hist, false, s);
+  launch_seg_pass(ca, ia, cb, ib, seg, nsb, rows, per, 16, hist, false, s);
+  launch_seg_pass(cb, ib, ca, ia, seg, nsb, rows, per, 24, hist, false, s);
   OvSet set[2];
   for (int k = 0; k < 2; ++k) {
     const int n = k ? nq : np;

@@ -1,0 +1,54 @@
+"""Tile binning beyond the sizes of one submap and one image."""
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2408_10154_amd import synth
+from tests.test_gpu_binning_sizes import SMALL, test_lists_equal_the_oracle as _lists_equal_the_oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("sizes", [[530000], [526000, 0, 300]])  # 259 and 257 sort blocks in the largest segment
+def test_scanned_sort_counts(gpu, sizes):
+    _lists_equal_the_oracle(gpu, sizes, SMALL, 0.9)
+
+
+def _records_batch(n, W, H, R=1):
+    """R renders of n items with random records of one tile or a few each."""
+    from paper_2408_10154_amd.render import GaussianSet, RenderBatch
+
+    shapes = dict(mean=(3, n), log_scale=(3, n), quat=(4, n), opacity_logit=(n,), rgb=(3, n))
+    g = GaussianSet(**{k: torch.zeros(s, device="cuda") for k, s in shapes.items()})
+    b = RenderBatch([(g, synth.camera(W, W, W / 2, H / 2, W, H), synth.identity_w2c())] * R, capacity=4 * n * R)
+    b.auto_grow = False
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n)
+    b.rec.zero_()
+    for k, scale in ((0, W), (1, H)):
+        b.rec[:, k] = torch.rand(n * R, device="cuda", generator=gen) * scale
+    b.rec[:, 6] = torch.rand(n * R, device="cuda", generator=gen) + 0.5
+    b.radius.fill_(1)
+    b.tiles.fill_(1)  # (binning only asks whether an item has tiles)
+    return b
+
+
+def _ms(f):
+    f()
+    best = np.inf
+    for _ in range(3):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        f()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b))
+    return best
+
+
+def test_binning_time_grows_with_the_items(gpu):
+    """16 times the items in about 16 times the time: a sort whose blocks add up
+    each other's counts takes 50 times as long at these sizes."""
+    few, many = (_ms(_records_batch(n, 1200, 680).bin_sort) for n in (4_000_000, 64_000_000))
+    assert many < 28 * few, (few, many)
