@@ -64,7 +64,8 @@ ls_status overlap_check_args(const float* p_mean, int32_t np, const float* q_mea
 namespace {
 
 struct Layout {
-  size_t k0, v0, k1, v1, hist, blk_cnt, kept, cnt, tile_total, tile_before, groups, tile_part, pose_part, loss_part, used, g2d,
+  size_t k0, v0, k1, v1, hist, blk_cnt, kept, cnt, tile_total, tile_before, groups, kept_off, bsum, first, tk, tv,
+      pair_hist, pair_seg, tile_part, pose_part, loss_part, used, g2d,
       total;
 };
 
@@ -85,10 +86,20 @@ Layout layout_of(const ls_batch* b, int64_t cap) {
   L.hist = take(4 * (size_t)seg_hist_words(b->sort_blocks, b->R));
   L.blk_cnt = take(4 * (size_t)b->sort_blocks);
   L.kept = take(4 * (size_t)b->R);
-  L.cnt = take(4 * (size_t)b->bincnt_off[b->R]);
-  L.tile_total = take(4 * T);
-  L.tile_before = take(4 * T);
-  L.groups = take(8 * ((T + 63) / 64 + 1));
+  if (b->bin_pairs) {
+    L.kept_off = take(4 * ((size_t)b->R + 1));
+    L.bsum = take(8 * (size_t)pair_item_blocks(M));
+    L.first = take(4 * (size_t)pair_spans_room(cap));
+    L.tk = take(4 * (size_t)cap);
+    L.tv = take(4 * (size_t)cap);
+    L.pair_hist = take(4 * (size_t)seg_hist_words(pair_sort_blocks_room(cap), 1));
+    L.pair_seg = take(32);
+  } else {
+    L.cnt = take(4 * (size_t)b->bincnt_off[b->R]);
+    L.tile_total = take(4 * T);
+    L.tile_before = take(4 * T);
+    L.groups = take(8 * ((T + 63) / 64 + 1));
+  }
   L.tile_part = take(4 * (size_t)kPoseAcc * std::max(b->T, 1));
   L.pose_part = take(4 * (size_t)kPoseAcc * std::max(b->nblk_items, 1));
   L.loss_part = take(4 * 8 * (size_t)std::max(b->T, 1));  // per 8x8 band {L1 sum, pixels in Omega}
@@ -285,11 +296,27 @@ static ls_status batch_host(const ls_render_job* jobs, int32_t R, ls_batch** out
   b->nblk_items = b->blk_off[R];
   b->nblk_pix = b->pblk_off[R];
   b->nblk_ssim = b->sblk_off[R];
-  // binning: radix sort blocks; then chunks of sorted items with their tile
-  // windows and count matrices, at most about 4,096 chunks (half as many for
-  // 16 renders of 150k and 120k items: lists 67 -> 101 us) and 16 M counts
-  // (64 MiB: 14 us to write and 28 us to scan at the rate of a large copy; only
-  // large images reach it)
+  // Binning: chunks of sorted items, each counted over all tiles of its render
+  // (binning.hip), or a sort of (tile, item) pairs (binning_pairs.hip).  Chunks cost by
+  // the tiles and by the items times the render's tile windows, pairs by the
+  // instances, of which only the item count is known here, and more launches.  The
+  // line is a fit to both over 800 batches of 300 to 5M items, 1 to 256 renders and 80
+  // to 2M tiles (us with chunks and with pairs: 100k items at 2560 x 1440 80 and 91,
+  // 300k 125 and 111; 5k at 4096 x 4096 57 and 54, 20k 111 and 79; 1M at 12000 x 9000
+  // 23,992 and 392; 32 x 4k at 1200 x 680 67 and 76, 128 x 4k 182 and 114; 16 x 20k at
+  // 1920 x 1080 122 and 127, 32 x 20k 185 and 167).  Chunks of a render with very many
+  // items per tile leave most threads idle (1M at 160 x 120 174 and 134, 300k 85 and 89).
+  constexpr int64_t kMaxPerTile = 8192;
+  int64_t item_windows = 0;
+  bool heaped = false;
+  for (const JobDev& d : b->jobs_h) {
+    item_windows += (int64_t)d.n * ls::windows_of(d.TX, d.TY);
+    heaped |= d.n > kMaxPerTile * d.TX * d.TY;
+  }
+  b->bin_pairs = heaped || 0.45 * b->T + 0.16 * item_windows > 60e3 + 0.22 * b->M;
+  // At most about 4,096 chunks (half as many for 16 renders of 150k and 120k items:
+  // lists 67 -> 101 us) and 16 M counts (64 MiB: 14 us to write and 28 us to scan at
+  // the rate of a large copy).
   b->bin_chunk = 512;
   b->bin_ramp = R == 1 || b->M / b->bin_chunk <= 512;
   const auto counts = [&] {
@@ -298,6 +325,7 @@ static ls_status batch_host(const ls_render_job* jobs, int32_t R, ls_batch** out
     return n;
   };
   while (b->bin_chunk < 1 << 20 && (b->M / b->bin_chunk > 4096 || counts() > 1 << 24)) b->bin_chunk *= 2;
+  b->bin_pairs |= counts() > 1 << 24;
   b->sortblk_off.assign(R + 1, 0);
   b->binwork_off.assign(R + 1, 0);
   b->bincnt_off.assign(R + 1, 0);
@@ -553,6 +581,11 @@ ls_status ls_bin_sort(const ls_batch* b, const ls_projected* p, const ls_bins* b
   bl.tile_total = at<uint32_t>(w, L.tile_total);
   bl.tile_before = at<uint32_t>(w, L.tile_before);
   bl.groups = at<uint64_t>(w, L.groups);
+  bl.M = b->M;
+  if (b->bin_pairs)
+    bl.pairs = PairLaunch{at<int32_t>(w, L.kept_off), at<uint64_t>(w, L.bsum),      at<uint32_t>(w, L.first),
+                          at<uint32_t>(w, L.tk),      at<uint32_t>(w, L.tv),        at<uint32_t>(w, L.pair_hist),
+                          {at<int32_t>(w, L.pair_seg), at<int64_t>(w, L.pair_seg + 16)}};
   bl.tile_of = bins->tile_of;
   bl.item = bins->item;
   bl.range = bins->range;

@@ -8,11 +8,12 @@
 //     16,384 items has them ranked by comparison, in a batch of such renders a
 //     block each sorts them in LDS, in one launch; larger ones take a histogram
 //     and a scatter per digit, and the scatter forms its digit bases from the
-//     block histograms itself.
+//     block histograms itself (or, of many blocks, a scan does).
 //  2. The sorted items are cut into chunks.  One block per chunk counts the
 //     items of every tile of its render, a scan over the chunks turns the
 //     counts into each chunk's first place in each tile's list, and one block
 //     per chunk then writes the instances straight to their final places.
+//     Large images and sparse batches go by binning_pairs.hip instead.
 //
 // Every instance is written once, and no (tile, item) pairs are sorted: the
 // pair sort it replaces moved each instance three times in 8 launches (all of
@@ -47,12 +48,18 @@ __global__ void k_fill_i32(int32_t* __restrict__ p, int64_t n, int32_t v) {
 
 constexpr int kSortWaves = kSortThreads / 64;
 constexpr int kSortBits = 8;
+// Words between two blocks' histograms: 256 counts, and some more so that one
+// digit's counts spread over the memory channels (109 M pairs, 26,700 blocks: 3,254
+// us at 256 words, 3,069 at 272, 3,081 at 320; 42 M, 10,300: 1,388, 1,419 and 1,265).
+constexpr int kHistRow = 320;
 template <int kBits>
 struct Digit {
   static constexpr int kBins = 1 << kBits;
   static constexpr int kPer = kBins > kSortThreads ? kBins / kSortThreads : 1;  // bins per thread (1 or 2)
   static constexpr int kThreads = kBins / kPer;                                 // threads with bins
-  __device__ __forceinline__ static uint32_t of(uint32_t key, int shift) { return (key >> shift) & (kBins - 1); }
+  __device__ __forceinline__ static uint32_t of(uint32_t key, int shift, uint32_t mask = kBins - 1) {
+    return (key >> shift) & mask;
+  }
 };
 
 // Exclusive prefix of one value per thread over the first kThreads threads (the
@@ -74,14 +81,14 @@ __device__ __forceinline__ uint32_t digit_excl(uint32_t v, uint32_t* wsum) {
 // counts in its own LDS row (cleared here).
 template <int kBits, int kPer>
 __device__ __forceinline__ void wave_ranks(const uint32_t (&key)[kPer], const bool (&ok)[kPer], int shift,
-                                           uint16_t* row, int lane, uint32_t (&rk)[kPer]) {
+                                           uint32_t mask, uint16_t* row, int lane, uint32_t (&rk)[kPer]) {
   const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
 #pragma unroll
   for (int d = 0; d < Digit<kBits>::kBins / 128; ++d) reinterpret_cast<uint32_t*>(row)[64 * d + lane] = 0u;
   __builtin_amdgcn_wave_barrier();
 #pragma unroll
   for (int j = 0; j < kPer; ++j) {
-    const uint32_t d = Digit<kBits>::of(key[j], shift);
+    const uint32_t d = Digit<kBits>::of(key[j], shift, mask);
     const uint64_t valid = __ballot(ok[j]);
     rk[j] = 0u;
     if (valid != 0ull) {  // uniform
@@ -141,7 +148,7 @@ __device__ __forceinline__ uint32_t digit_starts(uint16_t (*wcnt)[Digit<kBits>::
 // Digit counts of every block's keys: hist[block][digit].
 template <int kPer>
 __global__ __launch_bounds__(kSortThreads) void k_seg_hist(const uint32_t* __restrict__ keys, SegTable seg, int shift,
-                                                           uint32_t* __restrict__ hist) {
+                                                           uint32_t mask, uint32_t* __restrict__ hist) {
   using D = Digit<kSortBits>;
   constexpr int kKeys = kPer * kSortThreads;
   __shared__ uint32_t h[D::kBins];
@@ -160,9 +167,9 @@ __global__ __launch_bounds__(kSortThreads) void k_seg_hist(const uint32_t* __res
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < kPer; ++j)
-    if (j * kSortThreads + (int)threadIdx.x < m) atomicAdd(&h[D::of(key[j], shift)], 1u);
+    if (j * kSortThreads + (int)threadIdx.x < m) atomicAdd(&h[D::of(key[j], shift, mask)], 1u);
   __syncthreads();
-  for (int d = threadIdx.x; d < D::kBins; d += kSortThreads) hist[(int64_t)blockIdx.x * D::kBins + d] = h[d];
+  for (int d = threadIdx.x; d < D::kBins; d += kSortThreads) hist[(int64_t)blockIdx.x * kHistRow + d] = h[d];
 }
 
 // Sums of digit d's counts over the segment's blocks and over those before this
@@ -179,7 +186,7 @@ __device__ __forceinline__ void digit_bases(const uint32_t* __restrict__ rows, i
     uint32_t v[kAhead];
 #pragma unroll
     for (int k = 0; k < kAhead; ++k)
-      v[k] = r0 + k * kParts < nrows ? rows[(int64_t)(r0 + k * kParts) * D::kBins + d] : 0u;
+      v[k] = r0 + k * kParts < nrows ? rows[(int64_t)(r0 + k * kParts) * kHistRow + d] : 0u;
 #pragma unroll
     for (int k = 0; k < kAhead; ++k) {
       total += v[k];
@@ -210,7 +217,7 @@ __global__ __launch_bounds__(kSortThreads) void k_seg_scatter(const uint32_t* __
                                                               const uint32_t* __restrict__ vin,
                                                               uint32_t* __restrict__ kout,
                                                               uint32_t* __restrict__ vout, SegTable seg, int shift,
-                                                              const uint32_t* __restrict__ hist,
+                                                              uint32_t mask, const uint32_t* __restrict__ hist,
                                                               const int32_t* __restrict__ blk_cnt,
                                                               const uint32_t* __restrict__ sums) {
   using D = Digit<kSortBits>;
@@ -238,14 +245,14 @@ __global__ __launch_bounds__(kSortThreads) void k_seg_scatter(const uint32_t* __
   }
   uint32_t total = 0u, before = 0u, lstart[1];
   if (sums == nullptr) {
-    digit_bases(hist + (int64_t)b0 * D::kBins, nrows, c, sk, sv, total, before);
+    digit_bases(hist + (int64_t)b0 * kHistRow, nrows, c, sk, sv, total, before);
   } else if ((int)threadIdx.x < D::kThreads) {
     total = sums[s * D::kBins + threadIdx.x];
-    before = hist[(int64_t)blockIdx.x * D::kBins + threadIdx.x];
+    before = hist[(int64_t)blockIdx.x * kHistRow + threadIdx.x];
   }
   const uint32_t first = digit_excl<D::kThreads>(total, wsum[0]);  // of the thread's digit, in the segment
   if (kFirst && c == 0 && threadIdx.x == D::kThreads - 1) seg.len[s] = (int32_t)(first + total);
-  wave_ranks<kSortBits, kPer>(key, ok, shift, wcnt[w], lane, rk);
+  wave_ranks<kSortBits, kPer>(key, ok, shift, mask, wcnt[w], lane, rk);
   __syncthreads();
   digit_starts<kSortBits>(wcnt, wsum[1], lstart);
   if ((int)threadIdx.x < D::kThreads) delta[threadIdx.x] = first + before - lstart[0];
@@ -253,7 +260,7 @@ __global__ __launch_bounds__(kSortThreads) void k_seg_scatter(const uint32_t* __
 #pragma unroll
   for (int j = 0; j < kPer; ++j)
     if (ok[j]) {
-      const uint32_t pos = wcnt[w][D::of(key[j], shift)] + rk[j];
+      const uint32_t pos = wcnt[w][D::of(key[j], shift, mask)] + rk[j];
       sk[pos] = key[j];
       sv[pos] = val[j];
     }
@@ -264,7 +271,7 @@ __global__ __launch_bounds__(kSortThreads) void k_seg_scatter(const uint32_t* __
     const int i = j * kSortThreads + threadIdx.x;
     if (i < m) {
       const uint32_t k = sk[i];
-      const int64_t pos = out0 + (uint32_t)(delta[D::of(k, shift)] + (uint32_t)i);
+      const int64_t pos = out0 + (uint32_t)(delta[D::of(k, shift, mask)] + (uint32_t)i);
       if (!kLast) kout[pos] = k;
       vout[pos] = sv[i];
     }
@@ -272,39 +279,39 @@ __global__ __launch_bounds__(kSortThreads) void k_seg_scatter(const uint32_t* __
 }
 
 // Segments of many blocks: the digits' counts turned into each block's bases, in
-// place, and the segments' digit totals into sums.  32 digits of a segment to a
-// block, 32 threads to a digit, each a run of blocks.  kFirst as above.
+// place, and the segments' digit totals into sums.  kScanDigits digits of a
+// segment to a block, kParts threads to a digit, each a run of blocks.  kFirst as
+// above.
 //
-// A block that adds up its segment's counts for itself reads 1 KB per block, so a
-// pass reads the square of the blocks: past kScanRows of them the launch costs
-// less (binning without and with it at 1200 x 680: 500k items, 245 blocks, 96.6
-// and 100.6 us; 1M, 489, 157 and 150 us; 5M, 1,221, 496 and 404 us; 10M, 2,442,
-// 1,161 and 767 us).
-constexpr int kScanRows = 256;
+// A scatter block that adds up its segment's counts for itself reads 1 KB per
+// block, so a pass reads the square of the blocks: past kScanRows of them the
+// launch costs less (binning without and with it at 1200 x 680: 500k items, 245
+// blocks, 96 and 100 us; 1M, 489, 157 and 151 us; 10M, 2,442, 1,161 and 743 us).
+constexpr int kScanRows = 256, kScanDigits = 16;
 template <int kPer, bool kFirst>
 __global__ __launch_bounds__(1024) void k_seg_scan(SegTable seg, uint32_t* __restrict__ hist,
                                                    uint32_t* __restrict__ sums) {
   using D = Digit<kSortBits>;
-  constexpr int kKeys = kPer * kSortThreads, kDigits = 32, kParts = 1024 / kDigits, kAhead = 8;
-  __shared__ uint32_t part[kParts][kDigits];
-  const int s = blockIdx.x / (D::kBins / kDigits), d0 = blockIdx.x % (D::kBins / kDigits) * kDigits;
-  const int d = threadIdx.x % kDigits, p = threadIdx.x / kDigits;
+  constexpr int kKeys = kPer * kSortThreads, kParts = 1024 / kScanDigits, kAhead = 16;
+  __shared__ uint32_t part[kParts][kScanDigits];
+  const int s = blockIdx.x / (D::kBins / kScanDigits), d0 = blockIdx.x % (D::kBins / kScanDigits) * kScanDigits;
+  const int d = threadIdx.x % kScanDigits, p = threadIdx.x / kScanDigits;
   const int b0 = seg.blk_off[s], all = seg.blk_off[s + 1] - b0;
   const int rows = kFirst ? all : (seg.len[s] + kKeys - 1) / kKeys;
   const int per = (rows + kParts - 1) / kParts, lo = min(p * per, rows), hi = min(lo + per, rows);
-  uint32_t* __restrict__ col = hist + (int64_t)b0 * D::kBins + d0 + d;
+  uint32_t* __restrict__ col = hist + (int64_t)b0 * kHistRow + d0 + d;
   uint32_t sum = 0;
   for (int r = lo; r < hi; r += kAhead) {
     uint32_t v[kAhead];
 #pragma unroll
-    for (int k = 0; k < kAhead; ++k) v[k] = r + k < hi ? col[(int64_t)(r + k) * D::kBins] : 0u;
+    for (int k = 0; k < kAhead; ++k) v[k] = r + k < hi ? col[(int64_t)(r + k) * kHistRow] : 0u;
 #pragma unroll
     for (int k = 0; k < kAhead; ++k) sum += v[k];
   }
   part[p][d] = sum;
   __syncthreads();
   uint32_t run = 0, total = 0;
-#pragma unroll
+#pragma unroll 16
   for (int k = 0; k < kParts; ++k) {
     run += k < p ? part[k][d] : 0u;
     total += part[k][d];
@@ -312,11 +319,11 @@ __global__ __launch_bounds__(1024) void k_seg_scan(SegTable seg, uint32_t* __res
   for (int r = lo; r < hi; r += kAhead) {
     uint32_t v[kAhead];
 #pragma unroll
-    for (int k = 0; k < kAhead; ++k) v[k] = r + k < hi ? col[(int64_t)(r + k) * D::kBins] : 0u;
+    for (int k = 0; k < kAhead; ++k) v[k] = r + k < hi ? col[(int64_t)(r + k) * kHistRow] : 0u;
 #pragma unroll
     for (int k = 0; k < kAhead; ++k)
       if (r + k < hi) {
-        col[(int64_t)(r + k) * D::kBins] = run;
+        col[(int64_t)(r + k) * kHistRow] = run;
         run += v[k];
       }
   }
@@ -324,7 +331,7 @@ __global__ __launch_bounds__(1024) void k_seg_scan(SegTable seg, uint32_t* __res
 }
 
 int64_t seg_hist_words(int nblk, int nseg) {
-  return (int64_t)Digit<kSortBits>::kBins * ((int64_t)std::max(nblk, 1) + nseg);
+  return (int64_t)kHistRow * std::max(nblk, 1) + (int64_t)Digit<kSortBits>::kBins * nseg;
 }
 
 // ---------------------------------------------------------------------------
@@ -380,7 +387,7 @@ __global__ __launch_bounds__(kSortThreads) void k_depth_prep(const JobDev* __res
     }
   }
   __syncthreads();
-  for (int d = threadIdx.x; d < D::kBins; d += kSortThreads) hist[(int64_t)blockIdx.x * D::kBins + d] = h[d];
+  for (int d = threadIdx.x; d < D::kBins; d += kSortThreads) hist[(int64_t)blockIdx.x * kHistRow + d] = h[d];
   if (threadIdx.x == 0) blk_cnt[blockIdx.x] = (int32_t)run;
 }
 
@@ -532,7 +539,7 @@ __global__ __launch_bounds__(kSortThreads) void k_depth_sort_small(const JobDev*
   int m = 0;
 #pragma unroll 1
   for (int shift = 0; shift < 32; shift += kBits) {
-    wave_ranks<kBits, kPer>(key, ok, shift, wcnt[w], lane, rk);
+    wave_ranks<kBits, kPer>(key, ok, shift, D::kBins - 1, wcnt[w], lane, rk);
     __syncthreads();
     uint32_t lstart[D::kPer];
     const uint32_t upto = digit_starts<kBits>(wcnt, wsum, lstart);
@@ -1070,20 +1077,23 @@ void launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s) {
 template <int kPer, bool kFirst>
 static const uint32_t* seg_scan(const SegTable& seg, int blocks, int rows, uint32_t* hist, hipStream_t s) {
   if (rows <= kScanRows) return nullptr;
-  uint32_t* sums = hist + (int64_t)Digit<kSortBits>::kBins * blocks;
-  hipLaunchKernelGGL((k_seg_scan<kPer, kFirst>), dim3(8 * seg.S), dim3(1024), 0, s, seg, hist, sums);
+  uint32_t* sums = hist + (int64_t)kHistRow * blocks;
+  hipLaunchKernelGGL((k_seg_scan<kPer, kFirst>), dim3(Digit<kSortBits>::kBins / kScanDigits * seg.S), dim3(1024), 0, s,
+                     seg, hist, sums);
   return sums;
 }
 
 template <int kPer>
 static void seg_pass(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout, const SegTable& seg,
-                     int blocks, int rows, int shift, uint32_t* hist, bool last, hipStream_t s) {
+                     int blocks, int rows, int shift, int bits, uint32_t* hist, bool last, hipStream_t s) {
   const dim3 grid(blocks), block(kSortThreads);
-  hipLaunchKernelGGL(k_seg_hist<kPer>, grid, block, 0, s, kin, seg, shift, hist);
+  const uint32_t mask = (1u << bits) - 1u;
+  hipLaunchKernelGGL(k_seg_hist<kPer>, grid, block, 0, s, kin, seg, shift, mask, hist);
   const uint32_t* sums = seg_scan<kPer, false>(seg, blocks, rows, hist, s);
   const int32_t* none = nullptr;
   auto scatter = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, grid, block, 0, s, kin, vin, kout, vout, seg, shift, (const uint32_t*)hist, none, sums);
+    hipLaunchKernelGGL(kernel, grid, block, 0, s, kin, vin, kout, vout, seg, shift, mask, (const uint32_t*)hist, none,
+                       sums);
   };
   if (last)
     scatter(k_seg_scatter<kPer, false, true>);
@@ -1100,11 +1110,11 @@ static void depth_passes(const BinLaunch& b, const SegTable& seg, hipStream_t s)
                      b.tiles, b.k0, b.v0, b.hist, b.blk_cnt);
   const uint32_t* sums = seg_scan<kPer, true>(seg, b.sort_blocks, rows, b.hist, s);
   hipLaunchKernelGGL((k_seg_scatter<kPer, true, false>), grid, block, 0, s, (const uint32_t*)b.k0,
-                     (const uint32_t*)b.v0, b.k1, b.v1, seg, 0, (const uint32_t*)b.hist, (const int32_t*)b.blk_cnt,
-                     sums);
-  seg_pass<kPer>(b.k1, b.v1, b.k0, b.v0, seg, b.sort_blocks, rows, 8, b.hist, false, s);
-  seg_pass<kPer>(b.k0, b.v0, b.k1, b.v1, seg, b.sort_blocks, rows, 16, b.hist, false, s);
-  seg_pass<kPer>(b.k1, b.v1, b.k0, b.v0, seg, b.sort_blocks, rows, 24, b.hist, true, s);
+                     (const uint32_t*)b.v0, b.k1, b.v1, seg, 0, 255u, (const uint32_t*)b.hist,
+                     (const int32_t*)b.blk_cnt, sums);
+  seg_pass<kPer>(b.k1, b.v1, b.k0, b.v0, seg, b.sort_blocks, rows, 8, 8, b.hist, false, s);
+  seg_pass<kPer>(b.k0, b.v0, b.k1, b.v1, seg, b.sort_blocks, rows, 16, 8, b.hist, false, s);
+  seg_pass<kPer>(b.k1, b.v1, b.k0, b.v0, seg, b.sort_blocks, rows, 24, 8, b.hist, true, s);
 }
 
 void launch_bin_sort(const BinLaunch& b, hipStream_t s) {
@@ -1136,6 +1146,10 @@ void launch_bin_sort(const BinLaunch& b, hipStream_t s) {
                                           : depth_passes<4>;
     passes(b, seg, s);
   }
+  if (b.pairs.tk) {
+    launch_bin_pairs(b, s);
+    return;
+  }
   const dim3 work(8 * ((b.units + 7) / 8));
   if (b.units > 0)
     hipLaunchKernelGGL(k_chunk_count, work, dim3(kPlaceThreads), 0, s, b.jobs, b.tab, b.units,
@@ -1164,8 +1178,8 @@ void launch_bin_sort(const BinLaunch& b, hipStream_t s) {
 }
 
 void launch_seg_pass(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout, const SegTable& seg,
-                     int blocks, int rows, int per, int shift, uint32_t* hist, bool last, hipStream_t s) {
+                     int blocks, int rows, int per, int shift, int bits, uint32_t* hist, bool last, hipStream_t s) {
   const auto pass = per == 1 ? seg_pass<1> : per == 2 ? seg_pass<2> : per == 3 ? seg_pass<3> : seg_pass<4>;
-  pass(kin, vin, kout, vout, seg, blocks, rows, shift, hist, last, s);
+  pass(kin, vin, kout, vout, seg, blocks, rows, shift, bits, hist, last, s);
 }
 }  // namespace ls

@@ -76,22 +76,23 @@ inline int sort_blocks_of(int64_t n, int per) { return (int)((n + per * kSortThr
 // (320) 98.8 and 92.4, 3 x 80k 90.1 and 88.1; with 2, 3 and 4: 97k 77.5, 80.5
 // and 84.2, 200k 102, 105 and 107, 3 x 80k 90, 92 and 96, 8 x 150k 210 (586
 // blocks), 192 (391) and 200, 16 x 135k 172, 154 (704) and 148.
+constexpr int kSortResident = 512;
 template <class Blocks>
 inline int sort_per(int64_t max_n, const Blocks& blocks) {
-  constexpr int kRound = 64, kCus = 256, kResident = 2 * kCus;
+  constexpr int kRound = 64, kCus = kSortResident / 2;
   if (sort_blocks_of(max_n, 1) <= kRound && blocks(1) <= kCus) return 1;
   int per = 2;
-  while (per < kSortPerMax && blocks(per) > kResident) ++per;
+  while (per < kSortPerMax && blocks(per) > kSortResident) ++per;
   return per;
 }
 // Words of the digit histograms of `blocks` sort blocks and of the `segments`'
 // digit totals.
 int64_t seg_hist_words(int blocks, int segments);
-// One stable pass over the 8-bit digit at `shift` (binning.hip), from
+// One stable pass over the digit of `bits` <= 8 bits at `shift` (binning.hip), from
 // (kin, vin) to (kout, vout); last: kout is not written.  rows: the largest
 // segment's sort blocks.
 void launch_seg_pass(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout, const SegTable& seg,
-                     int blocks, int rows, int per, int shift, uint32_t* hist, bool last, hipStream_t s);
+                     int blocks, int rows, int per, int shift, int bits, uint32_t* hist, bool last, hipStream_t s);
 
 // Device tables of a batch's binning: per render the sort blocks, the chunk x
 // window work units and the count matrices (chunks x tiles words) before it.
@@ -107,6 +108,27 @@ struct BinTables {
 int windows_of(int TX, int TY);
 int bin_chunks(int n, int chunk, bool ramp);
 
+// Workspace of the pair sort (binning_pairs.hip); all NULL where the batch does
+// not take it.
+struct PairSegs {
+  int32_t* blk_off;  // [2]
+  int64_t* base;     // [1]
+};
+struct PairLaunch {
+  int32_t* kept_off;  // [R + 1]
+  uint64_t* bsum;     // [pair_item_blocks(M)]
+  uint32_t* first;    // [pair_spans_room(cap)]
+  uint32_t *tk, *tv;  // [cap]
+  uint32_t* hist;     // seg_hist_words(pair_sort_blocks_room(cap), 1)
+  PairSegs seg;
+};
+int64_t pair_item_blocks(int64_t M);
+// Room for the spans and sort blocks of every capacity up to `cap`: what a capacity
+// takes falls where its spans and blocks become longer, and a workspace for one
+// capacity serves the smaller ones.
+int64_t pair_spans_room(int64_t cap);
+int pair_sort_blocks_room(int64_t cap);
+
 struct BinLaunch {
   const JobDev* jobs;
   const int64_t* item_off;
@@ -116,6 +138,8 @@ struct BinLaunch {
   const int32_t* off256;        // [R + 1]: first block of 256 items of each render; blocks256 of them
   int64_t rank_pairs;           // sum over the renders of the squared item count
   int64_t counts;               // words of the count matrices
+  int64_t M;                    // items
+  PairLaunch pairs;
   const float* rec;
   const int32_t* radius;
   const int32_t* tiles;
@@ -134,6 +158,8 @@ struct BinLaunch {
   int32_t* count;
 };
 void launch_bin_sort(const BinLaunch& b, hipStream_t s);
+// The lists from the depth order (v0, kept) by a sort of pairs.
+void launch_bin_pairs(const BinLaunch& b, hipStream_t s);
 
 // used: 4 rows (one per band) of ustride = used_slots(capacity, T) 64-bit
 // words; the forward sets bit l of slot (start / 64) + tile + k of row q when

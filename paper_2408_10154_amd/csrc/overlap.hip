@@ -558,10 +558,10 @@ void launch_overlap(const float* p_mean, int np, const float* q_mean, int nq, co
                      np, q_mean, nq, (const float*)box, ca, ia);
   // both sets in one sort; four passes over the 30-bit codes end in (ca, ia)
   const SegTable seg{segs.blk_off, segs.base, 2, segs.len};
-  launch_seg_pass(ca, ia, cb, ib, seg, nsb, rows, per, 0, hist, false, s);
-  launch_seg_pass(cb, ib, ca, ia, seg, nsb, rows, per, 8, hist, false, s);
-  launch_seg_pass(ca, ia, cb, ib, seg, nsb, rows, per, 16, hist, false, s);
-  launch_seg_pass(cb, ib, ca, ia, seg, nsb, rows, per, 24, hist, false, s);
+  launch_seg_pass(ca, ia, cb, ib, seg, nsb, rows, per, 0, 8, hist, false, s);
+  launch_seg_pass(cb, ib, ca, ia, seg, nsb, rows, per, 8, 8, hist, false, s);
+  launch_seg_pass(ca, ia, cb, ib, seg, nsb, rows, per, 16, 8, hist, false, s);
+  launch_seg_pass(cb, ib, ca, ia, seg, nsb, rows, per, 24, 6, hist, false, s);
   OvSet set[2];
   for (int k = 0; k < 2; ++k) {
     const int n = k ? nq : np;

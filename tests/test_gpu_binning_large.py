@@ -5,14 +5,24 @@ import pytest
 import torch
 
 from paper_2408_10154_amd import synth
-from tests.test_gpu_binning_sizes import SMALL, test_lists_equal_the_oracle as _lists_equal_the_oracle
+from tests.test_gpu_binning_sizes import OVER, SMALL, WIDE, _records, test_lists_equal_the_oracle as _lists_equal
 
 pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("sizes", [[530000], [526000, 0, 300]])  # 259 and 257 sort blocks in the largest segment
 def test_scanned_sort_counts(gpu, sizes):
-    _lists_equal_the_oracle(gpu, sizes, SMALL, 0.9)
+    _lists_equal(gpu, sizes, SMALL, 0.9)
+
+
+@pytest.mark.parametrize("sizes,image,culled", [
+    ([3000], (6000, 6000), 0.0), ([1], (6000, 6000), 0.0), ([30000], (6000, 6000), 0.2),   # 18 bits: three digits of 6
+    ([600, 0, 2000, 1, 0], (4112, 4100), 0.1), ([17000, 300], (4600, 4600), 0.3),          # renders without items
+    ([9000, 20000], (16, 16), 0.0), ([9000], (16, 16), 1.0), ([70000], (33, 17), 0.2),     # over 8,192 items a tile
+    ([260] * 400, (640, 480), 0.1),                                                        # many small renders
+])
+def test_lists_by_pairs(gpu, sizes, image, culled):
+    _lists_equal(gpu, sizes, image, culled)
 
 
 def _records_batch(n, W, H, R=1):
@@ -52,3 +62,21 @@ def test_binning_time_grows_with_the_items(gpu):
     each other's counts takes 50 times as long at these sizes."""
     few, many = (_ms(_records_batch(n, 1200, 680).bin_sort) for n in (4_000_000, 64_000_000))
     assert many < 28 * few, (few, many)
+
+
+def test_binning_time_does_not_follow_the_image(gpu):
+    """The same items on an image of 80 times the tiles: distributing every item over
+    all tiles takes 50 times as long there."""
+    small, large = (_ms(_records_batch(300_000, W, H).bin_sort) for W, H in ((1200, 680), (8192, 8192)))
+    assert large < 8 * small, (small, large)
+
+
+def test_workspace_does_not_hold_items_times_tiles(gpu):
+    """64 renders of 4096 x 4096 with 4,000 items each and with one item each: less
+    than 100 MB of workspace apart (the records and sort buffers are 20 MB; a count
+    per tile and 64 items would be 700 MB)."""
+    from paper_2408_10154_amd import lib as L
+
+    batches = [_records_batch(n, 4096, 4096, 64) for n in (1, 4000)]
+    size = [L.ls_batch_query(b.h, 1 << 20).workspace_bytes for b in batches]
+    assert size[1] - size[0] < 100e6, size
