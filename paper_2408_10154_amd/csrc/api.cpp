@@ -314,18 +314,29 @@ static ls_status batch_host(const ls_render_job* jobs, int32_t R, ls_batch** out
     heaped |= d.n > kMaxPerTile * d.TX * d.TY;
   }
   b->bin_pairs = heaped || 0.45 * b->T + 0.16 * item_windows > 60e3 + 0.22 * b->M;
-  // At most about 4,096 chunks (half as many for 16 renders of 150k and 120k items:
-  // lists 67 -> 101 us) and 16 M counts (64 MiB: 14 us to write and 28 us to scan at
-  // the rate of a large copy).
-  b->bin_chunk = 512;
-  b->bin_ramp = R == 1 || b->M / b->bin_chunk <= 512;
-  const auto counts = [&] {
-    int64_t n = 0;
-    for (const JobDev& d : b->jobs_h) n += (int64_t)ls::bin_chunks(d.n, b->bin_chunk, b->bin_ramp) * d.TX * d.TY;
-    return n;
+  // The count matrices hold at most 8 M words, by larger chunks (2M items at 1200 x
+  // 680 205 us, 248 with 16 M words; 8 x 300k 268 us with either, 322 with 4 M), and
+  // there are at most about 4,096 chunks (half as many for 16 renders of 150k and 120k
+  // items: lists 67 -> 101 us).  Finer first chunks (chunk_first) help a single render
+  // and a batch of up to 384 chunks (8 x 4k items at 640 x 480, 288 chunks: 32 us, 36
+  // without; 16 x 4k, 576: 41 and 40; 128 x 1k, 2,048: 106 and 75).
+  constexpr int64_t kMaxCounts = 1 << 23, kMaxChunks = 4096, kRampChunks = 384;
+  int64_t chunks, counts;
+  const auto cut = [&](int chunk, bool ramp) {
+    b->bin_chunk = chunk;
+    b->bin_ramp = ramp;
+    chunks = counts = 0;
+    for (const JobDev& d : b->jobs_h) {
+      const int64_t c = ls::bin_chunks(d.n, chunk, ramp);
+      chunks += c;
+      counts += c * d.TX * d.TY;
+    }
   };
-  while (b->bin_chunk < 1 << 20 && (b->M / b->bin_chunk > 4096 || counts() > 1 << 24)) b->bin_chunk *= 2;
-  b->bin_pairs |= counts() > 1 << 24;
+  cut(512, true);
+  if (R > 1 && chunks > kRampChunks) cut(512, false);
+  while (b->bin_chunk < 1 << 20 && (b->M / b->bin_chunk > kMaxChunks || counts > kMaxCounts))
+    cut(2 * b->bin_chunk, b->bin_ramp);
+  b->bin_pairs |= counts > kMaxCounts;
   b->sortblk_off.assign(R + 1, 0);
   b->binwork_off.assign(R + 1, 0);
   b->bincnt_off.assign(R + 1, 0);

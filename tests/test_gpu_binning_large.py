@@ -25,6 +25,15 @@ def test_lists_by_pairs(gpu, sizes, image, culled):
     _lists_equal(gpu, sizes, image, culled)
 
 
+@pytest.mark.parametrize("sizes,image,culled", [
+    ([140000] * 16, SMALL, 0.97),       # 4,375 chunks of 512: chunks of 1,024 items
+    ([1100000], (1024, 1024), 0.93),    # 2,183 chunks x 4,096 tiles, with finer first chunks
+    ([4000] * 10, SMALL, 0.3), ([4000] * 11, SMALL, 0.3),  # 360 chunks with finer first ones, and 396: without
+])
+def test_chunks_of_other_sizes(gpu, sizes, image, culled):
+    _lists_equal(gpu, sizes, image, culled)
+
+
 def _records_batch(n, W, H, R=1):
     """R renders of n items with random records of one tile or a few each."""
     from paper_2408_10154_amd.render import GaussianSet, RenderBatch
