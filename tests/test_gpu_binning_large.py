@@ -89,3 +89,53 @@ def test_workspace_does_not_hold_items_times_tiles(gpu):
     batches = [_records_batch(n, 4096, 4096, 64) for n in (1, 4000)]
     size = [L.ls_batch_query(b.h, 1 << 20).workspace_bytes for b in batches]
     assert size[1] - size[0] < 100e6, size
+
+
+@pytest.mark.parametrize("frac", [0.0, 0.37, 1.0])
+@pytest.mark.parametrize("sizes,image,culled", [
+    ([3000], SMALL, 0.0),               # one launch less: a single render of up to 1,024 tiles
+    ([3000], OVER, 0.0),                # the groups' starts by every block
+    ([300], (4112, 4100), 0.0),         # over 65,536 tiles: their own launch
+    ([900], WIDE, 0.1),                 # several tile windows
+    ([17000], SMALL, 0.3),              # depth order by radix passes
+    ([5000] * 8, SMALL, 0.3),           # by a block per render
+    ([1100000], (1024, 1024), 0.95),    # chunks of 1,024 items
+    ([3000], (6000, 6000), 0.0), ([600, 0, 2000], (4600, 4600), 0.1), ([9000], (16, 16), 0.0),  # pairs
+])
+def test_capacity_bounds_every_form(gpu, sizes, image, culled, frac):
+    """Capacity 0, a fraction of the instances I, and I: count is {min(I, capacity),
+    I > capacity, I, 0}, nothing is written past the capacity in the lists or past the
+    workspace, ranges stay within the capacity, and at I the lists are those of an
+    ample capacity."""
+    from paper_2408_10154_amd import lib as L
+    from paper_2408_10154_amd.render import GaussianSet, RenderBatch
+
+    rng = np.random.default_rng(len(sizes) + image[0])
+    W, H = image
+    cam = synth.camera(W, W, W / 2, H / 2, W, H)
+    b = RenderBatch([(GaussianSet.from_numpy(synth.gaussians_in_box(rng, n, (-1, -1, 1), (1, 1, 2))), cam,
+                      synth.identity_w2c()) for n in sizes])
+    for r, n in enumerate(sizes):
+        if n:
+            o = int(b.item_off[r])
+            for dst, src in zip((b.rec, b.radius, b.tiles), _records(rng, n, cam, culled)):
+                dst[o:o + n] = torch.as_tensor(src, device="cuda")
+    b.bin_sort()
+    n = b.instances()
+    want = [t.clone() for t in (b.tile_of[:n], b.item[:n], b.range)]
+    cap, guard = int(n * frac), 4096
+    lists = [torch.full((cap + guard,), -7, dtype=torch.int32, device="cuda") for _ in range(2)]
+    need = int(L.ls_batch_query(b.h, cap).workspace_bytes)
+    work = torch.zeros(need + 256 + guard, dtype=torch.uint8, device="cuda")
+    at = (work.data_ptr() + 255) // 256 * 256
+    tail = at - work.data_ptr() + need
+    work[tail:] = 0xA5
+    bins = L.ls_bins(cap, lists[0].data_ptr(), lists[1].data_ptr(), b.range.data_ptr(), b.count.data_ptr(), at)
+    L.ls_bin_sort(b.h, b.proj, bins, L.C.c_void_p(torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    assert n > 0 and b.count.cpu().tolist() == [min(n, cap), int(n > cap), n, 0]
+    assert all(bool((t[cap:] == -7).all()) for t in lists) and bool((work[tail:] == 0xA5).all())
+    assert int(b.range.min()) >= 0 and int(b.range.max()) <= cap
+    if frac == 1.0:
+        for got, ref in zip((*(t[:n] for t in lists), b.range), want):
+            assert torch.equal(got, ref)
