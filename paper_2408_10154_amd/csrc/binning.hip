@@ -330,8 +330,8 @@ __global__ __launch_bounds__(1024) void k_seg_scan(SegTable seg, uint32_t* __res
   if (p == 0) sums[s * D::kBins + d0 + d] = total;
 }
 
-int64_t seg_hist_words(int nblk, int nseg) {
-  return (int64_t)kHistRow * std::max(nblk, 1) + (int64_t)Digit<kSortBits>::kBins * nseg;
+int64_t seg_hist_words(int64_t nblk, int nseg) {
+  return kHistRow * std::max<int64_t>(nblk, 1) + (int64_t)Digit<kSortBits>::kBins * nseg;
 }
 
 // ---------------------------------------------------------------------------

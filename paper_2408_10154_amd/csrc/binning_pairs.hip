@@ -29,9 +29,6 @@ static int64_t emit_span(int64_t cap) {
 int64_t pair_spans_room(int64_t cap) {
   return std::max(spans_of(cap, kSpanMax), std::min<int64_t>(spans_of(cap, kSpanMin), kSpanWaves));
 }
-int pair_sort_blocks_room(int64_t cap) {
-  return std::max(sort_blocks_of(cap, kSortPerMax), std::min(sort_blocks_of(cap, 1), kSortResident));
-}
 
 // The renders' first places in the sequence of all sorted items, kept_off[R] = K of
 // them, and the pairs as one segment of a sort of `blocks` blocks.  One block.

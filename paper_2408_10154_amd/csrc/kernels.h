@@ -1,6 +1,8 @@
 // Host-side launchers of the gfx950 kernels (defined next to each kernel).
 #pragma once
 
+#include <algorithm>
+
 #include "common.h"
 
 namespace ls {
@@ -85,9 +87,15 @@ inline int sort_per(int64_t max_n, const Blocks& blocks) {
   while (per < kSortPerMax && blocks(per) > kSortResident) ++per;
   return per;
 }
+// Room for the sort blocks of these sizes and of all smaller ones (blocks fall
+// where sort_per rises): a workspace for some size serves the smaller ones.
+template <class Blocks>
+inline int64_t sort_blocks_room(const Blocks& blocks) {
+  return std::max<int64_t>(blocks(kSortPerMax), std::min<int64_t>(blocks(1), kSortResident));
+}
 // Words of the digit histograms of `blocks` sort blocks and of the `segments`'
 // digit totals.
-int64_t seg_hist_words(int blocks, int segments);
+int64_t seg_hist_words(int64_t blocks, int segments);
 // One stable pass over the digit of `bits` <= 8 bits at `shift` (binning.hip), from
 // (kin, vin) to (kout, vout); last: kout is not written.  rows: the largest
 // segment's sort blocks.
@@ -123,11 +131,11 @@ struct PairLaunch {
   PairSegs seg;
 };
 int64_t pair_item_blocks(int64_t M);
-// Room for the spans and sort blocks of every capacity up to `cap`: what a capacity
-// takes falls where its spans and blocks become longer, and a workspace for one
-// capacity serves the smaller ones.
+// Room for the spans of every capacity up to `cap`, as of the sort blocks.
 int64_t pair_spans_room(int64_t cap);
-int pair_sort_blocks_room(int64_t cap);
+inline int64_t pair_sort_blocks_room(int64_t cap) {
+  return sort_blocks_room([&](int per) { return sort_blocks_of(cap, per); });
+}
 
 struct BinLaunch {
   const JobDev* jobs;

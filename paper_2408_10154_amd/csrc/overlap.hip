@@ -509,7 +509,8 @@ static OvLayout ov_layout(int np, int nq) {
   L.idx_a = take(4 * both);
   L.code_b = take(4 * both);
   L.idx_b = take(4 * both);
-  L.hist = take(4 * (size_t)seg_hist_words(ov_sort_blocks(np, nq, ov_sort_per(np, nq)), 2));
+  const int64_t room = sort_blocks_room([&](int per) { return ov_sort_blocks(np, nq, per); });
+  L.hist = take(4 * (size_t)seg_hist_words(room, 2));
   for (int s = 0; s < 2; ++s) {
     const int n = s ? nq : np;
     const int nleaf = (n + kOvLeaf - 1) / kOvLeaf, nsuper = (nleaf + kOvSuper - 1) / kOvSuper;

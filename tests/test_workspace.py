@@ -17,3 +17,14 @@ def test_registration_workspace_grows_with_the_capacity():
     for w, h in ((64, 48), (6000, 6000)):  # the lists by chunks and by pairs
         pair, keep = _host_pair(w=w, h=h)
         assert _non_decreasing([L.ls_register_workspace_size(pair, prm, c) for c in EDGES]), (w, h)
+
+
+def test_overlap_workspace_grows_with_the_points():
+    """In each set alone, in both together, and against the static scratch."""
+    size = L.ls_overlap_workspace_size
+    for other in (0, 1, 1 << 16, 1 << 18, (1 << 18) + 1, 1 << 19):
+        assert _non_decreasing([size(n, other) for n in EDGES]), other
+        assert _non_decreasing([size(other, n) for n in EDGES]), other
+    assert _non_decreasing([size(n, n) for n in EDGES])
+    mx = L.LS_OVERLAP_NOALLOC_MAX_POINTS
+    assert max(size(a, b) for a in EDGES for b in EDGES if max(a, b) <= mx) <= L.LS_OVERLAP_NOALLOC_BYTES
