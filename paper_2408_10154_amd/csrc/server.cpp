@@ -77,15 +77,33 @@ struct Slot {
   }
 };
 
-// Device bytes the server allocates per item / pixel / expected instance.
-constexpr double kBytesPerItem = 48 + 48 + 8 + 16 + 40 + 8;
-constexpr double kBytesPerPixel = 12 + 4 + 4 + 4 + 4 + 12 + 4;
-constexpr double kInstancesPerItem = 8.0;
-constexpr double kBytesPerInstance = 16 + 8;
+constexpr double kInstancesPerItem = 8.0;  // expected of a pair before its first iteration
+// Beyond the buffers' contents, once per server: the part pages at the ends of a
+// dozen allocations, and the graph (110k items at 256 x 192: 30 MB of contents, 46 MB
+// of device memory).
+constexpr size_t kServerBytes = 16u << 20;
 
-size_t estimate_bytes(int64_t items, int64_t pixels) {
-  return (size_t)(items * (kBytesPerItem + kInstancesPerItem * kBytesPerInstance) + pixels * kBytesPerPixel) +
-         (1u << 20);
+// A request is refused for its size only above this, whatever its buffers take.
+size_t refusal_bytes(int64_t items, int64_t pixels) { return (size_t)(360 * items + 44 * pixels) + (1u << 20); }
+
+// Device bytes of the server's buffers (items_, pixels_, tiles_, bins_, work_, the
+// tables) for a pair alone, from the batch's own layout.
+size_t contents_bytes(const RegPair& rp, int64_t items, int64_t pixels) {
+  constexpr int64_t kPerItem = 48 + 48 + 4 + 4, kPerPixel = 12 + 4 + 4 + 4 + 4 + 12 + 4;
+  std::vector<ls_render_job> jobs;
+  for (int dir = 0; dir < 2; ++dir) {
+    ls_render_job j{};
+    j.g = dir == 0 ? rp.pair.Q : rp.pair.P;
+    j.K = rp.pair.K;
+    jobs.insert(jobs.end(), dir == 0 ? rp.pair.vP : rp.pair.vQ, j);
+  }
+  ls_batch* b = nullptr;
+  if (batch_create_host(jobs.data(), (int32_t)jobs.size(), &b)) return refusal_bytes(items, pixels);
+  const int64_t cap = (int64_t)std::min<double>(items * kInstancesPerItem, (double)INT32_MAX);
+  const size_t bytes = (size_t)(kPerItem * items + kPerPixel * pixels + 8 * cap) + 8 * (size_t)b->T +
+                       batch_pose_workspace_bytes(b, cap) + batch_tables_bytes(b);
+  ls_batch_destroy(b);
+  return bytes;
 }
 
 }  // namespace
@@ -173,8 +191,9 @@ class Server {
     s->views = pair->vP + pair->vQ;
     s->items = (int64_t)pair->vP * pair->Q.n + (int64_t)pair->vQ * pair->P.n;
     s->pixels = (int64_t)s->views * pair->K.width * pair->K.height;
-    s->bytes = estimate_bytes(s->items, s->pixels);
-    if (s->bytes > prm_.hbm_budget_bytes) return LS_ERR_BUDGET;
+    s->bytes = contents_bytes(s->rp, s->items, s->pixels);
+    if (std::min(s->bytes + kServerBytes, refusal_bytes(s->items, s->pixels)) > prm_.hbm_budget_bytes)
+      return LS_ERR_BUDGET;
     s->remaining = prm->iters;
     s->t_submit = Clock::now();
     std::lock_guard<std::mutex> g(mu_);
@@ -267,7 +286,8 @@ class Server {
     bool changed = false;
     while (!waiting_.empty() && (int)active_.size() < prm_.max_slots) {
       Slot* s = waiting_.front();
-      if (active_bytes_ + s->bytes > prm_.hbm_budget_bytes) break;
+      // (a pair alone has passed submit's check)
+      if (!active_.empty() && kServerBytes + active_bytes_ + s->bytes > prm_.hbm_budget_bytes) break;
       if (prm_.max_active_pixels > 0 && !active_.empty() && active_pixels_ + s->pixels > prm_.max_active_pixels) break;
       // the tile lists of one launch set are indexed in int32: hold the head back while the
       // active set's expected instance count would pass that (a pair alone is always admitted)

@@ -240,3 +240,27 @@ def test_submit_orders_reads_after_the_producer_stream(pairs):
         r = sv.wait(ticket)
     assert r["status"] == 0
     assert _same(r, _plain(pairs[0]))
+
+
+def test_a_request_that_fits_is_admitted(gpu):
+    """The device memory that a request takes is a budget for it, give or take a
+    quarter, and two such requests run together in twice that."""
+    from paper_2408_10154_amd import lib as L
+    from paper_2408_10154_amd import register as REG
+    from paper_2408_10154_amd.serve import Server
+
+    p = _pair(14, 300000, 250000, 4, w=640, h=480, f=400.0)
+    prm = REG.default_params(4)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    with Server(budget_bytes=8 << 30) as sv:
+        sv.wait(sv.submit(*p["args"], params=prm))
+        taken = free - torch.cuda.mem_get_info()[0]
+    with Server(budget_bytes=taken * 3 // 4) as sv, pytest.raises(L.LsError) as e:
+        sv.submit(*p["args"], params=prm)
+    assert e.value.status == L.LS_ERR_BUDGET
+    for n in (1, 2):
+        with Server(budget_bytes=taken * n * 5 // 4, chunk_iters=1) as sv:
+            for t in [sv.submit(*p["args"], params=REG.default_params(200)) for _ in range(n)]:
+                assert sv.wait(t)["status"] == 0
+            assert sv.stats()["peak_active"] == n
