@@ -85,7 +85,7 @@ __device__ __forceinline__ void wave_ranks(const uint32_t (&key)[kPer], const bo
   const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
 #pragma unroll
   for (int d = 0; d < Digit<kBits>::kBins / 128; ++d) reinterpret_cast<uint32_t*>(row)[64 * d + lane] = 0u;
-  __builtin_amdgcn_wave_barrier();
+  wave_sync();
 #pragma unroll
   for (int j = 0; j < kPer; ++j) {
     const uint32_t d = Digit<kBits>::of(key[j], shift, mask);
@@ -105,7 +105,7 @@ __device__ __forceinline__ void wave_ranks(const uint32_t (&key)[kPer], const bo
       const uint32_t before = ok[j] ? row[d] : 0u;
       rk[j] = before + rank;
       if (ok[j] && rank == 0) row[d] = (uint16_t)(before + (uint32_t)__popcll(peers));
-      __builtin_amdgcn_wave_barrier();
+      wave_sync();
     }
   }
 }

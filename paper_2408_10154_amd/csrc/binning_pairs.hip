@@ -228,7 +228,7 @@ __global__ __launch_bounds__(64 * kEmitWaves) void k_pair_emit(const JobDev* __r
       marks[w][lane] = -1;
       const int64_t rel = (int64_t)off - W0;
       if (nt > 0 && rel >= 0 && rel < 64) marks[w][(int)rel] = lane;
-      __builtin_amdgcn_wave_barrier();
+      wave_sync();
       int o = wave_incl_max(marks[w][lane]);
       o = o < 0 ? carry : o;
       carry = __builtin_amdgcn_readlane(o, 63);
@@ -246,7 +246,7 @@ __global__ __launch_bounds__(64 * kEmitWaves) void k_pair_emit(const JobDev* __r
         kout[i] = (uint32_t)(o_key + dy * o_stride + q);
         vout[i] = o_it;
       }
-      __builtin_amdgcn_wave_barrier();
+      wave_sync();
       W0 = min(W0 + 64, cend);
     }
     kb += 64;

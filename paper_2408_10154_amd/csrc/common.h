@@ -163,6 +163,16 @@ __device__ __forceinline__ float wave_sum(float v) {
   return (r0 + r1) + (r2 + r3);
 }
 
+// Orders the wave's own LDS accesses, as handing a value to another lane takes (a
+// wave's LDS operations complete in order, so this only holds the compiler; the
+// wave barrier alone is no fence: a load of another type may pass it, or be
+// replaced by the lane's own store).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Inclusive prefix sum over the 64 lanes (DPP: shifts within 16-lane rows,
 // then the row ends broadcast to the later rows).
 __device__ __forceinline__ uint32_t wave_incl_sum(uint32_t v) {

@@ -224,13 +224,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8))) void k_
       s2[pos] = r2;
       spos[pos] = e - start;
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     int cw = __popcll(bal);
     if (lane == 0) {  // the walk takes two entries at a time: a last one that composites nowhere
       s0[cw] = make_float4(0.f, 0.f, 0.f, 0.f);
       s1[cw] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     // one step at staged entry j, transmittance Ti before and To after it:
     // no branch but for pixels that stop and entries that no pixel takes (whose
     // colour, should it be infinite, must not meet the weight 0)
@@ -291,7 +291,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8))) void k_
     // backward has an active lane
     const uint64_t um = __ballot(in && ((usedm >> pos) & 1ull));
     if (lane == 0) used[band * ustride + slot] = um;
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
   }
   if (!inside) return;
   const int64_t hw = (int64_t)J.W * J.H;
@@ -487,14 +487,6 @@ __device__ __forceinline__ BwdPixel bwd_pixel(const BandCtx& c, const JobDev& J,
     p.acc = bg0 * p.gR + bg1 * p.gG + bg2 * p.gB - gA;
   }
   return p;
-}
-
-// Orders the wave's own LDS accesses (a wave's LDS operations complete in
-// order, so this only holds the compiler).
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // What the gradients need of an entry is sums over the band's pixels of ds

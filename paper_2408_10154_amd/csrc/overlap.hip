@@ -319,7 +319,7 @@ __device__ __forceinline__ void ov_scan_leaf(const OvSet& c, int l, int lane, fl
                                    __int_as_float(c.idx[ci]))
                      : make_float4(INFINITY, INFINITY, INFINITY, __int_as_float(0x7fffffff));
   }
-  __builtin_amdgcn_wave_barrier();
+  wave_sync();
   const float4* half = stage + (lane >> 5) * (kOvLeaf / 2);
 #pragma unroll
   for (int j = 0; j < kOvLeaf / 2; ++j) {
@@ -327,7 +327,7 @@ __device__ __forceinline__ void ov_scan_leaf(const OvSet& c, int l, int lane, fl
     ov_take(o, sq_dist_rn(o.px, o.py, o.pz, b.x, b.y, b.z), __float_as_int(b.w));
   }
   ov_merge(o);
-  __builtin_amdgcn_wave_barrier();  // every lane has read the slot before it is refilled
+  wave_sync();  // every lane has read the slot before it is refilled
 }
 
 // Whether lane l's box is near enough to any of the queries.
