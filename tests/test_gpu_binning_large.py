@@ -139,3 +139,32 @@ def test_capacity_bounds_every_form(gpu, sizes, image, culled, frac):
     if frac == 1.0:
         for got, ref in zip((*(t[:n] for t in lists), b.range), want):
             assert torch.equal(got, ref)
+
+
+def test_depth_orders_and_list_forms_agree(gpu):
+    """The same records, runs of equal depth among them, as the first render of
+    batches that order by ranks, by a block per render, by radix passes of one and of
+    more keys a thread, and that list by chunks and by pairs: the first render's
+    instances are the same."""
+    from paper_2408_10154_amd.render import GaussianSet, RenderBatch
+
+    n = 5000
+    W, H = SMALL
+    cam, large = synth.camera(W, W, W / 2, H / 2, W, H), synth.camera(6000, 6000, 3000, 3000, 6000, 6000)
+    gs = GaussianSet.from_numpy(synth.gaussians_in_box(np.random.default_rng(0), 70000, (-1, -1, 1), (1, 1, 2)))
+    first = _records(np.random.default_rng(1), n, cam, 0.2)
+    want = None
+    for others in ([], [n] * 15, [17000], [70000], [(n, large)], [(17000, large)]):
+        others = [o if isinstance(o, tuple) else (o, cam) for o in others]
+        sets = [GaussianSet(**{k: getattr(gs, k)[..., :m].contiguous() for k in
+                               ("mean", "log_scale", "quat", "opacity_logit", "rgb")}) for m, _ in [(n, cam)] + others]
+        b = RenderBatch([(s, c, synth.identity_w2c()) for s, (_, c) in zip(sets, [(n, cam)] + others)])
+        b.project()
+        for dst, src in zip((b.rec, b.radius, b.tiles), first):
+            dst[:n] = torch.as_tensor(src, device="cuda")
+        b.bin_sort()
+        b.instances()
+        end = int(b.range[:int(b.tile_off[1])].max())
+        got = [t[:end].cpu().numpy() for t in (b.tile_of, b.item)]
+        want = want or got
+        assert end > n and all(np.array_equal(g, w) for g, w in zip(got, want)), others
