@@ -112,7 +112,7 @@ __device__ __forceinline__ void wave_ranks(const uint32_t (&key)[kPer], const bo
 
 // The block's digit starts, after every wave has ranked (and a barrier): each
 // wave's row turns into its first place for each digit in the block's digit
-// order (below kPerBlock <= 16,384 keys: 16 bits); lstart: the local starts of
+// order (at most 8,192 keys: 16 bits); lstart: the local starts of
 // the thread's digits (threads below kThreads); returns the number of keys up
 // to and with them.
 template <int kBits>
@@ -927,7 +927,7 @@ __device__ __forceinline__ uint64_t group_starts(const uint64_t* __restrict__ gr
 // for itself from the groups' sums; a launch for it and for the table took 3 to
 // 5 us.  More come from k_group_starts (kMany).  kOwn: a single render of up to
 // kPlaceThreads tiles whose counts, up to kOwnCounts, every block scans for
-// itself in two rounds of loads at most (4,096 items at 160 x 120, 2,800 counts:
+// itself in one to four rounds of loads (4,096 items at 160 x 120, 2,800 counts:
 // 4.2 us for k_chunk_scan against 1.1 us here; 23k items at 317 x 211, 22k
 // counts: 5.0 against 2.1 us).
 constexpr int kFewGroups = kPlaceThreads;

@@ -333,35 +333,28 @@ __device__ __forceinline__ float pair_sum(float a, float b, int lane) {
   return s + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(t), kCtrl, 0xF, 0xF, true));
 }
 
-// Sums of N values (N even, N <= 16) over the 64 lanes of the wave, by a
-// transposing reduction that halves the lanes holding each value at every
-// level while packing more values per register:
+// Sums of 12 values over the 64 lanes of the wave, by a transposing reduction that
+// halves the lanes holding each value at every level while packing more values per
+// register:
 //  - 32-lane swaps and adds: value 2k in the lower half of register h[k],
 //    2k + 1 in the upper half;
 //  - 16-lane swaps and adds: four values per register q[i], one per row
 //    (value 4 i + slot(r) in row r, slot = 0, 2, 1, 3);
-//  - within rows, swap-adds 8 lanes apart (q[0] with q[1], q[2] with q[3]),
-//    then 4 apart, leave one value per 4-lane group of one register, and two
-//    DPP adds sum each group.
-// The result: the lane that wave_value() names holds the total of that
-// value.  N = 10 costs 5 + 3 swaps and 17 VALU adds or selects; a plain row
-// sum after the 16-lane level would take 20 adds.  When N/2 is odd the last
-// 16-lane pair is the register with itself (its rows 1 and 3 repeat rows 0
-// and 2), and with fewer than three row registers the 8-apart level pairs a
-// register with itself: those duplicates are not named by wave_value().  The
-// whole wave must be active.
-template <int N>
-__device__ __forceinline__ float wave_sums(const float* g, int lane) {
-  static_assert(N % 2 == 0 && N <= 16, "an even number of values, at most 16");
-  constexpr int H = N / 2, O = (H + 1) / 2;
-  float h[H], q[O];
+//  - within rows, swap-adds 8 lanes apart (q[0] with q[1], q[2] with itself), then
+//    4 apart, leave one value per 4-lane group of one register, and two DPP adds
+//    sum each group.
+// The result: the lane that wave_value() names holds the total of that value; the
+// duplicates of q[2] are not named.  It costs 6 + 3 swaps and 18 VALU adds or
+// selects; a plain row sum after the 16-lane level would take 21 adds.  The whole
+// wave must be active.
+__device__ __forceinline__ float wave_sums(const float (&g)[12], int lane) {
+  float h[6], q[3];
 #pragma unroll
-  for (int k = 0; k < H; ++k) h[k] = swap32_sum(g[2 * k], g[2 * k + 1]);
+  for (int k = 0; k < 6; ++k) h[k] = swap32_sum(g[2 * k], g[2 * k + 1]);
 #pragma unroll
-  for (int i = 0; i < O; ++i) q[i] = swap16_sum(h[2 * i], h[2 * i + 1 < H ? 2 * i + 1 : 2 * i]);
+  for (int i = 0; i < 3; ++i) q[i] = swap16_sum(h[2 * i], h[2 * i + 1]);
   constexpr int kRor8 = 0x128, kHalfMirror = 0x141, kQuad1032 = 0xB1, kQuad2301 = 0x4E;
-  const float z0 = pair_sum<kRor8, 8>(q[0], O > 1 ? q[O > 1 ? 1 : 0] : q[0], lane);
-  const float z1 = O > 2 ? pair_sum<kRor8, 8>(q[O > 2 ? 2 : 0], q[O > 3 ? 3 : (O > 2 ? 2 : 0)], lane) : z0;
+  const float z0 = pair_sum<kRor8, 8>(q[0], q[1], lane), z1 = pair_sum<kRor8, 8>(q[2], q[2], lane);
   float y = pair_sum<kHalfMirror, 4>(z0, z1, lane);
   y += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(y), kQuad1032, 0xF, 0xF, true));
   y += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(y), kQuad2301, 0xF, 0xF, true));
@@ -372,26 +365,15 @@ __device__ __forceinline__ float wave_sums(const float* g, int lane) {
   return y;
 }
 
-// The value whose total lane `lane` holds after wave_sums<N>, or -1 for the
-// lanes that hold none, a duplicate, or one of the same group (exactly one
-// lane per value is named).
-template <int N>
+// The value whose total lane `lane` holds after wave_sums, or -1 for the lanes that
+// hold a duplicate or one of the same group (exactly one lane per value is named).
 __device__ __forceinline__ int wave_value(int lane) {
-  constexpr int O = (N / 2 + 1) / 2;
-  if (lane & 3) return -1;
   const int r = lane >> 4, grp = (lane >> 2) & 3;
-  // 8 apart: lanes 0-7 of a row keep q[0] (q[2]), 8-15 q[1] (q[3]); 4 apart:
+  // 8 apart: lanes 0-7 of a row keep q[0], 8-15 q[1], and both q[2]; 4 apart:
   // groups 0 and 2 keep the first register's, 1 and 3 the second's
-  int qi;
-  if (O > 2)
-    qi = (grp & 1) ? ((grp >> 1) ? 3 : 2) : (grp >> 1);
-  else if (O == 2)
-    qi = (grp & 1) ? -1 : (grp >> 1);
-  else
-    qi = grp == 0 ? 0 : -1;
-  if (qi < 0 || qi >= O) return -1;
-  const int v = 4 * qi + (((r & 1) << 1) | (r >> 1));
-  return v < N ? v : -1;
+  if ((lane & 3) || grp == 3) return -1;
+  const int qi = grp == 1 ? 2 : grp >> 1;
+  return 4 * qi + (((r & 1) << 1) | (r >> 1));
 }
 
 // Backward.  Per pixel, walking the list from n_last - 1 down to 0 with the
@@ -1103,8 +1085,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
           }
         }
         if (any) pose_terms(J.fx, J.fy, g, sum, Rd, td, pc);
-        const float out = wave_sums<kPoseAcc>(pc, lane);
-        const int v = wave_value<kPoseAcc>(lane);
+        const float out = wave_sums(pc, lane);
+        const int v = wave_value(lane);
         if (v >= 0) wred[w][v] = out;
       }
       __syncthreads();
