@@ -623,16 +623,19 @@ struct BandList {
   }
 };
 
-// Eight steps of the walk, staged entries e0 .. e0 + 7: ds and wgt (kPose: wgt
-// gD) of entry e0 + i at every pixel go to rows i and 8 + i.  Branch-free (padding
-// entries composite nowhere).  clamp: some staged entry's opacity reaches 0.99 (an
+// Eight steps of the walk, staged entries e0 .. e0 + 7, or the first four if no more
+// are listed (e0 + 4 >= n): ds and wgt (kPose: wgt gD) of entry e0 + i at every
+// pixel go to rows i and 8 + i.  Branch-free within four (padding entries composite
+// nowhere; short lists are mostly padding: 64 renders of 4k items at 640x480, 10
+// entries a tile, pose-only 660 -> 642 us and full 394 -> 381 us).  clamp: some staged entry's opacity reaches 0.99 (an
 // opacity below it bounds alpha, and the clamp can not act).  kPose rounds ds as
 // (T (v - acc)) alpha, and late[e] is the red that entry e adds after its green.
 template <bool kPose>
-__device__ __forceinline__ void walk_eight(BandLds& L, int lane, int e0, bool clamp, float fx, float fy,
+__device__ __forceinline__ void walk_eight(BandLds& L, int lane, int e0, int n, bool clamp, float fx, float fy,
                                            BwdPixel& px, const float* late) {
 #pragma unroll
   for (int h = 0; h < 8; h += 4) {
+    if (h == 4 && e0 + 4 >= n) break;  // uniform
     const float4 c = L.s2[e0 + h + (lane & 3)];
     f32x4 v = {0.f, 0.f, 0.f, 0.f};
     v = __builtin_amdgcn_mfma_f32_4x4x1f32(c.x, px.gR, v, 0, 0, 0);
@@ -752,6 +755,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
   const BandCtx c = band_ctx<false>(jobs, tile_off, R, unit, lane);
   const JobDev& J = jobs[c.r];
   const int start = range[2 * c.tile], end = range[2 * c.tile + 1];
+  if (start == end && !l1.loss_part) return;  // uniform
   BwdPixel px = bwd_pixel(c, J, bg0, bg1, bg2, fwd_T, fwd_n, up_rgb, up_depth, up_alpha, up_scale, l1);
   band_loss(l1, px, unit, lane);
   BandList list(L, used + c.band * ustride + (start >> 6) + c.tile, min(wave_max_i(px.nl), end - start));
@@ -764,11 +768,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
   row_factors(L.rows, lane, g, f);
   const bool hi = y & 4, b2 = y & 2, b1 = y & 1;
   const int k0 = 4 * (y & 1) + (y & 2) + (y >> 2);  // the value that this lane ends with
-  for (;;) {
-    const int n = list.take<false>(L, lane, start, items, rec);
-    if (n == 0) break;
+  for (int n = kBatch; n == kBatch;) {  // (a short batch is the last)
+    n = list.take<false>(L, lane, start, items, rec);
     for (int e0 = 0; e0 < n; e0 += 8) {
-      walk_eight<false>(L, lane, e0, list.clamp, fx, fy, px, nullptr);
+      walk_eight<false>(L, lane, e0, n, list.clamp, fx, fy, px, nullptr);
       float S[kGrad2D];
       row_sums(L, lane, e0, bx, ry, f, S);
       // sums over the entry's eight lanes, halving the lanes that hold a
@@ -827,7 +830,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
 // position: rounds of 128 392 us, of 64 473, of 256 in 51 KB and three blocks 445;
 // one wave per tile, its bands in turn, 476 us, and 97k 146 us.  Sums by pixel
 // rows, a wave per band and no common round, with the Jacobian per (entry, band):
-// 290 and 56 us, but other roundings.)
+// 290 and 56 us, but other roundings.)  Of short lists the fixed part counts: waves
+// without a chunk of 64 positions skip its sums, and no batch is taken after a
+// short one (64 renders of 4k items at 640x480, 10 entries a tile, 642 -> 610 us,
+// 128 of 2k at 160x120 96 -> 91; with a reduction of every entry in its band
+// 505 and 94, where dense ones took 472 us).  Less LDS for more waves spills: 892 us
+// with five on a SIMD.
 __device__ __forceinline__ float uniform(float x) {
   return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
 }
@@ -878,10 +886,10 @@ __device__ __forceinline__ void pose_walk(PoseBandLds& L, int lane, BandList& li
   const int k0 = b1 ? 4 + (x >> 2) : 2 * (x & 1) + (x >> 2);  // the value that this lane ends with
   const bool puts = !(b1 && b0);
   part += (lane >> 3) * kPoseRow + k0;
-  int place = 0;
-  for (int n; (n = list.take<true>(L, lane, start, items, rec, lo, top, place)) > 0; place += n)
+  for (int place = 0, n = kBatch; n == kBatch; place += n) {  // (a short batch is the last)
+    n = list.take<true>(L, lane, start, items, rec, lo, top, place);
     for (int e0 = 0; e0 < n; e0 += 8) {
-      walk_eight<true>(L, lane, e0, list.clamp, fx, fy, px, L.late);
+      walk_eight<true>(L, lane, e0, n, list.clamp, fx, fy, px, L.late);
       float S[kPoseRow];
       column_sums(L, lane, e0, colx, rowy, S);
       // sums over the entry's eight lanes, halving the lanes that hold a value at
@@ -896,6 +904,7 @@ __device__ __forceinline__ void pose_walk(PoseBandLds& L, int lane, BandList& li
       if (puts && e0 + (lane >> 3) < n) part[(place + e0) * kPoseRow] = v;
       wave_sync();
     }
+  }
 }
 
 // Whether the used entries of every band among the kPoseRound positions below
@@ -1033,6 +1042,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
   const JobDev& J = jobs[c.r];
   const int start = range[2 * tile], end = range[2 * tile + 1];
   const uint64_t* const words = used + (start >> 6) + tile;
+  if (start == end && !l1.loss_part) {  // uniform for the block
+    if ((int)threadIdx.x < kPoseAcc) tile_part[(int64_t)tile * kPoseAcc + threadIdx.x] = 0.f;
+    return;
+  }
   BwdPixel px = bwd_pixel(c, J, bg0, bg1, bg2, fwd_T, fwd_n, up_rgb, up_depth, up_alpha, up_scale, l1);
   band_loss(l1, px, 4 * tile + w, lane);
   const int mine = min(wave_max_i(px.nl), end - start);
@@ -1045,7 +1058,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
   if (last > 0) {     // uniform for the block
     // the render's correction, kept in scalar registers
     float Rd[9] = {1.f, 0.f, 0.f, 0.f, 1.f, 0.f, 0.f, 0.f, 1.f}, td[3] = {0.f, 0.f, 0.f};
-    if (pose) {
+    if (pose && 64 * w < last) {  // (the wave has a chunk)
       const float* pr = pose + 7 * c.r;
       pose_rot(pr[0], pr[1], pr[2], pr[3], Rd);
 #pragma unroll
@@ -1062,7 +1075,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
       lo = max(top - 64 * chunks, 0);
       pose_walk(L, lane, list, start, top, lo, items, rec, c.x0, c.y0, px, part[w]);
       const int chunk = w - chunk0;  // this wave's, if the round has it
-      const bool turn = chunk >= 0 && chunk < chunks;
+      const bool turn = chunk >= 0 && chunk < chunks && 64 * chunk < top;
       const int end = top - 64 * chunk, base = max(end - 64, 0);
       const bool has = turn && lane < end;
       PoseItem g;  // (loaded while the other waves walk)
@@ -1090,7 +1103,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         if (v >= 0) wred[w][v] = out;
       }
       __syncthreads();
-      chunk0 += chunks;
+      chunk0 += lo > 0 ? chunks : (top + 63) >> 6;
       if (chunk0 == 4 || lo == 0) {
         if ((int)threadIdx.x < kPoseAcc) {
           float s[4];
