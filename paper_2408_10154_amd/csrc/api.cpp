@@ -104,10 +104,12 @@ Layout layout_of(const ls_batch* b, int64_t cap) {
   L.pose_part = take(4 * (size_t)kPoseAcc * std::max(b->nblk_items, 1));
   L.loss_part = take(4 * 8 * (size_t)std::max(b->T, 1));  // per 8x8 band {L1 sum, pixels in Omega}
   L.used = take(8 * 4 * (size_t)used_slots(cap, b->T));  // per band a row of "used" bits, 64 entries a word
-  L.g2d = take(4 * (size_t)kGradStride * M);  // last: pose-only callers have no room for it
+  L.g2d = take(4 * (size_t)kGradStride * M * b->grad_copies);  // last: pose-only callers have no room for it
   L.total = off;
   return L;
 }
+
+GradCopies grad_copies(const ls_batch* b) { return GradCopies{b->grad_copies, (int64_t)kGradStride * b->M}; }
 
 template <typename T>
 T* at(void* base, size_t off) {
@@ -296,6 +298,13 @@ static ls_status batch_host(const ls_render_job* jobs, int32_t R, ls_batch** out
   b->nblk_items = b->blk_off[R];
   b->nblk_pix = b->pblk_off[R];
   b->nblk_ssim = b->sblk_off[R];
+  // Copies of the gradient accumulators, up to four (one per band of a tile), where
+  // items are few for the image: one per 16 bands (8x8 pixels) an item.  Full backward
+  // without and with, us: 2 x 300 items at 4096 x 4096, 873 bands an item, 962 and 510;
+  // 10k, 26 bands, 484 and 349; 50 at 4 x 1200 x 680, 258 bands, 85 and 49 (16 copies
+  // 503, 349 and 43); 1k, 13 bands, 64 (26 with one per 4 bands, but 4k of 8 times the
+  // area 161 and 170).
+  while (b->grad_copies < 4 && 4 * (int64_t)b->T > 16 * b->M * b->grad_copies) b->grad_copies *= 2;
   // Binning: chunks of sorted items, each counted over all tiles of its render
   // (binning.hip), or a sort of (tile, item) pairs (binning_pairs.hip).  Chunks cost by
   // the tiles and by the items times the render's tile windows, pairs by the
@@ -457,8 +466,8 @@ ls_status render_bwd_pose_l1(const ls_batch* b, const float* pose, const ls_proj
   const L1Targets l1{fwd->rgb, fwd->depth, tgt_rgb, tgt_depth, nullptr};
   launch_composite_bwd(b->jobs_d, b->tile_off_d, b->R, b->T, p->rec, p->aux, pose, bins->item, bins->range,
                        at<uint64_t>(bins->work, L.used), used_slots(bins->capacity, b->T), zero,
-                       fwd->T_final, fwd->n_last, nullptr, nullptr, nullptr, scale, at<float>(bins->work, L.g2d),
-                       at<float>(bins->work, L.tile_part), 1, s, &l1);
+                       fwd->T_final, fwd->n_last, nullptr, nullptr, nullptr, scale,
+                       at<float>(bins->work, L.g2d), grad_copies(b), at<float>(bins->work, L.tile_part), 1, s, &l1);
   return hip_check("pose-only backward with the L1 gradient");
 }
 
@@ -633,7 +642,7 @@ ls_status ls_render_bwd_tiles(const ls_batch* b, const float* pose, const ls_pro
   launch_composite_bwd(b->jobs_d, b->tile_off_d, b->R, b->T, p->rec, p->aux, pose, bins->item, bins->range,
                        at<uint64_t>(bins->work, L.used), used_slots(bins->capacity, b->T),
                        bg ? bg : zero, fwd->T_final, fwd->n_last, up->rgb, up->depth, up->alpha, up->scale,
-                       at<float>(bins->work, L.g2d), at<float>(bins->work, L.tile_part),
+                       at<float>(bins->work, L.g2d), grad_copies(b), at<float>(bins->work, L.tile_part),
                        (flags & LS_BWD_POSE_ONLY) ? 1 : 0, s);
   return hip_check("ls_render_bwd_tiles");
 }
@@ -654,7 +663,7 @@ ls_status ls_render_bwd_tiles_l1(const ls_batch* b, const float* pose, const ls_
   launch_composite_bwd(b->jobs_d, b->tile_off_d, b->R, b->T, p->rec, p->aux, pose, bins->item, bins->range,
                        at<uint64_t>(bins->work, L.used), used_slots(bins->capacity, b->T),
                        bg ? bg : zero, fwd->T_final, fwd->n_last, nullptr, nullptr, nullptr, inv_count,
-                       at<float>(bins->work, L.g2d), at<float>(bins->work, L.tile_part),
+                       at<float>(bins->work, L.g2d), grad_copies(b), at<float>(bins->work, L.tile_part),
                        (flags & LS_BWD_POSE_ONLY) ? 1 : 0, s, &l1);
   return hip_check("ls_render_bwd_tiles_l1");
 }
@@ -710,8 +719,8 @@ ls_status ls_render_bwd_project(const ls_batch* b, const float* pose, const ls_p
     }
   }
   launch_project_bwd(b->jobs_d, b->blk_off_d, b->R, b->nblk_items, pose, p->radius, p->aux,
-                     at<float>(bins->work, L.g2d), b->grads_d, want_gauss, at<float>(bins->work, L.pose_part),
-                     pose_grad != nullptr, pose_grad, s);
+                     at<float>(bins->work, L.g2d), grad_copies(b), b->grads_d, want_gauss,
+                     at<float>(bins->work, L.pose_part), pose_grad != nullptr, pose_grad, s);
   return hip_check("ls_render_bwd_project");
 }
 
@@ -765,7 +774,7 @@ ls_status ls_render_bwd_project_adam(const ls_batch* b, float* pose, const ls_pr
   }
   const Layout L = layout_of(b, bins->capacity);
   launch_project_bwd(b->jobs_d, b->blk_off_d, b->R, b->nblk_items, pose, p->radius, p->aux,
-                     at<float>(bins->work, L.g2d), nullptr, 1, at<float>(bins->work, L.pose_part),
+                     at<float>(bins->work, L.g2d), grad_copies(b), nullptr, 1, at<float>(bins->work, L.pose_part),
                      pose_grad != nullptr, pose_grad, s, &a);
   return hip_check("ls_render_bwd_project_adam");
 }

@@ -20,6 +20,7 @@ struct ls_batch {
   int64_t rank_pairs = 0; // sum over the renders of the squared item count
   int sort_blocks = 0;    // radix sort blocks over all renders
   int sort_per = 0;       // keys per thread of them
+  int grad_copies = 1;    // copies of the image-space gradient accumulators
   bool bin_pairs = false; // the lists by a sort of pairs instead of by chunks
   int bin_chunk = 0;      // sorted items per binning chunk
   bool bin_ramp = false;  // the first chunks are smaller

@@ -740,17 +740,20 @@ __device__ __forceinline__ void band_loss(const L1Targets& l1, const BwdPixel& p
 // band) pairs: two requests per pair 183-216 us, one per pair 148 us at 40
 // bytes per item and 124 us at 64, none 116 us, before the XCDs took turns).  The
 // projection backward applies the factors that are the same for all pixels
-// (conic, halves, 1 / opacity) once per item.
+// (conic, halves, 1 / opacity) once per item.  Few items over very many tiles make
+// their lines wait: such a batch has copies of the accumulators (grad_copies), a
+// tile's bands adding to different ones, and the projection backward adds them up.
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_composite_bwd(
     const JobDev* __restrict__ jobs, const int32_t* __restrict__ tile_off, int R, int T_total,
     const float4* __restrict__ rec, const int32_t* __restrict__ items, const int32_t* __restrict__ range,
     const uint64_t* __restrict__ used, int64_t ustride, float bg0, float bg1, float bg2,
     const float* __restrict__ fwd_T, const int32_t* __restrict__ fwd_n, const float* __restrict__ up_rgb,
     const float* __restrict__ up_depth, const float* __restrict__ up_alpha, const float* __restrict__ up_scale,
-    float* __restrict__ g2d, L1Targets l1) {
+    float* __restrict__ g2d, GradCopies copies, L1Targets l1) {
   __shared__ __attribute__((aligned(16))) FullBandLds L;
   const int unit = xcd_turns<64>(blockIdx.x, 4 * T_total);
   if (unit >= 4 * T_total) return;
+  g2d += (unit & (copies.n - 1)) * copies.stride;
   const int lane = threadIdx.x;
   const BandCtx c = band_ctx<false>(jobs, tile_off, R, unit, lane);
   const JobDev& J = jobs[c.r];
@@ -1200,7 +1203,7 @@ void launch_composite_bwd(const JobDev* jobs, const int32_t* tile_off, int R, in
                           const uint64_t* used, int64_t ustride, const float* bg, const float* Tf,
                           const int32_t* nl,
                           const float* up_rgb, const float* up_depth, const float* up_alpha, const float* up_scale,
-                          float* g2d, float* tile_part, int pose_only, hipStream_t s,
+                          float* g2d, GradCopies copies, float* tile_part, int pose_only, hipStream_t s,
                           const L1Targets* l1) {
   if (T <= 0) return;
   const L1Targets l1v = l1 ? *l1 : L1Targets{nullptr, nullptr, nullptr, nullptr, nullptr};
@@ -1213,6 +1216,7 @@ void launch_composite_bwd(const JobDev* jobs, const int32_t* tile_off, int R, in
     return;
   }
   hipLaunchKernelGGL(k_composite_bwd, dim3(xcd_grid(4 * T)), dim3(64), 0, s, jobs, tile_off, R, T, rec4, items, range,
-                     used, ustride, bg[0], bg[1], bg[2], Tf, nl, up_rgb, up_depth, up_alpha, up_scale, g2d, l1v);
+                     used, ustride, bg[0], bg[1], bg[2], Tf, nl, up_rgb, up_depth, up_alpha, up_scale, g2d, copies,
+                     l1v);
 }
 }  // namespace ls

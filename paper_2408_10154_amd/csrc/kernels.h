@@ -14,6 +14,13 @@ ls_status api_hip_check(const char* what);
 
 void launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s);
 
+// Copies of the image-space gradient accumulators, `stride` floats apart (a power
+// of two of them; 1: the accumulators alone).
+struct GradCopies {
+  int n;
+  int64_t stride;
+};
+
 struct ViewOpt;
 // live (or NULL: every render) gates each render on its active flag: the
 // items of a frozen render project to radius 0, so it has no tile instances.
@@ -50,7 +57,8 @@ struct GaussAdamArgs {
 // apply one Adam step to each Gaussian's parameters (the arrays its render
 // job points to) from its gradient; culled items step with zero gradients.
 void launch_project_bwd(const JobDev* jobs, const int32_t* blk_off, int R, int nblk, const float* pose,
-                        const int32_t* radius, const float* aux, float* g2d, const GradDev* grads, int want_gauss,
+                        const int32_t* radius, const float* aux, float* g2d, GradCopies copies,
+                        const GradDev* grads, int want_gauss,
                         float* pose_part, int want_pose, float* pose_grad, hipStream_t s,
                         const GaussAdamArgs* adam = nullptr);
 void launch_pose_reduce_tiles(const JobDev* jobs, int R, const float* pose, const float* tile_part, float* pose_grad,
@@ -205,7 +213,8 @@ void launch_composite_bwd(const JobDev* jobs, const int32_t* tile_off, int R, in
                           const float* aux, const float* pose, const int32_t* items, const int32_t* range,
                           const uint64_t* used, int64_t ustride, const float* bg, const float* Tf, const int32_t* nl,
                           const float* up_rgb,
-                          const float* up_depth, const float* up_alpha, const float* up_scale, float* g2d,
+                          const float* up_depth, const float* up_alpha, const float* up_scale,
+                          float* g2d, GradCopies copies,
                           float* tile_part, int pose_only, hipStream_t s,
                           const L1Targets* l1 = nullptr);
 

@@ -123,8 +123,9 @@ template <bool kAdam>
 __global__ __launch_bounds__(256) void k_project_bwd(const JobDev* __restrict__ jobs, const int32_t* __restrict__ blk_off,
                                                      int R, const float* __restrict__ pose,
                                                      const int32_t* __restrict__ radius, const float4* __restrict__ aux,
-                                                     float* __restrict__ g2d, const GradDev* __restrict__ grads,
-                                                     int want_gauss, float* __restrict__ pose_part, int want_pose,
+                                                     float* __restrict__ g2d, GradCopies copies,
+                                                     const GradDev* __restrict__ grads, int want_gauss,
+                                                     float* __restrict__ pose_part, int want_pose,
                                                      GaussAdamArgs adam) {
   const int r = find_segment<int32_t>(blk_off, R, (int32_t)blockIdx.x);
   const JobDev& J = jobs[r];
@@ -167,10 +168,16 @@ __global__ __launch_bounds__(256) void k_project_bwd(const JobDev* __restrict__ 
     float4* gp4 = reinterpret_cast<float4*>(gp);
     const float4 g0 = gp4[0], g1 = gp4[1];
     const float2 g2 = reinterpret_cast<const float2*>(gp)[4];
-    const float gi[kGrad2D] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w, g2.x, g2.y};
+    float gi[kGrad2D] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w, g2.x, g2.y};
     // leave the accumulator cleared for the next backward
     gp4[0] = gp4[1] = make_float4(0.f, 0.f, 0.f, 0.f);
     reinterpret_cast<float2*>(gp)[4] = make_float2(0.f, 0.f);
+    for (int c = 1; c < copies.n; ++c)
+#pragma unroll
+      for (int k = 0; k < kGrad2D; ++k) {
+        gi[k] += gp[c * copies.stride + k];
+        gp[c * copies.stride + k] = 0.f;
+      }
     const float4 a0 = aux[item * 3 + 0], a1 = aux[item * 3 + 1], a2 = aux[item * 3 + 2];
     const float p[3] = {a0.x, a0.y, a0.z};
     const float s6[6] = {a0.w, a1.x, a1.y, a1.z, a1.w, a2.x};
@@ -356,15 +363,16 @@ void launch_project(const JobDev* jobs, const int32_t* blk_off, int R, int nblk,
                        radius, tiles, reinterpret_cast<float4*>(aux), live);
 }
 void launch_project_bwd(const JobDev* jobs, const int32_t* blk_off, int R, int nblk, const float* pose,
-                        const int32_t* radius, const float* aux, float* g2d, const GradDev* grads, int want_gauss,
+                        const int32_t* radius, const float* aux, float* g2d, GradCopies copies,
+                        const GradDev* grads, int want_gauss,
                         float* pose_part, int want_pose, float* pose_grad, hipStream_t s, const GaussAdamArgs* adam) {
   if (nblk > 0) {
     if (adam)
       hipLaunchKernelGGL(k_project_bwd<true>, dim3(nblk), dim3(256), 0, s, jobs, blk_off, R, pose, radius,
-                         reinterpret_cast<const float4*>(aux), g2d, grads, 1, pose_part, want_pose, *adam);
+                         reinterpret_cast<const float4*>(aux), g2d, copies, grads, 1, pose_part, want_pose, *adam);
     else
       hipLaunchKernelGGL(k_project_bwd<false>, dim3(nblk), dim3(256), 0, s, jobs, blk_off, R, pose, radius,
-                         reinterpret_cast<const float4*>(aux), g2d, grads, want_gauss, pose_part, want_pose,
+                         reinterpret_cast<const float4*>(aux), g2d, copies, grads, want_gauss, pose_part, want_pose,
                          GaussAdamArgs{});
   }
   if (want_pose)
