@@ -177,7 +177,7 @@ ls_status batch_loss_exposure(const ls_batch* b, int kind, const ls_loss_params*
                               float* egrad, float* loss, float* grad_rgb, float* grad_depth, float* grad_scale,
                               hipStream_t s) {
   if (kind == 1)
-    launch_loss_track(b->jobs_d, b->pblk_off_d, b->R, b->nblk_pix, pred->rgb, pred->depth, pred->alpha, tgt_rgb,
+    launch_loss_track(b->jobs_d, b->pblk_off_d, b->R, b->nblk_pix, b->max_pblk, pred->rgb, pred->depth, pred->alpha, tgt_rgb,
                       tgt_depth, prm->lambda_c, prm->inlier_k, prm->alpha_power, b->sel_d, b->median_d, grad_rgb,
                       grad_depth, b->loss_part_d, loss, grad_scale, s, expo, epart, egrad);
   else
@@ -188,7 +188,7 @@ ls_status batch_loss_exposure(const ls_batch* b, int kind, const ls_loss_params*
 
 ls_status batch_loss_tracking(const ls_batch* b, const ls_image* pred, const ls_loss_params* prm, float* loss,
                               float* grad_rgb, float* grad_depth, float* grad_scale, hipStream_t s) {
-  launch_loss_track(b->jobs_d, b->pblk_off_d, b->R, b->nblk_pix, pred->rgb, pred->depth, pred->alpha, nullptr, nullptr,
+  launch_loss_track(b->jobs_d, b->pblk_off_d, b->R, b->nblk_pix, b->max_pblk, pred->rgb, pred->depth, pred->alpha, nullptr, nullptr,
                     prm->lambda_c, prm->inlier_k, prm->alpha_power, b->sel_d, b->median_d, grad_rgb, grad_depth,
                     b->loss_part_d, loss, grad_scale, s);
   return hip_check("tracking loss over per-render targets");
@@ -297,6 +297,7 @@ static ls_status batch_host(const ls_render_job* jobs, int32_t R, ls_batch** out
   b->T = b->tile_off[R];
   b->nblk_items = b->blk_off[R];
   b->nblk_pix = b->pblk_off[R];
+  for (int r = 0; r < R; ++r) b->max_pblk = std::max(b->max_pblk, b->pblk_off[r + 1] - b->pblk_off[r]);
   b->nblk_ssim = b->sblk_off[R];
   // Copies of the gradient accumulators, up to four (one per band of a tile), where
   // items are few for the image: one per 16 bands (8x8 pixels) an item.  Full backward
@@ -819,7 +820,7 @@ ls_status ls_loss_tracking(const ls_batch* b, const ls_image* pred, const float*
     return fail(LS_ERR_INVALID, "NULL image arguments");
   ls_status st;
   if ((st = ls::check_loss_params(prm, pred)) || (st = ensure_device(b))) return st;
-  launch_loss_track(b->jobs_d, b->pblk_off_d, b->R, b->nblk_pix, pred->rgb, pred->depth, pred->alpha, tgt_rgb,
+  launch_loss_track(b->jobs_d, b->pblk_off_d, b->R, b->nblk_pix, b->max_pblk, pred->rgb, pred->depth, pred->alpha, tgt_rgb,
                     tgt_depth, prm->lambda_c, prm->inlier_k, prm->alpha_power, b->sel_d,
                     median ? median : b->median_d, grad_rgb, grad_depth, b->loss_part_d, loss, grad_scale, s);
   return hip_check("ls_loss_tracking");

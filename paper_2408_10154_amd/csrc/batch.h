@@ -15,6 +15,7 @@ struct ls_batch {
   int64_t P = 0;
   int nblk_items = 0;
   int nblk_pix = 0;
+  int max_pblk = 0;  // of the render with the most
   int nblk_ssim = 0;  // mapping-loss SSIM blocks (3 channels x 32x32 tiles per render)
   int max_items = 0;      // most items of a render
   int64_t rank_pairs = 0; // sum over the renders of the squared item count

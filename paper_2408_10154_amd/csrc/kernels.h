@@ -411,7 +411,8 @@ void launch_loss_l1(const JobDev* jobs, const int32_t* pblk_off_d, int R, int np
 // Tracking loss with masks; sel = per-render selection workspace
 // (sel_words(R) uint32, zero on first use, histograms left zeroed after each
 // call).
-void launch_loss_track(const JobDev* jobs, const int32_t* pblk_off_d, int R, int npblk, const float* pred_rgb,
+void launch_loss_track(const JobDev* jobs, const int32_t* pblk_off_d, int R, int npblk, int max_pblk,
+                       const float* pred_rgb,
                        const float* pred_depth, const float* pred_alpha, const float* tgt_rgb, const float* tgt_depth,
                        float lambda_c, float inlier_k, int alpha_power, uint32_t* sel, float* median, float* g_rgb,
                        float* g_depth, float* part, float* loss, float* scale, hipStream_t s,

@@ -304,15 +304,22 @@ __device__ __forceinline__ void clear_bins(uint32_t* bins, bool first) {
   for (int i = threadIdx.x; i < kSelBins; i += 256) bins[i] = 0u;
 }
 
+// Histogram of the depth errors' digit of this pass.  kMany: `per` pieces of
+// kLossBlockPix pixels to a block and `share` blocks to a render (some past a smaller
+// render's end); else one piece, without the loop.
+template <bool kMany>
 __global__ __launch_bounds__(256) void k_err_hist(const JobDev* __restrict__ jobs, const int32_t* __restrict__ pblk_off,
                                                   int R, const float* __restrict__ pred_depth,
-                                                  const float* __restrict__ tgt_depth, SelWork sel, int pass) {
+                                                  const float* __restrict__ tgt_depth, SelWork sel, int pass, int per,
+                                                  int share) {
   __shared__ uint32_t h[kSelBins];
-  const int r = find_segment<int32_t>(pblk_off, R, (int32_t)blockIdx.x);
+  const int r = kMany ? (int)blockIdx.x / share : find_segment<int32_t>(pblk_off, R, (int32_t)blockIdx.x);
   const JobDev& J = jobs[r];
   const int64_t hw = (int64_t)J.W * J.H;
-  const int64_t b0 = (int64_t)(blockIdx.x - pblk_off[r]) * kLossBlockPix;
-  const bool first = (int)blockIdx.x == pblk_off[r];  // the render's first block
+  const int64_t piece = kMany ? (int64_t)(blockIdx.x - r * share) * per : (int64_t)blockIdx.x - pblk_off[r];
+  const int64_t b0 = piece * kLossBlockPix;
+  if (kMany && b0 >= hw) return;
+  const bool first = piece == 0;  // the render's first block
   const int shift = sel_shift(pass), nb = sel_bins(pass);
   // every pixel of the thread is loaded before any is counted (one wait for
   // memory, overlapping the histogram clear)
@@ -332,11 +339,30 @@ __global__ __launch_bounds__(256) void k_err_hist(const JobDev* __restrict__ job
     if (pass == 2) clear_bins(sel.bins(0, r), first);
   }
   __syncthreads();
+  for (int i = 0;;) {
+    float td1[kLossPix], pd1[kLossPix];
+    const bool more = kMany && ++i < per && b0 + (int64_t)i * kLossBlockPix < hw;
+    if (more) {
 #pragma unroll
-  for (int k = 0; k < kLossPix; ++k) {
-    if (!(td[k] > 0.f)) continue;  // out-of-image pixels carry td = 0
-    const uint32_t bits = __float_as_uint(depth_error(pd[k], td[k]));
-    if ((bits & st.mask) == st.prefix) atomicAdd(&h[(bits >> shift) & (uint32_t)(nb - 1)], 1u);
+      for (int k = 0; k < kLossPix; ++k) {  // the next piece, while this one is counted
+        const int64_t p = b0 + (int64_t)i * kLossBlockPix + (int64_t)k * 256 + threadIdx.x;
+        const bool in = p < hw;
+        td1[k] = in ? (tgt_depth ? tgt_depth[J.pix_off + p] : J.tgt_depth[p]) : 0.f;
+        pd1[k] = in ? pred_depth[J.pix_off + p] : 0.f;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < kLossPix; ++k) {
+      if (!(td[k] > 0.f)) continue;  // out-of-image pixels carry td = 0
+      const uint32_t bits = __float_as_uint(depth_error(pd[k], td[k]));
+      if ((bits & st.mask) == st.prefix) atomicAdd(&h[(bits >> shift) & (uint32_t)(nb - 1)], 1u);
+    }
+    if (!more) break;
+#pragma unroll
+    for (int k = 0; k < kLossPix; ++k) {
+      td[k] = td1[k];
+      pd[k] = pd1[k];
+    }
   }
   __syncthreads();
   uint32_t* __restrict__ g = sel.bins(pass, r);
@@ -466,7 +492,9 @@ void launch_loss_l1(const JobDev* jobs, const int32_t* pblk_off_d, int R, int np
                      (const float*)epart, egrad, (uint32_t*)nullptr);
 }
 
-void launch_loss_track(const JobDev* jobs, const int32_t* pblk_off_d, int R, int npblk, const float* pred_rgb,
+constexpr int kHistBlocks = 1024;
+void launch_loss_track(const JobDev* jobs, const int32_t* pblk_off_d, int R, int npblk, int max_pblk,
+                       const float* pred_rgb,
                        const float* pred_depth, const float* pred_alpha, const float* tgt_rgb, const float* tgt_depth,
                        float lambda_c, float inlier_k, int alpha_power, uint32_t* sel, float* median, float* g_rgb,
                        float* g_depth, float* part, float* loss, float* scale, hipStream_t s, const float* expo,
@@ -474,10 +502,18 @@ void launch_loss_track(const JobDev* jobs, const int32_t* pblk_off_d, int R, int
   const SelWork w{reinterpret_cast<SelState*>(sel), sel + 8 * (int64_t)R, R};
   const bool select = inlier_k > 0.f;
   if (npblk > 0) {
+    // Each block of the histograms reads the last pass's bins and adds its own to the
+    // render's, which takes as long as a piece of its pixels.  So past kHistBlocks
+    // pieces a block has several (loss without and with, us: 4096 x 4096 974 and 352,
+    // 2048 x 1536 183 and 102, 16 x 1920 x 1080 661 and 481; at 512 blocks the last
+    // 547, at 2,048 the second 116), unless renders of very different sizes would
+    // leave most blocks without one.
+    const int per = (npblk + kHistBlocks - 1) / kHistBlocks, share = (max_pblk + per - 1) / per;
+    const bool many = per > 1 && (int64_t)share * R <= npblk;
     if (select)
       for (int pass = 0; pass < 3; ++pass)
-        hipLaunchKernelGGL(k_err_hist, dim3(npblk), dim3(256), 0, s, jobs, pblk_off_d, R, pred_depth, tgt_depth, w,
-                           pass);
+        hipLaunchKernelGGL(many ? k_err_hist<true> : k_err_hist<false>, dim3(many ? share * R : npblk), dim3(256), 0, s,
+                           jobs, pblk_off_d, R, pred_depth, tgt_depth, w, pass, per, share);
     hipLaunchKernelGGL(k_loss_track, dim3(npblk), dim3(256), 0, s, jobs, pblk_off_d, R, pred_rgb, pred_depth,
                        pred_alpha, tgt_rgb, tgt_depth, w, median, lambda_c, inlier_k, alpha_power, g_rgb, g_depth,
                        part, expo, epart);

@@ -1,0 +1,34 @@
+"""Median of the depth errors where a block counts several pieces of 1,024 pixels."""
+
+import pytest
+import torch
+
+from paper_2408_10154_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("images", [
+    [(1024, 1024)], [(1025, 1024)],                       # 1,024 pieces, one a block, and 1,025
+    [(1100, 1000), (60, 40)], [(64, 48), (1531, 1373)],   # a short last piece, blocks past the smaller render's end
+    [(1100, 1000)] + [(60, 40)] * 3,                      # one a block: sizes differ too much
+    [(640, 480)] * 4, [(2048, 1600)],
+])
+def test_median_of_many_pieces(gpu, images):
+    """The value itself, twice on one batch (the histograms are left cleared)."""
+    from paper_2408_10154_amd.render import GaussianSet, RenderBatch
+
+    g = GaussianSet(**{k: torch.zeros(s, device="cuda") for k, s in (
+        ("mean", (3, 1)), ("log_scale", (3, 1)), ("quat", (4, 1)), ("opacity_logit", (1,)), ("rgb", (3, 1)))})
+    b = RenderBatch([(g, synth.camera(W, W, W / 2, H / 2, W, H), synth.identity_w2c()) for W, H in images])
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(len(images))
+    rand = lambda n: torch.rand(n, device="cuda", generator=gen)  # noqa: E731
+    rgb, alpha, tgt_rgb = rand(3 * b.P), rand(b.P), rand(3 * b.P)
+    for scale in (1.0, 1e-4):
+        depth, tgt = 2 + scale * rand(b.P), torch.where(rand(b.P) < 0.3, 0.0, 2 + scale * rand(b.P))
+        median = b.loss_tracking(tgt_rgb, tgt, pred=(rgb, depth, alpha))[1]
+        for r in range(b.R):
+            p, t = (x[int(b.pix_off[r]):int(b.pix_off[r + 1])] for x in (depth, tgt))
+            err = (p - t).abs()[t > 0].sort().values
+            assert float(median[r]) == float(err[(len(err) - 1) // 2]), (r, scale)
