@@ -838,9 +838,9 @@ ls_status ls_loss_mapping(const ls_batch* b, const ls_image* pred, const float* 
     return fail(LS_ERR_INVALID, "mapping-loss weights must be finite, lambda_ssim in [0, 1]");
   ls_status st;
   if ((st = ensure_device(b))) return st;
-  launch_loss_mapping(b->jobs_d, b->sblk_off_d, b->nblk_ssim, b->R, pred->rgb, pred->depth, tgt_rgb, tgt_depth,
-                      prm->lambda_ssim, prm->lambda_color, prm->lambda_depth, grad_rgb, grad_depth, b->map_part_d,
-                      loss, grad_scale, s);
+  launch_loss_mapping(b->jobs_d, b->nblk_pix, b->max_pblk, b->sblk_off_d, b->nblk_ssim, b->R, pred->rgb, pred->depth,
+                      tgt_rgb, tgt_depth, prm->lambda_ssim, prm->lambda_color, prm->lambda_depth, grad_rgb, grad_depth,
+                      b->map_part_d, loss, grad_scale, s);
   return hip_check("ls_loss_mapping");
 }
 

@@ -32,3 +32,30 @@ def test_median_of_many_pieces(gpu, images):
             p, t = (x[int(b.pix_off[r]):int(b.pix_off[r + 1])] for x in (depth, tgt))
             err = (p - t).abs()[t > 0].sort().values
             assert float(median[r]) == float(err[(len(err) - 1) // 2]), (r, scale)
+
+
+@pytest.mark.parametrize("images", [
+    [(64, 64)], [(65, 64)], [(33, 17)] * 9, [(64, 64), (1000, 900)],  # one part, two, one of several, limited by the mean
+    [(2048, 1024)], [(2049, 1024)],                                   # 64 parts, and 256
+])
+def test_valid_pixels_in_parts(gpu, images):
+    """The depth term alone: its gradients are +-1 / |Omega|, so they give the count."""
+    from paper_2408_10154_amd.render import GaussianSet, RenderBatch
+
+    g = GaussianSet(**{k: torch.zeros(s, device="cuda") for k, s in (
+        ("mean", (3, 1)), ("log_scale", (3, 1)), ("quat", (4, 1)), ("opacity_logit", (1,)), ("rgb", (3, 1)))})
+    b = RenderBatch([(g, synth.camera(W, W, W / 2, H / 2, W, H), synth.identity_w2c()) for W, H in images])
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(len(images))
+    b.depth.uniform_(1, 2, generator=gen)
+    tgt = torch.where(torch.rand(b.P, device="cuda", generator=gen) < 0.3, 0.0, 3.0)
+    loss, _, grad, _ = b.loss_mapping(torch.zeros(3 * b.P, device="cuda"), tgt, lambda_color=0.0)
+    for r in range(b.R):
+        at = slice(int(b.pix_off[r]), int(b.pix_off[r + 1]))
+        valid = tgt[at] > 0
+        n = int(valid.sum())
+        got = -grad[at][valid]
+        assert n > 0 and bool((grad[at][~valid] == 0).all()) and bool((got == got[0]).all())
+        assert round(1.0 / float(got[0])) == n, r
+        want = float((3.0 - b.depth[at][valid].double()).sum()) / n
+        assert abs(float(loss[r]) - want) <= 1e-5 * want, r  # (sums of up to 2 M terms of one sign)
