@@ -450,8 +450,8 @@ __global__ __launch_bounds__(kMapReduceThreads) void k_map_reduce(const JobDev* 
                                                                   const int32_t* __restrict__ sblk_off, int R,
                                                                   const float* __restrict__ part,
                                                                   const float* __restrict__ valid, int parts,
-                                                                  float lambda_ssim, float lambda_color, float lambda_depth,
-                                                                  float* __restrict__ loss,
+                                                                  float lambda_ssim, float lambda_color,
+                                                                  float lambda_depth, float* __restrict__ loss,
                                                                   float* __restrict__ scale) {
   constexpr int kWaves = kMapReduceThreads / 64, kAhead = 4;
   __shared__ float ws[3][kWaves];
