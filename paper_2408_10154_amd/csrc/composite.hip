@@ -826,12 +826,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
 // An entry costs about 23 VALU instructions in the walk and 14 in the sums (53
 // with the products in the walk and a reduction of six values an entry).  Bound
 // by their issue and by the waves that wait for the tile's slowest at a round's
-// end: 16 views of 640x480 of 150k/120k 472 -> 374 us, 97k at 640x480 92 -> 69 us.
+// end: 16 views of 640x480 of 150k/120k 472 -> 358 us, 97k at 640x480 92 -> 68 us.
 // What a round costs besides its entries is the larger part of the wait, so rounds
 // are long: 256 positions where each band's entries fit kPosePlaces places (39 KB
 // of LDS, four blocks on a CU), else 128, which always fit.  (One place per
-// position: rounds of 128 392 us, of 64 473, of 256 in 51 KB and three blocks 445;
-// one wave per tile, its bands in turn, 476 us, and 97k 146 us.  Sums by pixel
+// position: rounds of 128 392 us, of 64 473, of 256 in 51 KB and three blocks 445, to
+// 374 then; one wave per tile, its bands in turn, 476 us, and 97k 146 us.  Sums by pixel
 // rows, a wave per band and no common round, with the Jacobian per (entry, band):
 // 290 and 56 us, but other roundings.)  Of short lists the fixed part counts: waves
 // without a chunk of 64 positions skip its sums, and no batch is taken after a
