@@ -219,7 +219,7 @@ static BatchTables batch_tables(const ls_batch* b) {
   t.binwork_off = take(4 * R1);
   t.bincnt_off = take(8 * R1);
   t.loss_part = take(8 * (size_t)std::max(b->nblk_pix, 1));
-  t.map_part = take(4 * (3 * (size_t)b->nblk_ssim + (size_t)kValidParts * b->R));
+  t.map_part = take(4 * (3 * (size_t)b->nblk_ssim + (size_t)(kValidParts + kValidPartsMany) * b->R));
   t.grads = take(sizeof(GradDev) * b->R);
   t.sel = take(4 * (size_t)ls::sel_words(b->R));
   t.median = take(4 * (size_t)b->R);

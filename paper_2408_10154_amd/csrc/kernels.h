@@ -421,9 +421,9 @@ constexpr int kSelHistBins = 2048;
 inline int64_t sel_words(int R) { return (int64_t)R * (8 + 3 * kSelHistBins); }
 
 // Mapping loss (mapping_loss.hip).  SSIM blocks of a W x H render (3 colour
-// channels x 32 x 32 tiles); map_part: 3 floats per SSIM block + up to kValidParts per render.
+// channels x 32 x 32 tiles); map_part: 3 floats per SSIM block + kValidParts + kValidPartsMany per render.
 int ssim_blocks(int W, int H);
-constexpr int kValidParts = 256;
+constexpr int kValidParts = 64, kValidPartsMany = 256;
 void launch_loss_mapping(const JobDev* jobs, int npblk, int max_pblk, const int32_t* sblk_off_d, int nsblk, int R,
                          const float* pred_rgb,
                          const float* pred_depth, const float* tgt_rgb, const float* tgt_depth, float lambda_ssim,

@@ -99,16 +99,18 @@ __global__ __launch_bounds__(256) void k_valid_inv(const int32_t* __restrict__ p
   if (threadIdx.x == 0) inv[r] = c > 0.f ? 1.f / c : 0.f;
 }
 
-// The same in `parts` parts per render, for a kernel whose waves add them up for
-// themselves (valid_inv); a launch for that took 2 to 5 us.
+// The same in kValidParts parts per render, for a kernel whose waves add them up for
+// themselves (valid_inv); a launch for that took 2 to 5 us.  `blocks` of a render
+// write a part each, and zeros to the parts that are no block's; where they are more
+// than the parts, k_valid_fold adds them up.
 constexpr int kValidThreads = 1024;
 __global__ __launch_bounds__(kValidThreads) void k_valid_parts(const JobDev* __restrict__ jobs,
-                                                               const float* __restrict__ tgt_depth, int parts,
+                                                               const float* __restrict__ tgt_depth, int blocks,
                                                                float* __restrict__ part) {
   constexpr int kAhead = 8;
-  const int r = blockIdx.x / parts, b = blockIdx.x - r * parts;
+  const int r = blockIdx.x / blocks, b = blockIdx.x - r * blocks;
   const JobDev& J = jobs[r];
-  const int64_t hw = (int64_t)J.W * J.H, step = (int64_t)parts * kValidThreads;
+  const int64_t hw = (int64_t)J.W * J.H, step = (int64_t)blocks * kValidThreads;
   const float* __restrict__ td = tgt_depth ? tgt_depth + J.pix_off : J.tgt_depth;
   int cnt = 0;
   for (int64_t p0 = (int64_t)b * kValidThreads + threadIdx.x; p0 < hw; p0 += kAhead * step) {
@@ -126,15 +128,24 @@ __global__ __launch_bounds__(kValidThreads) void k_valid_parts(const JobDev* __r
     float all = 0.f;
 #pragma unroll
     for (int k = 0; k < kValidThreads / 64; ++k) all += ws[k];
-    part[blockIdx.x] = all;
+    part[(int64_t)r * max(blocks, kValidParts) + b] = all;
   }
+  const int k = b + blocks * (1 + threadIdx.x);
+  if (k < kValidParts) part[(int64_t)r * kValidParts + k] = 0.f;
+}
+
+__global__ __launch_bounds__(kValidParts) void k_valid_fold(const float* __restrict__ many, float* __restrict__ part) {
+  float c = 0.f;  // (whole numbers: any order)
+#pragma unroll
+  for (int k = 0; k < kValidPartsMany / kValidParts; ++k)
+    c += many[(int64_t)blockIdx.x * kValidPartsMany + k * kValidParts + threadIdx.x];
+  part[(int64_t)blockIdx.x * kValidParts + threadIdx.x] = c;
 }
 
 // 1 / |Omega| of render r (0 when no pixel has a target depth), in every lane.
-__device__ __forceinline__ float valid_inv(const float* __restrict__ part, int parts, int r) {
-  float c = 0.f;  // (whole numbers: any order)
-  for (int k = threadIdx.x & 63; k < parts; k += 64) c += part[r * parts + k];
-  c = wave_sum(c);
+__device__ __forceinline__ float valid_inv(const float* __restrict__ part, int r) {
+  static_assert(kValidParts == 64, "a part per lane");
+  const float c = wave_sum(part[r * kValidParts + (threadIdx.x & 63)]);
   return c > 0.f ? 1.f / c : 0.f;
 }
 
@@ -161,7 +172,7 @@ __global__ __launch_bounds__(256) void k_loss_ssim(const JobDev* __restrict__ jo
                                                    const float* __restrict__ pred_depth,
                                                    const float* __restrict__ tgt_rgb,
                                                    const float* __restrict__ tgt_depth,
-                                                   const float* __restrict__ valid, int parts, SsimWindow win,
+                                                   const float* __restrict__ valid, SsimWindow win,
                                                    float lambda_ssim, float lambda_color, float lambda_depth,
                                                    float* __restrict__ g_rgb, float* __restrict__ g_depth,
                                                    float* __restrict__ part) {
@@ -176,7 +187,7 @@ __global__ __launch_bounds__(256) void k_loss_ssim(const JobDev* __restrict__ jo
   const int ch = local / (tx * ty);
   const int t = local - ch * tx * ty;
   const int x0 = (t % tx) * kSsimT, y0 = (t / tx) * kSsimT;
-  const float inv = valid_inv(valid, parts, r);
+  const float inv = valid_inv(valid, r);
   const int64_t hw = (int64_t)W * H;
   const float* __restrict__ X = pred_rgb + 3 * J.pix_off + ch * hw;
   const float* __restrict__ Y = (tgt_rgb ? tgt_rgb + 3 * J.pix_off : J.tgt_rgb) + ch * hw;
@@ -449,14 +460,14 @@ constexpr int kMapReduceThreads = 1024;
 __global__ __launch_bounds__(kMapReduceThreads) void k_map_reduce(const JobDev* __restrict__ jobs,
                                                                   const int32_t* __restrict__ sblk_off, int R,
                                                                   const float* __restrict__ part,
-                                                                  const float* __restrict__ valid, int parts,
-                                                                  float lambda_ssim, float lambda_color,
-                                                                  float lambda_depth, float* __restrict__ loss,
+                                                                  const float* __restrict__ valid, float lambda_ssim,
+                                                                  float lambda_color, float lambda_depth,
+                                                                  float* __restrict__ loss,
                                                                   float* __restrict__ scale) {
   constexpr int kWaves = kMapReduceThreads / 64, kAhead = 4;
   __shared__ float ws[3][kWaves];
   const int r = blockIdx.x, end = sblk_off[r + 1];
-  const float inv = valid_inv(valid, parts, r);
+  const float inv = valid_inv(valid, r);
   float s = 0.f, c = 0.f, d = 0.f;
   for (int b = sblk_off[r] + threadIdx.x; b < end; b += kAhead * kMapReduceThreads) {
     float v[kAhead][3];
@@ -568,21 +579,22 @@ void launch_loss_mapping(const JobDev* jobs, int npblk, int max_pblk, const int3
                          float lambda_color, float lambda_depth, float* g_rgb, float* g_depth, float* map_part,
                          float* loss, float* scale, hipStream_t s) {
   float* valid = map_part + 3 * (int64_t)nsblk;
-  // A part per 4,096 pixels, up to 64, which one load takes, and 256 of large images
-  // (with 64 whatever the size 512 renders of 33 x 17 took 57 us, 3.8 with one, and
-  // 4096 x 4096 108 us, 31 with 256; but 16 x 640 x 480 with 75 parts 277 us for the
-  // whole loss, 266 with 64), and no more than a render's pieces of 1,024 on average.
-  const int most = max_pblk > 2048 ? kValidParts : 64;
-  const int parts = std::max(1, std::min({(max_pblk + 3) / 4, npblk / R, most}));
-  hipLaunchKernelGGL(k_valid_parts, dim3(parts * R), dim3(kValidThreads), 0, s, jobs, tgt_depth, parts, valid);
+  // A block per 1,024 pixels of a render, up to 64, and 256 of large images (with 64
+  // whatever the size 512 renders of 33 x 17 took 57 us, 4 with one, and 4096 x 4096
+  // 108 us, 37 with 256), but no more than that on average over the renders.
+  const bool many = max_pblk > 2048 && npblk / R >= kValidPartsMany;
+  const int blocks = many ? kValidPartsMany : std::max(1, std::min({max_pblk, npblk / R, kValidParts}));
+  float* count = many ? valid + (int64_t)kValidParts * R : valid;
+  hipLaunchKernelGGL(k_valid_parts, dim3(blocks * R), dim3(kValidThreads), 0, s, jobs, tgt_depth, blocks, count);
+  if (many) hipLaunchKernelGGL(k_valid_fold, dim3(R), dim3(kValidParts), 0, s, (const float*)count, valid);
   if (nsblk > 0) {
     const int grid = 8 * ((nsblk + 7) / 8);
     hipLaunchKernelGGL(k_loss_ssim, dim3(grid), dim3(kBlock), 0, s, jobs, sblk_off_d, R, nsblk, pred_rgb, pred_depth,
-                       tgt_rgb, tgt_depth, (const float*)valid, parts, ssim_window(), lambda_ssim, lambda_color,
+                       tgt_rgb, tgt_depth, (const float*)valid, ssim_window(), lambda_ssim, lambda_color,
                        lambda_depth, g_rgb, g_depth, map_part);
   }
   hipLaunchKernelGGL(k_map_reduce, dim3(R), dim3(kMapReduceThreads), 0, s, jobs, sblk_off_d, R, (const float*)map_part,
-                     (const float*)valid, parts, lambda_ssim, lambda_color, lambda_depth, loss, scale);
+                     (const float*)valid, lambda_ssim, lambda_color, lambda_depth, loss, scale);
 }
 
 void launch_loss_isotropic(const float* log_scale, int64_t n, float lambda_reg, float* loss, float* grad, float* part,

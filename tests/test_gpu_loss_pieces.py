@@ -35,8 +35,8 @@ def test_median_of_many_pieces(gpu, images):
 
 
 @pytest.mark.parametrize("images", [
-    [(64, 64)], [(65, 64)], [(33, 17)] * 9, [(64, 64), (1000, 900)],  # one part, two, one of several, limited by the mean
-    [(2048, 1024)], [(2049, 1024)],                                   # 64 parts, and 256
+    [(64, 64)], [(65, 64)], [(33, 17)] * 9, [(64, 64), (1000, 900)],  # 4 and 5 blocks, one, limited by the mean
+    [(2048, 1024)], [(2049, 1024)],                                   # 64 blocks, and 256
 ])
 def test_valid_pixels_in_parts(gpu, images):
     """The depth term alone: its gradients are +-1 / |Omega|, so they give the count."""
