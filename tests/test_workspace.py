@@ -1,5 +1,7 @@
 """Workspace sizes (host only): room for a size is room for every smaller one."""
 
+import numpy as np
+
 from paper_2408_10154_amd import lib as L
 from tests.test_abi import _host_pair
 
@@ -28,3 +30,19 @@ def test_overlap_workspace_grows_with_the_points():
     assert _non_decreasing([size(n, n) for n in EDGES])
     mx = L.LS_OVERLAP_NOALLOC_MAX_POINTS
     assert max(size(a, b) for a in EDGES for b in EDGES if max(a, b) <= mx) <= L.LS_OVERLAP_NOALLOC_BYTES
+
+
+def test_fewer_views_fit_in_the_workspace_of_all():
+    """A registration that keeps its best views runs them in the workspace of the
+    full set, whatever form their lists take."""
+    rng = np.random.default_rng(0)
+    lg = lambda a, b: int(round(a * (b / a) ** rng.random()))  # noqa: E731
+    prm = L.ls_reg_params(10, 0.01, 0.01, 0.9, 0.999, 1e-8)
+    for _ in range(2000):
+        v, n, w, cap = (lg(1, 60), lg(1, 60)), (lg(100, 500_000), lg(100, 500_000)), lg(16, 4000), lg(1000, 50_000_000)
+        k = int(rng.choice([1, 2, max(1, min(v) - 1), max(1, max(v) - 1)]))
+        size = []
+        for a, b in (v, (min(v[0], k), min(v[1], k))):
+            pair, keep = _host_pair(vp=a, vq=b, n_p=n[0], n_q=n[1], w=w, h=max(16, int(0.7 * w)))
+            size.append(L.ls_register_workspace_size(pair, prm, cap))
+        assert size[1] <= size[0], (v, n, w, cap, k)
