@@ -6,8 +6,7 @@ from paper_2408_10154_amd import lib as L
 from tests.test_abi import _host_pair
 
 # around the sizes where a radix sort's blocks, and the pair sort's spans, become longer
-EDGES = sorted({max(0, k + d) for k in (0, 1 << 16, 1 << 18, 1 << 19, 3 << 18, 1 << 20, 3 << 19, 1 << 21, 1 << 22, 1 << 23)
-                for d in (-1, 0, 1, 1025)})
+EDGES = sorted({max(0, (k << 16) + d) for k in (0, 1, 4, 8, 12, 16, 24, 32, 64, 128) for d in (-1, 0, 1, 1025)})
 
 
 def _non_decreasing(sizes):
