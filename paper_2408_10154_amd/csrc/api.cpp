@@ -328,9 +328,12 @@ static ls_status batch_host(const ls_render_job* jobs, int32_t R, ls_batch** out
   // 680 205 us, 248 with 16 M words; 8 x 300k 268 us with either, 322 with 4 M), and
   // there are at most about 4,096 chunks (half as many for 16 renders of 150k and 120k
   // items: lists 67 -> 101 us).  Finer first chunks (chunk_first) help a single render
-  // and a batch of up to 384 chunks (8 x 4k items at 640 x 480, 288 chunks: 32 us, 36
-  // without; 16 x 4k, 576: 41 and 40; 128 x 1k, 2,048: 106 and 75).
-  constexpr int64_t kMaxCounts = 1 << 23, kMaxChunks = 4096, kRampChunks = 384;
+  // and a batch of up to 560 chunks, the more the larger the splats: of 832 batches
+  // with splats of 0.8 to 6 cm, those of 384 to 512 chunks are 0.92 to 1.5 times as
+  // fast with them, 1.06 on average, of 640 to 768 0.79 to 1.5, 0.97, past 1,024 0.82
+  // (8 x 8.4k items of 0.8 cm at 1200 x 680 65 us and 64 without, of 6 cm 91 and 121;
+  // 32 x 4k of 0.8 cm at 640 x 480 61 and 43).
+  constexpr int64_t kMaxCounts = 1 << 23, kMaxChunks = 4096, kRampChunks = 560;
   int64_t chunks, counts;
   const auto cut = [&](int chunk, bool ramp) {
     b->bin_chunk = chunk;

@@ -28,7 +28,7 @@ def test_lists_by_pairs(gpu, sizes, image, culled):
 @pytest.mark.parametrize("sizes,image,culled", [
     ([140000] * 16, SMALL, 0.97),       # 4,375 chunks of 512: chunks of 1,024 items
     ([1100000], (1024, 1024), 0.93),    # 2,183 chunks x 4,096 tiles, with finer first chunks
-    ([4000] * 10, SMALL, 0.3), ([4000] * 11, SMALL, 0.3),  # 360 chunks with finer first ones, and 396: without
+    ([4000] * 15, SMALL, 0.3), ([4000] * 16, SMALL, 0.3),  # 540 chunks with finer first ones, and 576: without
 ])
 def test_chunks_of_other_sizes(gpu, sizes, image, culled):
     _lists_equal(gpu, sizes, image, culled)
@@ -168,3 +168,42 @@ def test_depth_orders_and_list_forms_agree(gpu):
         got = [t[:end].cpu().numpy() for t in (b.tile_of, b.item)]
         want = want or got
         assert end > n and all(np.array_equal(g, w) for g, w in zip(got, want)), others
+
+
+@pytest.mark.parametrize("sizes,image", [([3000, 0, 2000], (4600, 4600)), ([9000], (16, 16)), ([5000] * 3, SMALL)])
+def test_lists_in_a_graph(gpu, sizes, image):
+    """Binning captured once and replayed on other records, with eager calls and
+    synchronizations between the replays: each replay's lists are the eager ones."""
+    from paper_2408_10154_amd.render import GaussianSet, RenderBatch
+
+    W, H = image
+    cam = synth.camera(W, W, W / 2, H / 2, W, H)
+    rng = np.random.default_rng(0)
+    jobs = [(GaussianSet.from_numpy(synth.gaussians_in_box(rng, n, (-1, -1, 1), (1, 1, 2))), cam, synth.identity_w2c())
+            for n in sizes]
+    b, eager = (RenderBatch(jobs, capacity=3_000_000) for _ in range(2))
+    b.auto_grow = eager.auto_grow = False
+
+    def fill():
+        for r, n in enumerate(sizes):
+            if n:
+                o = int(b.item_off[r])
+                for name, src in zip(("rec", "radius", "tiles"), _records(rng, n, cam, rng.uniform(0, 0.9))):
+                    for x in (b, eager):
+                        getattr(x, name)[o:o + n] = torch.as_tensor(src, device="cuda")
+
+    fill()
+    b.bin_sort()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        b.bin_sort()
+    for _ in range(4):
+        fill()
+        graph.replay()
+        eager.bin_sort()
+        torch.cuda.synchronize()
+        assert b.count.tolist() == eager.count.tolist() and int(b.count[1]) == 0
+        n = int(b.count[0])
+        assert all(torch.equal(x[:n], y[:n]) for x, y in ((b.tile_of, eager.tile_of), (b.item, eager.item)))
+        assert torch.equal(b.range, eager.range)
