@@ -86,19 +86,25 @@ Layout layout_of(const ls_batch* b, int64_t cap) {
   L.hist = take(4 * (size_t)seg_hist_words(b->sort_blocks, b->R));
   L.blk_cnt = take(4 * (size_t)b->sort_blocks);
   L.kept = take(4 * (size_t)b->R);
-  if (b->bin_pairs) {
+  const size_t lists = off;
+  if (b->pair_cap >= 0) {
+    const int64_t c = std::min(cap, b->pair_cap);
     L.kept_off = take(4 * ((size_t)b->R + 1));
     L.bsum = take(8 * (size_t)pair_item_blocks(M));
-    L.first = take(4 * (size_t)pair_spans_room(cap));
-    L.tk = take(4 * (size_t)cap);
-    L.tv = take(4 * (size_t)cap);
-    L.pair_hist = take(4 * (size_t)seg_hist_words(pair_sort_blocks_room(cap), 1));
+    L.first = take(4 * (size_t)pair_spans_room(c));
+    L.tk = take(4 * (size_t)c);
+    L.tv = take(4 * (size_t)c);
+    L.pair_hist = take(4 * (size_t)seg_hist_words(pair_sort_blocks_room(c), 1));
     L.pair_seg = take(32);
-  } else {
+  }
+  if (cap > b->pair_cap) {  // (in the same place: a capacity's room is the smaller ones' too)
+    const size_t pairs = off;
+    off = lists;
     L.cnt = take(4 * (size_t)b->bincnt_off[b->R]);
     L.tile_total = take(4 * T);
     L.tile_before = take(4 * T);
     L.groups = take(8 * ((T + 63) / 64 + 1));
+    off = std::max(off, pairs);
   }
   L.tile_part = take(4 * (size_t)kPoseAcc * std::max(b->T, 1));
   L.pose_part = take(4 * (size_t)kPoseAcc * std::max(b->nblk_items, 1));
@@ -309,23 +315,29 @@ static ls_status batch_host(const ls_render_job* jobs, int32_t R, ls_batch** out
   // Binning: chunks of sorted items, each counted over all tiles of its render
   // (binning.hip), or a sort of (tile, item) pairs (binning_pairs.hip).  Chunks cost by
   // the tiles and by the items times the render's tile windows, pairs by the
-  // instances, of which only the item count is known here, and more launches.  The
-  // line is a fit to both over 800 batches of 300 to 5M items, 1 to 256 renders and 80
-  // to 2M tiles (us with chunks and with pairs: 100k items at 2560 x 1440 80 and 91,
-  // 300k 125 and 111; 5k at 4096 x 4096 57 and 54, 20k 111 and 79; 1M at 12000 x 9000
-  // 23,992 and 392; 32 x 4k at 1200 x 680 67 and 76, 128 x 4k 182 and 114; 16 x 20k at
-  // 1920 x 1080 122 and 127, 32 x 20k 185 and 167).  Chunks of a render with very many
-  // items per tile leave most threads idle (1M at 160 x 120 174 and 134, 300k 85 and 89).
-  constexpr int64_t kMaxPerTile = 8192;
-  int64_t item_windows = 0;
+  // instances, which the lists' capacity bounds, and more launches.  The line is a
+  // fit to both over 700 batches of 300 to 2M items of 0.3 to 8 cm, 1 to 192 renders
+  // and 80 to 0.4M tiles, with the capacity 1 to 3 times the instances or 6 to 16 times
+  // the items: 0.5 to 1.1 % over the better form on average (us with chunks and with
+  // pairs: 300k items of 0.5 cm at 2560 x 1440 125 and 111; 20k of 1 cm at 4096 x 4096
+  // 111 and 79; 1M at 12000 x 9000 23,992 and 392; 128 x 4k at 1200 x 680 of 2 cm 182 and
+  // 114, of 8 cm 419 and 779; 16 x 20k at 1920 x 1080 of 8 cm 459 and 1,057).  Chunks of a
+  // render with very many items per tile leave most threads idle (600k at 160 x 120
+  // 1.05 to 1.76 times, 2M 1.4 to 2.3 times; 200k 0.95 to 1.25).
+  constexpr int64_t kMaxPerTile = 4096;
+  int64_t item_windows = 0, max_tiles = 0;
   bool heaped = false;
   for (const JobDev& d : b->jobs_h) {
     item_windows += (int64_t)d.n * ls::windows_of(d.TX, d.TY);
     heaped |= d.n > kMaxPerTile * d.TX * d.TY;
+    max_tiles = std::max(max_tiles, (int64_t)d.TX * d.TY);
   }
-  b->bin_pairs = heaped || 0.45 * b->T + 0.16 * item_windows > 60e3 + 0.22 * b->M;
-  // The count matrices hold at most 8 M words, by larger chunks (2M items at 1200 x
-  // 680 205 us, 248 with 16 M words; 8 x 300k 268 us with either, 322 with 4 M), and
+  const double line = 0.4 * b->T + 0.12 * item_windows - 30e3 - 0.15 * b->M;
+  b->pair_cap = heaped ? INT64_MAX : line > 0. ? (int64_t)(line / 0.015) : -1;
+  // The count matrices hold at most 8 M words, by larger chunks, and 16 M of images
+  // from 32,768 tiles on, which come here with many instances (2M items at 1200 x 680
+  // 228 us, 272 with 16 M words; 400k of 3 cm at 4096 x 4096 1,444 us with 8 M and 876,
+  // 1M at 6000 x 4000 8,060 and 3,938; 8 x 300k at 1200 x 680 268 either way), and
   // there are at most about 4,096 chunks (half as many for 16 renders of 150k and 120k
   // items: lists 67 -> 101 us).  Finer first chunks (chunk_first) help a single render
   // and a batch of up to 560 chunks, the more the larger the splats: of 832 batches
@@ -333,7 +345,8 @@ static ls_status batch_host(const ls_render_job* jobs, int32_t R, ls_batch** out
   // fast with them, 1.06 on average, of 640 to 768 0.79 to 1.5, 0.97, past 1,024 0.82
   // (8 x 8.4k items of 0.8 cm at 1200 x 680 65 us and 64 without, of 6 cm 91 and 121;
   // 32 x 4k of 0.8 cm at 640 x 480 61 and 43).
-  constexpr int64_t kMaxCounts = 1 << 23, kMaxChunks = 4096, kRampChunks = 560;
+  constexpr int64_t kMaxChunks = 4096, kRampChunks = 560;
+  const int64_t max_counts = max_tiles >= 1 << 15 ? 1 << 24 : 1 << 23;
   int64_t chunks, counts;
   const auto cut = [&](int chunk, bool ramp) {
     b->bin_chunk = chunk;
@@ -347,9 +360,9 @@ static ls_status batch_host(const ls_render_job* jobs, int32_t R, ls_batch** out
   };
   cut(512, true);
   if (R > 1 && chunks > kRampChunks) cut(512, false);
-  while (b->bin_chunk < 1 << 20 && (b->M / b->bin_chunk > kMaxChunks || counts > kMaxCounts))
+  while (b->bin_chunk < 1 << 20 && (b->M / b->bin_chunk > kMaxChunks || counts > max_counts))
     cut(2 * b->bin_chunk, b->bin_ramp);
-  b->bin_pairs |= counts > kMaxCounts;
+  if (counts > max_counts) b->pair_cap = INT64_MAX;
   b->sortblk_off.assign(R + 1, 0);
   b->binwork_off.assign(R + 1, 0);
   b->bincnt_off.assign(R + 1, 0);
@@ -606,7 +619,7 @@ ls_status ls_bin_sort(const ls_batch* b, const ls_projected* p, const ls_bins* b
   bl.tile_before = at<uint32_t>(w, L.tile_before);
   bl.groups = at<uint64_t>(w, L.groups);
   bl.M = b->M;
-  if (b->bin_pairs)
+  if (bins->capacity <= b->pair_cap)
     bl.pairs = PairLaunch{at<int32_t>(w, L.kept_off), at<uint64_t>(w, L.bsum),      at<uint32_t>(w, L.first),
                           at<uint32_t>(w, L.tk),      at<uint32_t>(w, L.tv),        at<uint32_t>(w, L.pair_hist),
                           {at<int32_t>(w, L.pair_seg), at<int64_t>(w, L.pair_seg + 16)}};

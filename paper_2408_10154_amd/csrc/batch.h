@@ -22,7 +22,7 @@ struct ls_batch {
   int sort_blocks = 0;    // radix sort blocks over all renders
   int sort_per = 0;       // keys per thread of them
   int grad_copies = 1;    // copies of the image-space gradient accumulators
-  bool bin_pairs = false; // the lists by a sort of pairs instead of by chunks
+  int64_t pair_cap = -1;  // most list capacity with which they are made by a sort of pairs instead of by chunks
   int bin_chunk = 0;      // sorted items per binning chunk
   bool bin_ramp = false;  // the first chunks are smaller
   int bin_units = 0;      // binning work units (chunk x tile window) over all renders

@@ -613,7 +613,7 @@ int windows_of(int TX, int TY) {
 // `ramp` a render's first chunks are therefore cut finer, 64 items (16 chunks),
 // then 128 and 256 (16 chunks each), so that no block writes many times the
 // others' instances (k_place: 200k items 92 -> 29 us, 4 renders of 21k and 17k
-// items 17 -> 14 us).  A batch of more than 512 chunks fills the CUs as it is,
+// items 17 -> 14 us).  A batch of more than 560 chunks fills the CUs as it is,
 // and finer chunks only add counts to scan (16 renders of 150k and 120k items:
 // counts and lists 104 us without, 121 us with; 8 of 150k 53 and 66 us).
 constexpr int kRamp = 16 * (64 + 128 + 256);

@@ -2,7 +2,8 @@
 // items' (tile, item) pairs, emitted in depth order and sorted by tile.
 //
 // Distributing every sorted item over all of its render's tiles (binning.hip) costs
-// in proportion to items x tiles, this to the instances; batch_host draws the line.
+// in proportion to items x tiles, this to the instances; batch_host draws the line by
+// the lists' capacity.
 // Bound by the passes over the pairs, 20 bytes each and in runs of a few dozen keys:
 // 110 M pairs of 20-bit keys 2.8 ms (emission 0.33, a pass 0.7), 16 M of 0.56 M tiles
 // 0.46 ms; below a few million by the launches, 12 after the depth order (300k items,

@@ -124,8 +124,8 @@ struct BinTables {
 int windows_of(int TX, int TY);
 int bin_chunks(int n, int chunk, bool ramp);
 
-// Workspace of the pair sort (binning_pairs.hip); all NULL where the batch does
-// not take it.
+// Workspace of the pair sort (binning_pairs.hip); all NULL where the lists are not
+// made by it.
 struct PairSegs {
   int32_t* blk_off;  // [2]
   int64_t* base;     // [1]

@@ -18,7 +18,7 @@ def test_scanned_sort_counts(gpu, sizes):
 @pytest.mark.parametrize("sizes,image,culled", [
     ([3000], (6000, 6000), 0.0), ([1], (6000, 6000), 0.0), ([30000], (6000, 6000), 0.2),   # 18 bits: three digits of 6
     ([600, 0, 2000, 1, 0], (4112, 4100), 0.1), ([17000, 300], (4600, 4600), 0.3),          # renders without items
-    ([9000, 20000], (16, 16), 0.0), ([9000], (16, 16), 1.0), ([70000], (33, 17), 0.2),     # over 8,192 items a tile
+    ([9000, 20000], (16, 16), 0.0), ([9000], (16, 16), 1.0), ([70000], (33, 17), 0.2),     # over 4,096 items a tile
     ([260] * 400, (640, 480), 0.1),                                                        # many small renders
 ])
 def test_lists_by_pairs(gpu, sizes, image, culled):
@@ -139,6 +139,35 @@ def test_capacity_bounds_every_form(gpu, sizes, image, culled, frac):
     if frac == 1.0:
         for got, ref in zip((*(t[:n] for t in lists), b.range), want):
             assert torch.equal(got, ref)
+
+
+def test_capacity_chooses_the_form(gpu):
+    """32 renders of 1,000 items at 1200 x 680: lists by pairs up to a capacity of 680k,
+    by chunks above; the same lists, in the workspace of the larger capacity too."""
+    from paper_2408_10154_amd import lib as L
+    from paper_2408_10154_amd.render import GaussianSet, RenderBatch
+
+    n, R = 1000, 32
+    cam = synth.camera(600, 600, 600, 340, 1200, 680)
+    gs = GaussianSet.from_numpy(synth.gaussians_in_box(np.random.default_rng(0), n, (-1, -1, 1), (1, 1, 2)))
+    b = RenderBatch([(gs, cam, synth.identity_w2c())] * R, capacity=800_000)
+    for dst, src in zip((b.rec, b.radius, b.tiles), _records(np.random.default_rng(1), n * R, cam, 0.1)):
+        dst[:] = torch.as_tensor(src, device="cuda")
+    b.bin_sort()
+    count, ranges = b.count.clone(), b.range.clone()
+    I = int(count[0])
+    want = [t[:I].clone() for t in (b.tile_of, b.item)]
+    assert 100_000 < I < 600_000
+    for cap in (I, 600_000, 680_000, 690_000, 800_000):
+        b.work.fill_(0xA5)
+        for t in (b.tile_of, b.item, b.range, b.count):
+            t.fill_(-7)
+        bins = L.ls_bins(cap, b.tile_of.data_ptr(), b.item.data_ptr(), b.range.data_ptr(), b.count.data_ptr(),
+                         b.bins.work)
+        L.ls_bin_sort(b.h, b.proj, bins, L.C.c_void_p(torch.cuda.current_stream().cuda_stream))
+        assert torch.equal(b.count, count) and torch.equal(b.range, ranges), cap
+        assert all(torch.equal(t[:I], w) for t, w in zip((b.tile_of, b.item), want)), cap
+        assert all(bool((t[cap:] == -7).all()) for t in (b.tile_of, b.item)), cap
 
 
 def test_depth_orders_and_list_forms_agree(gpu):

@@ -6,7 +6,8 @@ from paper_2408_10154_amd import lib as L
 from tests.test_abi import _host_pair
 
 # around the sizes where a radix sort's blocks, and the pair sort's spans, become longer
-EDGES = sorted({max(0, (k << 16) + d) for k in (0, 1, 4, 8, 12, 16, 24, 32, 64, 128) for d in (-1, 0, 1, 1025)})
+EDGES = sorted({max(0, (k << 16) + d) for k in (0, 1, 4, 8, 12, 16, 24, 32, 64, 128, 256, 512, 2048)
+                for d in (-1, 0, 1, 1025)})
 
 
 def _non_decreasing(sizes):
@@ -15,8 +16,9 @@ def _non_decreasing(sizes):
 
 def test_registration_workspace_grows_with_the_capacity():
     prm = L.ls_reg_params(10, 0.01, 0.01, 0.9, 0.999, 1e-8)
-    for w, h in ((64, 48), (6000, 6000)):  # the lists by chunks and by pairs
-        pair, keep = _host_pair(w=w, h=h)
+    # the lists by chunks, by pairs, and by pairs up to 33 M, 10 M and 2 M instances
+    for w, h, views in ((64, 48, 3), (6000, 6000, 100), (6000, 6000, 7), (2000, 2000, 60), (1200, 680, 16)):
+        pair, keep = _host_pair(vp=views, vq=views, w=w, h=h)
         assert _non_decreasing([L.ls_register_workspace_size(pair, prm, c) for c in EDGES]), (w, h)
 
 
