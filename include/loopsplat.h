@@ -121,7 +121,8 @@ typedef struct {
  * image sizes or focal lengths, or NULL Gaussian arrays with n > 0. */
 ls_status ls_batch_create(const ls_render_job* jobs, int32_t R, ls_batch** out);
 ls_status ls_batch_destroy(ls_batch* b);
-/* Sizes of the batch and the workspace needed for `capacity` tile instances. */
+/* Sizes of the batch and the workspace needed for `capacity` tile instances (never
+ * less for a larger capacity: a workspace serves the smaller ones too). */
 ls_status ls_batch_query(const ls_batch* b, int64_t capacity, ls_batch_info* info);
 /* Host copies of the per-render offsets: item_off, pix_off [R+1] and
  * tile_off [R+1] (any may be NULL). */
@@ -443,7 +444,8 @@ ls_status ls_adjust_submaps(const ls_submap_adjust* subs, int32_t count, hipStre
  *                   OR = counts[1] / counts[0] (0 when |K| = 0)
  *   work            device scratch of ls_overlap_workspace_size(np, nq) bytes
  * The means must be finite (they are not checked; a non-finite coordinate
- * gives unspecified matches).  ls_overlap_workspace_size returns 0 for
+ * gives unspecified matches).  ls_overlap_workspace_size never falls with a
+ * size, so a workspace serves smaller sets too; it returns 0 for
  * negative counts.  Errors: LS_ERR_INVALID (sizes, NULL arrays, non-finite T,
  * tau not > 0), LS_ERR_CAPACITY (work_bytes too small). */
 size_t ls_overlap_workspace_size(int32_t np, int32_t nq);
